@@ -41,6 +41,10 @@ __device__ __forceinline__ int64_t q_offset(const Dims& D, UnitIdx u, int q) {
   int g = q / D.P, i = q - g * D.P;
   return u.b * D.q_sb + u.l * D.q_sl + (int64_t)(u.h * D.G + g) * D.q_sh + (int64_t)i * D.d;
 }
+// the first kernel of a call clears the words its last kernel counts in (one workgroup per unit: `first`)
+__device__ __forceinline__ void clear_sync(const ScorePlan& pl, int unit, bool first) {
+  if (pl.sync != nullptr && first && threadIdx.x < kSyncWords) pl.sync[(int64_t)unit * kSyncWords + threadIdx.x] = 0u;
+}
 // where the one extra (max, sum) entry of (unit, query q) lives in `part`, behind the slices of all units: the block of
 // the CaP keys on the vector-ALU path, the windowed head on the matrix-core path
 __device__ __forceinline__ int64_t extra_block_index(const Dims& D, const ScorePlan& pl, int unit, int q) {

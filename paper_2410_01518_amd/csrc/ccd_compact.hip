@@ -6,6 +6,8 @@
 // then the workgroup synchronises, then the rows are stored.  A store of chunk c lands in rows
 // [c*R, (c+1)*R), and every later chunk reads only rows >= (c+1)*R, so the only reads a store could overtake
 // are those of its own chunk, which the barrier orders.  Out of place the same code runs without the barrier.
+#include <algorithm>
+
 #include "ccd_common.h"
 #include "ccd_rope.h"
 #include "ccd_select_body.h"
@@ -29,7 +31,7 @@ __device__ __forceinline__ uint4 load_streaming(const char* p) {
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-constexpr int kCpThreads = 1024;
+constexpr int kCpThreads = 1024;          // compaction of a kept list that is ready in memory
 constexpr int kCpUnroll = 4;
 
 // Appending a chunk of new context behind the cached tokens (Sec. 3.2: the pot is filled until it is full): rows
@@ -132,133 +134,171 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
   }
 }
 
-// Selection and compaction of one unit in ONE workgroup (ccd_compress, rows of up to 32768 tokens): the kept indices
-// stay in LDS (in the space of the staged score row, which is dead by then) and K and V chunks move together, two
-// 16-byte loads per tensor in flight per thread.  Against a selection kernel followed by a compaction kernel this
-// saves a launch, the drain of a latency-bound grid, and the trip of keep_idx through memory; the compaction part
-// runs as fast as with a workgroup per tensor (measured 88.5 against 89.3 us).
-constexpr int kScUnroll = 2;
-constexpr int kSplitFillWorkgroups = 256;   // one 1024-thread workgroup per compute unit
+// Selection and compaction of a unit in one kernel (ccd_compress, rows of up to 32768 tokens): the kept list stays in LDS
+// and K and V rows move together.  Against a selection kernel followed by a compaction kernel this saves a launch, the drain
+// of a latency-bound grid, and the trip of keep_idx through memory.
+//
+// One workgroup per unit when the units fill the chip: it walks the destination rows in ascending chunks (see the top of
+// the file) and is bound by HBM (80 us for 537 MB: 6.7 TB/s), behind about 10 us of selection.
+//
+// SHARED (few units): several workgroups per unit.  Each runs the whole selection for itself - same inputs, same list -
+// and then draws chunks of the unit's destination rows by ticket.  A chunk's sources are loaded into registers and the
+// chunk is marked as loaded; it is stored once all chunks BEFORE it are marked, since those are the only ones whose sources
+// (keep[j] >= j) it can overwrite.  A workgroup draws tickets while it runs, and between a draw and its mark it waits at
+// most for smaller chunks: the owner of the smallest unmarked chunk therefore never waits, and no order of dispatch and no
+// number of resident workgroups can make anybody wait for ever.  Nothing has to be made visible but the marks
+// themselves: a chunk's loads are complete before its mark, and nobody reads rows that were stored.
+// Against dealing out column segments to at most eight workgroups per unit: 8 units, 2048 -> 1024, 23 -> 13 us with the
+// carried novelty, which took a kernel of its own; 8 units, 32768 -> 4096: 113 -> 57 us.
+//
+// Threads: the moving of one workgroup per unit wants 16 waves (512 threads with twice the rows each: 2 - 3 us slower on 256
+// units), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
+// that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
+constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
+constexpr int kScUnroll = 2;                // rows per thread and tensor in flight
+constexpr int kSharedFillWorkgroups = 256;  // one workgroup per compute unit
+// ... SHARED (half with ROPE, whose coefficients take as many registers again): at most 64 KiB of each tensor per workgroup
+constexpr int sh_unroll(int threads, bool rope) { return 4096 / threads / (rope ? 2 : 1); }
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t agent_add(uint32_t* p, uint32_t v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // ROPE (CR-RoPE, Sec. 3.5): the kernel also writes Krot[j] = rotary embedding at position j of the kept key j, for all
 // j < k (rows that stay where they are included, so every kept K row is read); the pot itself keeps the plain keys.
-//
-// SPLIT (calls with few units, which leave most of the chip idle): `parts` workgroups per unit.  Each of them runs
-// the whole selection for itself (same inputs, same kept list; only the first writes scores and keep_idx) and then
-// moves its share of the bytes: one tensor (K for even parts, V for odd ones) and one column segment of
-// ROWB / (parts / 2) bytes of every row (at least 128 bytes; the whole row with ROPE, which pairs columns d/2 apart).
-// The shares are disjoint, so the workgroups of a unit need no ordering among themselves.  Carried novelty is not
-// compacted here in this form (its entries are still being read by the other workgroups' selections).
-constexpr int kScSplitUnroll = 4;
-
-template <int KPT, int ROWB, bool ROPE, bool BF16, bool SPLIT>
-__global__ __launch_bounds__(kCpThreads) void select_compact_kernel(Dims D, const float* __restrict__ u,
-                                                                    float* novelty, int carry_novelty, float* scores,
-                                                                    int32_t* __restrict__ keep_idx, char* Kbuf,
-                                                                    char* Vbuf, const float* __restrict__ rope_cos,
-                                                                    const float* __restrict__ rope_sin, char* Krot,
-                                                                    int parts) {
-  __shared__ TopkShared<kCpThreads> sh;
-  __shared__ __attribute__((aligned(16))) float u_stage[KPT * kCpThreads + 2 * kStagePad];
-  int32_t* keep_lds = reinterpret_cast<int32_t*>(u_stage);
-  if constexpr (SPLIT) {
-    const int part = blockIdx.x % parts, unit = D.unit0 + blockIdx.x / parts;
-    finalize_select_body<kCpThreads, KPT, true>(D, unit, u, novelty, part == 0 ? scores : nullptr,
-                                                part == 0 ? keep_idx : nullptr, sh, u_stage, keep_lds);
-    __syncthreads();
-    const bool is_v = part & 1;
-    const int seg = part >> 1, lanes = (ROWB / 16) / (parts >> 1);     // 16-byte lanes per row segment: 8, 16 or 32
-    const int lane_shift = __ffs(lanes) - 1;
-    const int lane_in_row = seg * lanes + (threadIdx.x & (lanes - 1));
-    const int row_in_pass = threadIdx.x >> lane_shift, rows_per_pass = kCpThreads >> lane_shift;
-    const int lane_off = lane_in_row * 16;
-    const int64_t ubytes = kv_offset(D, decode_unit(D, unit)) * (int64_t)(ROWB / D.d);
-    char* tb = (is_v ? Vbuf : Kbuf) + ubytes;
-    char* rb = ROPE ? Krot + ubytes : nullptr;
-    const bool rot = ROPE && !is_v;
-    const int half_d = D.d / 2;
-    for (int base = 0; base < D.k; base += rows_per_pass * kScSplitUnroll) {
-      uint4 a[kScSplitUnroll];
-      bool move[kScSplitUnroll];
-      RopeCoef<ROWB, BF16> coef[ROPE ? kScSplitUnroll : 1];
-#pragma unroll
-      for (int i = 0; i < kScSplitUnroll; ++i) {
-        const int j = base + i * rows_per_pass + row_in_pass;
-        move[i] = false;
-        if (j < D.k) {
-          const int sidx = keep_lds[j];
-          move[i] = sidx != j;
-          if (move[i] || rot) a[i] = load_streaming(tb + (int64_t)sidx * ROWB + lane_off);
-          if (ROPE && rot) coef[i].load(lane_in_row, rope_cos + (int64_t)j * half_d, rope_sin + (int64_t)j * half_d);
-        }
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < kScSplitUnroll; ++i) {
-        const int j = base + i * rows_per_pass + row_in_pass;
-        if (move[i]) store_streaming(tb + (int64_t)j * ROWB + lane_off, a[i]);
-        if (ROPE && rot && j < D.k)
-          store_streaming(rb + (int64_t)j * ROWB + lane_off, rope_lane<ROWB, BF16>(a[i], lane_in_row, coef[ROPE ? i : 0]));
-      }
-    }
-    return;
+// ROWB, BF16: row bytes and cache type where ROPE needs them at compile time (ROWB is 0 without: `row_shift` = log2 of the
+// 16-byte lanes of a row).
+template <int CH, int ROWB, bool BF16, bool SHARED>
+__global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_compact_kernel(Dims D, const float* __restrict__ u,
+                                                                     float* novelty, int carry_novelty, float* scores,
+                                                                     int32_t* __restrict__ keep_idx, char* Kbuf,
+                                                                     char* Vbuf, const float* __restrict__ rope_cos,
+                                                                     const float* __restrict__ rope_sin, char* Krot,
+                                                                     int row_shift, int wgs_per_unit, int chunk_rows,
+                                                                     uint32_t* sync) {
+  constexpr bool ROPE = ROWB > 0;
+  constexpr int THREADS = sc_threads(SHARED, CH == kLdsRow);
+  constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
+  __shared__ SelectShared<THREADS, CH> sh;
+  // The kept list: in LDS for short rows; a long row leaves no room for it, and it is read back from keep_idx, where this
+  // workgroup has just put it
+  __shared__ uint16_t keep_lds[kRegs ? CH * 4 * THREADS : 1];
+  __shared__ int ticket_lds;
+  __shared__ int last_lds;
+  const int part = SHARED ? blockIdx.x % wgs_per_unit : 0;
+  const int unit = D.unit0 + (SHARED ? blockIdx.x / wgs_per_unit : blockIdx.x);
+  const UnitIdx ui = decode_unit(D, unit);
+  uint32_t* sy = SHARED ? sync + (int64_t)unit * kSyncWords : nullptr;
+  if (SHARED && threadIdx.x == 0) ticket_lds = (int)agent_add(&sy[kSyncTicket], 1u);
+  int32_t* keep_out = keep_idx + (int64_t)unit * D.k;
+  float* nov = (D.T > 0 || carry_novelty) ? novelty + nov_offset(D, ui) : nullptr;
+  {
+    Row<THREADS, CH> row(D, sh, unit, u, nullptr, nov);
+    select_row<THREADS, CH, true>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr,
+                         [&](int pos, int t, int c, int i) {
+                           if (kRegs) keep_lds[pos] = (uint16_t)t;
+                           else       keep_out[pos] = t;
+                           // carried novelty moves up with the rows: every thread has had its entries in registers
+                           // since before the barriers of the selection
+                           if constexpr (kRegs && !SHARED) { if (carry_novelty) nov[pos] = row.nv[4 * c + i]; }
+                         });
   }
-  const int unit = D.unit0 + blockIdx.x;
-  finalize_select_body<kCpThreads, KPT, true>(D, unit, u, novelty, scores, keep_idx, sh, u_stage, keep_lds);
   __syncthreads();
-
-  if (carry_novelty) {
-    // novelty carried per head: its kept entries move up like the rows (keep[j] >= j: a chunk's sources are read
-    // before anything at or above them is written)
-    float* nov = novelty + nov_offset(D, decode_unit(D, unit));
-    for (int base = 0; base < D.k; base += kCpThreads) {
-      const int j = base + threadIdx.x;
-      float v = 0.f;
-      if (j < D.k) v = nov[keep_lds[j]];
+  auto keep = [&](int j) { return kRegs ? (int)keep_lds[j] : keep_out[j]; };
+  if (kRegs && part == 0)
+    for (int j = threadIdx.x; j < D.k; j += THREADS) keep_out[j] = keep_lds[j];
+  auto compact_novelty = [&]() {      // (keep[j] >= j: a chunk's sources are read before anything at or above them is written)
+    constexpr int kN = 8;
+    for (int base = 0; base < D.k; base += kN * THREADS) {
+      float v[kN];
+#pragma unroll
+      for (int i = 0; i < kN; ++i) {
+        const int j = base + i * THREADS + threadIdx.x;
+        if (j < D.k) v[i] = nov[keep(j)];
+      }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (j < D.k) nov[j] = v;
+#pragma unroll
+      for (int i = 0; i < kN; ++i) {
+        const int j = base + i * THREADS + threadIdx.x;
+        if (j < D.k) nov[j] = v[i];
+      }
     }
-  }
+  };
+  if constexpr (!kRegs && !SHARED) { if (carry_novelty) compact_novelty(); }
 
-  constexpr int kLanesPerRow = ROWB / 16;
-  constexpr int kRowsPerPass = kCpThreads / kLanesPerRow;
-  const int64_t ubytes = kv_offset(D, decode_unit(D, unit)) * (int64_t)(ROWB / D.d);
+  const int rowb = ROPE ? ROWB : 16 << row_shift;
+  const int64_t ubytes = kv_offset(D, ui) * (int64_t)(D.dtype == 0 ? 4 : 2);
+  const int half_d = D.d / 2;
+  const int lane_shift = ROPE ? __ffs(ROWB / 16) - 1 : row_shift;
   char* kb = Kbuf + ubytes;
   char* vb = Vbuf + ubytes;
   char* rb = ROPE ? Krot + ubytes : nullptr;
-  const int lane_in_row = threadIdx.x % kLanesPerRow;
+  const int lane_in_row = threadIdx.x & ((1 << lane_shift) - 1);
   const int lane_off = lane_in_row * 16;
-  const int row_in_pass = threadIdx.x / kLanesPerRow;
-  const int half_d = D.d / 2;
-  for (int base = 0; base < D.k; base += kRowsPerPass * kScUnroll) {
-    uint4 a[kScUnroll], b[kScUnroll];
-    bool move[kScUnroll];
-    RopeCoef<ROWB, BF16> coef[ROPE ? kScUnroll : 1];
+  const int row_in_pass = threadIdx.x >> lane_shift, rows_per_pass = THREADS >> lane_shift;
+  constexpr int kUnroll = !SHARED ? kScUnroll : sh_unroll(THREADS, ROPE);
+
+  if (SHARED && carry_novelty && threadIdx.x == 0)
+    last_lds = agent_add(&sy[kSyncSelected], 1u) == (uint32_t)(wgs_per_unit - 1);
+  int base = SHARED ? ticket_lds * chunk_rows : 0;
+  while (base < D.k) {
+    const int end = SHARED ? min(D.k, base + chunk_rows) : D.k;
+    uint4 a[kUnroll], b[kUnroll];
+    bool move[kUnroll];
+    RopeCoef<ROPE ? ROWB : 128, BF16> coef[ROPE ? kUnroll : 1];
 #pragma unroll
-    for (int i = 0; i < kScUnroll; ++i) {
-      const int j = base + i * kRowsPerPass + row_in_pass;
+    for (int i = 0; i < kUnroll; ++i) {
+      const int j = base + i * rows_per_pass + row_in_pass;
       move[i] = false;
-      if (j < D.k) {
-        const int sidx = keep_lds[j];             // written by this workgroup: ascending, in [j, n)
+      if (j < end) {
+        const int sidx = keep(j);                 // ascending, in [j, n)
         move[i] = sidx != j;
-        if (move[i] || ROPE) a[i] = load_streaming(kb + (int64_t)sidx * ROWB + lane_off);
-        if (move[i]) b[i] = load_streaming(vb + (int64_t)sidx * ROWB + lane_off);
-        if (ROPE) coef[i].load(lane_in_row, rope_cos + (int64_t)j * half_d, rope_sin + (int64_t)j * half_d);
+        if (move[i] || ROPE) a[i] = load_streaming(kb + (int64_t)sidx * rowb + lane_off);
+        if (move[i]) b[i] = load_streaming(vb + (int64_t)sidx * rowb + lane_off);
+        if constexpr (ROPE) coef[i].load(lane_in_row, rope_cos + (int64_t)j * half_d, rope_sin + (int64_t)j * half_d);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kScUnroll; ++i) {
-      const int j = base + i * kRowsPerPass + row_in_pass;
-      if (move[i]) {
-        store_streaming(kb + (int64_t)j * ROWB + lane_off, a[i]);
-        store_streaming(vb + (int64_t)j * ROWB + lane_off, b[i]);
+    int next = base + kUnroll * rows_per_pass;
+    if constexpr (SHARED) {
+      if (threadIdx.x < 64) {
+        const int chunk = base / chunk_rows, lane = threadIdx.x;
+        if (lane == 0) {
+          __hip_atomic_fetch_or(&sy[kSyncMarks + chunk / 32], 1u << (chunk % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ticket_lds = (int)agent_add(&sy[kSyncTicket], 1u);
+        }
+        const int below = chunk - 32 * lane;      // chunks before this one that lane's word of marks holds
+        const uint32_t want = below >= 32 ? 0xFFFFFFFFu : (below > 0 ? (1u << below) - 1u : 0u);
+        const uint32_t* word = &sy[kSyncMarks + min(lane, kSyncMarkWords - 1)];
+        while (!__all((want & ~agent_load(word)) == 0u)) __builtin_amdgcn_s_sleep(1);
       }
-      if (ROPE && j < D.k)
-        store_streaming(rb + (int64_t)j * ROWB + lane_off, rope_lane<ROWB, BF16>(a[i], lane_in_row, coef[ROPE ? i : 0]));
+      __syncthreads();
+      next = ticket_lds * chunk_rows;
+    }
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i) {
+      const int j = base + i * rows_per_pass + row_in_pass;
+      if (move[i]) {
+        store_streaming(kb + (int64_t)j * rowb + lane_off, a[i]);
+        store_streaming(vb + (int64_t)j * rowb + lane_off, b[i]);
+      }
+      if constexpr (ROPE) {
+        if (j < end)
+          store_streaming(rb + (int64_t)j * rowb + lane_off, rope_lane<ROWB, BF16>(a[i], lane_in_row, coef[i]));
+      }
+    }
+    base = next;
+  }
+  if constexpr (SHARED) {
+    // all workgroups of the unit have read the novelty they select by once the last one has selected
+    if (carry_novelty) {
+      __syncthreads();
+      if (last_lds) compact_novelty();
     }
   }
 }
@@ -300,43 +340,52 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(Dims D, const char* __re
 
 }  // namespace
 
-bool select_compact_supported(const Dims& D) { return D.n <= 32 * kCpThreads; }
+bool select_compact_supported(const Dims& D) { return D.n <= kLdsRowTokens; }
 
 // pooling + NuC lift + top-k + in-place compaction of K and V (and of carried per-head novelty).
 // Krot != nullptr: CR-RoPE of the kept keys on the side (rope_cos / rope_sin: [>= k, d/2] fp32).
-// A launch with so few units that most compute units would stay idle gives every unit 2, 4 or 8 workgroups (see the
-// kernel); carried novelty then follows in a small kernel of its own.
+// sync: kSyncWords zeros per unit.
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
-                           hipStream_t s) {
+                           uint32_t* sync, hipStream_t s) {
   const int rowb = D.d * (D.dtype == 0 ? 4 : 2);
-  const int max_parts = Krot != nullptr ? 2 : 2 * (rowb / 128);
-  int parts = 1;
-  while (parts * 2 <= max_parts && (int64_t)D.units_run * parts * 2 <= kSplitFillWorkgroups) parts *= 2;
-  const bool split = parts > 1;
-  const dim3 grid((unsigned)D.units_run * parts), block(kCpThreads);
-#define CCD_LAUNCH(KPT, RB, ROPE, BF, SPLIT)                                                                           \
-  launch((select_compact_kernel<KPT, RB, ROPE, BF, SPLIT>), grid, block, s, D, u, novelty,                \
-                     (carry_novelty && !SPLIT) ? 1 : 0, scores, keep_idx, (char*)K, (char*)V, rope_cos, rope_sin,        \
-                     (char*)Krot, parts)
-#define CCD_LAUNCH_RB(KPT, ROPE, SPLIT)                                           \
-  if (rowb == 128) CCD_LAUNCH(KPT, 128, ROPE, true, SPLIT);                        \
-  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(KPT, 256, ROPE, true, SPLIT);    \
-  else if (rowb == 256) CCD_LAUNCH(KPT, 256, ROPE, false, SPLIT);                   \
-  else CCD_LAUNCH(KPT, 512, ROPE, false, SPLIT)
-#define CCD_LAUNCH_SPLIT(KPT, ROPE)                              \
-  if (split) { CCD_LAUNCH_RB(KPT, ROPE, true); } else { CCD_LAUNCH_RB(KPT, ROPE, false); }
-  const int kpt = (D.n + kCpThreads - 1) / kCpThreads;
-  if (Krot == nullptr) {
-    if (kpt <= 4) { CCD_LAUNCH_SPLIT(4, false); } else if (kpt <= 16) { CCD_LAUNCH_SPLIT(16, false); } else { CCD_LAUNCH_SPLIT(32, false); }
-  } else {
-    if (kpt <= 4) { CCD_LAUNCH_SPLIT(4, true); } else if (kpt <= 16) { CCD_LAUNCH_SPLIT(16, true); } else { CCD_LAUNCH_SPLIT(32, true); }
+  const int row_shift = rowb == 128 ? 3 : (rowb == 256 ? 4 : 5);
+  // Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
+  // sh_unroll rows per thread; 32 marks per word bound the number of chunks.
+  const bool lds_row = D.n > 16 * sc_threads(true, false);
+  const int rows_per_pass = sc_threads(true, lds_row) >> row_shift;
+  const int max_rows = rows_per_pass * sh_unroll(sc_threads(true, lds_row), Krot != nullptr);
+  int per_unit = std::min(kSharedFillWorkgroups / std::max(D.units_run, 1), (D.k + rows_per_pass - 1) / rows_per_pass);
+  int chunk_rows = 0;
+  if (per_unit > 1) {
+    chunk_rows = std::min((D.k + per_unit - 1) / per_unit, max_rows);
+    chunk_rows = (chunk_rows + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
+    if (D.k > chunk_rows * 32 * kSyncMarkWords) per_unit = 1;
+    else per_unit = std::min(per_unit, (D.k + chunk_rows - 1) / chunk_rows);
   }
-#undef CCD_LAUNCH_SPLIT
+  const bool shared = per_unit > 1;
+  if (!shared) per_unit = 1;
+  const int threads = sc_threads(shared, shared && lds_row);
+  const dim3 grid((unsigned)D.units_run * per_unit), block(threads);
+#define CCD_LAUNCH(CH, RB, BF, SHARED)                                                                                  \
+  launch((select_compact_kernel<CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
+         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunk_rows, sync)
+#define CCD_LAUNCH_RB(CH, SHARED)                                          \
+  if (Krot == nullptr) CCD_LAUNCH(CH, 0, true, SHARED);                    \
+  else if (rowb == 128) CCD_LAUNCH(CH, 128, true, SHARED);                 \
+  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(CH, 256, true, SHARED); \
+  else if (rowb == 256) CCD_LAUNCH(CH, 256, false, SHARED);                \
+  else CCD_LAUNCH(CH, 512, false, SHARED)
+#define CCD_LAUNCH_SHARED(CH) \
+  if (shared) { CCD_LAUNCH_RB(CH, true); } else { CCD_LAUNCH_RB(CH, false); }
+  const int chunks = shared && lds_row ? 8 : (D.n + 4 * threads - 1) / (4 * threads);     // per thread
+  if (chunks <= 1)      { CCD_LAUNCH_SHARED(1); }
+  else if (chunks <= 2) { CCD_LAUNCH_SHARED(2); }
+  else if (chunks <= 4 && shared) { CCD_LAUNCH_RB(4, true); }
+  else                  { CCD_LAUNCH_SHARED(kLdsRow); }
+#undef CCD_LAUNCH_SHARED
 #undef CCD_LAUNCH_RB
 #undef CCD_LAUNCH
-  if (split && carry_novelty)
-    launch(compact_novelty_kernel, dim3(D.units_run), block, s, D, keep_idx, novelty);
 }
 
 void launch_rope_rows(const Dims& D, const void* K, const float* rope_cos, const float* rope_sin, int count, void* Krot,

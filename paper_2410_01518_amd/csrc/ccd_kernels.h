@@ -27,6 +27,9 @@ struct Dims {
   int64_t nov_sb, nov_sl, nov_sh;
 };
 
+// What the workgroups that share a unit's selection and compaction agree on (launch_select_compact), per unit
+constexpr int kSyncTicket = 0, kSyncSelected = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16;
+
 struct ScorePlan {
   int use_mfma;   // 1: bf16 matrix-core kernels, 0: vector-ALU kernels
   int slice1;     // tokens per workgroup in the statistics pass
@@ -36,6 +39,7 @@ struct ScorePlan {
   int cap_block;  // 1 (vector-ALU path): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
   int head_block; // 1 (matrix-core path): `part` also holds the statistics of the windowed head (sliding window)
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass
+  uint32_t* sync;   // kSyncWords words per unit that the first score kernel of a call clears (null: none)
   int unit_kernel;  // 1 (matrix-core path): both passes in one kernel, one workgroup per unit (launch_score_unit)
 };
 
@@ -88,10 +92,10 @@ void launch_finalize_select(const Dims& D, const float* u, const float* novelty,
 
 // selection and compaction of a unit in one workgroup (rows short enough to be staged in LDS)
 bool select_compact_supported(const Dims& D);
-// (carry_novelty: the novelty is carried per head and its kept entries are compacted in place like the rows)
+// (sync: kSyncWords zeros per unit; carry_novelty: the novelty is carried per head and its kept entries are compacted in place like the rows)
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
-                           hipStream_t s);
+                           uint32_t* sync, hipStream_t s);
 // CR-RoPE of the first `count` rows of every unit (Sec. 3.5): Krot[j] = rotary embedding at position j of K[j]
 void launch_rope_rows(const Dims& D, const void* K, const float* rope_cos, const float* rope_sin, int count, void* Krot,
                       hipStream_t s);

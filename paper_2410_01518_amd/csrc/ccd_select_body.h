@@ -1,4 +1,4 @@
-// Pooling + NuC lift + final top-k of one unit (Sec. 3.3.3 step 2), as a workgroup-level device function.
+// NuC slots + pooling + NuC lift + final top-k of one unit (Sec. 3.3.3), as a workgroup-level device function.
 #pragma once
 #include <float.h>
 
@@ -7,8 +7,37 @@
 
 namespace ccd {
 
+// four consecutive floats whose address is only known to be a multiple of four bytes
+struct __attribute__((packed, aligned(4))) Floats4 { float v[4]; };
+__device__ __forceinline__ void store_row4(float* row, int t, int n, const float (&x)[4]) {
+  if (t + 3 < n) {
+    *reinterpret_cast<Floats4*>(row + t) = Floats4{{x[0], x[1], x[2], x[3]}};
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (t + i < n) row[t + i] = x[i];
+  }
+}
+// elements t .. t + 3 of a row of n values; `fill` past the end
+__device__ __forceinline__ void load_row4(float (&out)[4], const float* __restrict__ row, int t, int n, float fill) {
+  // (one branch for the whole wave: a chunk loop keeps its vector loads in flight together)
+  if (__all(t + 3 < n)) {
+    const Floats4 f = *reinterpret_cast<const Floats4*>(row + t);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = f.v[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = row[min(t + i, n - 1)];
+      out[i] = t + i < n ? v : fill;
+    }
+  }
+}
+
+constexpr int kPoolReach = 4;   // windows of up to 2 * 4 + 1 tokens are pooled from three vector loads
+
+// pooled score of token t, any window
 __device__ __forceinline__ float pooled(const float* __restrict__ u, int t, int n, int w, int mode) {
-  if (mode == 0 || w <= 1) return u[t];
   const int r = w >> 1;
   const int lo = max(0, t - r), hi = min(n - 1, t + r);
   if (mode == 1) {
@@ -21,198 +50,408 @@ __device__ __forceinline__ float pooled(const float* __restrict__ u, int t, int 
   return s / (float)w;
 }
 
-// Token ownership inside the workgroup.  Striped: thread t owns tokens t, t+THREADS, ... (coalesced global access
-// with any KPT).  Blocked: thread t owns the KPT consecutive tokens t*KPT ..: the pooling window of all of them is
-// KPT + 2r consecutive values, and ranks in token order need one workgroup scan instead of one per round.
-template <int THREADS, int KPT, bool BLOCKED>
-__device__ __forceinline__ int owned_token(int tid, int j) { return BLOCKED ? tid * KPT + j : tid + j * THREADS; }
-
-constexpr int kStagePad = 4;   // blocked pooling reads up to 4 tokens before and after a thread's tokens
-
-// Pooled scores of the KPT consecutive tokens of one thread from the LDS copy of the row (token t at
-// stage[t + kStagePad]), for windows of at most 2*kStagePad + 1: KPT/4 + 2 vector reads, the rest in registers.
-template <int KPT>
-__device__ __forceinline__ void pooled_block(float (&out)[KPT], const float* stage, int t0, int n, int w, int mode) {
-  static_assert(KPT % 4 == 0, "vector reads of four tokens");
-  float win[KPT + 2 * kStagePad];
+// Pooling straight from the row in global memory: the row was written by the kernel before this one and is served by the
+// caches; a copy in LDS would cost a barrier and, for the longest rows, 128 KiB.  Two steps, so that a chunk loop can
+// have the loads of several chunks in flight: `win` holds tokens t - 4 .. t + 7, the row's ends filled with what is neutral
+// for the mode (max clips its window at the ends, avg pads with zeros).
+struct PoolSpec {
+  int n, w, mode;
+  bool plain, wide;      // no pooling; a window that does not fit `win`
+  __device__ __forceinline__ explicit PoolSpec(const Dims& D)
+      : n(D.n), w(D.pool_w), mode(D.pool_mode), plain(D.pool_mode == 0 || D.pool_w <= 1), wide(D.pool_w > 2 * kPoolReach + 1) {}
+};
+__device__ __forceinline__ void pool_load(float (&win)[12], const float* __restrict__ u, int t, const PoolSpec& P) {
+  if (P.wide) return;
+  const float fill = P.mode == 1 ? -INFINITY : 0.f;
+  if (__all(t >= 4 && t + 7 < P.n)) {
+    const Floats4 a = *reinterpret_cast<const Floats4*>(u + t - 4), b = *reinterpret_cast<const Floats4*>(u + t),
+                  c = *reinterpret_cast<const Floats4*>(u + t + 4);
 #pragma unroll
-  for (int i = 0; i < KPT / 4 + 2; ++i) {
-    const float4 v = *reinterpret_cast<const float4*>(stage + t0 + 4 * i);   // tokens t0 - 4 + 4i ..
-    win[4 * i] = v.x; win[4 * i + 1] = v.y; win[4 * i + 2] = v.z; win[4 * i + 3] = v.w;
-  }
-  const int r = w >> 1;
+    for (int i = 0; i < 4; ++i) { win[i] = a.v[i]; win[4 + i] = b.v[i]; win[8 + i] = c.v[i]; }
+  } else {
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    const int t = t0 + j;
-    float m = win[j + kStagePad], sum = 0.f;
-#pragma unroll
-    for (int o = -kStagePad; o <= kStagePad; ++o) {
-      const bool in = o >= -r && o <= r && t + o >= 0 && t + o < n;
-      const float v = win[j + kStagePad + o];
-      m = in ? fmaxf(m, v) : m;
-      sum += in ? v : 0.f;
+    for (int i = 0; i < 12; ++i) {
+      const int x = t - 4 + i;
+      const float v = u[min(max(x, 0), P.n - 1)];
+      win[i] = x >= 0 && x < P.n ? v : fill;
     }
-    out[j] = mode == 1 ? m : sum / (float)w;
   }
 }
-
-// NuC slots (Sec. 3.3.3 step 1): bit j of the result = the thread's j-th token is among the T tokens of largest
-// novelty of the row `nov` (n values).  NaN and -inf never qualify, so fewer than T may be marked; ties go to the lower index.  The
-// novelty keys stay in registers; the row is read once.  Every thread of the workgroup must call this.
-template <int THREADS, int KPT, bool BLOCKED>
-__device__ __forceinline__ uint64_t nuc_slots_of_row(const float* __restrict__ nov, int n, int T,
-                                                     TopkShared<THREADS>& sh, int& phase) {
-  static_assert(KPT <= 64, "one bit per owned token");
-  const int tid = threadIdx.x;
-  uint64_t nuc = 0;
-  uint32_t key[KPT];
+__device__ __forceinline__ void pool_reduce(float (&out)[4], const float (&win)[12], const float* __restrict__ u, int t,
+                                            const PoolSpec& P) {
+  if (P.plain) {
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    const int t = owned_token<THREADS, KPT, BLOCKED>(tid, j);
-    key[j] = t < n ? novelty_key(nov[t]) : 0u;
-  }
-  uint32_t tau, need;
-  radix_threshold<THREADS, KPT, BLOCKED, true>([&](int j, int) { return key[j]; }, n, (uint32_t)max(T, 0), sh, phase, tau, need);
-  if (BLOCKED) {
-    uint32_t n_eq = 0;
+    for (int i = 0; i < 4; ++i) out[i] = win[4 + i];
+  } else if (P.wide) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) {
+      const float v = t + i < P.n ? pooled(u, t + i, P.n, P.w, P.mode) : 0.f;
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) n_eq += (tid * KPT + j < n && key[j] == tau) ? 1u : 0u;
-    uint32_t tot;
-    uint32_t eq_rank = block_exclusive_scan<THREADS>(n_eq, sh, phase, tot);
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const bool valid = tid * KPT + j < n, eq = valid && key[j] == tau;
-      nuc |= (uint64_t)(valid && (key[j] > tau || (eq && eq_rank < need))) << j;
-      eq_rank += eq ? 1u : 0u;
+      for (int j = 0; j < 4; ++j) out[j] = i == j ? v : out[j];
     }
   } else {
-    uint32_t eq_base = 0;
+    const int r = P.w >> 1;
+    if (P.mode == 1) {
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      if (j * THREADS >= n) continue;      // uniform: whole rounds beyond n are skipped
-      const int t = tid + j * THREADS;
-      const bool eq = t < n && key[j] == tau;
-      uint32_t tot;
-      const uint32_t rank = block_rank<THREADS>(eq, sh, phase, tot);
-      nuc |= (uint64_t)(t < n && (key[j] > tau || (eq && eq_base + rank < need))) << j;
-      eq_base += tot;
+      for (int i = 0; i < 4; ++i) out[i] = fmaxf(fmaxf(win[4 + i], win[3 + i]), win[5 + i]);      // r >= 1
+#pragma unroll
+      for (int o = 2; o <= kPoolReach; ++o) {
+        if (o > r) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = fmaxf(fmaxf(out[i], win[4 + i - o]), win[4 + i + o]);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i] = 0.f;
+#pragma unroll
+      for (int o = -kPoolReach; o <= kPoolReach; ++o) {
+        if (o < -r || o > r) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] += win[4 + i + o];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i] /= (float)P.w;
     }
   }
-  return nuc;
 }
 
-// u != nullptr: score <- pooled u with +inf at the NuC slots of the unit's novelty row (novelty may be null when
-// D.T == 0), written to `scores` if that is not null.
-// u == nullptr: score <- scores (must not be null).      keep_idx != nullptr: keep_idx <- top-k of score.
-// Executed by a whole workgroup of THREADS threads, each owning at most KPT tokens (n <= THREADS * KPT).
-// u_stage (LDS, THREADS * KPT + 2 * kStagePad floats, 16-byte aligned, or null): the unit's row of u is copied there
-// first, so that the pooling window reads LDS instead of issuing a chain of dependent global loads per token.
-// BLOCKED needs u_stage.  keep_lds (BLOCKED only, or null): a second copy of the kept indices, k entries in LDS; it
-// may alias u_stage.  Ends without a barrier.
-template <int THREADS, int KPT, bool BLOCKED>
-__device__ __forceinline__ void finalize_select_body(const Dims& D, int unit, const float* __restrict__ u,
-                                                     const float* __restrict__ novelty, float* scores,
-                                                     int32_t* __restrict__ keep_idx, TopkShared<THREADS>& sh,
-                                                     float* u_stage, int32_t* keep_lds = nullptr) {
-  const int tid = threadIdx.x, n = D.n;
-  int phase = 0;
-  float sc[KPT];
-  if (u != nullptr) {
-    const float* uu = u + (int64_t)unit * n;
-    const bool pooling = D.pool_mode != 0 && D.pool_w > 1;
-    const bool stage = u_stage != nullptr && pooling;
-    if (stage) {
+// Where the keys of a row live between the steps of its selection, by the length of the row:
+//   CH = 1, 2, 4   registers: CH chunks of four tokens per thread (rows of up to 4 CH THREADS tokens)
+//   kLdsRow        LDS (up to 32768 tokens: 128 KiB), first the novelty keys, then the score keys.  (In registers such a
+//                  row takes hundreds of spilled scalar registers, the comparison masks of the unrolled steps.)
+//   kLongRow       nowhere: every step pools the row again (up to 65536 tokens), LDS holds four lift flags per chunk
+constexpr int kLdsRow = 0, kLongRow = -1;
+constexpr int kLdsRowTokens = 32768, kMaxTokens = 65536;
+template <int THREADS, int CH>
+struct RowStore {
+  static constexpr bool kRegs = CH > 0;
+  static constexpr int kMaxChunks = kRegs ? CH : (CH == kLdsRow ? kLdsRowTokens : kMaxTokens) / (4 * THREADS);
+  static constexpr int kLdsWords = kRegs ? 4 : (CH == kLdsRow ? kLdsRowTokens : kMaxTokens / 16);
+};
+
+template <int THREADS, int CH>
+struct SelectShared {
+  TopkShared<THREADS> topk;
+  uint32_t sums[2][RowStore<THREADS, CH>::kMaxChunks * (THREADS / 64)];
+  __attribute__((aligned(16))) uint32_t row[RowStore<THREADS, CH>::kLdsWords];
+};
+
+// One workgroup's view of one row: chunk loops, keys, novelty.  nov may be null when D.T == 0 and novelty is not carried.
+template <int THREADS, int CH>
+struct Row {
+  using Store = RowStore<THREADS, CH>;
+  static constexpr bool kRegs = Store::kRegs, kLds = CH == kLdsRow;
+  const Dims& D;
+  SelectShared<THREADS, CH>& sh;
+  const float* u;          // raw scores, or null: the scores are given
+  const float* given;
+  const float* nov;
+  const PoolSpec pool;
+  int rounds;              // chunks per thread, whole groups
+  uint32_t key[kRegs ? 4 * CH : 1];
+  float nv[kRegs ? 4 * CH : 1];      // the thread's novelty
+  uint64_t slots = 0;                // kLds: bit 4 c + i: token i of chunk c has a NuC slot
+
+  __device__ __forceinline__ Row(const Dims& D_, SelectShared<THREADS, CH>& sh_, int unit, const float* u_, const float* given_,
+                                 const float* nov_)
+      : D(D_), sh(sh_), u(u_ ? u_ + (int64_t)unit * D_.n : nullptr), given(given_ ? given_ + (int64_t)unit * D_.n : nullptr),
+        nov(nov_), pool(D_),
+        rounds(kRegs ? CH : (D_.n + 4 * THREADS * kGroup - 1) / (4 * THREADS * kGroup) * kGroup) {}
+  __device__ __forceinline__ int token(int c) const { return 4 * (c * THREADS + (int)threadIdx.x); }
+  // load(x, c) for kGroup chunks at a time, then use(x, c): a group's loads are in flight together.  Chunks past the end
+  // are empty (their keys are 0).
+  static constexpr int kGroup = kRegs ? CH : 4;
+  static_assert(kRegs || Store::kMaxChunks % kGroup == 0, "whole groups fit");
+  template <class X, class Load, class Use>
+  __device__ __forceinline__ void chunks(Load&& load, Use&& use) {
+    int c0 = 0;
+#pragma unroll 1
+    do {
+      X x[kGroup];
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const int t = tid + j * THREADS;            // striped copy: coalesced
-        if (t < n) u_stage[t + kStagePad] = uu[t];
+      for (int g = 0; g < kGroup; ++g) load(x[g].v, kRegs ? g : c0 + g);
+#pragma unroll
+      for (int g = 0; g < kGroup; ++g) use(x[g].v, kRegs ? g : c0 + g);
+      c0 += kGroup;
+    } while (!kRegs && c0 < rounds);
+  }
+  struct Keys4 { uint32_t v[4]; };
+  struct Vals4 { float v[4]; };
+  struct Window { float v[12]; };
+
+  // novelty: read once and kept (registers; LDS), or read from memory every time
+  template <class Use>
+  __device__ __forceinline__ void first_novelty_chunks(Use&& use) {
+    if constexpr (kRegs) {
+      each_novelty_chunk(use);
+    } else {
+      chunks<Vals4>([&](float (&f)[4], int c) { load_row4(f, nov, token(c), D.n, -INFINITY); },
+                    [&](float (&f)[4], int c) {
+                      const uint32_t k[4] = {novelty_key(f[0]), novelty_key(f[1]), novelty_key(f[2]), novelty_key(f[3])};
+                      if (kLds) *reinterpret_cast<uint4*>(&sh.row[token(c)]) = make_uint4(k[0], k[1], k[2], k[3]);
+                      use(k, c);
+                    });
+    }
+  }
+  template <class Use>
+  __device__ __forceinline__ void each_novelty_chunk(Use&& use) {
+    chunks<Keys4>(
+        [&](uint32_t (&k)[4], int c) {
+          if constexpr (kLds) {
+            const uint4 v = *reinterpret_cast<const uint4*>(&sh.row[token(c)]);
+            k[0] = v.x; k[1] = v.y; k[2] = v.z; k[3] = v.w;
+          } else {
+            float f[4];
+            if constexpr (kRegs) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) f[i] = nv[4 * c + i];
+            } else {
+              load_row4(f, nov, token(c), D.n, -INFINITY);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k[i] = novelty_key(f[i]);    // 0 past the end
+          }
+        },
+        use);
+  }
+  __device__ __forceinline__ void load_novelty() {
+    if constexpr (kRegs) {
+      if (nov == nullptr) return;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        float f[4];
+        load_row4(f, nov, token(c), D.n, -INFINITY);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nv[4 * c + i] = f[i];
       }
     }
-    // the NuC slots of the row: the workgroup barriers inside also make the staged row visible
-    uint64_t nuc = 0;
-    if (D.T > 0) {
-      nuc = nuc_slots_of_row<THREADS, KPT, BLOCKED>(novelty + nov_offset(D, decode_unit(D, unit)), n, D.T, sh, phase);
-    } else if (stage) {
+  }
+  // scores before the lift, in two steps (see pool_load)
+  __device__ __forceinline__ void load_window(float (&win)[12], int c) const {
+    if (u != nullptr) {
+      pool_load(win, u, token(c), pool);
+    } else {
+      float f[4];
+      load_row4(f, given, token(c), D.n, 0.f);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) win[4 + i] = f[i];
+    }
+  }
+  __device__ __forceinline__ void values(float (&f)[4], const float (&win)[12], int c) const {
+    if (u != nullptr) {
+      pool_reduce(f, win, u, token(c), pool);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (fabsf(f[i]) < FLT_MIN) f[i] = 0.f;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[i] = win[4 + i];
+    }
+  }
+  // k: the chunk's score keys (0 past the end); lifted ones already hold the key of +inf where kLds
+  __device__ __forceinline__ void put_keys(const uint32_t (&k)[4], int c) {
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) key[4 * c + i] = k[i];
+    } else if constexpr (kLds) {
+      *reinterpret_cast<uint4*>(&sh.row[token(c)]) = make_uint4(k[0], k[1], k[2], k[3]);
+    } else {
+      reinterpret_cast<uint8_t*>(sh.row)[token(c) >> 2] = 0;
+    }
+  }
+  __device__ __forceinline__ void lift(uint32_t slot, int c) {         // bit i: token i of the chunk
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if ((slot >> i) & 1u) key[4 * c + i] = kHiFrom;
+    } else if constexpr (kLds) {
+      slots |= (uint64_t)slot << (4 * c);
+    } else {
+      reinterpret_cast<uint8_t*>(sh.row)[token(c) >> 2] = (uint8_t)slot;
+    }
+  }
+  template <class Use>
+  __device__ __forceinline__ void each_key_chunk(Use&& use) {
+    chunks<Keys4>(
+        [&](uint32_t (&k)[4], int c) {
+          if constexpr (kRegs) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k[i] = key[4 * c + i];
+          } else if constexpr (kLds) {
+            const uint4 v = *reinterpret_cast<const uint4*>(&sh.row[token(c)]);
+            k[0] = v.x; k[1] = v.y; k[2] = v.z; k[3] = v.w;
+          } else {
+            float win[12], f[4];
+            load_window(win, c);
+            values(f, win, c);
+            const uint32_t flags = reinterpret_cast<const uint8_t*>(sh.row)[token(c) >> 2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k[i] = token(c) + i < D.n ? ((flags >> i) & 1u ? kHiFrom : score_key(f[i])) : 0u;
+          }
+        },
+        use);
+  }
+};
+
+// Executed by a whole workgroup of THREADS threads.
+// row.u given: score <- pooled u with +inf at the NuC slots, written to `scores` if that is not null.
+// else: score <- row.given.
+// SELECT: emit(place, token, c, i) is called by the thread that owns it for every kept token (the top-k of score), in
+// ascending order of a thread's tokens; c, i: its chunk and place in it.  Ends without a barrier.
+//
+// Barriers, when the row's keys are ordinary, no bin holds more than 64 candidates and T > 0: classes (of novelty and
+// scores together; one after the other where they take turns in LDS), two per threshold, ranks - six in all, or seven.
+template <int THREADS, int CH, bool SELECT, class Emit>
+__device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_row, Emit&& emit) {
+  using R = Row<THREADS, CH>;
+  const Dims& D = row.D;
+  SelectShared<THREADS, CH>& sh = row.sh;
+  const int n = D.n;
+  row.load_novelty();
+  topk_clear(sh.topk);
+
+  const bool lift = row.u != nullptr && D.T > 0;
+  const bool score_first = !R::kLds || !lift;
+  KeyClasses cs{0xFFFFFFFFu, 0u, 0u, 0u}, cn{0xFFFFFFFFu, 0u, 0u, 0u};
+  auto score_stage = [&]() {
+    row.template chunks<typename R::Window>(
+        [&](float (&win)[12], int c) { row.load_window(win, c); },
+        [&](float (&win)[12], int c) {
+          float f[4];
+          row.values(f, win, c);
+          uint32_t k[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) k[i] = row.token(c) + i < n ? score_key(f[i]) : 0u;
+          if constexpr (R::kLds) {
+            const uint32_t slot = (uint32_t)(row.slots >> (4 * c)) & 15u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if ((slot >> i) & 1u) { k[i] = kHiFrom; f[i] = INFINITY; }
+          }
+          // (elsewhere the slots of the NuC tokens are overwritten below)
+          if (row.u != nullptr && scores_row != nullptr) store_row4(scores_row, row.token(c), n, f);
+          if constexpr (SELECT) {
+            row.put_keys(k, c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) classify(k[i], cs);
+          }
+        });
+    if (SELECT) publish_classes(cs, sh.topk, 0);
+  };
+  if (score_first) score_stage();
+  if (lift) {
+    row.first_novelty_chunks([&](const uint32_t (&k)[4], int) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) classify(k[i], cn);
+    });
+    publish_classes(cn, sh.topk, 1);
+  }
+  if (SELECT || lift) __syncthreads();
+
+  uint32_t n_slots = 0;
+  if (lift) {
+    cn = combine_classes(sh.topk, 1);
+    n_slots = min((uint32_t)D.T, cn.n_hi + cn.n_mid);     // NaN and -inf never take a slot
+  }
+  if (n_slots > 0) {
+    auto each_novelty_key = [&](auto&& f) {
+      row.each_novelty_chunk([&](const uint32_t (&k)[4], int) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f(k[i]);
+      });
+    };
+    const Threshold th = n_slots <= cn.n_hi
+                             ? Threshold{kHiFrom, n_slots, cn.n_hi}
+                             : radix_threshold(each_novelty_key, cn.mn, cn.mx, n_slots - cn.n_hi, cn.n_mid, sh.topk, 0);
+    const bool some = th.need < th.n_eq;                  // only some of the equal tokens: by rank in token order
+    auto equal_before = [&](const uint32_t (&k)[4], uint32_t& mine) {     // inclusive scan over the wave's round
+      mine = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mine += k[i] == th.tau ? 1u : 0u;
+      return wave_inclusive_scan(mine, 0u, OpAdd{});
+    };
+    if (some) {
+      row.each_novelty_chunk([&](const uint32_t (&k)[4], int c) {
+        uint32_t mine;
+        put_round_sum<THREADS>(equal_before(k, mine), sh.sums[0], c);
+      });
       __syncthreads();
     }
-    if (stage) uu = u_stage + kStagePad;
-    if (BLOCKED && pooling && D.pool_w <= 2 * kStagePad + 1) {
-      pooled_block<KPT>(sc, u_stage, tid * KPT, n, D.pool_w, D.pool_mode);
-    } else {
+    row.each_novelty_chunk([&](const uint32_t (&k)[4], int c) {
+      uint32_t slot = 0;
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const int t = owned_token<THREADS, KPT, BLOCKED>(tid, j);
-        sc[j] = t < n ? pooled(uu, t, n, D.pool_w, D.pool_mode) : 0.f;
+      for (int i = 0; i < 4; ++i) slot |= k[i] >= th.tau ? 1u << i : 0u;
+      if (some) {
+        uint32_t mine;
+        const uint32_t inc = equal_before(k, mine);
+        uint32_t eq = RoundBases<THREADS, RowStore<THREADS, CH>::kMaxChunks>(sh.sums[0], row.rounds).of(c) + inc - mine;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (k[i] == th.tau && eq++ >= th.need) slot &= ~(1u << i);
       }
-    }
+      if (!R::kLds && scores_row != nullptr) {
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const int t = owned_token<THREADS, KPT, BLOCKED>(tid, j);
-      float v = sc[j];
-      sc[j] = -INFINITY;
-      if (t < n) {
-        if (fabsf(v) < FLT_MIN) v = 0.f;
-        sc[j] = ((nuc >> j) & 1u) ? INFINITY : v;
-        if (scores != nullptr) scores[(int64_t)unit * n + t] = sc[j];
+        for (int i = 0; i < 4; ++i)
+          if ((slot >> i) & 1u) scores_row[row.token(c) + i] = INFINITY;
       }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const int t = owned_token<THREADS, KPT, BLOCKED>(tid, j);
-      sc[j] = t < n ? scores[(int64_t)unit * n + t] : -INFINITY;
-    }
+      if (SELECT || R::kLds) row.lift(slot, c);
+    });
   }
-
-  if (keep_idx != nullptr || keep_lds != nullptr) {
-    int32_t* out = keep_idx != nullptr ? keep_idx + (int64_t)unit * D.k : nullptr;
-    uint32_t key[KPT];
+  if (!score_first) {
+    score_stage();
+    if (SELECT) __syncthreads();
+  }
+  if constexpr (SELECT) {
+    auto each_key = [&](auto&& f) {
+      row.each_key_chunk([&](const uint32_t (&k)[4], int) {
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) key[j] = score_key(sc[j]);
-    uint32_t tau, need;
-    radix_threshold<THREADS, KPT, BLOCKED, false>([&](int j, int) { return key[j]; }, n, (uint32_t)D.k, sh, phase, tau, need);
-    if (BLOCKED) {
-      // token order is thread order, then j.  A token's place among the kept ones is the number of larger keys
-      // before it plus the number of threshold ties before it, capped at `need`: one scan over the two per-thread
-      // counts packed into one word (blocked ownership is only used for n <= 32768, so both stay below 2^16)
-      uint32_t n_gt = 0, n_eq = 0;
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const bool valid = tid * KPT + j < n;
-        n_gt += (valid && key[j] > tau) ? 1u : 0u;
-        n_eq += (valid && key[j] == tau) ? 1u : 0u;
-      }
-      uint32_t tot;
-      const uint32_t before = block_exclusive_scan<THREADS>((n_gt << 16) | n_eq, sh, phase, tot);
-      uint32_t gt_rank = before >> 16, eq_rank = before & 0xFFFFu;
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const bool valid = tid * KPT + j < n;
-        const bool gt = valid && key[j] > tau, eq = valid && key[j] == tau;
-        if (gt || (eq && eq_rank < need)) {
-          const uint32_t pos = gt_rank + min(eq_rank, need);
-          if (out != nullptr) out[pos] = tid * KPT + j;
-          if (keep_lds != nullptr) keep_lds[pos] = tid * KPT + j;
-        }
-        gt_rank += gt ? 1u : 0u;
-        eq_rank += eq ? 1u : 0u;
-      }
-    } else {
-      uint32_t eq_base = 0, out_base = 0;
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        if (j * THREADS >= n) continue;      // uniform: whole rounds beyond n are skipped
-        const int t = tid + j * THREADS;
-        const bool eq = t < n && key[j] == tau;
-        uint32_t tot;
-        const uint32_t erank = block_rank<THREADS>(eq, sh, phase, tot);
-        const bool sel = t < n && (key[j] > tau || (eq && eq_base + erank < need));
-        eq_base += tot;
-        const uint32_t srank = block_rank<THREADS>(sel, sh, phase, tot);
-        if (sel) out[out_base + srank] = t;
-        out_base += tot;
+        for (int i = 0; i < 4; ++i) f(k[i]);
+      });
+    };
+    cs = combine_classes(sh.topk, 0);
+    if (lift && score_first) {
+      if (cs.n_mid < (uint32_t)n) {
+        // rows with -inf, NaN or +inf among the pooled scores: which of them were lifted is only known now
+        KeyClasses c2{0xFFFFFFFFu, 0u, 0u, 0u};
+        each_key([&](uint32_t k) { classify(k, c2); });
+        publish_classes(c2, sh.topk, 2);
+        __syncthreads();
+        cs = combine_classes(sh.topk, 2);
+      } else {
+        cs.n_hi = n_slots;                                // all ordinary before the lift; the range may be a little wide
+        cs.n_mid = (uint32_t)n - n_slots;
       }
     }
+    const uint32_t k = (uint32_t)D.k;
+    Threshold th;
+    if (k <= cs.n_hi)                 th = {kHiFrom, k, cs.n_hi};
+    else if (k <= cs.n_hi + cs.n_mid) th = radix_threshold(each_key, cs.mn, cs.mx, k - cs.n_hi, cs.n_mid, sh.topk, 1);
+    else                              th = {kLoUpTo, k - cs.n_hi - cs.n_mid, (uint32_t)n - cs.n_hi - cs.n_mid};
+    // a token's place among the kept ones is the number of larger keys before it plus the number of threshold ties
+    // before it, capped at `need`: both counts in one word (at most 65536 tokens, so exclusive counts fit 16 bits)
+    auto count = [&](const uint32_t (&k)[4]) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v += (k[i] > th.tau ? 0x10000u : 0u) + (k[i] == th.tau ? 1u : 0u);
+      return v;
+    };
+    row.each_key_chunk([&](const uint32_t (&k)[4], int c) {
+      put_round_sum<THREADS>(wave_inclusive_scan(count(k), 0u, OpAdd{}), sh.sums[1], c);
+    });
+    __syncthreads();
+    const RoundBases<THREADS, RowStore<THREADS, CH>::kMaxChunks> bases(sh.sums[1], row.rounds);
+    row.each_key_chunk([&](const uint32_t (&k)[4], int c) {
+      const uint32_t mine = count(k);
+      const uint32_t before = bases.of(c) + wave_inclusive_scan(mine, 0u, OpAdd{}) - mine;
+      uint32_t gt = before >> 16, eq = before & 0xFFFFu;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool is_gt = k[i] > th.tau, is_eq = k[i] == th.tau;
+        if (is_gt || (is_eq && eq < th.need)) emit((int)(gt + min(eq, th.need)), row.token(c) + i, c, i);
+        gt += is_gt ? 1u : 0u;
+        eq += is_eq ? 1u : 0u;
+      }
+    });
   }
 }
 

@@ -1,19 +1,28 @@
-// Exact top-k threshold selection inside one workgroup, shared by the NuC-slot job and the final selection.
+// Exact top-k threshold selection inside one workgroup, shared by the NuC slots and the final selection.
 //
-// Keys are order-preserving 32-bit images of fp32 values.  An MSB-first radix select with digits of up to 11 bits
+// Keys are order-preserving 32-bit images of fp32 values.  An MSB-first radix select with digits of up to 10 bits
 // (LDS histogram, one atomic per candidate key and pass) over the range the keys actually span yields the threshold
-// key tau and the number `need` of keys equal to tau that still belong to the k largest: a token is selected iff key > tau, or key == tau and fewer than
-// `need` equal tokens precede it in token order (lowest index wins ties).
+// key tau and the number `need` of keys equal to tau that still belong to the k largest: a token is selected iff
+// key > tau, or key == tau and fewer than `need` equal tokens precede it in token order (lowest index wins ties).
+//
+// What bounds it: nothing but latency.  A row is a few KB, yet every step depends on the step before it, and a barrier
+// with the cross-wave bookkeeping around it costs about 0.9 us with 16 waves.  Hence eight waves instead of 16 where the
+// kernel has no other use for them (the bookkeeping is per wave), counts by ballots on the scalar unit, and every wave works out digits and thresholds for
+// itself from LDS instead of having one wave do it and broadcast: one barrier per histogram pass and one behind the last
+// candidates, where three and two were needed.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace ccd {
 
-constexpr int kRadixBins = 2048;
+constexpr int kBinBits = 10, kBins = 1 << kBinBits;
 constexpr int kCandMax = 256;   // at most this many keys left in the chosen bin: they are ranked directly
 
-// fp32 -> uint32 with the same order; NaN ranks with -inf and -0 equals +0
+constexpr uint32_t kHiFrom = 0xFF800000u;   // score_key(+inf)
+constexpr uint32_t kLoUpTo = 0x007FFFFFu;   // score_key(-inf)
+
+// fp32 -> uint32 with the same order; NaN ranks with -inf and -0 equals +0.  No key is 0.
 __device__ __forceinline__ uint32_t score_key(float x) {
   if (x != x) x = -INFINITY;
   x += 0.0f;
@@ -39,221 +48,202 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, uint32_t ide
   v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31
   return v;
 }
-// the operation over all 64 lanes, in every lane
+struct OpAdd { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
+struct OpMin { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return min(a, b); } };
+struct OpMax { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return max(a, b); } };
+// the operation over all 64 lanes, as a scalar
 template <class Op>
 __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t identity, Op op) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v, identity, op), 63);
 }
+// the operation over each aligned group of N = 8 or 16 lanes, as a scalar; all groups hold the same values
+template <int N, class Op>
+__device__ __forceinline__ uint32_t reduce_group(uint32_t v, Op op) {
+  static_assert(N == 8 || N == 16, "");
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));    // quad_perm [2,3,0,1]
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));   // row_half_mirror
+  if (N == 16) v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // row_mirror
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 
+// what radix_threshold and its callers share in LDS; two sets of everything, so that the NuC slots and the final
+// selection need no barrier between them
 template <int THREADS>
 struct TopkShared {
-  uint32_t hist[kRadixBins];
-  uint32_t wave_sum[2][THREADS / 64];   // ping-pong: one barrier per scan
-  uint32_t red[4][THREADS / 64];        // per-wave class counts and key range of radix_threshold
-  uint32_t digit, remaining;
-  uint32_t bin_count, cand_n;           // keys in the chosen bin; candidates gathered so far
-  uint32_t cand_key[kCandMax];          // the keys that share all digits fixed so far, once they are few
+  static constexpr int kWaves = THREADS / 64;
+  __attribute__((aligned(16))) uint32_t hist[2][kBins];
+  __attribute__((aligned(16))) uint32_t cand[2][kCandMax];   // the keys that share all digits fixed so far, once they are few
+  uint4 classes[3][kWaves];                                  // per wave: class counts and key range (KeyClasses)
+  uint32_t cand_n[2];
+  uint32_t found[2][3];                                      // threshold among more than 64 candidates
 };
-
-// Exclusive prefix sum of v over the workgroup in thread order; `total` receives the workgroup's sum.
+// to be followed by a barrier before the first radix_threshold
 template <int THREADS>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, TopkShared<THREADS>& sh, int& phase, uint32_t& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t inc = wave_inclusive_scan(v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-  if (lane == 63) sh.wave_sum[phase][wave] = inc;
-  __syncthreads();
-  uint32_t before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < THREADS / 64; ++w) {
-    const uint32_t c = sh.wave_sum[phase][w];
-    before += (w < wave) ? c : 0u;
-    tot += c;
-  }
-  phase ^= 1;
-  total = tot;
-  return before + inc - v;
+__device__ __forceinline__ void topk_clear(TopkShared<THREADS>& sh) {
+  for (int i = threadIdx.x; i < 2 * kBins / 4; i += THREADS) reinterpret_cast<uint4*>(&sh.hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < 2 * kCandMax / 4) reinterpret_cast<uint4*>(&sh.cand[0][0])[threadIdx.x] = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < 2) sh.cand_n[threadIdx.x] = 0;
 }
 
-// Exclusive prefix count of a predicate (ballot/popcount inside the wave).
+// Scores of one row share a few exponents, and a quarter or half of them are the +inf of the NuC slots: the top bits of
+// such keys fall into a handful of histogram bins, and a wave's 64 LDS atomics on one address serialise.  So keys are
+// split into three classes by fixed bounds - at or above the key of +inf, at or below the key of -inf, ordinary - with
+// counts and, for the ordinary ones, the range.  The class that holds the k-th largest is known from the counts; inside
+// it - the two outer ones hold a single value each - the digits are taken from key - mn over the range actually spanned.
+struct KeyClasses { uint32_t mn, mx, n_mid, n_hi; };
+
+// A thread's keys folded into its wave's classes (counts are wave totals and scalar; mn and mx are per lane)
+__device__ __forceinline__ void classify(uint32_t key, KeyClasses& c) {
+  const bool hi = key >= kHiFrom, mid = !hi && key > kLoUpTo;
+  c.n_hi += (uint32_t)__popcll(__ballot(hi));
+  c.n_mid += (uint32_t)__popcll(__ballot(mid));
+  c.mn = mid ? min(c.mn, key) : c.mn;
+  c.mx = mid ? max(c.mx, key) : c.mx;
+}
+// set `which` of sh.classes; a barrier, then combine_classes
 template <int THREADS>
-__device__ __forceinline__ uint32_t block_rank(bool pred, TopkShared<THREADS>& sh, int& phase, uint32_t& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t bal = __ballot(pred);
-  const uint32_t r = __popcll(bal & ((1ull << lane) - 1ull));
-  if (lane == 0) sh.wave_sum[phase][wave] = __popcll(bal);
-  __syncthreads();
-  uint32_t before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < THREADS / 64; ++w) {
-    const uint32_t c = sh.wave_sum[phase][w];
-    before += (w < wave) ? c : 0u;
-    tot += c;
-  }
-  phase ^= 1;
-  total = tot;
-  return before + r;
+__device__ __forceinline__ void publish_classes(KeyClasses c, TopkShared<THREADS>& sh, int which) {
+  const uint32_t mn = wave_reduce(c.mn, 0xFFFFFFFFu, OpMin{}), mx = wave_reduce(c.mx, 0u, OpMax{});
+  if ((threadIdx.x & 63) == 0) sh.classes[which][threadIdx.x >> 6] = make_uint4(mn, mx, c.n_mid, c.n_hi);
+}
+template <int THREADS>
+__device__ __forceinline__ KeyClasses combine_classes(const TopkShared<THREADS>& sh, int which) {
+  constexpr int W = THREADS / 64;
+  const uint4 v = sh.classes[which][threadIdx.x & (W - 1)];
+  return {reduce_group<W>(v.x, OpMin{}), reduce_group<W>(v.y, OpMax{}), reduce_group<W>(v.z, OpAdd{}), reduce_group<W>(v.w, OpAdd{})};
 }
 
-// Threshold of the kk largest of the keys of tokens 0 .. n-1, 1 <= kk <= n.  Thread tid owns KPT tokens
-// (n <= THREADS * KPT): tid + j*THREADS, or tid*KPT + j when BLOCKED; key_of(j, t) returns the key of the thread's
-// j-th token t, which the caller holds in registers.
-// On return #{key > tau} < kk <= #{key >= tau} and need = kk - #{key > tau}.  Ends with a barrier.
-// ABOVE_LOW_ONLY: keys at or below the key of -inf never qualify (novelty: NaN and -inf map to key 0): kk is first
-// cut down to the number of other keys, and if none is left nothing is selected (tau = 0xFFFFFFFF, need = 0).
-//
-// Scores of one row share a few exponents, and a quarter or half of them are the +inf of the NuC slots: the top
-// 11 bits of such keys fall into a handful of histogram bins, and a wave's 64 LDS atomics on one address serialise
-// (measured: 5.2 us for the first pass against 1.4 us for the later ones).  So the keys are first split into three
-// classes by fixed bounds - at or above the key of +inf, at or below the key of -inf, ordinary - with counts and, for
-// the ordinary ones, minimum and maximum from one workgroup reduction.  The class that holds the kk-th largest is
-// known from the counts; inside it the digits are taken from key - lo over the range hi - lo actually spanned, most
-// significant first, 11 bits at a time (fewer passes when the range is narrow, none when it is a single value).
-template <int THREADS, int KPT, bool BLOCKED = false, bool ABOVE_LOW_ONLY = false, class KeyFn>
-__device__ __forceinline__ void radix_threshold(KeyFn key_of, int n, uint32_t kk, TopkShared<THREADS>& sh, int& phase, uint32_t& tau,
-                                uint32_t& need) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kBinsPerThread = kRadixBins / THREADS;
-  constexpr int kWaves = THREADS / 64;
-  static_assert(THREADS >= kCandMax, "one thread ranks one candidate");
-  constexpr uint32_t kHiFrom = 0xFF800000u;   // score_key(+inf)
-  constexpr uint32_t kLoUpTo = 0x007FFFFFu;   // score_key(-inf)
+struct Threshold { uint32_t tau, need, n_eq; };   // n_eq: keys equal to tau in all; need of them are wanted
 
-  // class counts and the range of the ordinary keys
-  uint32_t c_hi = 0, c_mid = 0, mn = 0xFFFFFFFFu, mx = 0u;
-#pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    const int t = BLOCKED ? tid * KPT + j : tid + j * THREADS;
-    if (t < n) {
-      const uint32_t key = key_of(j, t);
-      const bool hi = key >= kHiFrom, mid = !hi && key > kLoUpTo;
-      c_hi += hi ? 1u : 0u;
-      c_mid += mid ? 1u : 0u;
-      mn = mid ? min(mn, key) : mn;
-      mx = mid ? max(mx, key) : mx;
-    }
-  }
-  c_hi = wave_reduce(c_hi, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-  c_mid = wave_reduce(c_mid, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-  mn = wave_reduce(mn, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
-  mx = wave_reduce(mx, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
-  for (int i = tid; i < kRadixBins; i += THREADS) sh.hist[i] = 0;
-  if (lane == 0) {
-    sh.red[0][wave] = c_hi;
-    sh.red[1][wave] = c_mid;
-    sh.red[2][wave] = mn;
-    sh.red[3][wave] = mx;
-  }
-  __syncthreads();                             // wave results and the cleared histogram are visible
-  uint32_t n_hi = 0, n_mid = 0;
-  mn = 0xFFFFFFFFu;
-  mx = 0u;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    n_hi += sh.red[0][w];
-    n_mid += sh.red[1][w];
-    mn = min(mn, sh.red[2][w]);
-    mx = max(mx, sh.red[3][w]);
-  }
-
-  if (ABOVE_LOW_ONLY) {
-    kk = min(kk, n_hi + n_mid);
-    if (kk == 0) {                               // uniform
-      __syncthreads();
-      tau = 0xFFFFFFFFu;
-      need = 0;
-      return;
-    }
-  }
-  // the class of the kk-th largest key: candidates are the keys in [lo, hi]; `remaining` of them are wanted
-  uint32_t lo, hi, remaining;
-  if (kk <= n_hi) {
-    lo = kHiFrom; hi = 0xFFFFFFFFu; remaining = kk;
-  } else if (kk <= n_hi + n_mid) {
-    lo = mn; hi = mx; remaining = kk - n_hi;
-  } else {
-    lo = 0u; hi = kLoUpTo; remaining = kk - n_hi - n_mid;
-  }
-  int rem_bits = 32 - __clz(hi - lo);          // bits of key - lo not yet fixed (__clz(0) = 32)
-  if (rem_bits == 0) __syncthreads();          // a single candidate value: no pass, but still end with a barrier
+// The `remaining`-th largest of the `count` keys of the workgroup that lie in [lo, hi] (1 <= remaining <= count).
+// each_key(f): calls f(key) for every key of the thread; keys outside [lo, hi] take no part.  hist[which] must be cleared
+// and the clearing visible; ends without a barrier.
+template <int THREADS, class EachKey>
+__device__ __forceinline__ Threshold radix_threshold(EachKey&& each_key, uint32_t lo, uint32_t hi, uint32_t remaining,
+                                                     uint32_t count, TopkShared<THREADS>& sh, int which) {
+  const int lane = threadIdx.x & 63;
+  uint32_t* hist = sh.hist[which];
+  const uint32_t span = hi - lo;
+  int rem_bits = 32 - __clz(span);             // bits of key - lo not yet fixed (__clz(0) = 32)
   uint32_t prefix = 0;                         // the fixed high bits of tau - lo, as a value (already shifted down)
+  if (rem_bits == 0) return {lo, remaining, count};
+  bool first = true;
 #pragma unroll 1
-  while (rem_bits > 0) {
-    const int width = min(11, rem_bits), shift = rem_bits - width;
+  while (true) {
+    const int width = min(kBinBits, rem_bits), shift = rem_bits - width;
     const uint32_t dmask = (1u << width) - 1u;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const int t = BLOCKED ? tid * KPT + j : tid + j * THREADS;
-      if (t < n) {
-        const uint32_t key = key_of(j, t);
-        const uint32_t rel = key - lo;
-        if (key >= lo && key <= hi && (uint32_t)((uint64_t)rel >> rem_bits) == prefix)
-          atomicAdd(&sh.hist[(rel >> shift) & dmask], 1u);
-      }
-    }
+    each_key([&](uint32_t key) {
+      const uint32_t rel = key - lo;
+      if (rel <= span && (first || (rel >> rem_bits) == prefix)) atomicAdd(&hist[(rel >> shift) & dmask], 1u);
+    });
     __syncthreads();
-    // thread 0 owns the highest bins: prefix sums in thread order are counts of larger digits.  Each thread
-    // clears the bins it has read: the histogram is zero again before the next pass adds to it (two barriers on).
-    uint32_t h[kBinsPerThread], mine = 0;
+    // Lane 0 owns the highest 16 bins, so inclusive sums in lane order count the keys of larger digits; then the same over
+    // the bins of the lane in which the wanted key falls.
+    constexpr int kPerLane = kBins / 64;
+    uint32_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < kBinsPerThread; ++i) {
-      const int bin = kRadixBins - 1 - (tid * kBinsPerThread + i);
-      h[i] = sh.hist[bin];
-      sh.hist[bin] = 0;
-      mine += h[i];
+    for (int i = 0; i < kPerLane; i += 4) {
+      const uint4 v = *reinterpret_cast<const uint4*>(&hist[kBins - kPerLane * (lane + 1) + i]);
+      mine += v.x + v.y + v.z + v.w;
     }
-    uint32_t tot;
-    uint32_t excl = block_exclusive_scan<THREADS>(mine, sh, phase, tot);
-#pragma unroll
-    for (int i = 0; i < kBinsPerThread; ++i) {
-      const uint32_t incl = excl + h[i];
-      if (excl < remaining && remaining <= incl) {
-        sh.digit = kRadixBins - 1 - (tid * kBinsPerThread + i);
-        sh.remaining = remaining - excl;
-        sh.bin_count = h[i];
-        sh.cand_n = 0;
-      }
-      excl = incl;
-    }
-    __syncthreads();
-    prefix = (prefix << width) | sh.digit;
-    remaining = sh.remaining;
+    const uint32_t incl = wave_inclusive_scan(mine, 0u, OpAdd{});
+    const int owner = __ffsll((unsigned long long)__ballot(incl >= remaining)) - 1;
+    remaining -= (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), owner);
+    const int top = kBins - kPerLane * owner - 1;           // the owner's highest bin
+    const uint32_t h = lane < kPerLane ? hist[top - lane] : 0u;
+    const uint32_t incl2 = wave_inclusive_scan(h, 0u, OpAdd{});
+    const int at_bin = __ffsll((unsigned long long)__ballot(incl2 >= remaining)) - 1;
+    const uint32_t n_cand = (uint32_t)__builtin_amdgcn_readlane((int)h, at_bin);
+    remaining -= (uint32_t)__builtin_amdgcn_readlane((int)incl2, at_bin) - n_cand;
+    const uint32_t dig = (uint32_t)(top - at_bin);
+    prefix = (prefix << width) | dig;
     rem_bits = shift;
-    const uint32_t n_cand = sh.bin_count;
-    if (rem_bits > 0 && n_cand <= (uint32_t)kCandMax) {      // uniform over the workgroup
+    first = false;
+    if (rem_bits == 0) return {lo + prefix, remaining, n_cand};
+    if (n_cand <= (uint32_t)kCandMax) {
       // Few keys share the digits fixed so far (the digits are spread over the range, so this is the rule after one
       // pass): gather them and rank them against each other instead of two more histogram passes.
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const int t = BLOCKED ? tid * KPT + j : tid + j * THREADS;
-        if (t < n) {
-          const uint32_t key = key_of(j, t);
-          const uint32_t rel = key - lo;
-          if (key >= lo && key <= hi && (uint32_t)((uint64_t)rel >> rem_bits) == prefix)
-            sh.cand_key[atomicAdd(&sh.cand_n, 1u)] = key;
-        }
-      }
+      each_key([&](uint32_t key) {
+        const uint32_t rel = key - lo;
+        if (rel <= span && (rel >> rem_bits) == prefix) sh.cand[which][atomicAdd(&sh.cand_n[which], 1u)] = key;
+      });
       __syncthreads();
-      if ((uint32_t)tid < n_cand) {
-        const uint32_t mine = sh.cand_key[tid];
+      // gt = candidates above mine; the wanted key is the smallest one with fewer than `remaining` above it.  (The list is
+      // padded with zeros, which are above nothing; it is read four at a time, all lanes the same address.)
+      const uint4* list = reinterpret_cast<const uint4*>(sh.cand[which]);
+      if (n_cand <= 64) {
+        const uint32_t c = sh.cand[which][lane];
+        uint32_t gt = 0;
+        for (uint32_t i = 0; i < n_cand; i += 8) {
+          const uint4 v = list[i / 4], w = list[i / 4 + 1];
+          gt += (v.x > c ? 1u : 0u) + (v.y > c ? 1u : 0u) + (v.z > c ? 1u : 0u) + (v.w > c ? 1u : 0u);
+          gt += (w.x > c ? 1u : 0u) + (w.y > c ? 1u : 0u) + (w.z > c ? 1u : 0u) + (w.w > c ? 1u : 0u);
+        }
+        const uint32_t tau = wave_reduce(gt < remaining && (uint32_t)lane < n_cand ? c : 0xFFFFFFFFu, 0xFFFFFFFFu, OpMin{});
+        const uint64_t is = __ballot(c == tau);
+        return {tau, remaining - (uint32_t)__builtin_amdgcn_readlane((int)gt, __ffsll((unsigned long long)is) - 1),
+                (uint32_t)__popcll(is)};
+      }
+      if (threadIdx.x < n_cand) {
+        const uint32_t c = sh.cand[which][threadIdx.x];
         uint32_t gt = 0, ge = 0;
-        for (uint32_t i = 0; i < n_cand; ++i) {
-          const uint32_t other = sh.cand_key[i];
-          gt += other > mine ? 1u : 0u;
-          ge += other >= mine ? 1u : 0u;
+        for (uint32_t i = 0; i < n_cand; i += 4) {
+          const uint4 v = list[i / 4];
+          gt += (v.x > c ? 1u : 0u) + (v.y > c ? 1u : 0u) + (v.z > c ? 1u : 0u) + (v.w > c ? 1u : 0u);
+          ge += (v.x >= c ? 1u : 0u) + (v.y >= c ? 1u : 0u) + (v.z >= c ? 1u : 0u) + (v.w >= c ? 1u : 0u);
         }
-        if (gt < remaining && remaining <= ge) {             // the threshold key (equal keys write the same values)
-          sh.digit = mine;
-          sh.remaining = remaining - gt;
+        if (gt < remaining && remaining <= ge) {             // (equal keys write the same values)
+          sh.found[which][0] = c;
+          sh.found[which][1] = remaining - gt;
+          sh.found[which][2] = ge - gt;
         }
       }
       __syncthreads();
-      tau = sh.digit;
-      need = sh.remaining;
-      return;
+      return {sh.found[which][0], sh.found[which][1], sh.found[which][2]};
+    }
+    __syncthreads();                           // every wave has read the histogram
+    for (int i = threadIdx.x; i < kBins / 4; i += THREADS) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+  }
+}
+
+// Ranks in token order.  A row is dealt out in chunks of four consecutive tokens: chunk c of thread t starts at token
+// 4 (c * THREADS + t), so the 64 chunks of a wave's round c follow each other, and the rounds c * (THREADS / 64) + wave
+// follow each other in the row.  `sums` (LDS, MAXCH * THREADS / 64 words): every wave puts the total of each of its rounds there
+// (put_round_sum), a barrier, then RoundBases hands out the sum of all rounds before one.
+template <int THREADS>
+__device__ __forceinline__ void put_round_sum(uint32_t inclusive, uint32_t* sums, int c) {
+  if ((threadIdx.x & 63) == 63) sums[c * (THREADS / 64) + (threadIdx.x >> 6)] = inclusive;
+}
+template <int THREADS, int MAXCH>
+struct RoundBases {
+  static constexpr int kWaves = THREADS / 64;
+  static constexpr int kPer = (MAXCH * kWaves + 63) / 64;   // entry e sits in lane e / kPer
+  static_assert(kWaves % kPer == 0, "the place of a wave's entries inside a lane does not depend on c");
+  uint32_t s;
+  int wave;
+  __device__ __forceinline__ RoundBases(const uint32_t* sums, int rounds) {
+    const int lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t v[kPer], mine = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = lane * kPer + i;
+      v[i] = e < rounds * kWaves ? sums[e] : 0u;
+      mine += v[i];
+    }
+    uint32_t run = wave_inclusive_scan(mine, 0u, OpAdd{}) - mine;
+    s = run;
+#pragma unroll
+    for (int i = 1; i < kPer; ++i) {
+      run += v[i - 1];
+      s = wave % kPer == i ? run : s;
     }
   }
-  tau = lo + prefix;
-  need = remaining;
-}
+  __device__ __forceinline__ uint32_t of(int c) const {
+    return (uint32_t)__builtin_amdgcn_readlane((int)s, (c * kWaves + wave) / kPer);
+  }
+};
 
 }  // namespace ccd

@@ -185,7 +185,7 @@ static bool path_refused(const Dims& D, const ScorePlan& pl) {
 }
 
 struct Workspace {
-  size_t off_part, off_lse, off_u, total;
+  size_t off_part, off_lse, off_u, off_sync, total;
 };
 
 // The layout does not depend on the kernel path, so a workspace sized once serves either.
@@ -196,6 +196,7 @@ static Workspace layout_workspace(const Dims& D) {
   w.off_part = off;   off = align_up(off + (size_t)D.units * max_slices * D.GP * sizeof(float2), 256);
   w.off_lse = off;    off = align_up(off + (size_t)D.units * D.GP * sizeof(float), 256);
   w.off_u = off;      off = align_up(off + (size_t)D.units * D.n * sizeof(float), 256);
+  w.off_sync = off;   off = align_up(off + (size_t)D.units * kSyncWords * sizeof(uint32_t), 256);
   w.total = off;
   return w;
 }
@@ -451,7 +452,7 @@ static int compress_impl(const ccd_shape_t* shape, const void* Q_cat, void* K, v
   if (!aligned16(lse)) return CCD_EALIGN;
   const void* K_attn = K_score != nullptr ? K_score : K;     // the keys the CaP queries attend to
   const Dims D = make_dims(shape);
-  const ScorePlan pl = plan_score(D, K_cap != nullptr);
+  ScorePlan pl = plan_score(D, K_cap != nullptr);
   if (path_refused(D, pl)) return CCD_EUNSUPPORTED;
   if (pl.use_mfma && D.head - D.head0 > mfma_max_slice()) return CCD_EUNSUPPORTED;   // (a matrix-core path was named)
   const Workspace w = layout_workspace(D);
@@ -463,10 +464,12 @@ static int compress_impl(const ccd_shape_t* shape, const void* Q_cat, void* K, v
   const float* u = reinterpret_cast<const float*>(ws + w.off_u);
   const bool per_head = shape->nov_stride_l != 0 || shape->nov_stride_h != 0;
   if (g_prof.on) ++g_prof.calls;
+  uint32_t* sync = reinterpret_cast<uint32_t*>(ws + w.off_sync);
+  pl.sync = sync;
   run_cap_scores(D, pl, w, Q_cat, K_attn, K_cap, lse, ws, st);
   if (select_compact_supported(D)) {
     g_prof.begin(kStSelCompact, st);
-    launch_select_compact(D, u, novelty, per_head, scores_opt, keep_idx, K, V, rope_cos, rope_sin, K_rot, st);
+    launch_select_compact(D, u, novelty, per_head, scores_opt, keep_idx, K, V, rope_cos, rope_sin, K_rot, sync, st);
     g_prof.end(st);
     return launch_status();
   }

@@ -1,0 +1,82 @@
+"""Selection and compaction at the sizes where their kernels change: rows held in registers, in LDS or pooled anew, one
+workgroup per unit or several that share it, rows just below, at and above every limit; bit-exact against the oracle's
+selection of the same fp32 scores."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ccd_oracle as O
+from paper_2410_01518_amd import infinipot as ip
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [1, 3, 4, 63, 257, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16385, 32767, 32768, 32769, 65535]
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("n", ROWS)
+def test_select(n, ties):
+    """Scores as they come (spread, +inf of NuC slots, NaN, -inf, -0) or of a few values only: ties at the threshold."""
+    rng = np.random.default_rng(n)
+    s = rng.standard_normal((2, n)).astype(np.float32)
+    if ties:
+        s = np.round(s * 2.0) / 2.0
+    s[:, rng.random(n) < 0.2] = np.inf
+    s[1, rng.random(n) < 0.1] = -np.inf
+    s[1, rng.random(n) < 0.05] = np.nan
+    for k in sorted({1, max(1, n // 3), max(1, n - 1), n}):
+        K = torch.empty((1, 1, 2, n, 64), dtype=torch.bfloat16, device="cuda")
+        shape = ip.make_shape(None, K, None, k=k)
+        keep = torch.empty((1, 1, 2, k), dtype=torch.int32, device="cuda")
+        print(f"select n={n} k={k} ties={ties}", flush=True)
+        ip.ccd_select(shape, gu.to_dev(s.reshape(1, 1, 2, n)), keep)
+        want = np.stack([O.select(r, k) for r in s])
+        assert np.array_equal(gu.to_host(keep).reshape(2, k), want)
+
+
+# (units, n, k, fp32, rope): chunks of a shared unit at, below and above one pass, one ticket and several per workgroup, a
+# number of units just below and above the one that shares; rows in registers (one, two, four chunks a thread) and in LDS
+SHARED = [(1, 300, 1, False, False), (1, 300, 299, False, False), (1, 2048, 1024, True, False), (3, 2049, 700, False, True),
+          (2, 4097, 4000, False, False), (2, 8193, 5000, True, False), (1, 16390, 9000, False, True), (1, 32768, 20001, False, False),
+          (127, 600, 333, False, False), (128, 600, 333, False, False), (129, 600, 333, False, True), (2, 33000, 5000, False, False)]
+
+
+@pytest.mark.parametrize("units,n,k,fp32,rope", SHARED)
+@pytest.mark.parametrize("per_head", [True, False])
+def test_compress_moves_what_the_scores_say(units, n, k, fp32, rope, per_head):
+    g = torch.Generator(device="cuda").manual_seed(units * n + k)
+    dt = torch.float32 if fp32 else torch.bfloat16
+    d = 64
+    K = torch.randn((1, 1, units, n, d), generator=g, device="cuda").to(dt)
+    V = torch.randn((1, 1, units, n, d), generator=g, device="cuda").to(dt)
+    Q = torch.randn((1, 1, units, 2, d), generator=g, device="cuda").to(dt)
+    nov = torch.rand((1, 1, units, n) if per_head else (1, n), generator=g, device="cuda")
+    nov[..., : n // 4] = torch.round(nov[..., : n // 4] * 8) / 8          # ties among the NuC slots
+    K0, V0, nov0 = K.clone(), V.clone(), nov.clone()
+    shape = ip.make_shape(Q, K, nov, k=k, T=k // 2, pool_w=7)
+    ws = ip.alloc_workspace(shape)
+    ws.fill_(0xA5)                                                          # no reliance on what the workspace held
+    keep = torch.empty((1, 1, units, k), dtype=torch.int32, device="cuda")
+    scores = torch.empty((1, 1, units, n), dtype=torch.float32, device="cuda")
+    print(f"compress units={units} n={n} k={k} fp32={fp32} rope={rope} per_head={per_head}", flush=True)
+    if rope:
+        ang = torch.arange(k, device="cuda")[:, None] * 10000.0 ** (-2.0 * torch.arange(d // 2, device="cuda") / d)[None, :]
+        cos, sin, K_rot = ang.cos().contiguous(), ang.sin().contiguous(), torch.zeros_like(K)
+        ip.ccd_compress_rope(shape, Q, K, V, nov, keep, cos, sin, K_rot, ws, scores=scores)
+    else:
+        ip.ccd_compress(shape, Q, K, V, nov, keep, ws, scores=scores)
+    kh, sh = gu.to_host(keep).reshape(units, k), gu.to_host(scores).reshape(units, n)
+    assert (np.isposinf(sh).sum(1) == k // 2).all()
+    assert np.array_equal(kh, np.stack([O.select(r, k) for r in sh]))
+    idx = keep.long()[..., None].expand(-1, -1, -1, -1, d)
+    for new, old in ((K, K0), (V, V0)):
+        assert torch.equal(new[..., :k, :], torch.gather(old, 3, idx)) and torch.equal(new[..., k:, :], old[..., k:, :])
+    if per_head:
+        assert torch.equal(nov[..., :k], torch.gather(nov0, 3, keep.long())) and torch.equal(nov[..., k:], nov0[..., k:])
+    else:
+        assert torch.equal(nov, nov0)
+    if rope:
+        ref = torch.zeros_like(K)
+        ip.ccd_cr_rope(ip.make_shape(None, K, None, k=k), K, cos, sin, k, ref)
+        assert torch.equal(K_rot, ref)
