@@ -108,13 +108,22 @@ def _check(code: int) -> int:
     return code
 
 
+# The address and the stream handle go in as plain integers, which ctypes turns into pointers by the declared argument types.
+# torch.cuda.current_stream() builds a Stream object through several layers of Python (6 us of a call that takes 30 us in
+# all on a small pot); the raw handle is one C call.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -130,29 +139,24 @@ def make_shape(Q_cat, K, novelty, *, k, T=0, pool_w=1, pool_mode=CCD_POOL_MAX, s
     """Shape descriptor from tensor geometry: Q_cat [B,L,Hq,P,d], K [B,L,Hkv,n_cap,d], novelty [B,n] or
     [B,L,Hkv,n_cap] (may be None when T == 0).  Q_cat may be None for calls that do not read it."""
     B, L, Hkv, n_cap, d = K.shape
-    s = ccd_shape_t()
-    s.B, s.L, s.Hkv, s.d, s.n_cap = B, L, Hkv, d, n_cap
-    s.n_valid = n_cap if n_valid is None else n_valid
-    s.k, s.T, s.pool_w, s.pool_mode, s.scale = k, T, pool_w, pool_mode, scale
-    s.window = window
-    s.score_path = score_path
-    s.dtype = _dtype_code(K)
-    assert K.stride(4) == 1 and K.stride(3) == d, "K rows must be contiguous with stride d"
-    s.kv_stride_b, s.kv_stride_l, s.kv_stride_h = K.stride(0), K.stride(1), K.stride(2)
+    kb, kl, kh, kt, ke = K.stride()
+    assert ke == 1 and kt == d, "K rows must be contiguous with stride d"
     if Q_cat is not None:
-        assert Q_cat.stride(4) == 1 and Q_cat.stride(3) == d
-        s.Hq, s.P = Q_cat.shape[2], Q_cat.shape[3]
-        s.q_stride_b, s.q_stride_l, s.q_stride_h = Q_cat.stride(0), Q_cat.stride(1), Q_cat.stride(2)
+        Hq, P = Q_cat.shape[2], Q_cat.shape[3]
+        qb, ql, qh, qt, qe = Q_cat.stride()
+        assert qe == 1 and qt == d
     else:
-        s.Hq, s.P = Hkv, 1
-        s.q_stride_h = d
+        Hq, P = Hkv, 1
+        qb, ql, qh = 0, 0, d
+    nb = nl = nh = 0
     if novelty is not None:
         assert novelty.dtype == torch.float32 and novelty.stride(-1) == 1
         if novelty.dim() == 2:
-            s.nov_stride_b = novelty.stride(0)
+            nb = novelty.stride(0)
         else:
-            s.nov_stride_b, s.nov_stride_l, s.nov_stride_h = novelty.stride(0), novelty.stride(1), novelty.stride(2)
-    return s
+            nb, nl, nh, _ = novelty.stride()
+    return ccd_shape_t(B, L, Hq, Hkv, d, n_cap if n_valid is None else n_valid, n_cap, k, P, T, pool_w, pool_mode,
+                       _dtype_code(K), scale, window, score_path, kb, kl, kh, qb, ql, qh, nb, nl, nh)
 
 
 def ccd_workspace_bytes(shape: ccd_shape_t) -> int:
