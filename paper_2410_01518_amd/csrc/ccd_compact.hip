@@ -36,10 +36,12 @@ constexpr int kCpUnroll = 4;
 
 // Appending a chunk of new context behind the cached tokens (Sec. 3.2: the pot is filled until it is full): rows
 // [n, n + count) of every unit of K and V take the chunk's rows, dense [units, count, d] on the source side.  A unit's
-// share is one contiguous run on both sides; the grid is (unit, tensor, segment of 64 KiB), 16 bytes per lane and
-// four of them in flight.  Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.
+// share is one contiguous run on both sides; the grid is (unit, tensor, segment of 16 KiB), 16 bytes per lane and
+// four of them in flight.  Bound by HBM (256 units, 2048 tokens: 537 MB in 84 us) or, for a few units, by how many compute
+// units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.
 constexpr int kApThreads = 256;
-constexpr int kApSegBytes = kApThreads * 16 * 16;     // bytes one workgroup moves: 64 KiB
+constexpr int kApLoads = 4;
+constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
                                                                  const float* nov_new, int nov_per_head) {
@@ -52,21 +54,18 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
   char* dst = (isV ? V : K) + (kv_offset(D, ui) + (int64_t)D.n * D.d) * esz;
   const char* src = (isV ? Vnew : Knew) + (int64_t)unit * run;
   const int64_t b0 = (int64_t)seg * kApSegBytes + threadIdx.x * 16;
+  uint4 v[kApLoads];
 #pragma unroll
-  for (int r = 0; r < 16; r += 4) {
-    uint4 v[4];
+  for (int i = 0; i < kApLoads; ++i) {
+    const int64_t b = b0 + i * (kApThreads * 16);
+    if (b < run) v[i] = load_streaming(src + b);
+  }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t b = b0 + (int64_t)(r + i) * (kApThreads * 16);
-      if (b < run) v[i] = load_streaming(src + b);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t b = b0 + (int64_t)(r + i) * (kApThreads * 16);
-      if (b < run) {          // the keys are read again by the next score pass, the values not before the compaction
-        if (isV) store_streaming(dst + b, v[i]);
-        else     *reinterpret_cast<uint4*>(dst + b) = v[i];
-      }
+  for (int i = 0; i < kApLoads; ++i) {
+    const int64_t b = b0 + i * (kApThreads * 16);
+    if (b < run) {          // the keys are read again by the next score pass, the values not before the compaction
+      if (isV) store_streaming(dst + b, v[i]);
+      else     *reinterpret_cast<uint4*>(dst + b) = v[i];
     }
   }
   if (novelty != nullptr && !isV && seg == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0))) {
