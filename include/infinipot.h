@@ -81,7 +81,8 @@ typedef struct {
                               /* fp32 caches on CCD_PATH_MFMA_UNIT: every fp32 value enters as the sum of two    */
                               /* bf16 values and a product as three bf16 products (scores within 1e-3 for        */
                               /* logits up to about 140, measured; 4e-4 at 65); d = 64 only, no window, no K_cap  */
-                              /* (CCD_EUNSUPPORTED otherwise; CCD_PATH_AUTO then takes the vector ALUs).          */
+                              /* (CCD_EUNSUPPORTED otherwise; CCD_PATH_AUTO then takes sums of six bf16 products  */
+                              /* by token slices, to fp32 accuracy).                                             */
   int64_t kv_stride_b, kv_stride_l, kv_stride_h;    /* K, V: [B, L, Hkv, n_cap, d], strides in elements */
   int64_t q_stride_b, q_stride_l, q_stride_h;       /* Q_cat: [B, L, Hq, P, d]                          */
   int64_t nov_stride_b, nov_stride_l, nov_stride_h; /* novelty fp32: [B, n] shared by layers and heads  */

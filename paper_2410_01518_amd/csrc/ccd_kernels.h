@@ -36,11 +36,12 @@ struct ScorePlan {
   int n_slices1;
   int slice2;     // tokens per workgroup in the probability pass
   int n_slices2;
-  int cap_block;  // 1 (vector-ALU path): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
+  int cap_block;  // 1 (fp32 caches, vector-ALU path): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
   int head_block; // 1 (matrix-core path): `part` also holds the statistics of the windowed head (sliding window)
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass
   uint32_t* sync;   // kSyncWords words per unit that the first score kernel of a call clears (null: none)
   int unit_kernel;  // 1 (matrix-core path): both passes in one kernel, one workgroup per unit (launch_score_unit)
+  int split_kernel; // 1 (fp32 caches): the two passes as sums of bf16 products (launch_stats_split, launch_prob_split)
 };
 
 ScorePlan plan_score(const Dims& D, bool cap_keys);
@@ -79,6 +80,14 @@ void launch_head_stats_mfma(const Dims& D, const ScorePlan& pl, const void* Q, c
 // (lse in log2 units, or the caller's natural-log ones when pl.lse_given)
 void launch_head_prob_mfma(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float* lse, float* u,
                            hipStream_t s);
+
+// fp32 caches: the two passes on the matrix cores to fp32 accuracy (any head dimension, window and CaP keys; launch_merge in
+// between).  plan_split chooses the token slices, K_cap as in launch_cap_block_stats_valu (pl.cap_block must be 1 with it).
+void plan_split(const Dims& D, int compute_units, int min_slice, ScorePlan& pl);
+void launch_stats_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
+                        hipStream_t s);
+void launch_prob_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float* lse2, float* u,
+                       hipStream_t s);
 
 // The same on the vector-ALU path: statistics of CaP key j under CaP query i for j <= i, written to `part` behind
 // the slices of all units (pl.cap_block must be 1; launch_merge then takes them in).  K_cap as above.

@@ -177,6 +177,9 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
       pl.unit_kernel = (2 * D.units_run >= cus || rounds * sweeps * D.n <= 6000) ? 1 : 0;
     }
   }
+  // every other fp32 call: sums of six bf16 products, by token slices (256 units of 4096 tokens, 256 query rows of 128
+  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them)
+  if (D.dtype == CCD_FP32 && D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) plan_split(D, compute_units(), kMinSlice, pl);
   return pl;
 }
 // a path the caller named that this call cannot take
@@ -282,8 +285,9 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     pl.lse_given = 1;
     float* lse_rw = const_cast<float*>(lse);   // only read when pl.lse_given
     g_prof.begin(kStProb, st);
-    if (pl.use_mfma) launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
-    else             launch_prob_valu(D, pl, Q, K, lse, u, st);
+    if (pl.use_mfma)          launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
+    else if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse, u, st);
+    else                      launch_prob_valu(D, pl, Q, K, lse, u, st);
     g_prof.end(st);
     if (pl.use_mfma && D.head > 0) {
       g_prof.begin(kStHead, st);
@@ -292,8 +296,8 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     }
     return;
   }
-  if (K_cap != nullptr && !pl.use_mfma) {    // (the matrix-core pass 2 takes the CaP keys in its prologue)
-    pl.cap_block = 1;
+  if (K_cap != nullptr && !pl.use_mfma) pl.cap_block = 1;   // (the bf16 pass 2 takes the CaP keys in its prologue)
+  if (pl.cap_block && !pl.split_kernel) {
     g_prof.begin(kStCapBlock, st);
     launch_cap_block_stats_valu(D, pl, Q, K_cap, part, st);
     g_prof.end(st);
@@ -318,13 +322,15 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     }
   } else {
     g_prof.begin(kStStats, st);
-    launch_stats_valu(D, pl, Q, K, part, st);
+    if (pl.split_kernel) launch_stats_split(D, pl, Q, K, K_cap, part, st);
+    else                 launch_stats_valu(D, pl, Q, K, part, st);
     g_prof.end(st);
     g_prof.begin(kStMerge, st);
     launch_merge(D, pl, part, lse2, st);
     g_prof.end(st);
     g_prof.begin(kStProb, st);
-    launch_prob_valu(D, pl, Q, K, lse2, u, st);
+    if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse2, u, st);
+    else                 launch_prob_valu(D, pl, Q, K, lse2, u, st);
     g_prof.end(st);
   }
 }

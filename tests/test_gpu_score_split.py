@@ -1,0 +1,65 @@
+"""fp32 caches scored as sums of six bf16 products (token slices): the edges of its stages, slices, row blocks and sweeps under
+every option, against the oracle and to fp32 accuracy."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import ccd_oracle as O
+from paper_2410_01518_amd import infinipot as ip
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# (units, G, P, n, d, options).  Row blocks of 32 query rows: one, two, three, four, five to eight, a second sweep of 256;
+# stages of 64 tokens: one row, just around a tile and a stage, several slices of 256; 260 units: one slice of eleven stages.
+# (Head dimension 64 takes this path with CaP keys, a window or few long rows only.)
+CASES = [
+    (1, 1, 1, 1, 128, ""), (2, 1, 5, 31, 128, ""), (2, 1, 32, 33, 128, "lse"), (1, 1, 33, 64, 128, "kcat"),
+    (2, 2, 40, 65, 128, "kcat"), (1, 3, 32, 255, 128, "window"), (1, 4, 32, 257, 128, "kcat window"),
+    (2, 3, 43, 449, 128, "lse window"), (1, 2, 128, 1000, 128, "kcat window"), (3, 4, 64, 769, 128, ""),
+    (1, 2, 129, 520, 128, "kcat"), (1, 8, 70, 333, 128, "window"), (1, 8, 64, 1409, 128, "lse"),
+    (260, 1, 2, 700, 128, "kcat"), (260, 2, 3, 700, 128, "window"),
+    (1, 1, 3, 7001, 64, ""), (2, 2, 20, 300, 64, "kcat"), (1, 4, 80, 515, 64, "kcat window"), (3, 1, 33, 130, 64, "window"),
+    (260, 1, 2, 700, 64, "window"),
+]
+
+
+@pytest.mark.parametrize("units,G,P,n,d,options", CASES)
+def test_scores(units, G, P, n, d, options):
+    rng = np.random.default_rng(units * n + G * P)
+    Q = rng.standard_normal((1, 1, units * G, P, d)).astype(np.float32)
+    K = rng.standard_normal((1, 1, units, n, d)).astype(np.float32)
+    K[:, :, :, rng.integers(0, n, max(1, n // 50))] *= 4.0
+    Kc = rng.standard_normal((1, 1, units, P, d)).astype(np.float32) if "kcat" in options else None
+    window = max(P, n * 2 // 3) if "window" in options else 0
+    lse = (3.0 + rng.random((1, 1, units * G, P))).astype(np.float32) if "lse" in options else None
+    dK = gu.to_dev(K)
+    shape = ip.make_shape(gu.to_dev(Q), dK, None, k=n, T=0, pool_w=1, window=window)
+    ws = ip.alloc_workspace(shape)
+    ws.fill_(0xFF)                                             # nothing relied on, and NaN where it is read too early
+    scores = torch.empty((1, 1, units, n), dtype=torch.float32, device="cuda")
+    print(f"split units={units} G={G} P={P} n={n} d={d} {options}", flush=True)
+    if lse is not None:
+        rc = ip.ccd_score_lse(shape, gu.to_dev(Q), dK, gu.to_dev(lse), None, scores, ws)
+    elif Kc is not None:
+        rc = ip.ccd_score_kcat(shape, gu.to_dev(Q), dK, gu.to_dev(Kc), None, scores, ws)
+    else:
+        rc = ip.ccd_score(shape, gu.to_dev(Q), dK, None, scores, ws)
+    assert rc == ip.CCD_OK
+    got = gu.to_host(scores).reshape(units, n).astype(np.float64)
+    scale = 1.0 / math.sqrt(d)
+    Qu, Ku = Q.reshape(units, G * P, d).astype(np.float64), K.reshape(units, n, d).astype(np.float64)
+    for i in range(units):
+        if lse is not None:
+            ref = O.cap_scores_given_lse(Qu[i], Ku[i], scale, lse.reshape(units, -1)[i], P=P, window=window)
+        else:
+            ref = O.cap_scores(Qu[i], Ku[i], scale, K_cap=None if Kc is None else Kc[0, 0, i].astype(np.float64), P=P, window=window)
+        # A logit rounds at most ten times (eight additions of the large products, the small ones' sum, the scale), each by
+        # 2^-24 of sum |q k| scale log2(e) at most; a probability carries that twice (logit and normaliser), times ln 2.
+        # Behind that, 64 roundings of sums, exponentials and merges.
+        size = (np.abs(Qu[i]) @ np.abs(Ku[i]).T).max() * scale / math.log(2.0)
+        bound = (2.0 * math.log(2.0) * 10.0 * size + 64.0) * 2.0 ** -24
+        err = np.abs(got[i] - ref)
+        assert (err <= bound * ref + 2.0 * G * P * gu.FLT_MIN).all(), (i, float((err / np.maximum(ref, 1e-30)).max()), bound)
