@@ -1,0 +1,29 @@
+"""NuC score from logits on either side of the number of rows at which its workgroups change size, and at the edges of a
+workgroup's first loads (four per thread, of 16 bytes)."""
+import pytest
+import torch
+
+from paper_2410_01518_amd import infinipot as ip
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,V", [(1023, 333), (1024, 333), (2, 32768), (3, 32761), (2, 32776), (2, 65553)])
+def test_rows(dtype, rows, V):
+    print(f"nuc {dtype} rows={rows} V={V}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    z = torch.empty((rows, (V + 7) // 8 * 8), device="cuda").normal_(0.0, 4.0, generator=g).to(dtype)[:, :V]
+    labels = torch.randint(0, V, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    labels[1] = -1
+    nov = torch.empty(rows, device="cuda")
+    assert ip.ccd_nuc_from_logits(z, labels, nov) == ip.CCD_OK
+    z64 = z.double()
+    lse = torch.logsumexp(z64, -1)
+    zl = z64.gather(1, labels.clamp(min=0).long()[:, None])[:, 0]
+    want = torch.where(labels >= 0, lse - zl, torch.full_like(lse, -float("inf")))
+    # sums of V exponentials in fp32 and one fast log2: 4e-6 absolute; the rounding of max + log and of the difference
+    tol = 4e-6 + 3 * 2.0 ** -24 * (lse.abs() + zl.abs())
+    ok = labels >= 0
+    assert torch.equal(nov[~ok].double(), want[~ok])
+    assert bool(((nov.double() - want).abs() <= tol)[ok].all())
