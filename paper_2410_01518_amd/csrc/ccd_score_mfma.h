@@ -506,12 +506,27 @@ __device__ __forceinline__ void score_pass_body(const Dims& D, const ScorePlan& 
           const float Mh = fmaxf(cap.x, hd.x);
           cap = make_float2(Mh, cap.y * fast_exp2(cap.x - Mh) + hd.y * fast_exp2(hd.x - Mh));
         }
+        // Sixteen loads in flight, the last ones over again past the end: a few units with long rows have 64 slices and
+        // more, and one load after another took as long as the pass itself (8 units
+        // of 32768 tokens, 256 query rows: pass 2 44 -> 33 us; 8 slices: 11.2 -> 10.3 us)
+        constexpr int kFly = 16;
+        const int n = pl.n_slices1;
         float M = cap.x;
-        for (int j = 0; j < pl.n_slices1; ++j) M = fmaxf(M, p[(int64_t)j * D.GP].x);
+        for (int j0 = 0; j0 < n; j0 += kFly) {
+          float m[kFly];
+#pragma unroll
+          for (int j = 0; j < kFly; ++j) m[j] = p[(int64_t)min(j0 + j, n - 1) * D.GP].x;
+#pragma unroll
+          for (int j = 0; j < kFly; ++j) M = fmaxf(M, m[j]);
+        }
         float z = cap.y * fast_exp2(cap.x - M);
-        for (int j = 0; j < pl.n_slices1; ++j) {
-          const float2 v = p[(int64_t)j * D.GP];
-          z += v.y * fast_exp2(v.x - M);
+        for (int j0 = 0; j0 < n; j0 += kFly) {
+          float2 v[kFly];
+#pragma unroll
+          for (int j = 0; j < kFly; ++j) v[j] = p[(int64_t)min(j0 + j, n - 1) * D.GP];
+#pragma unroll
+          for (int j = 0; j < kFly; ++j)
+            if (j0 + j < n) z += v[j].y * fast_exp2(v[j].x - M);
         }
         lse = M + __log2f(z);
         if (pl.head_block && slice == 0) lse_out[(int64_t)unit * D.GP + q] = lse;   // for the head's probabilities
