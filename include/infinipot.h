@@ -139,7 +139,7 @@ CCD_API int ccd_compress(const ccd_shape_t* shape, const void* Q_cat, void* K, v
  * nothing is launched.  Allocates nothing (the first call on a GPU looks the buffer's address up once).  All calls on
  * one GPU share the one buffer, whose contents are scratch and need not start at any value: calls that overlap in time
  * on the same GPU (two streams, two threads) race; on different GPUs they do not. */
-#define CCD_NOALLOC_WORKSPACE_BYTES (16u << 20)
+#define CCD_NOALLOC_WORKSPACE_BYTES ((16u << 20) + (8u << 10))
 CCD_API int ccd_compress_noalloc(const ccd_shape_t* shape, const void* Q_cat, void* K, void* V, float* novelty,
                          float* scores_opt, int32_t* keep_idx, void* hip_stream);
 

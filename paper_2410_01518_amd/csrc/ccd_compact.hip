@@ -38,7 +38,8 @@ constexpr int kCpUnroll = 4;
 // [n, n + count) of every unit of K and V take the chunk's rows, dense [units, count, d] on the source side.  A unit's
 // share is one contiguous run on both sides; the grid is (unit, tensor, segment of 16 KiB), 16 bytes per lane and
 // four of them in flight.  Bound by HBM (256 units, 2048 tokens: 537 MB in 84 us) or, for a few units, by how many compute
-// units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.
+// units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.
+// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
@@ -190,7 +191,6 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
 constexpr int kScUnroll = 2;                // rows per thread and tensor in flight
-constexpr int kSharedFillWorkgroups = 256;  // one workgroup per compute unit
 // ... SHARED (half with ROPE, whose coefficients take as many registers again): at most 64 KiB of each tensor per workgroup
 constexpr int sh_unroll(int threads, bool rope) { return 4096 / threads / (rope ? 2 : 1); }
 
@@ -378,7 +378,7 @@ bool select_compact_supported(const Dims& D) { return D.n <= kLdsRowTokens; }
 
 // pooling + NuC lift + top-k + in-place compaction of K and V (and of carried per-head novelty).
 // Krot != nullptr: CR-RoPE of the kept keys on the side (rope_cos / rope_sin: [>= k, d/2] fp32).
-// sync: kSyncWords zeros per unit.
+// sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units.
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
                            uint32_t* sync, hipStream_t s) {

@@ -27,7 +27,9 @@ struct Dims {
   int64_t nov_sb, nov_sl, nov_sh;
 };
 
-// What the workgroups that share a unit's selection and compaction agree on (launch_select_compact), per unit
+// What the workgroups that share a unit's selection and compaction agree on (launch_select_compact), per unit.  Units are
+// shared while there are two compute units for each: calls with more units need no such words.
+constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgroups / 2;
 constexpr int kSyncTicket = 0, kSyncSelected = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16;
 
 struct ScorePlan {
@@ -101,7 +103,8 @@ void launch_finalize_select(const Dims& D, const float* u, const float* novelty,
 
 // selection and compaction of a unit in one workgroup (rows short enough to be staged in LDS)
 bool select_compact_supported(const Dims& D);
-// (sync: kSyncWords zeros per unit; carry_novelty: the novelty is carried per head and its kept entries are compacted in place like the rows)
+// (sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units; carry_novelty: the novelty is carried per head
+// and its kept entries are compacted in place like the rows)
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
                            uint32_t* sync, hipStream_t s);

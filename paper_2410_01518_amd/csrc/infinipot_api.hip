@@ -199,7 +199,8 @@ static Workspace layout_workspace(const Dims& D) {
   w.off_part = off;   off = align_up(off + (size_t)D.units * max_slices * D.GP * sizeof(float2), 256);
   w.off_lse = off;    off = align_up(off + (size_t)D.units * D.GP * sizeof(float), 256);
   w.off_u = off;      off = align_up(off + (size_t)D.units * D.n * sizeof(float), 256);
-  w.off_sync = off;   off = align_up(off + (size_t)D.units * kSyncWords * sizeof(uint32_t), 256);
+  w.off_sync = off;
+  if (D.units <= kMaxSharedUnits) off = align_up(off + (size_t)D.units * kSyncWords * sizeof(uint32_t), 256);   // 8 KiB at most
   w.total = off;
   return w;
 }
@@ -470,7 +471,7 @@ static int compress_impl(const ccd_shape_t* shape, const void* Q_cat, void* K, v
   const float* u = reinterpret_cast<const float*>(ws + w.off_u);
   const bool per_head = shape->nov_stride_l != 0 || shape->nov_stride_h != 0;
   if (g_prof.on) ++g_prof.calls;
-  uint32_t* sync = reinterpret_cast<uint32_t*>(ws + w.off_sync);
+  uint32_t* sync = D.units <= kMaxSharedUnits ? reinterpret_cast<uint32_t*>(ws + w.off_sync) : nullptr;
   pl.sync = sync;
   run_cap_scores(D, pl, w, Q_cat, K_attn, K_cap, lse, ws, st);
   if (select_compact_supported(D)) {

@@ -198,7 +198,7 @@ def ccd_compress(shape, Q_cat, K, V, novelty, keep_idx, workspace, scores=None, 
                                      _stream(stream)))
 
 
-NOALLOC_WORKSPACE_BYTES = 16 << 20
+NOALLOC_WORKSPACE_BYTES = (16 << 20) + (8 << 10)
 
 
 def ccd_compress_noalloc(shape, Q_cat, K, V, novelty, keep_idx, scores=None, stream=None) -> int:

@@ -84,6 +84,18 @@ def test_workspace_bytes():
     assert ip.ccd_workspace_bytes(_shape(n_valid=1024, n_cap=1024)) > n
 
 
+@pytest.mark.parametrize("L,Hkv", [(1, 1), (16, 8), (43, 3), (32, 8), (80, 8)])
+def test_workspace_of_score_statistics_rows_and_shared_units(L, Hkv):
+    """Statistics of every slice of 256 tokens and one more, log-sum-exps, the score row; 64 bytes per unit of calls with few
+    units, which the library's own buffer has beyond 16 MiB: a call that fits 16 MiB without them fits it with them."""
+    up = lambda x: (x + 255) // 256 * 256
+    units, gp, n = L * Hkv, 4 * 16, 3001
+    s = _shape(L=L, Hkv=Hkv, Hq=4 * Hkv, n_valid=n, n_cap=n)
+    base = up(units * ((n + 255) // 256 + 1) * gp * 8) + up(units * gp * 4) + up(units * n * 4)
+    assert ip.ccd_workspace_bytes(s) == base + (up(64 * units) if units <= 128 else 0)
+    assert ip.NOALLOC_WORKSPACE_BYTES == (16 << 20) + 64 * 128
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(k=0), ip.CCD_EINVAL), (dict(k=513), ip.CCD_EINVAL), (dict(T=257), ip.CCD_EINVAL), (dict(T=-1), ip.CCD_EINVAL),
     (dict(Hq=7), ip.CCD_EINVAL), (dict(B=0), ip.CCD_EINVAL), (dict(P=0), ip.CCD_EINVAL),
