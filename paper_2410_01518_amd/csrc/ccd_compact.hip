@@ -191,6 +191,9 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
 constexpr int kScUnroll = 2;                // rows per thread and tensor in flight
+// The wait for smaller chunks takes microseconds.  It is bounded (seconds) for calls that overlap on one workspace, which is an
+// error of the caller: one call may clear the other's marks, and their results are undefined, but their kernels end.
+constexpr int kMarkPolls = 1 << 22;
 // ... SHARED (half with ROPE, whose coefficients take as many registers again): at most 64 KiB of each tensor per workgroup
 constexpr int sh_unroll(int threads, bool rope) { return 4096 / threads / (rope ? 2 : 1); }
 
@@ -309,7 +312,7 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
         const int below = chunk - 32 * lane;      // chunks before this one that lane's word of marks holds
         const uint32_t want = below >= 32 ? 0xFFFFFFFFu : (below > 0 ? (1u << below) - 1u : 0u);
         const uint32_t* word = &sy[kSyncMarks + min(lane, kSyncMarkWords - 1)];
-        while (!__all((want & ~agent_load(word)) == 0u)) __builtin_amdgcn_s_sleep(1);
+        for (int i = 0; i < kMarkPolls && !__all((want & ~agent_load(word)) == 0u); ++i) __builtin_amdgcn_s_sleep(1);
       }
       __syncthreads();
       next = ticket_lds * chunk_rows;
