@@ -5,7 +5,8 @@
 // rows of one (unit, tensor) in ascending chunks; inside a chunk every source row is first loaded into registers,
 // then the workgroup synchronises, then the rows are stored.  A store of chunk c lands in rows
 // [c*R, (c+1)*R), and every later chunk reads only rows >= (c+1)*R, so the only reads a store could overtake
-// are those of its own chunk, which the barrier orders.  Out of place the same code runs without the barrier.
+// are those of its own chunk, which the barrier orders.  A tensor that is
+// moved out of place beside one in place takes the same code without the barrier; both out of place: gather_rows_kernel.
 #include <algorithm>
 
 #include "ccd_common.h"
