@@ -145,6 +145,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
         const int qr = qc + rb * 32 + acc_row(r, half);
         const float l = lse2[(int64_t)unit * D.GP + min(qr, D.GP - 1)] * lse_mul;
         nl[r] = qr < D.GP ? -l : -INFINITY;
+        // A last CaP token whose window holds no cached token (window == P) takes no part either: a normaliser over cached
+        // tokens alone is -infinity for it, and its masked logits would come out as -infinity + infinity.
+        if (D.head > 0 && D.win_off + D.P > D.n && qr % D.P == D.P - 1) nl[r] = -INFINITY;
       }
       if (D.head > 0 && tid < kSplitRows) sm.first[tid] = D.win_off + (qc + tid) % D.P;
     }

@@ -56,10 +56,46 @@ def test_scores(units, G, P, n, d, options):
             ref = O.cap_scores_given_lse(Qu[i], Ku[i], scale, lse.reshape(units, -1)[i], P=P, window=window)
         else:
             ref = O.cap_scores(Qu[i], Ku[i], scale, K_cap=None if Kc is None else Kc[0, 0, i].astype(np.float64), P=P, window=window)
-        # A logit rounds at most ten times (eight additions of the large products, the small ones' sum, the scale), each by
-        # 2^-24 of sum |q k| scale log2(e) at most; a probability carries that twice (logit and normaliser), times ln 2.
-        # Behind that, 64 roundings of sums, exponentials and merges.
-        size = (np.abs(Qu[i]) @ np.abs(Ku[i]).T).max() * scale / math.log(2.0)
-        bound = (2.0 * math.log(2.0) * 10.0 * size + 64.0) * 2.0 ** -24
-        err = np.abs(got[i] - ref)
-        assert (err <= bound * ref + 2.0 * G * P * gu.FLT_MIN).all(), (i, float((err / np.maximum(ref, 1e-30)).max()), bound)
+        _assert_close(got[i], ref, Qu[i], Ku[i], scale, i)
+
+
+def _assert_close(got, ref, Q, K, scale, what):
+    # A logit rounds at most ten times (eight additions of the large products, the small ones' sum, the scale), each by
+    # 2^-24 of sum |q k| scale log2(e) at most; a probability carries that twice (logit and normaliser), times ln 2.
+    # Behind that, 64 roundings of sums, exponentials and merges.
+    size = (np.abs(Q) @ np.abs(K).T).max() * scale / math.log(2.0)
+    bound = (2.0 * math.log(2.0) * 10.0 * size + 64.0) * 2.0 ** -24
+    err = np.abs(got - ref)
+    assert (err <= bound * ref + 2.0 * len(Q) * gu.FLT_MIN).all(), (what, float((err / np.maximum(ref, 1e-30)).max()), bound)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("units,G,P,n,d", [(2, 2, 5, 40, 128), (1, 3, 33, 129, 64), (1, 9, 32, 300, 128)])
+def test_normaliser_of_a_row_that_sees_no_token(units, G, P, n, d, dtype):
+    """window == P hides every cached token from the last CaP token of a head; its normaliser over the cached tokens is
+    -inf.  It adds nothing to any score."""
+    rng = np.random.default_rng(n)
+    Q = rng.standard_normal((1, 1, units * G, P, d)).astype(np.float32)
+    K = rng.standard_normal((1, 1, units, n, d)).astype(np.float32)
+    if dtype == "bf16":
+        Q, K = (O.round_bf16_bits(x) for x in (Q, K))
+    scale = 1.0 / math.sqrt(d)
+    Qu, Ku = O.to_f64(Q).reshape(units, G * P, d), O.to_f64(K).reshape(units, n, d)
+    hidden = np.arange(n)[None, :] < (n + np.arange(G * P) % P + 1 - P)[:, None]
+    with np.errstate(divide="ignore"):
+        lse = np.stack([np.log(np.where(hidden, 0.0, np.exp(scale * Qu[i] @ Ku[i].T)).sum(1)) for i in range(units)])
+    assert (np.isneginf(lse).sum(1) == G).all()
+    lse = lse.astype(np.float32).reshape(1, 1, units * G, P)
+    dQ, dK = gu.to_dev(Q), gu.to_dev(K)
+    shape = ip.make_shape(dQ, dK, None, k=n, T=0, pool_w=1, window=P)
+    ws = ip.alloc_workspace(shape)
+    scores = torch.empty((1, 1, units, n), dtype=torch.float32, device="cuda")
+    print(f"no token seen: {dtype} units={units} G={G} P={P} n={n} d={d}", flush=True)
+    assert ip.ccd_score_lse(shape, dQ, dK, gu.to_dev(lse), None, scores, ws) == ip.CCD_OK
+    got = gu.to_host(scores).reshape(units, n).astype(np.float64)
+    for i in range(units):
+        rows = np.isfinite(lse.reshape(units, -1)[i])
+        A = np.exp(scale * Qu[i][rows] @ Ku[i].T - lse.reshape(units, -1)[i][rows, None].astype(np.float64))
+        ref = np.where(hidden[rows], 0.0, A).sum(0)
+        assert (got[i][: n - P + 1] == 0.0).all()
+        _assert_close(got[i], ref, Qu[i], Ku[i], scale, i)
