@@ -6,7 +6,11 @@
 // product taken as qh kh + (qh km + qm kh + qm km + qh kl + ql kh): six bf16 products with fp32 accumulation.  The three
 // products left out are below 2^-24 of |q k| together, less than the rounding of one fp32 multiplication; the five small ones
 // have a sum of their own, so that only the eight additions of qh kh (four for head dimension 64) round at the logit's
-// size, where a chain of fp32 fmas rounds 128 (64) times.  (Elements beyond the largest bf16, 3.39e38, count as infinite.)
+// size, where a chain of fp32 fmas rounds 128 (64) times.
+//
+// An element that rounds to an infinite bf16 (infinities, and finite values from 3.396e38 on) leaves remainders that are no
+// numbers, and every logit it takes part in comes out as NaN, which reaches each sum that such a logit enters.  So the sums
+// tell: a row's statistics of a slice, or a token's score, that come out as NaN are computed again by a chain of fp32 fmas.
 //
 // Bound by the matrix cores: 6 x 2 x 68.7 GFLOP for 256 units of 4096 tokens and 256 query rows of 128 elements.  A workgroup
 // of eight waves (two per SIMD: one folds while the other one multiplies) takes one slice of a unit's tokens and up to 256
@@ -65,7 +69,28 @@ struct SplitLds {
   bf16x8 k[2][2][3 * KQ][64];                // [buffer][tile][h: 0.., m: KQ.., l: 2 KQ..][lane]
   float ub[4][kSplitWaves][kStage];          // pass 2: token sums of a stage per row block; pass 1: (reference, sum) pairs at the end
   int first[kSplitRows];                     // pass 2 under a window: the first token a query row sees
+  int nan_out;                               // pass 2: some token's sum is NaN
 };
+
+// logit of a query row that is held in registers and a key (times the scale), as the vector-ALU kernels take it
+template <int HD>
+__device__ __forceinline__ float plain_dot(const float4 (&a)[HD / 4], const float* __restrict__ b) {
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < HD / 4; ++i) {
+    const float4 v = load4(b + 4 * i);
+    acc = fmaf(a[i].x, v.x, acc);
+    acc = fmaf(a[i].y, v.y, acc);
+    acc = fmaf(a[i].z, v.z, acc);
+    acc = fmaf(a[i].w, v.w, acc);
+  }
+  return acc;
+}
+template <int HD>
+__device__ __forceinline__ void load_row(float4 (&a)[HD / 4], const float* __restrict__ p) {
+#pragma unroll
+  for (int i = 0; i < HD / 4; ++i) a[i] = load4(p + 4 * i);
+}
 
 // PASS 1: part[unit, slice, q] = (maximum, sum of 2^(x - maximum)) of the log2-domain logits x of query row q over the slice;
 //   slice n_slices1 (causal variant) stands for the CaP tokens' own keys, of which row g * P + i sees 0 .. i.
@@ -94,6 +119,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, col = lane & 31, half = lane >> 5;
   const float c = D.scale_log2;
+  if (PASS == 2 && tid == 0) sm.nan_out = 0;   // (set by the same wave)
 
   // staging: eight consecutive threads take the same elements of eight consecutive rows (their LDS writes are contiguous)
   const int st_c = (tid >> 3) % (HD / 8), st_row = (tid / HD) * 8 + (tid & 7);
@@ -246,6 +272,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
       if (wave == 0 && t < t1) {
         float v = sm.ub[it & 3][0][lane];
         for (int b = 1; b < blocks; ++b) v += sm.ub[it & 3][b][lane];
+        if (v != v) sm.nan_out = 1;
         float* out = u + (int64_t)unit * D.n + t;
         *out = qc == 0 ? v : *out + v;
       }
@@ -291,11 +318,36 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
           const float mm = fmaxf(a.x, b.x);
           a = make_float2(mm, a.y * fast_exp2((a.x - mm) * c) + b.y * fast_exp2((b.x - mm) * c));
         }
-        part[cap ? extra_block_index(D, pl, unit, q) : ((int64_t)unit * pl.n_slices1 + slice) * D.GP + q] =
-            make_float2(a.x * c, a.y);
+        a.x *= c;
+        if (a.y != a.y) {         // again, one token after the other (a -infinite logit has no part in it)
+          float4 qr[HD / 4];
+          load_row<HD>(qr, Q + q_offset(D, ui, q));
+          a = make_float2(-INFINITY, 0.f);
+          for (int t = max(t0, lo); t <= hi; ++t) {
+            const float x = plain_dot<HD>(qr, Ku + (int64_t)t * HD) * c;
+            if (x > a.x) a = make_float2(x, a.y * fast_exp2(a.x - x) + 1.f);
+            else if (x != -INFINITY) a.y += fast_exp2(x - a.x);
+          }
+        }
+        part[cap ? extra_block_index(D, pl, unit, q) : ((int64_t)unit * pl.n_slices1 + slice) * D.GP + q] = a;
       }
     }
     __syncthreads();          // the LDS tables are rewritten by the next sweep
+  }
+  if (PASS == 2 && __builtin_expect(__builtin_amdgcn_readfirstlane(sm.nan_out) != 0, 0)) {
+    for (int t = t0 + tid; t < t1; t += kSplitThreads) {
+      float* out = u + (int64_t)unit * D.n + t;
+      const float v = *out;
+      if (v == v) continue;
+      float4 kr[HD / 4];
+      load_row<HD>(kr, Ku + (int64_t)t * HD);
+      float sum = 0.f;
+      for (int q = 0; q < D.GP; ++q) {
+        if (D.window > 0 && t < D.win_off + q % D.P) continue;
+        sum += fast_exp2(fmaf(plain_dot<HD>(kr, Q + q_offset(D, ui, q)), c, -lse2[(int64_t)unit * D.GP + q] * lse_mul));
+      }
+      *out = sum;
+    }
   }
 }
 

@@ -59,12 +59,12 @@ def test_scores(units, G, P, n, d, options):
         _assert_close(got[i], ref, Qu[i], Ku[i], scale, i)
 
 
-def _assert_close(got, ref, Q, K, scale, what):
+def _assert_close(got, ref, Q, K, scale, what, rounds=10):
     # A logit rounds at most ten times (eight additions of the large products, the small ones' sum, the scale), each by
     # 2^-24 of sum |q k| scale log2(e) at most; a probability carries that twice (logit and normaliser), times ln 2.
     # Behind that, 64 roundings of sums, exponentials and merges.
     size = (np.abs(Q) @ np.abs(K).T).max() * scale / math.log(2.0)
-    bound = (2.0 * math.log(2.0) * 10.0 * size + 64.0) * 2.0 ** -24
+    bound = (2.0 * math.log(2.0) * rounds * size + 64.0) * 2.0 ** -24
     err = np.abs(got - ref)
     assert (err <= bound * ref + 2.0 * len(Q) * gu.FLT_MIN).all(), (what, float((err / np.maximum(ref, 1e-30)).max()), bound)
 
@@ -99,3 +99,51 @@ def test_normaliser_of_a_row_that_sees_no_token(units, G, P, n, d, dtype):
         ref = np.where(hidden[rows], 0.0, A).sum(0)
         assert (got[i][: n - P + 1] == 0.0).all()
         _assert_close(got[i], ref, Qu[i], Ku[i], scale, i)
+
+
+@pytest.mark.parametrize("kind", ["large keys", "large queries", "infinite keys"])
+@pytest.mark.parametrize("units,G,P,n,d,options", [(2, 2, 5, 40, 128, ""), (1, 5, 60, 700, 128, "kcat"), (1, 2, 33, 300, 64, "kcat window"),
+                                                   (2, 1, 20, 333, 128, "lse window"), (1, 4, 64, 520, 128, "window")])
+def test_elements_beyond_the_largest_bf16(units, G, P, n, d, options, kind):
+    """A finite element above the largest bf16 counts with its value (the elements it meets are small: moderate logits); an
+    infinite one that takes a token's logits to -inf leaves that token a score of zero and the others theirs."""
+    rng = np.random.default_rng(units * n + d)
+    Q = rng.standard_normal((1, 1, units * G, P, d)).astype(np.float32)
+    K = rng.standard_normal((1, 1, units, n, d)).astype(np.float32)
+    Kc = rng.standard_normal((1, 1, units, P, d)).astype(np.float32) if "kcat" in options else None
+    tokens, col, big, small = rng.integers(0, n, 5), 7, np.float32(3.4e38), lambda m: (1.2e-38 * (1.0 + 3.0 * rng.random(m))).astype(np.float32)
+    if kind == "large queries":
+        K[..., col] = small(K.shape[:-1])
+        Q[0, 0, :, P // 2, col] = big
+        if Kc is not None:
+            Kc[..., col] = small(Kc.shape[:-1])
+    else:
+        Q[..., col] = small(Q.shape[:-1])
+        K[0, 0, :, tokens, col] = -np.inf if kind == "infinite keys" else big
+        if Kc is not None and kind == "large keys":
+            Kc[0, 0, :, P // 3, col] = big
+    window = max(P, n * 2 // 3) if "window" in options else 0
+    lse = (3.0 + rng.random((1, 1, units * G, P))).astype(np.float32) if "lse" in options else None
+    dQ, dK = gu.to_dev(Q), gu.to_dev(K)
+    shape = ip.make_shape(dQ, dK, None, k=n, T=0, pool_w=1, window=window)
+    ws = ip.alloc_workspace(shape)
+    scores = torch.empty((1, 1, units, n), dtype=torch.float32, device="cuda")
+    print(f"{kind}: units={units} G={G} P={P} n={n} d={d} {options}", flush=True)
+    if lse is not None:
+        ip.ccd_score_lse(shape, dQ, dK, gu.to_dev(lse), None, scores, ws)
+    elif Kc is not None:
+        ip.ccd_score_kcat(shape, dQ, dK, gu.to_dev(Kc), None, scores, ws)
+    else:
+        ip.ccd_score(shape, dQ, dK, None, scores, ws)
+    got = gu.to_host(scores).reshape(units, n).astype(np.float64)
+    scale = 1.0 / math.sqrt(d)
+    Qu, Ku = Q.reshape(units, G * P, d).astype(np.float64), K.reshape(units, n, d).astype(np.float64)
+    for i in range(units):
+        if lse is not None:
+            ref = O.cap_scores_given_lse(Qu[i], Ku[i], scale, lse.reshape(units, -1)[i], P=P, window=window)
+        else:
+            ref = O.cap_scores(Qu[i], Ku[i], scale, K_cap=None if Kc is None else Kc[0, 0, i].astype(np.float64), P=P, window=window)
+        fin = np.where(np.isinf(Ku[i]), 0.0, Ku[i])
+        _assert_close(got[i], ref, Qu[i], fin, scale, i, rounds=d + 2)      # a chain of d fmas, and the scale
+        if kind == "infinite keys":
+            assert (got[i][tokens] == 0.0).all()
