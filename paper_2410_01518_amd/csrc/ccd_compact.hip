@@ -12,6 +12,7 @@
 #include "ccd_common.h"
 #include "ccd_rope.h"
 #include "ccd_select_body.h"
+#include "ccd_ticket.h"
 
 namespace ccd {
 
@@ -192,8 +193,10 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
 constexpr int kScUnroll = 2;                // rows per thread and tensor in flight
-// The wait for smaller chunks takes microseconds.  It is bounded (seconds) for calls that overlap on one workspace, which is an
-// error of the caller: one call may clear the other's marks, and their results are undefined, but their kernels end.
+// Calls that overlap on one workspace are an error of the caller: one call clears the other's words, or leaves anything at all
+// in them where the shapes differ.  Their results are undefined, but every access stays in the pot and their kernels end: a
+// ticket counts only if it names a chunk of this call, a workgroup takes no more of them than there are chunks, and its waits
+// for smaller chunks, which take microseconds, are bounded (seconds in all).
 constexpr int kMarkPolls = 1 << 22;
 // ... SHARED (half with ROPE, whose coefficients take as many registers again): at most 64 KiB of each tensor per workgroup
 constexpr int sh_unroll(int threads, bool rope) { return 4096 / threads / (rope ? 2 : 1); }
@@ -215,8 +218,8 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
                                                                      int32_t* __restrict__ keep_idx, char* Kbuf,
                                                                      char* Vbuf, const float* __restrict__ rope_cos,
                                                                      const float* __restrict__ rope_sin, char* Krot,
-                                                                     int row_shift, int wgs_per_unit, int chunk_rows,
-                                                                     uint32_t* sync) {
+                                                                     int row_shift, int wgs_per_unit, int chunks,
+                                                                     int chunk_rows, uint32_t* sync) {
   constexpr bool ROPE = ROWB > 0;
   constexpr int THREADS = sc_threads(SHARED, CH == kLdsRow);
   constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
@@ -224,13 +227,13 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
   // The kept list: in LDS for short rows; a long row leaves no room for it, and it is read back from keep_idx, where this
   // workgroup has just put it
   __shared__ uint16_t keep_lds[kRegs ? CH * 4 * THREADS : 1];
-  __shared__ int ticket_lds;
+  __shared__ uint32_t ticket_lds;
   __shared__ int last_lds;
   const int part = SHARED ? blockIdx.x % wgs_per_unit : 0;
   const int unit = D.unit0 + (SHARED ? blockIdx.x / wgs_per_unit : blockIdx.x);
   const UnitIdx ui = decode_unit(D, unit);
   uint32_t* sy = SHARED ? sync + (int64_t)unit * kSyncWords : nullptr;
-  if (SHARED && threadIdx.x == 0) ticket_lds = (int)agent_add(&sy[kSyncTicket], 1u);
+  if (SHARED && threadIdx.x == 0) ticket_lds = agent_add(&sy[kSyncTicket], 1u);
   int32_t* keep_out = keep_idx + (int64_t)unit * D.k;
   float* nov = (D.T > 0 || carry_novelty) ? novelty + nov_offset(D, ui) : nullptr;
   {
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
                          });
   }
   __syncthreads();
-  auto keep = [&](int j) { return kRegs ? (int)keep_lds[j] : keep_out[j]; };
+  auto keep = [&](int j) { return kRegs ? (int)keep_lds[j] : min(max(keep_out[j], 0), D.n - 1); };
   if (kRegs && part == 0)
     for (int j = threadIdx.x; j < D.k; j += THREADS) keep_out[j] = keep_lds[j];
   auto compact_novelty = [&]() {      // (keep[j] >= j: a chunk's sources are read before anything at or above them is written)
@@ -282,7 +285,9 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
 
   if (SHARED && carry_novelty && threadIdx.x == 0)
     last_lds = agent_add(&sy[kSyncSelected], 1u) == (uint32_t)(wgs_per_unit - 1);
-  int base = SHARED ? ticket_lds * chunk_rows : 0;
+  uint32_t ticket = SHARED ? ticket_lds : 0u;
+  int base = SHARED ? chunk_first_row(ticket, chunks, chunk_rows, D.k) : 0;
+  int taken = 0, polls = kMarkPolls;
   while (base < D.k) {
     const int end = SHARED ? min(D.k, base + chunk_rows) : D.k;
     uint4 a[kUnroll], b[kUnroll];
@@ -305,18 +310,19 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
     int next = base + kUnroll * rows_per_pass;
     if constexpr (SHARED) {
       if (threadIdx.x < 64) {
-        const int chunk = base / chunk_rows, lane = threadIdx.x;
+        const int chunk = (int)ticket, lane = threadIdx.x;
         if (lane == 0) {
           __hip_atomic_fetch_or(&sy[kSyncMarks + chunk / 32], 1u << (chunk % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ticket_lds = (int)agent_add(&sy[kSyncTicket], 1u);
+          ticket_lds = agent_add(&sy[kSyncTicket], 1u);
         }
         const int below = chunk - 32 * lane;      // chunks before this one that lane's word of marks holds
         const uint32_t want = below >= 32 ? 0xFFFFFFFFu : (below > 0 ? (1u << below) - 1u : 0u);
         const uint32_t* word = &sy[kSyncMarks + min(lane, kSyncMarkWords - 1)];
-        for (int i = 0; i < kMarkPolls && !__all((want & ~agent_load(word)) == 0u); ++i) __builtin_amdgcn_s_sleep(1);
+        for (; polls > 0 && !__all((want & ~agent_load(word)) == 0u); --polls) __builtin_amdgcn_s_sleep(1);
       }
       __syncthreads();
-      next = ticket_lds * chunk_rows;
+      ticket = ticket_lds;
+      next = ++taken < chunks ? chunk_first_row(ticket, chunks, chunk_rows, D.k) : D.k;
     }
 #pragma unroll
     for (int i = 0; i < kUnroll; ++i) {
@@ -403,11 +409,12 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   }
   const bool shared = per_unit > 1;
   if (!shared) per_unit = 1;
+  const int chunks = shared ? (D.k + chunk_rows - 1) / chunk_rows : 0;
   const int threads = sc_threads(shared, shared && lds_row);
   const dim3 grid((unsigned)D.units_run * per_unit), block(threads);
 #define CCD_LAUNCH(CH, RB, BF, SHARED)                                                                                  \
   launch((select_compact_kernel<CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
-         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunk_rows, sync)
+         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync)
 #define CCD_LAUNCH_RB(CH, SHARED)                                          \
   if (Krot == nullptr) CCD_LAUNCH(CH, 0, true, SHARED);                    \
   else if (rowb == 128) CCD_LAUNCH(CH, 128, true, SHARED);                 \
@@ -416,11 +423,11 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   else CCD_LAUNCH(CH, 512, false, SHARED)
 #define CCD_LAUNCH_SHARED(CH) \
   if (shared) { CCD_LAUNCH_RB(CH, true); } else { CCD_LAUNCH_RB(CH, false); }
-  const int chunks = shared && lds_row ? 8 : (D.n + 4 * threads - 1) / (4 * threads);     // per thread
-  if (chunks <= 1)      { CCD_LAUNCH_SHARED(1); }
-  else if (chunks <= 2) { CCD_LAUNCH_SHARED(2); }
-  else if (chunks <= 4 && shared) { CCD_LAUNCH_RB(4, true); }
-  else                  { CCD_LAUNCH_SHARED(kLdsRow); }
+  const int token_chunks = shared && lds_row ? 8 : (D.n + 4 * threads - 1) / (4 * threads);     // per thread
+  if (token_chunks <= 1)      { CCD_LAUNCH_SHARED(1); }
+  else if (token_chunks <= 2) { CCD_LAUNCH_SHARED(2); }
+  else if (token_chunks <= 4 && shared) { CCD_LAUNCH_RB(4, true); }
+  else                        { CCD_LAUNCH_SHARED(kLdsRow); }
 #undef CCD_LAUNCH_SHARED
 #undef CCD_LAUNCH_RB
 #undef CCD_LAUNCH

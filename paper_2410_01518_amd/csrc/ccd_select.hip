@@ -21,7 +21,11 @@ __global__ __launch_bounds__(kSelThreads) void finalize_select_kernel(Dims D, co
   Row<kSelThreads, CH> row(D, sh, unit, u, scores, nov);
   int32_t* out = SELECT ? keep_idx + (int64_t)unit * D.k : nullptr;
   select_row<kSelThreads, CH, SELECT>(row, scores != nullptr ? scores + (int64_t)unit * D.n : nullptr,
-                         [&](int pos, int t, int, int) { out[pos] = t; });
+                         [&](int pos, int t, int, int) {
+                           // (a row that is pooled anew in every step may be overwritten meanwhile by a call that overlaps on
+                           // the workspace: the list is undefined then, but stays in its place)
+                           if (CH != kLongRow || pos < D.k) out[pos] = t;
+                         });
 }
 
 }  // namespace
