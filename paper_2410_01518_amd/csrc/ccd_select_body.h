@@ -53,7 +53,8 @@ __device__ __forceinline__ float pooled(const float* __restrict__ u, int t, int 
 // Pooling straight from the row in global memory: the row was written by the kernel before this one and is served by the
 // caches; a copy in LDS would cost a barrier and, for the longest rows, 128 KiB.  Two steps, so that a chunk loop can
 // have the loads of several chunks in flight: `win` holds tokens t - 4 .. t + 7, the row's ends filled with what is neutral
-// for the mode (max clips its window at the ends, avg pads with zeros).
+// for the mode (max clips its window at the ends: a NaN never replaces a number, and a window of NaN stays NaN; avg pads with
+// zeros).
 struct PoolSpec {
   int n, w, mode;
   bool plain, wide;      // no pooling; a window that does not fit `win`
@@ -62,7 +63,7 @@ struct PoolSpec {
 };
 __device__ __forceinline__ void pool_load(float (&win)[12], const float* __restrict__ u, int t, const PoolSpec& P) {
   if (P.wide) return;
-  const float fill = P.mode == 1 ? -INFINITY : 0.f;
+  const float fill = P.mode == 1 ? __builtin_nanf("") : 0.f;
   if (__all(t >= 4 && t + 7 < P.n)) {
     const Floats4 a = *reinterpret_cast<const Floats4*>(u + t - 4), b = *reinterpret_cast<const Floats4*>(u + t),
                   c = *reinterpret_cast<const Floats4*>(u + t + 4);

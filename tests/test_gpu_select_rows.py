@@ -80,3 +80,19 @@ def test_compress_moves_what_the_scores_say(units, n, k, fp32, rope, per_head):
         ref = torch.zeros_like(K)
         ip.ccd_cr_rope(ip.make_shape(None, K, None, k=k), K, cos, sin, k, ref)
         assert torch.equal(K_rot, ref)
+
+
+@pytest.mark.parametrize("mode", [ip.CCD_POOL_MAX, ip.CCD_POOL_AVG])
+@pytest.mark.parametrize("n", [2, 300, 4097, 9000, 33000])
+def test_scores_that_are_nan_stay_nan_at_the_ends_of_a_row(n, mode):
+    """A NaN key makes every probability of its unit NaN; pooling clips its window at the ends of the row and keeps the NaN."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    K = torch.randn((1, 1, 2, n, 64), generator=g, device="cuda").to(torch.bfloat16)
+    K[0, 0, 1, n // 2, 3] = float("nan")
+    Q = torch.randn((1, 1, 2, 2, 64), generator=g, device="cuda").to(torch.bfloat16)
+    shape = ip.make_shape(Q, K, None, k=max(1, n // 2), T=0, pool_w=7, pool_mode=mode)
+    ws = ip.alloc_workspace(shape)
+    scores = torch.empty((1, 1, 2, n), dtype=torch.float32, device="cuda")
+    print(f"nan scores n={n} mode={mode}", flush=True)
+    assert ip.ccd_score(shape, Q, K, None, scores, ws) == ip.CCD_OK
+    assert bool(torch.isfinite(scores[0, 0, 0]).all()) and bool(torch.isnan(scores[0, 0, 1]).all())
