@@ -36,18 +36,59 @@ __device__ __forceinline__ void load_row4(float (&out)[4], const float* __restri
 
 constexpr int kPoolReach = 4;   // windows of up to 2 * 4 + 1 tokens are pooled from three vector loads
 
-// pooled score of token t, any window
-__device__ __forceinline__ float pooled(const float* __restrict__ u, int t, int n, int w, int mode) {
-  const int r = w >> 1;
-  const int lo = max(0, t - r), hi = min(n - 1, t + r);
-  if (mode == 1) {
-    float m = u[lo];
-    for (int j = lo + 1; j <= hi; ++j) m = fmaxf(m, u[j]);
-    return m;
+// elements j .. j + 3 of a row, `fill` before its start and past its end
+__device__ __forceinline__ void load_clipped4(float (&v)[4], const float* __restrict__ u, int j, int n, float fill) {
+  if (__all(j >= 0 && j + 3 < n)) {
+    const Floats4 f = *reinterpret_cast<const Floats4*>(u + j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = f.v[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = u[min(max(j + i, 0), n - 1)];
+      v[i] = j + i >= 0 && j + i < n ? x : fill;
+    }
   }
-  float s = 0.f;
-  for (int j = lo; j <= hi; ++j) s += u[j];
-  return s / (float)w;
+}
+// Pooled scores of tokens t .. t + 3 for windows of more than 2 * kPoolReach + 1: four windows share all but three elements at
+// either end, so they are pooled together, four elements a load, each window in the order of its elements.  Bound by these loads
+// from the caches, a sixteenth of one load per element and window (select_compact with its score pass, windows of 31 / 255 tokens:
+// 256 units of 4096 tokens 91 -> 68 us / 295 -> 99 us; 8 units of 65536 tokens, which pool in every step, 2.8 -> 0.56 ms).
+template <bool MAX>
+__device__ __forceinline__ void pooled_wide(float (&out)[4], const float* __restrict__ u, int t, int n, int w) {
+  const int last = w - 1, first = t - (w >> 1);                // element o of the four: token first + o; window i: o in [i, i + last]
+  const float fill = MAX ? __builtin_nanf("") : 0.f;           // (neutral: fmaxf passes over NaN)
+  auto put = [&](int i, float v) { out[i] = MAX ? fmaxf(out[i], v) : out[i] + v; };
+  float v[4];
+  load_clipped4(v, u, first, n, fill);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[i] = fill;
+#pragma unroll
+    for (int e = i; e < 4; ++e) put(i, v[e]);
+  }
+  int o = 4;
+#pragma unroll 1
+  for (; o + 3 <= last; o += 4) {
+    load_clipped4(v, u, first + o, n, fill);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put(i, v[e]);
+  }
+#pragma unroll 1
+  for (; o <= last + 3; o += 4) {
+    load_clipped4(v, u, first + o, n, fill);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (o + e <= i + last) put(i, v[e]);
+  }
+  if (!MAX) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] /= (float)w;
+  }
 }
 
 // Pooling straight from the row in global memory: the row was written by the kernel before this one and is served by the
@@ -84,12 +125,8 @@ __device__ __forceinline__ void pool_reduce(float (&out)[4], const float (&win)[
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = win[4 + i];
   } else if (P.wide) {
-#pragma unroll 1
-    for (int i = 0; i < 4; ++i) {
-      const float v = t + i < P.n ? pooled(u, t + i, P.n, P.w, P.mode) : 0.f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) out[j] = i == j ? v : out[j];
-    }
+    if (P.mode == 1) pooled_wide<true>(out, u, t, P.n, P.w);
+    else             pooled_wide<false>(out, u, t, P.n, P.w);
   } else {
     const int r = P.w >> 1;
     if (P.mode == 1) {

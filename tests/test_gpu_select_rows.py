@@ -96,3 +96,34 @@ def test_scores_that_are_nan_stay_nan_at_the_ends_of_a_row(n, mode):
     print(f"nan scores n={n} mode={mode}", flush=True)
     assert ip.ccd_score(shape, Q, K, None, scores, ws) == ip.CCD_OK
     assert bool(torch.isfinite(scores[0, 0, 0]).all()) and bool(torch.isnan(scores[0, 0, 1]).all())
+
+
+@pytest.mark.parametrize("w", [9, 11, 13, 31, 255])
+@pytest.mark.parametrize("n", [3, 50, 4099, 9001, 33000])
+def test_pooling_windows_wider_than_a_register_window(n, w):
+    """Pooled scores are the maximum, or the sum in token order over w, of the scores without pooling: bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(n + w)
+    K = torch.randn((1, 1, 2, n, 64), generator=g, device="cuda").to(torch.bfloat16)
+    Q = torch.randn((1, 1, 2, 2, 64), generator=g, device="cuda").to(torch.bfloat16)
+
+    def score(w, mode):
+        shape = ip.make_shape(Q, K, None, k=max(1, n // 2), T=0, pool_w=w, pool_mode=mode)
+        scores = torch.empty((1, 1, 2, n), dtype=torch.float32, device="cuda")
+        keep = torch.empty((1, 1, 2, max(1, n // 2)), dtype=torch.int32, device="cuda")
+        K1, V1 = K.clone(), K.clone()
+        assert ip.ccd_compress(shape, Q, K1, V1, None, keep, ip.alloc_workspace(shape), scores=scores) in (ip.CCD_OK, ip.CCD_NOOP)
+        return gu.to_host(scores).reshape(2, n), gu.to_host(keep).reshape(2, -1)
+
+    print(f"wide pooling n={n} w={w}", flush=True)
+    u, _ = score(1, ip.CCD_POOL_NONE)
+    r = w // 2
+    for mode, fill in ((ip.CCD_POOL_MAX, -np.inf), (ip.CCD_POOL_AVG, 0.0)):
+        got, keep = score(w, mode)
+        pad = np.pad(u, ((0, 0), (r, r)), constant_values=np.float32(fill))
+        want = pad[:, :n].copy()
+        for o in range(1, w):
+            want = np.maximum(want, pad[:, o:o + n]) if mode == ip.CCD_POOL_MAX else want + pad[:, o:o + n]
+        if mode == ip.CCD_POOL_AVG:
+            want = want / np.float32(w)
+        assert np.array_equal(got, want)
+        assert np.array_equal(keep, np.stack([O.select(row, keep.shape[1]) for row in got]))
