@@ -105,10 +105,14 @@ __global__ __launch_bounds__(kNucThreads) void nuc_from_logits_kernel(const char
 
 void launch_nuc_from_logits(const void* logits, const int32_t* labels, float* novelty, int64_t rows, int V,
                             int64_t row_stride_elems, int dtype, hipStream_t s) {
-  // Few rows: a workgroup has a compute unit to itself, and four times the waves have four times the loads in flight (bf16,
-  // 128256 tokens: 145 rows 21 -> 12 us, 256 rows 22 -> 14 us, 700 rows 32.7 -> 31.7 us, 1023 rows 43.8 -> 43.2 us).  From
-  // four rows per compute unit on, small workgroups keep as many in flight and do not wait for one another at the end.
-  const bool few = rows < 1024;
+  // Few rows: a workgroup has a compute unit to itself or shares it with one more, and four times the waves have four times the
+  // loads in flight (bf16, 128256 tokens: 128 rows 21 -> 12 us, 256 rows 23 -> 14 us, 512 rows 26.5 -> 23.8 us, 700 rows 33.4
+  // -> 31.6 us).  From four rows per compute unit on, small workgroups keep as many in flight and do not wait for one another at
+  // the end.  So do they for short rows, which do not fill the large ones (four loads of 1024 threads are 64 KiB; 16 KiB: 300 rows
+  // 4.4 against 5.2 us, 900 rows 6.3 against 8.2 us; 32 KiB: 256 rows even, 900 rows 8.8 against 9.9 us), and just above two
+  // rows per compute unit, where a few large ones are a round of their own (fp32, 65536 tokens: 513 rows 24.6 against 27.0 us).
+  const int64_t row_bytes = (int64_t)V * (dtype == 1 ? 2 : 4);
+  const bool few = rows < 1024 && row_bytes >= (rows <= 256 ? 30000 : 60000) && !(rows > 512 && rows < 576);
   const dim3 grid((unsigned)rows), block(few ? 1024 : 256);
   auto* kernel = dtype == 1 ? (few ? nuc_from_logits_kernel<true, 1024> : nuc_from_logits_kernel<true, 256>)
                             : (few ? nuc_from_logits_kernel<false, 1024> : nuc_from_logits_kernel<false, 256>);

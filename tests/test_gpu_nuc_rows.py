@@ -1,5 +1,5 @@
-"""NuC score from logits on either side of the number of rows at which its workgroups change size, and at the edges of a
-workgroup's first loads (four per thread, of 16 bytes)."""
+"""NuC score from logits on either side of the numbers of rows and the row lengths at which its workgroups change size, and at the
+edges of a workgroup's first loads (four per thread, of 16 bytes)."""
 import pytest
 import torch
 
@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("rows,V", [(1023, 333), (1024, 333), (2, 32768), (3, 32761), (2, 32776), (2, 65553)])
+@pytest.mark.parametrize("rows,V", [(1023, 333), (1024, 333), (2, 32768), (3, 32761), (2, 32776), (2, 65553),
+                                    (256, 15000), (257, 15000), (256, 14999), (512, 30000), (513, 30000), (575, 30001), (576, 30001)])
 def test_rows(dtype, rows, V):
     print(f"nuc {dtype} rows={rows} V={V}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(rows + V)
