@@ -61,6 +61,20 @@ def algorithmic_flops(cfg) -> float:
     return 2.0 * cfg.units * cfg.G * cfg.P * cfg.N * cfg.d
 
 
+def score_kernel_rate(stage, dtype, score_path, flops, seconds):
+    """The unit a score kernel is bound by and the rate it reaches.  fp32 products run as bf16 products on the matrix cores -
+    three in the unit kernel (values as hi + lo), six in the passes over token slices that the automatic choice takes otherwise -
+    and are counted as executed; score_path 1 names the vector ALUs."""
+    if score_path == 1:
+        return {"kernel": stage, "bound": "alu", "achieved": flops / seconds / 1e12, "peak": VALU_FP32_PEAK_TFLOPS, "unit": "TFLOP/s"}
+    products = 1 if dtype == "bf16" else 3 if stage == "score_unit" else 6
+    r = {"kernel": stage, "bound": "mfma", "achieved": products * flops / seconds / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
+         "unit": "TFLOP/s"}
+    if products > 1:
+        r["note"] = f"fp32 values as sums of bf16: {products} bf16 products per fp32 product, counted as executed"
+    return r
+
+
 def stream_measure(reps, dev, torch, ip, synth):
     """Streaming use of the step (Sec. 3.2): a 131072-token context of a 32-layer, 8-KV-head, d 128 model is fed into a
     pot of 4096 in 2048-token chunks (seeded synthetic K, V, novelty already resident in HBM); whenever the next chunk
@@ -533,14 +547,7 @@ def main() -> int:
         t = stage_avg_us[stage] * 1e-6
         if stage in ("score_stats", "score_prob", "score_unit"):
             flops = algorithmic_flops(cfg) * (2 if stage == "score_unit" and not args.lse else 1)   # both passes in one kernel
-            if stage == "score_unit" and cfg.dtype == "fp32":
-                # an fp32 product runs as three bf16 products on the matrix cores: executed flops against the bf16 peak
-                r = {"kernel": stage, "bound": "mfma", "achieved": 3 * flops / t / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "note": "fp32 values as hi + lo bf16: three bf16 products per fp32 product, counted as executed"}
-            elif args.score_path == 1 or cfg.dtype == "fp32":
-                r = {"kernel": stage, "bound": "alu", "achieved": flops / t / 1e12, "peak": VALU_FP32_PEAK_TFLOPS, "unit": "TFLOP/s"}
-            else:
-                r = {"kernel": stage, "bound": "mfma", "achieved": flops / t / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s"}
+            r = score_kernel_rate(stage, cfg.dtype, args.score_path, flops, t)
         else:
             r = {"kernel": stage, "bound": "hbm", "achieved": ab[stage] / t / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s"}
         r["frac"] = r["achieved"] / r["peak"]

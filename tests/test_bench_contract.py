@@ -31,6 +31,19 @@ def test_algorithmic_figures_of_the_headline_configuration():
     assert bench.algorithmic_flops(cfg) == 2.0 * units * 256 * 4096 * 128
 
 
+@pytest.mark.parametrize("stage,dtype,path,bound,products", [
+    ("score_unit", "bf16", 0, "mfma", 1), ("score_stats", "bf16", 2, "mfma", 1), ("score_prob", "bf16", 1, "alu", 1),
+    ("score_stats", "fp32", 0, "mfma", 6), ("score_prob", "fp32", 0, "mfma", 6), ("score_unit", "fp32", 0, "mfma", 3),
+    ("score_unit", "fp32", 3, "mfma", 3), ("score_stats", "fp32", 1, "alu", 1)])
+def test_bound_of_the_score_kernels(stage, dtype, path, bound, products):
+    """A pass over 256 units of 4096 fp32 tokens (68.7 GFLOP) takes 330 us on the matrix cores: 208 TFLOP/s of fp32 products, more
+    than the vector ALUs have."""
+    import bench
+    r = bench.score_kernel_rate(stage, dtype, path, 68.7e9, 330e-6)
+    assert r["bound"] == bound and abs(r["achieved"] - products * 68.7e9 / 330e-6 / 1e12) < 1e-9 * r["achieved"]
+    assert r["peak"] == (bench.VALU_FP32_PEAK_TFLOPS if bound == "alu" else bench.MFMA_BF16_PEAK_TFLOPS)
+
+
 @pytest.mark.gpu
 def test_json_line_has_the_contract_keys():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--steps", "8", "--warmup", "2", "--cpu-units", "4"],
