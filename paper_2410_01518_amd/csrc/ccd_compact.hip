@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
                                                                  const float* nov_new, int nov_per_head) {
   const int seg = blockIdx.x % segs;
   const int ut = blockIdx.x / segs;
-  const int unit = ut >> 1;
+  const int unit = D.unit0 + (ut >> 1);
   const bool isV = ut & 1;
   const UnitIdx ui = decode_unit(D, unit);
   const int64_t run = (int64_t)count * D.d * esz;                         // bytes of a unit's share
@@ -452,9 +452,15 @@ void launch_append(const Dims& D, int count, void* K, void* V, const void* K_new
   const int esz = D.dtype == 0 ? 4 : 2;
   const int64_t run = (int64_t)count * D.d * esz;
   const int segs = (int)((run + kApSegBytes - 1) / kApSegBytes);
-  dim3 grid((unsigned)(D.units * 2 * segs)), block(kApThreads);
-  launch(append_rows_kernel, grid, block, s, D, esz, count, segs, (char*)K, (char*)V, (const char*)K_new,
-         (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0);
+  // (a grid has fewer than 2^32 threads: millions of units go in several launches)
+  const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 31) / ((int64_t)2 * segs * kApThreads));
+  Dims R = D;
+  for (int64_t u0 = 0; u0 < D.units; u0 += most) {
+    R.unit0 = (int)u0;
+    R.units_run = (int)std::min<int64_t>(most, D.units - u0);
+    launch(append_rows_kernel, dim3(2u * R.units_run * segs), dim3(kApThreads), s, R, esz, count, segs, (char*)K, (char*)V,
+           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0);
+  }
 }
 
 void launch_compact(const Dims& D, const void* Ksrc, const void* Vsrc, const int32_t* keep_idx, void* Kdst, void* Vdst,

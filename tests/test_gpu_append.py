@@ -17,8 +17,8 @@ def _cfg(**kw):
     return synth.CCDConfig(**base)
 
 
-# (cache type, head dimension, pot size, cached tokens, chunk length): chunk shares of a unit below, at and above one
-# workgroup's 64 KiB, not multiples of it, an empty pot, a chunk that fills the pot exactly, an empty chunk
+# (cache type, head dimension, pot size, cached tokens, chunk length): chunk shares of a unit below, at and above four and more of
+# the 16 KiB a workgroup moves, not multiples of it, an empty pot, a chunk that fills the pot exactly, an empty chunk
 CASES = [
     ("bf16", 128, 700, 300, 100), ("bf16", 128, 700, 0, 700), ("bf16", 128, 4096, 2048, 2048), ("bf16", 64, 515, 3, 509),
     ("fp32", 64, 600, 100, 257), ("fp32", 128, 300, 299, 1), ("bf16", 128, 700, 300, 0), ("bf16", 128, 1300, 7, 1033),
@@ -100,3 +100,22 @@ def test_streaming_pot_appends_and_distils_like_the_oracle():
         np.testing.assert_array_equal(gu.to_host(pot.K)[..., :n, :], hK[..., :n, :])
         np.testing.assert_array_equal(gu.to_host(pot.V)[..., :n, :], hV[..., :n, :])
         np.testing.assert_array_equal(gu.to_host(pot.novelty)[..., :n], hn[..., :n])
+
+
+def test_append_to_more_units_than_one_grid_has_threads_for():
+    """Four million units whose shares of 16.5 KiB take two workgroups a tensor: more than 2^32 threads, so several launches.  The
+    layers of a sequence are one piece of memory, and K and V are one chunk: 69 GB of it."""
+    B, L, rows = 2, (1 << 21) + 1, 129
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 69 GB of device memory")
+    K, V = (torch.zeros((B, 1, 1, rows, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    new = torch.empty((B, L, 1, rows, 64), dtype=torch.bfloat16, device="cuda")
+    new[0], new[1] = 1.0, 2.0
+    shape = ip.make_shape(None, K.expand(B, L, 1, rows, 64), None, k=1, n_valid=0)
+    print(f"append units={B * L} rows={rows}", flush=True)
+    assert ip.ccd_append(shape, K, V, None, new, new, None) == ip.CCD_OK
+    torch.cuda.synchronize()
+    del new
+    torch.cuda.empty_cache()
+    for t in (K, V):
+        assert bool((t[0] == 1.0).all()) and bool((t[1] == 2.0).all())
