@@ -348,7 +348,7 @@ def test_fused_compress_rows_of_several_thousand_tokens(per_head, N, score_path)
     _check_fused(cfg, inp, ref, dev, scores, keep, per_head)
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 64)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("fused", [True, False])
 def test_strided_layouts(dtype, d, fused):
     """K and V stored head-major with padding rows ([B, Hkv + 1, L, n_cap + 8, d], seen as [B, L, Hkv, n_cap, d] through

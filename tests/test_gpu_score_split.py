@@ -22,7 +22,7 @@ CASES = [
     (1, 2, 129, 520, 128, "kcat"), (1, 8, 70, 333, 128, "window"), (1, 8, 64, 1409, 128, "lse"),
     (260, 1, 2, 700, 128, "kcat"), (260, 2, 3, 700, 128, "window"),
     (1, 1, 3, 7001, 64, ""), (2, 2, 20, 300, 64, "kcat"), (1, 4, 80, 515, 64, "kcat window"), (3, 1, 33, 130, 64, "window"),
-    (260, 1, 2, 700, 64, "window"),
+    (260, 1, 2, 700, 64, "window"), (1, 1, 2100, 2600, 64, "window"),
 ]
 
 

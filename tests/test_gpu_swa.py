@@ -59,9 +59,8 @@ def test_scores_under_a_sliding_window(case, with_cap, path):
     cfg = _cfg(**SWA_CASES[case]["cfg"])
     window = SWA_CASES[case]["window"](cfg)
     if cfg.dtype == "fp32":
-        if path != ip.CCD_PATH_MFMA_SLICES:
-            pytest.skip("fp32 caches have one path")
-        path = ip.CCD_PATH_AUTO
+        # the automatic choice (sums of six bf16 products) and the vector ALUs, the two paths that take a window
+        path = ip.CCD_PATH_AUTO if path == ip.CCD_PATH_MFMA_SLICES else ip.CCD_PATH_VALU
     print(f"swa case={case} window={window} with_cap={with_cap} path={path} {cfg}", flush=True)
     got, ref = _score(cfg, window, with_cap=with_cap, path=path)
     gu.assert_scores_close(got, ref["scores"], cfg.G * cfg.P)
