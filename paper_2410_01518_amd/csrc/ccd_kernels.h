@@ -51,7 +51,9 @@ ScorePlan plan_score(const Dims& D, bool cap_keys);
 // pass 1: per (unit, slice, query) running maximum and sum of exp2 of the log2-domain logits
 void launch_stats_valu(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, float2* part, hipStream_t s);
 // merge the per-slice statistics into one log2-sum-exp per (unit, query)
-void launch_merge(const Dims& D, const ScorePlan& pl, const float2* part, float* lse2, hipStream_t s);
+// (Q, K, K_cap are read where statistics of launch_stats_split came out as NaN)
+void launch_merge(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,
+                  float* lse2, hipStream_t s);
 // pass 2: u[unit, t] = sum over queries of exp2(logit2 - lse2)
 // (lse2 in log2 units, or the caller's natural-log-sum-exps when pl.lse_given)
 void launch_prob_valu(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float* lse2, float* u,

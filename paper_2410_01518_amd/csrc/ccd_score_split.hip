@@ -10,7 +10,8 @@
 //
 // An element that rounds to an infinite bf16 (infinities, and finite values from 3.396e38 on) leaves remainders that are no
 // numbers, and every logit it takes part in comes out as NaN, which reaches each sum that such a logit enters.  So the sums
-// tell: a row's statistics of a slice, or a token's score, that come out as NaN are computed again by a chain of fp32 fmas.
+// tell: a row's statistics of a slice (in the merge kernel), or a token's score (at the end of pass 2), that come out as NaN are
+// computed again by a chain of fp32 fmas.  Calls without such elements pay 0.2 % (256 units of 4096 tokens) to 1.5 % (short rows).
 //
 // Bound by the matrix cores: 6 x 2 x 68.7 GFLOP for 256 units of 4096 tokens and 256 query rows of 128 elements.  A workgroup
 // of eight waves (two per SIMD: one folds while the other one multiplies) takes one slice of a unit's tokens and up to 256
@@ -69,7 +70,7 @@ struct SplitLds {
   bf16x8 k[2][2][3 * KQ][64];                // [buffer][tile][h: 0.., m: KQ.., l: 2 KQ..][lane]
   float ub[4][kSplitWaves][kStage];          // pass 2: token sums of a stage per row block; pass 1: (reference, sum) pairs at the end
   int first[kSplitRows];                     // pass 2 under a window: the first token a query row sees
-  int nan_out;                               // pass 2: some token's sum is NaN
+  int nan_out;                               // pass 2: some token's score is NaN
 };
 
 // logit of a query row that is held in registers and a key (times the scale), as the vector-ALU kernels take it
@@ -90,6 +91,28 @@ template <int HD>
 __device__ __forceinline__ void load_row(float4 (&a)[HD / 4], const float* __restrict__ p) {
 #pragma unroll
   for (int i = 0; i < HD / 4; ++i) a[i] = load4(p + 4 * i);
+}
+// Scores that came out as NaN again, by a chain of fp32 fmas for every logit (the merge kernel does the same for statistics): u[t] =
+// sum of 2^(x - lse[q]) over the rows q that see token t (first + q % P and later ones), t in [t0, t1).  By one wave.  Not inlined:
+// the kernel around has no registers to spare, and code that is jumped over costs a miss of the instruction cache per launch
+// (inlined: 1 us a pass).
+template <int HD>
+__device__ __noinline__ void scores_again(int GP, int P, int first, int t0, int t1, const float* __restrict__ Q, int64_t q_sh,
+                                          const float* __restrict__ Ku, float c, const float* __restrict__ lse, float lse_mul,
+                                          float* __restrict__ u) {
+  __threadfence_block();
+  for (int t = t0 + (int)(threadIdx.x & 63); t < t1; t += 64) {
+    if (u[t] == u[t]) continue;
+    float4 kr[HD / 4];
+    load_row<HD>(kr, Ku + (int64_t)t * HD);
+    float sum = 0.f;
+    for (int q = 0; q < GP; ++q) {
+      const int g = q / P, i = q - g * P;
+      if (t < first + i) continue;
+      sum += fast_exp2(fmaf(plain_dot<HD>(kr, Q + g * q_sh + (int64_t)i * HD), c, -lse[q] * lse_mul));
+    }
+    u[t] = sum;
+  }
 }
 
 // PASS 1: part[unit, slice, q] = (maximum, sum of 2^(x - maximum)) of the log2-domain logits x of query row q over the slice;
@@ -119,7 +142,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, col = lane & 31, half = lane >> 5;
   const float c = D.scale_log2;
-  if (PASS == 2 && tid == 0) sm.nan_out = 0;   // (set by the same wave)
+  if (PASS == 2 && tid == 0) sm.nan_out = 0;   // (set and read by the same wave)
 
   // staging: eight consecutive threads take the same elements of eight consecutive rows (their LDS writes are contiguous)
   const int st_c = (tid >> 3) % (HD / 8), st_row = (tid / HD) * 8 + (tid & 7);
@@ -171,9 +194,14 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
         const int qr = qc + rb * 32 + acc_row(r, half);
         const float l = lse2[(int64_t)unit * D.GP + min(qr, D.GP - 1)] * lse_mul;
         nl[r] = qr < D.GP ? -l : -INFINITY;
-        // A last CaP token whose window holds no cached token (window == P) takes no part either: a normaliser over cached
-        // tokens alone is -infinity for it, and its masked logits would come out as -infinity + infinity.
-        if (D.head > 0 && D.win_off + D.P > D.n && qr % D.P == D.P - 1) nl[r] = -INFINITY;
+      }
+      // A last CaP token whose window holds no cached token (window == P) takes no part either: a normaliser over cached tokens
+      // alone is -infinity for it, and its masked logits would come out as -infinity + infinity.
+      if (D.head > 0 && D.win_off + D.P > D.n) {
+#pragma unroll 1
+        for (int i = D.P - 1; i < D.GP; i += D.P)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) nl[r] = qc + rb * 32 + acc_row(r, half) == i ? -INFINITY : nl[r];
       }
       if (D.head > 0 && tid < kSplitRows) sm.first[tid] = D.win_off + (qc + tid) % D.P;
     }
@@ -318,37 +346,15 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
           const float mm = fmaxf(a.x, b.x);
           a = make_float2(mm, a.y * fast_exp2((a.x - mm) * c) + b.y * fast_exp2((b.x - mm) * c));
         }
-        a.x *= c;
-        if (a.y != a.y) {         // again, one token after the other (a -infinite logit has no part in it)
-          float4 qr[HD / 4];
-          load_row<HD>(qr, Q + q_offset(D, ui, q));
-          a = make_float2(-INFINITY, 0.f);
-          for (int t = max(t0, lo); t <= hi; ++t) {
-            const float x = plain_dot<HD>(qr, Ku + (int64_t)t * HD) * c;
-            if (x > a.x) a = make_float2(x, a.y * fast_exp2(a.x - x) + 1.f);
-            else if (x != -INFINITY) a.y += fast_exp2(x - a.x);
-          }
-        }
-        part[cap ? extra_block_index(D, pl, unit, q) : ((int64_t)unit * pl.n_slices1 + slice) * D.GP + q] = a;
+        part[cap ? extra_block_index(D, pl, unit, q) : ((int64_t)unit * pl.n_slices1 + slice) * D.GP + q] =
+            make_float2(a.x * c, a.y);
       }
     }
     __syncthreads();          // the LDS tables are rewritten by the next sweep
   }
-  if (PASS == 2 && __builtin_expect(__builtin_amdgcn_readfirstlane(sm.nan_out) != 0, 0)) {
-    for (int t = t0 + tid; t < t1; t += kSplitThreads) {
-      float* out = u + (int64_t)unit * D.n + t;
-      const float v = *out;
-      if (v == v) continue;
-      float4 kr[HD / 4];
-      load_row<HD>(kr, Ku + (int64_t)t * HD);
-      float sum = 0.f;
-      for (int q = 0; q < D.GP; ++q) {
-        if (D.window > 0 && t < D.win_off + q % D.P) continue;
-        sum += fast_exp2(fmaf(plain_dot<HD>(kr, Q + q_offset(D, ui, q)), c, -lse2[(int64_t)unit * D.GP + q] * lse_mul));
-      }
-      *out = sum;
-    }
-  }
+  if (PASS == 2 && wave == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(sm.nan_out) != 0, 0))
+    scores_again<HD>(D.GP, D.P, D.window > 0 ? D.win_off : -D.P, t0, t1, Q + q_offset(D, ui, 0), D.q_sh, Ku, c,
+                     lse2 + (int64_t)unit * D.GP, lse_mul, u + (int64_t)unit * D.n);
 }
 
 }  // namespace

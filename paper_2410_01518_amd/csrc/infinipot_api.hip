@@ -327,7 +327,7 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     else                 launch_stats_valu(D, pl, Q, K, part, st);
     g_prof.end(st);
     g_prof.begin(kStMerge, st);
-    launch_merge(D, pl, part, lse2, st);
+    launch_merge(D, pl, Q, K, K_cap, part, lse2, st);
     g_prof.end(st);
     g_prof.begin(kStProb, st);
     if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse2, u, st);
