@@ -39,9 +39,12 @@ constexpr int kCpUnroll = 4;
 // Appending a chunk of new context behind the cached tokens (Sec. 3.2: the pot is filled until it is full): rows
 // [n, n + count) of every unit of K and V take the chunk's rows, dense [units, count, d] on the source side.  A unit's
 // share is one contiguous run on both sides; the grid is (unit, tensor, segment of 16 KiB), 16 bytes per lane and
-// four of them in flight.  Bound by HBM (256 units, 2048 tokens: 537 MB in 84 us) or, for a few units, by how many compute
-// units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.
-// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.
+// four loads in flight (a store waits for all of them, and for the store before it).  Bound by HBM (256 units, 2048 tokens: 537 MB
+// in 84 us) or, for a few units, by how many compute
+// units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  (Where chunk and pot stay in
+// the memory-side cache from one call to the next, 130 to 270 MB in all, those of 64 KiB were 4 to 11 % faster.)
+// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.  One workgroup per head copies it, one
+// entry per thread after the other: 32768 tokens of 8 units take 57 us with novelty and 37 us without.
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
@@ -120,7 +123,8 @@ __global__ __launch_bounds__(kCpThreads) void compact_rows_kernel(Dims D, const 
   }
 }
 
-// Out of place nothing orders the rows: (unit, tensor, run of destination rows) per workgroup, four rows per lane in flight.
+// Out of place nothing orders the rows: (unit, tensor, run of destination rows) per workgroup, four rows per lane, three of them in
+// flight (the compiler puts the first row's load behind the test that guards its store).
 // Bound by HBM; the kernel above has two workgroups per unit, which leave the chip idle with few units (45 units, 3001 -> 1499
 // rows of 128 bytes: 17.4 -> 8.3 us).
 constexpr int kGaThreads = 256;
@@ -189,10 +193,12 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // carried novelty, which took a kernel of its own; 8 units, 32768 -> 4096: 113 -> 57 us.
 //
 // Threads: the moving of one workgroup per unit wants 16 waves (512 threads with twice the rows each: 2 - 3 us slower on 256
-// units), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
+// units, with a thread's rows loaded one after the other, see kScUnroll), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
-constexpr int kScUnroll = 2;                // rows per thread and tensor in flight
+// Rows per thread and chunk.  The loads of one row, K and V, travel together, but the next row's wait for them: they stand under a
+// condition, and behind the wait that ends a chunk in inline assembly the compiler takes their registers for still in use.
+constexpr int kScUnroll = 2;
 // Calls that overlap on one workspace are an error of the caller: one call clears the other's words, or leaves anything at all
 // in them where the shapes differ.  Their results are undefined, but every access stays in the pot and their kernels end: a
 // ticket counts only if it names a chunk of this call, a workgroup takes no more of them than there are chunks, and its waits
@@ -251,7 +257,9 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_comp
   auto keep = [&](int j) { return kRegs ? (int)keep_lds[j] : min(max(keep_out[j], 0), D.n - 1); };
   if (kRegs && part == 0)
     for (int j = threadIdx.x; j < D.k; j += THREADS) keep_out[j] = keep_lds[j];
-  auto compact_novelty = [&]() {      // (keep[j] >= j: a chunk's sources are read before anything at or above them is written)
+  // (keep[j] >= j: a chunk's sources are read before anything at or above them is written; the eight loads of a thread go out one
+  // after the other)
+  auto compact_novelty = [&]() {
     constexpr int kN = 8;
     for (int base = 0; base < D.k; base += kN * THREADS) {
       float v[kN];

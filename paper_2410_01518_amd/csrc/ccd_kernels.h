@@ -29,6 +29,7 @@ struct Dims {
 
 // What the workgroups that share a unit's selection and compaction agree on (launch_select_compact), per unit.  Units are
 // shared while there are two compute units for each: calls with more units need no such words.
+// (256 compute units: a constant, since it sizes a part of the workspace, which is asked for without a device.)
 constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgroups / 2;
 constexpr int kSyncTicket = 0, kSyncSelected = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16;
 

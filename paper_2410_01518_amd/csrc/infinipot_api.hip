@@ -167,7 +167,11 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
   // fp32 caches: the unit kernel (fp32 values as sums of bf16 products on the matrix cores) where it exists - head
   // dimension 64, plain softmax over the cached tokens - when asked for, and by itself unless a few units with long
   // rows would leave most of the chip idle under it (a workgroup takes about 27 us per 1000 tokens and sweep of 256
-  // query rows; measured faster than the vector-ALU kernels from 4 units of 512 tokens to 256 units of 4096)
+  // query rows).  Against the six-product kernels below (a whole call, 16 to 256 query rows): from half the chip's units on the unit
+  // kernel is 1.0 to 1.3 times faster at 128 units and 1.2 to 1.7 times at 192 to 400, for 512 to 16384 tokens.  The second line
+  // was drawn against the vector ALUs: up to 100 units it is 1.1 times faster at 512 tokens, but from 1024 tokens on the six-product
+  // kernels are (1 to 32 units, 256 query rows: 1024 tokens 60 against 45 us, 3000 tokens 120 against 53 us, 6000 tokens 210
+  // against 70 us), and more accurate.
   if (D.dtype == CCD_FP32 && score_unit_supported(D) && !cap_keys && D.window == 0) {
     if (D.score_path == CCD_PATH_MFMA_UNIT) {
       pl.unit_kernel = 1;
@@ -178,7 +182,10 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
     }
   }
   // every other fp32 call: sums of six bf16 products, by token slices (256 units of 4096 tokens, 256 query rows of 128
-  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them)
+  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them).  With handed-in
+  // normalisers there is one pass, and eight query rows leave the matrix tiles mostly empty: the vector ALUs are then even at 100 and
+  // 256 units and 1.1 to 1.25 times faster at 129, 160 and 400, whose last round is short (129 units of 4096 tokens: 63 against 80 us;
+  // 32 query rows: 121 against 86 us).  These calls stay here for accuracy (see ccd_score_split.hip).
   if (D.dtype == CCD_FP32 && D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) plan_split(D, compute_units(), kMinSlice, pl);
   return pl;
 }
@@ -605,7 +612,7 @@ const char* ccd_strerror(int code) {
     case CCD_EUNSUPPORTED:
       return "unsupported: head dimension not 64 or 128, unknown dtype or pool mode, more than 65536 tokens, a matrix-core "
              "score path that an fp32 cache cannot take (token slices; units with a head dimension other than 64, a window "
-             "or CaP keys), or a matrix-core score path named for a window with more than about 2000 CaP tokens";
+             "or CaP keys), or a matrix-core score path named for a bf16 cache and a window with more than about 2000 CaP tokens";
     case CCD_EALIGN: return "pointer or stride not 16-byte aligned";
     case CCD_EWORKSPACE:
       return "workspace null, misaligned or too small (ccd_compress_noalloc: the shape needs more than the built-in "
