@@ -37,7 +37,7 @@ def _draw(seed):
 
 
 def _draw_wide(seed):
-    """Long rows on a few units (the selection with 16 or 32 tokens per thread, or the separate kernels above 32768
+    """Long rows on a few units (keys of a row in registers, in LDS, or pooled anew by the separate kernels above 32768
     tokens), or many units with short rows (one selection + compaction workgroup per unit)."""
     r = np.random.default_rng(5000 + seed)
     dtype = "bf16" if r.random() < 0.8 else "fp32"
