@@ -43,8 +43,8 @@ constexpr int kCpUnroll = 4;
 // in 84 us) or, for a few units, by how many compute
 // units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  (Where chunk and pot stay in
 // the memory-side cache from one call to the next, 130 to 270 MB in all, those of 64 KiB were 4 to 11 % faster.)
-// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j.  One workgroup per head copies it, one
-// entry per thread after the other: 32768 tokens of 8 units take 57 us with novelty and 37 us without.
+// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, copied by the workgroups that move the keys
+// of those tokens (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
@@ -66,6 +66,11 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
     const int64_t b = b0 + i * (kApThreads * 16);
     if (b < run) v[i] = load_streaming(src + b);
   }
+  const int seg_tokens = kApSegBytes / (D.d * esz), j = seg * seg_tokens + threadIdx.x;      // 32, 64 or 128
+  const bool carry = novelty != nullptr && !isV && (nov_per_head || (ui.l == 0 && ui.h == 0)) &&
+                     (int)threadIdx.x < seg_tokens && j < count;
+  float nv = 0.f;
+  if (carry) nv = nov_new[(int64_t)ui.b * count + j];
 #pragma unroll
   for (int i = 0; i < kApLoads; ++i) {
     const int64_t b = b0 + i * (kApThreads * 16);
@@ -74,11 +79,7 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
       else     *reinterpret_cast<uint4*>(dst + b) = v[i];
     }
   }
-  if (novelty != nullptr && !isV && seg == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0))) {
-    float* nd = novelty + nov_offset(D, ui) + D.n;
-    const float* ns = nov_new + (int64_t)ui.b * count;
-    for (int j = threadIdx.x; j < count; j += kApThreads) nd[j] = ns[j];
-  }
+  if (carry) novelty[nov_offset(D, ui) + D.n + j] = nv;
 }
 
 template <int ROWB>
