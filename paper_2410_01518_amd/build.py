@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libinfinipot.so")
-SOURCES = ["infinipot_api.hip", "ccd_score_valu.hip", "ccd_score_mfma.hip", "ccd_score_unit.hip", "ccd_score_split.hip", "ccd_select.hip", "ccd_compact.hip",
+SOURCES = ["infinipot_api.hip", "ccd_score_valu.hip", "ccd_score_mfma.hip", "ccd_score_unit.hip", "ccd_score_split.hip", "ccd_score_direct.hip", "ccd_select.hip", "ccd_compact.hip",
            "ccd_nuc.hip"]
 # ccd_score_unit.hip keeps its query fragments at fixed places in the accumulation registers (named in its inline
 # assembly): the compiler must put nothing of its own there, so matrix-instruction results go to vector registers and

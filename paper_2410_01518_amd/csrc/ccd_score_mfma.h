@@ -118,6 +118,16 @@ __device__ __forceinline__ void load_k_frags(bf16x8 (&a)[HD / 16], const uint8_t
     a[ks] = *reinterpret_cast<const bf16x8*>(lds + SLOT * Tiles<HD>::kSlotBytes + koff[ks]);
 }
 
+// fragments of one 32-token tile, straight from global memory: lane (col, half) holds elements 16 ks + 8 half .. + 7
+// of token row t_tile + col (rows past t_last re-read row t_last: masked in pass 1, never stored in pass 2)
+template <int HD>
+__device__ __forceinline__ void load_k_tile(bf16x8 (&a)[HD / 16], const uint16_t* __restrict__ Ku, int t_tile, int t_last,
+                                            int col, int half) {
+  const uint16_t* p = Ku + (int64_t)min(t_tile + col, t_last) * HD + half * 8;
+#pragma unroll
+  for (int ks = 0; ks < HD / 16; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(p + ks * 16);
+}
+
 template <int HD>
 __device__ __forceinline__ void load_q_frags(bf16x8 (&bq)[kQB][HD / 16], const Dims& D, UnitIdx ui, const uint16_t* Q,
                                              int qbase, int col, int half) {

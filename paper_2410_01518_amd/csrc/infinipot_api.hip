@@ -123,6 +123,24 @@ static int pick_slice(const Dims& D) {
   return kMinSlice;
 }
 
+// bf16 calls that do not take the unit kernel: do the direct kernels pay, or the slice kernels (whose plan is `pl`)?  The direct
+// ones compute query rows by 64 instead of 256 and start faster, the slice kernels keep the matrix cores busier once they run.
+// Append + distill, slice kernels against direct (128 elements):
+//   up to 192 of every 256 rows in use: 24 / 64 / 150 units of 2500 tokens, 32 rows 49 / 91 / 154 against 42 / 72 / 130 us; 100 rows
+//   50 / 93 / 157 against 45 / 79 / 144 us; 24 units of 30000 tokens 321 (32 rows) and 325 (100 rows) against 283 and 307 us
+//   256 rows, few blocks of 64 tokens and rows (8 units of 2048 tokens are 1024): 39.7 against 30.7 us; 64 units of 700 (2816) 44.5
+//   against 42.7 us
+//   256 rows, more of them: the slice kernels where their grid fills its rounds of two workgroups per compute unit (8 units of 32768
+//   tokens, a whole round: 160 against 171 us), the direct ones where it does not (24 units of 9000 tokens, 864 workgroups on 512
+//   places: 140 against 126 us), up to where either takes long (24 units of 30000 tokens: 343 against 361 us)
+static bool direct_pays(const Dims& D, const ScorePlan& pl) {
+  const int64_t rows = (D.GP + 63) / 64, rows_slices = (D.GP + 255) / 256 * 4;
+  if (4 * rows <= 3 * rows_slices) return true;
+  const int64_t blocks = (int64_t)D.units_run * ((D.n + 63) / 64) * rows, slots = score_slots();
+  const int64_t wgs = (int64_t)(D.units_run + 7) / 8 * 8 * pl.n_slices1, room = (wgs + slots - 1) / slots * slots * pl.slice1;
+  return blocks <= 4096 || (blocks <= 32768 && 100 * (int64_t)D.units_run * D.n < 85 * room);
+}
+
 static ScorePlan plan_mfma(const Dims& D) {
   ScorePlan pl{};
   pl.use_mfma = 1;
@@ -133,7 +151,7 @@ static ScorePlan plan_mfma(const Dims& D) {
   pl.head_block = 0;
   pl.lse_given = 0;
   // One workgroup per unit (both passes in one kernel) when the units fill at least three fifths of the chip round by
-  // round; the slice kernels otherwise (few units: they cut a unit into token slices).  Measured on the headline shape
+  // round; kernels that cut a unit into token slices otherwise.  Unit against slice kernels, measured on the headline shape
   // with 128 / 192 / 256 / 320 units: 180 / 223 / 220 / 393 us per call against 147 / 246 / 233 / 412 us, and with
   // 32 to 128 query rows per unit (the unit kernel then sweeps 64 or 128 rows at a time) it is 15 - 20 % ahead.
   if (D.score_path == CCD_PATH_MFMA_UNIT) {
@@ -143,6 +161,7 @@ static ScorePlan plan_mfma(const Dims& D) {
     const int rounds = (D.units_run + cus - 1) / cus;
     pl.unit_kernel = (5 * (int64_t)D.units_run >= 3 * (int64_t)rounds * cus) ? 1 : 0;
   }
+  if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel && direct_pays(D, pl)) plan_direct(D, compute_units(), kMinSlice, pl);
   return pl;
 }
 
@@ -293,18 +312,28 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     pl.lse_given = 1;
     float* lse_rw = const_cast<float*>(lse);   // only read when pl.lse_given
     g_prof.begin(kStProb, st);
-    if (pl.use_mfma)          launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
+    if (pl.direct_kernel)     launch_prob_direct(D, pl, Q, K, part, lse, u, st);
+    else if (pl.use_mfma)     launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
     else if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse, u, st);
     else                      launch_prob_valu(D, pl, Q, K, lse, u, st);
     g_prof.end(st);
-    if (pl.use_mfma && D.head > 0) {
+    if (pl.use_mfma && !pl.direct_kernel && D.head > 0) {
       g_prof.begin(kStHead, st);
       launch_head_prob_mfma(D, pl, Q, K, lse, u, st);
       g_prof.end(st);
     }
     return;
   }
-  if (K_cap != nullptr && !pl.use_mfma) pl.cap_block = 1;   // (the bf16 pass 2 takes the CaP keys in its prologue)
+  if (K_cap != nullptr && (!pl.use_mfma || pl.direct_kernel)) pl.cap_block = 1;   // (launch_prob_mfma takes the CaP keys in its prologue)
+  if (pl.direct_kernel) {
+    g_prof.begin(kStStats, st);
+    launch_stats_direct(D, pl, Q, K, K_cap, part, st);
+    g_prof.end(st);
+    g_prof.begin(kStProb, st);
+    launch_prob_direct(D, pl, Q, K, part, nullptr, u, st);
+    g_prof.end(st);
+    return;
+  }
   if (pl.cap_block && !pl.split_kernel) {
     g_prof.begin(kStCapBlock, st);
     launch_cap_block_stats_valu(D, pl, Q, K_cap, part, st);
