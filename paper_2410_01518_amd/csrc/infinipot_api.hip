@@ -150,16 +150,14 @@ static ScorePlan plan_mfma(const Dims& D) {
   pl.cap_block = 0;
   pl.head_block = 0;
   pl.lse_given = 0;
-  // One workgroup per unit (both passes in one kernel) when the units fill at least three fifths of the chip round by
-  // round; kernels that cut a unit into token slices otherwise.  Unit against slice kernels, measured on the headline shape
-  // with 128 / 192 / 256 / 320 units: 180 / 223 / 220 / 393 us per call against 147 / 246 / 233 / 412 us, and with
+  // One workgroup per unit (both passes in one kernel) when the units fill at least three fifths of the chip (what is left of the
+  // units after whole rounds: units_in_whole_rounds); kernels that cut a unit into token slices otherwise.  Unit against slice
+  // kernels, measured on the headline shape with 128 / 192 / 256 units: 180 / 223 / 220 us per call against 147 / 246 / 233 us, and with
   // 32 to 128 query rows per unit (the unit kernel then sweeps 64 or 128 rows at a time) it is 15 - 20 % ahead.
   if (D.score_path == CCD_PATH_MFMA_UNIT) {
     pl.unit_kernel = 1;
   } else if (D.score_path == CCD_PATH_AUTO && score_unit_supported(D)) {
-    const int cus = compute_units();
-    const int rounds = (D.units_run + cus - 1) / cus;
-    pl.unit_kernel = (5 * (int64_t)D.units_run >= 3 * (int64_t)rounds * cus) ? 1 : 0;
+    pl.unit_kernel = 5 * D.units_run >= 3 * compute_units() ? 1 : 0;
   }
   if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel && direct_pays(D, pl)) plan_direct(D, compute_units(), kMinSlice, pl);
   return pl;
@@ -211,6 +209,25 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
 // a path the caller named that this call cannot take
 static bool path_refused(const Dims& D, const ScorePlan& pl) {
   return D.dtype == CCD_FP32 && D.score_path == CCD_PATH_MFMA_UNIT && !pl.unit_kernel;
+}
+
+// The leading units of a call that the unit kernel takes; the plan of the others is made for them alone.  One workgroup fits a
+// compute unit, so a few units beyond whole rounds cost a round of their own, while kernels that cut them into slices spread them
+// over the chip - for two launches, and more time per token: a last round that is half empty runs faster than a full one (more
+// bandwidth and clock for those who are there).  Scores of all units by the unit kernel against such a rest by itself, append + distill:
+//   rest of 8 / 32 / 64 (at most a quarter of the chip): 1200 tokens and 16 rows 133 / 138 / 145 against 124 / 130 / 140 us, 2500
+//   tokens and 256 rows 300 / 321 / 355 against 257 / 294 / 351 us; 300 tokens and 16 rows 58 / 60 / 62 against 61 / 63 / 65 us
+//   rest of 128: 2500 tokens and 256 rows 676 against 695 us, 8192 tokens and 256 rows 1798 against 1768 us, 32768 tokens and 1024
+//   rows 16.9 against 15.9 ms
+static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_keys) {
+  if (!pl.unit_kernel || D.score_path != CCD_PATH_AUTO) return D.units_run;
+  const int cus = compute_units(), rest = D.units_run % cus;
+  if (rest == 0 || rest == D.units_run) return D.units_run;
+  Dims R = D;
+  R.units_run = rest;
+  const int64_t work = (int64_t)D.n * ((D.GP + 63) / 64) * D.d;
+  const bool pays = 4 * rest <= cus ? work >= 128 * 1000 : (2 * rest <= cus && work >= 128 * 32768);
+  return pays && !plan_score(R, cap_keys).unit_kernel ? D.units_run - rest : D.units_run;
 }
 
 struct Workspace {
@@ -283,6 +300,16 @@ static int launch_status() { return hipGetLastError() == hipSuccess ? CCD_OK : C
 // with it K_cap) is not needed, the probabilities follow from one pass over K.
 static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, const void* Q, const void* K,
                            const void* K_cap, const float* lse, char* ws, hipStream_t st) {
+  const int lead = units_in_whole_rounds(D, pl, K_cap != nullptr);
+  if (lead < D.units_run) {
+    Dims part = D;
+    part.units_run = lead;
+    run_cap_scores(part, pl, w, Q, K, K_cap, lse, ws, st);
+    part.unit0 = D.unit0 + lead;
+    part.units_run = D.units_run - lead;
+    run_cap_scores(part, plan_score(part, K_cap != nullptr), w, Q, K, K_cap, lse, ws, st);
+    return;
+  }
   float2* part = reinterpret_cast<float2*>(ws + w.off_part);
   float* lse2 = reinterpret_cast<float*>(ws + w.off_lse);
   float* u = reinterpret_cast<float*>(ws + w.off_u);
