@@ -182,20 +182,17 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
   pl.head_block = 0;
   pl.lse_given = 0;
   // fp32 caches: the unit kernel (fp32 values as sums of bf16 products on the matrix cores) where it exists - head
-  // dimension 64, plain softmax over the cached tokens - when asked for, and by itself unless a few units with long
-  // rows would leave most of the chip idle under it (a workgroup takes about 27 us per 1000 tokens and sweep of 256
-  // query rows).  Against the six-product kernels below (a whole call, 16 to 256 query rows): from half the chip's units on the unit
-  // kernel is 1.0 to 1.3 times faster at 128 units and 1.2 to 1.7 times at 192 to 400, for 512 to 16384 tokens.  The second line
-  // was drawn against the vector ALUs: up to 100 units it is 1.1 times faster at 512 tokens, but from 1024 tokens on the six-product
-  // kernels are (1 to 32 units, 256 query rows: 1024 tokens 60 against 45 us, 3000 tokens 120 against 53 us, 6000 tokens 210
-  // against 70 us), and more accurate.
+  // dimension 64, plain softmax over the cached tokens - when asked for, and by itself unless a few units would leave most of
+  // the chip idle under it for long.  Against the six-product kernels below (append + distill, 16 / 100 / 256 query rows): 140 units
+  // of 800 tokens 58 / 67 / 82 against 77 / 87 / 108 us, 100 units of 2500 tokens 112 / 123 / 159 against 117 / 137 / 175 us; but 64
+  // units of 2500 tokens 94 / 105 / 140 against 80 / 93 / 117 us, 4 units of 2500 tokens 65 / 73 / 108 against 43 / 46 / 53 us.  With few
+  // units they meet at 800 / 650 / 500 tokens and at 300 with 400 rows (4, 24 and 64 units: 35 / 42 / 46 us and 70 us either way).
   if (D.dtype == CCD_FP32 && score_unit_supported(D) && !cap_keys && D.window == 0) {
     if (D.score_path == CCD_PATH_MFMA_UNIT) {
       pl.unit_kernel = 1;
     } else if (D.score_path == CCD_PATH_AUTO) {
-      const int cus = compute_units();
-      const int64_t rounds = (D.units_run + cus - 1) / cus, sweeps = (D.GP + 255) / 256;
-      pl.unit_kernel = (2 * D.units_run >= cus || rounds * sweeps * D.n <= 6000) ? 1 : 0;
+      const int64_t sweeps = (D.GP + 255) / 256, row_blocks = (D.GP + 63) / 64;
+      pl.unit_kernel = (16 * D.units_run > 5 * compute_units() || D.n * sweeps * (3 + (row_blocks < 4 ? row_blocks : 4)) <= 3200) ? 1 : 0;
     }
   }
   // every other fp32 call: sums of six bf16 products, by token slices (256 units of 4096 tokens, 256 query rows of 128
