@@ -27,16 +27,15 @@ namespace {
 
 constexpr int kRowsPerWave = kQB * 32;       // query rows of a wave: 64
 constexpr int kTilesPerWave = 2;             // tiles a wave has in LDS at a time
-// Tokens per workgroup at most.  Longer slices read the query rows and the statistics less often (24 units of 30000 tokens, 32 rows:
-// slices of 256 / 512 / 1024 and 512 323 / 287 / 284 us for append + distill), as long as there is a workgroup and a quarter per
-// compute unit (4 units of 2500 tokens: 32 / 36 / 41 us).
-constexpr int kDirectMaxSlice1 = 1024, kDirectMaxSlice2 = 512;
+// Tokens per workgroup at most (pass 2: its token sums lie where the query rows were)
+constexpr int kDirectMaxSlice1 = 4096, kDirectMaxSlice2 = 2048;
 
 // The query rows of all waves and the tiles, in the swizzled order of ccd_score_mfma.h: in pass 1, and with up to 64 query rows, 16
 // + 64 KiB (head dimension 128); with 128 query rows 32 + 32 KiB; with more 64 + 16 KiB.  No more than half of the LDS of a
 // compute unit: what waves tell each other lies where the query rows were, once these are in registers.
 template <int HD>
 struct DirectLds {
+  static_assert(kDirectMaxSlice2 * 4 <= kQB * Tiles<HD>::kSlotBytes, "the sums of a row block fit where its rows were");
   __attribute__((aligned(1024))) uint8_t rows[(kQB + 4 * kTilesPerWave) * Tiles<HD>::kSlotBytes];
 };
 
@@ -260,17 +259,26 @@ unsigned direct_grid(const Dims& D, int slices, int per_item) {
 
 }  // namespace
 
-// The longest slices that leave a workgroup and a quarter per compute unit (see kDirectMaxSlice1); pass 2 not below two tiles a wave
+// Slices: two workgroups fit a compute unit, so the rounds of the grid times what one takes - its batches of tiles, and as much as
+// three of them before and behind these - are the time of a pass; a workgroup that has its compute unit to itself is an eighth faster.
+// (Powers of two with at least 1.25 workgroups per compute unit, before: 45 units of 3001 tokens were 540 workgroups on 512 places,
+// two rounds, step by step 52.7 -> 48.3 us; 120 units of 2500 tokens and 256 rows 152 -> 138 us for append + distill.)
 void plan_direct(const Dims& D, int compute_units, int min_slice, ScorePlan& pl) {
   const int row_blocks = (D.GP + kRowsPerWave - 1) / kRowsPerWave, groups = row_blocks <= 1 ? 4 : (row_blocks <= 2 ? 2 : 1);
-  const int64_t enough = 5 * (int64_t)compute_units / 4;
-  auto longest = [&](int least, int most, int per_slice) {
-    int slice = most;
-    while (slice > least && (int64_t)D.units_run * ((D.n + slice - 1) / slice) * per_slice < enough) slice /= 2;
-    return slice;
+  auto best_slice = [&](int batch, int most, int per_slice) {
+    int best = batch;
+    int64_t best_cost = INT64_MAX;
+    for (int slice = batch; slice <= most; slice += batch) {
+      const int64_t wgs = (int64_t)D.units_run * ((D.n + slice - 1) / slice) * per_slice;
+      const int64_t rounds = (wgs + 2 * compute_units - 1) / (2 * compute_units);
+      const int64_t cost = rounds * (3 + slice / batch) * (wgs <= compute_units ? 7 : 8);
+      if (cost < best_cost) { best_cost = cost; best = slice; }
+      if (slice >= D.n) break;
+    }
+    return best;
   };
-  pl.slice1 = longest(min_slice, kDirectMaxSlice1, row_blocks);
-  pl.slice2 = longest(groups * kTilesPerWave * kStep, kDirectMaxSlice2, 1);
+  pl.slice1 = best_slice(4 * kTilesPerWave * kStep, kDirectMaxSlice1, row_blocks);
+  pl.slice2 = best_slice(groups * kTilesPerWave * kStep, kDirectMaxSlice2, 1);
   pl.n_slices1 = (D.n + pl.slice1 - 1) / pl.slice1;
   pl.n_slices2 = (D.n + pl.slice2 - 1) / pl.slice2;
   pl.direct_kernel = 1;

@@ -126,19 +126,19 @@ static int pick_slice(const Dims& D) {
 // bf16 calls that do not take the unit kernel: do the direct kernels pay, or the slice kernels (whose plan is `pl`)?  The direct
 // ones compute query rows by 64 instead of 256 and start faster, the slice kernels keep the matrix cores busier once they run.
 // Append + distill, slice kernels against direct (128 elements):
-//   up to 192 of every 256 rows in use: 24 / 64 / 150 units of 2500 tokens, 32 rows 49 / 91 / 154 against 42 / 72 / 130 us; 100 rows
-//   50 / 93 / 157 against 45 / 79 / 144 us; 24 units of 30000 tokens 321 (32 rows) and 325 (100 rows) against 283 and 307 us
-//   256 rows, few blocks of 64 tokens and rows (8 units of 2048 tokens are 1024): 39.7 against 30.7 us; 64 units of 700 (2816) 44.5
-//   against 42.7 us
-//   256 rows, more of them: the slice kernels where their grid fills its rounds of two workgroups per compute unit (8 units of 32768
-//   tokens, a whole round: 160 against 171 us), the direct ones where it does not (24 units of 9000 tokens, 864 workgroups on 512
-//   places: 140 against 126 us), up to where either takes long (24 units of 30000 tokens: 343 against 361 us)
+//   up to 192 of every 256 rows in use: 24 / 64 / 150 units of 2500 tokens, 32 rows 49 / 91 / 154 against 42 / 72 / 129 us; 100 rows
+//   50 / 93 / 157 against 46 / 77 / 145 us; 24 units of 30000 tokens 321 (32 rows) and 325 (100 rows) against 273 and 299 us
+//   256 rows, few blocks of 64 tokens and rows (8 units of 2048 tokens are 1024): 39.7 against 30.7 us; 8 units of 32768 tokens
+//   (16384) 163 against 157 us
+//   256 rows, more of them: the slice kernels where their grid fills its rounds of two workgroups per compute unit (128 units of 4096
+//   tokens: 208 against 231 us), the direct ones where it does not (64 units of 9000 tokens, 576 workgroups on 512 places: 275
+//   against 262 us), up to where either takes many rounds (120 units of 9000 tokens: 474 against 505 us)
 static bool direct_pays(const Dims& D, const ScorePlan& pl) {
   const int64_t rows = (D.GP + 63) / 64, rows_slices = (D.GP + 255) / 256 * 4;
   if (4 * rows <= 3 * rows_slices) return true;
   const int64_t blocks = (int64_t)D.units_run * ((D.n + 63) / 64) * rows, slots = score_slots();
   const int64_t wgs = (int64_t)(D.units_run + 7) / 8 * 8 * pl.n_slices1, room = (wgs + slots - 1) / slots * slots * pl.slice1;
-  return blocks <= 4096 || (blocks <= 32768 && 100 * (int64_t)D.units_run * D.n < 85 * room);
+  return blocks <= 16384 || (blocks <= 40000 && 100 * (int64_t)D.units_run * D.n < 85 * room);
 }
 
 static ScorePlan plan_mfma(const Dims& D) {
