@@ -197,6 +197,11 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // units, with a thread's rows loaded one after the other, see kScUnroll), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
+// Waves per SIMD to compile for: 64 registers instead of 72 for rows of up to 4096 tokens, so that two workgroups fit a compute unit
+// when there are more units than these: one selects while the other one moves rows, and the last round is not alone (append +
+// distill with given normalisers, 2000 tokens: 400 / 640 units 257 / 438 -> 251 / 427 us, 600 tokens 85 / 129 -> 78 / 121 us; up to 256
+// units the same; 300 units of 2000 tokens 182 -> 186 us).  With CR-RoPE 13 registers would be spilled (256 units 363 -> 383 us).
+constexpr int sc_min_waves(bool shared, int chunks, int rope_row) { return !shared && chunks == 1 && rope_row == 0 ? 8 : 1; }
 // Rows per thread and chunk.  The loads of one row, K and V, travel together, but the next row's wait for them: they stand under a
 // condition, and behind the wait that ends a chunk in inline assembly the compiler takes their registers for still in use.
 constexpr int kScUnroll = 2;
@@ -220,7 +225,7 @@ __device__ __forceinline__ uint32_t agent_add(uint32_t* p, uint32_t v) {
 // ROWB, BF16: row bytes and cache type where ROPE needs them at compile time (ROWB is 0 without: `row_shift` = log2 of the
 // 16-byte lanes of a row).
 template <int CH, int ROWB, bool BF16, bool SHARED>
-__global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow)) void select_compact_kernel(Dims D, const float* __restrict__ u,
+__global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHARED, CH, ROWB)) void select_compact_kernel(Dims D, const float* __restrict__ u,
                                                                      float* novelty, int carry_novelty, float* scores,
                                                                      int32_t* __restrict__ keep_idx, char* Kbuf,
                                                                      char* Vbuf, const float* __restrict__ rope_cos,
