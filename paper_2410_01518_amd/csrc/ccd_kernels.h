@@ -44,9 +44,12 @@ struct ScorePlan {
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass
   uint32_t* sync;   // kSyncWords words per unit that the first score kernel of a call clears (null: none)
   int unit_kernel;  // 1 (matrix-core path): both passes in one kernel, one workgroup per unit (launch_score_unit)
-  int direct_kernel;  // 1 (bf16 caches, calls that do not fill the chip): the two passes of launch_stats_direct, launch_prob_direct
+  int direct_kernel;  // 1 (calls that do not fill the chip): the two passes of launch_stats_direct, launch_prob_direct
   int split_kernel; // 1 (fp32 caches): the two passes as sums of bf16 products (launch_stats_split, launch_prob_split)
 };
+
+// smallest token slice any plan uses: sizes the per-slice statistics
+constexpr int kMinSlice = 256;
 
 ScorePlan plan_score(const Dims& D, bool cap_keys);
 
@@ -95,14 +98,14 @@ void launch_stats_split(const Dims& D, const ScorePlan& pl, const void* Q, const
 void launch_prob_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float* lse2, float* u,
                        hipStream_t s);
 
-// bf16 caches, calls that do not fill the chip: the two passes over short slices (any head dimension, window and CaP keys;
-// pl.cap_block must be 1 with K_cap).  plan_direct chooses the slices; pass 2 merges the statistics itself; lse: the caller's
-// normalisers when pl.lse_given, else null.
-void plan_direct(const Dims& D, int compute_units, int min_slice, ScorePlan& pl);
+// Calls that do not fill the chip: the two passes over short slices (any head dimension and cache type, window and CaP keys;
+// pl.cap_block must be 1 with K_cap).  plan_direct chooses the slices; pass 2 merges the statistics itself.  lse_io: the caller's
+// normalisers when pl.lse_given (read only), else where fp32 calls put those in log2 units.
+void plan_direct(const Dims& D, int compute_units, ScorePlan& pl);
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
                          hipStream_t s);
-void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float2* part, const float* lse,
-                        float* u, hipStream_t s);
+void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,
+                        float* lse_io, float* u, hipStream_t s);
 
 // The same on the vector-ALU path: statistics of CaP key j under CaP query i for j <= i, written to `part` behind
 // the slices of all units (pl.cap_block must be 1; launch_merge then takes them in).  K_cap as above.

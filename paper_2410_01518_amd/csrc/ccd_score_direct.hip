@@ -1,15 +1,17 @@
-// Representative score of Eq. 2 for bf16 caches on the matrix cores, for calls that do not fill the chip: two passes over short
-// token slices.
+// Representative score of Eq. 2 on the matrix cores for calls that do not fill the chip: two passes over short token slices.  bf16
+// caches, and fp32 caches as sums of six bf16 products (ccd_fp32.h, ccd_score_split.hip).
 //
 // Such a call is bound by latency: the slice kernels of ccd_score_mfma.hip take about 10 us a pass whatever its size - two
 // rounds of DMA through the LDS ring with a barrier each, then eight tiles one after the other in a slice of 256 tokens, while
-// waves that have no query rows compute zeros.  Here a workgroup requests everything it needs first at once (its query rows and
-// two tiles per wave, by DMA in whole lines: fragments loaded straight from memory, 32 bytes of a row at a time, took 1 to 2 us
-// longer and twice the time when there was more to do), and the work is cut until it covers the chip:
+// waves that have no query rows compute zeros - and the six-product kernels 9 to 23 us and another 4 for their merge.  Here a
+// workgroup requests everything it needs first at once (its query rows and one or two tiles per wave, by DMA in whole lines: bf16
+// fragments loaded straight from memory, 32 bytes of a row at a time, took 1 to 2 us longer and twice the time when there was more
+// to do), and the work is cut until it covers the chip:
 //
-//   pass 1  a workgroup takes (unit, slice of tokens, 64 query rows); its four waves take turns at pairs of tiles, each with a
-//           running maximum and sum per row, merged through LDS.  The workgroups that share a slice are placed on one XCD.
-//   pass 2  a workgroup takes (unit, slice of tokens); its waves lie side by side over one, two or four blocks of 64 query rows
+//   pass 1  a workgroup takes (unit, slice of tokens, 64 query rows - fp32: 32, whose three fragments fill the registers); its four
+//           waves take turns at the tiles, each with a running maximum and sum per row, merged through LDS.  The workgroups that
+//           share a slice are placed on one XCD.
+//   pass 2  a workgroup takes (unit, slice of tokens); its waves lie side by side over one, two or four blocks of query rows
 //           and over the tiles.  It merges the statistics of the unit's slices for itself.
 //
 // A sliding window and the CaP keys (one more slice of pass 1) are masked in the tiles they touch: no kernels of their own.
@@ -17,52 +19,121 @@
 //
 // Measured per pass, slice kernels against these: 8 units of 2048 tokens, 256 query rows 11.4 / 11.5 -> 5.9 / 8.1 us; 15 units of
 // 448 tokens, 48 rows 9.5 / 9.5 -> 5.7 / 6.5 us; 48 units of 800 tokens under a window with CaP keys 4.1 + 9.2 + 10.8 + 4.5 -> 5.3 +
-// 6.5 us.  (Steps of one tile per wave with the next ones under way, so that pass 1 can have 256 rows to a workgroup: 2 to 3 us
-// slower on these, no faster on longer ones.)  Which calls come here: direct_pays in infinipot_api.hip.
-#include "ccd_score_mfma.h"
+// 6.5 us.  fp32, append + distill: 4 units of 820 tokens, 100 rows, 64 / 128 elements 39 / 51 -> 28 / 33 us.  (Steps of one tile per wave
+// with the next ones under way, so that pass 1 can have 256 rows to a workgroup: 2 to 3 us slower on small calls, no faster on
+// longer ones.)  Which calls come here: direct_pays and plan_score in infinipot_api.hip.
+#include <type_traits>
+
+#include "ccd_fp32.h"
 
 namespace ccd {
 
 namespace {
 
-constexpr int kRowsPerWave = kQB * 32;       // query rows of a wave: 64
-constexpr int kTilesPerWave = 2;             // tiles a wave has in LDS at a time
 // Tokens per workgroup at most (pass 2: its token sums lie where the query rows were)
-constexpr int kDirectMaxSlice1 = 4096, kDirectMaxSlice2 = 2048;
+constexpr int kDirectMaxSlice1 = 4096, kDirectMaxSlice2 = 1024;
 
-// The query rows of all waves and the tiles, in the swizzled order of ccd_score_mfma.h: in pass 1, and with up to 64 query rows, 16
-// + 64 KiB (head dimension 128); with 128 query rows 32 + 32 KiB; with more 64 + 16 KiB.  No more than half of the LDS of a
-// compute unit: what waves tell each other lies where the query rows were, once these are in registers.
-template <int HD>
-struct DirectLds {
-  static_assert(kDirectMaxSlice2 * 4 <= kQB * Tiles<HD>::kSlotBytes, "the sums of a row block fit where its rows were");
-  __attribute__((aligned(1024))) uint8_t rows[(kQB + 4 * kTilesPerWave) * Tiles<HD>::kSlotBytes];
+// Rows of HD elements of type ET (uint16_t: bf16 bits; float) in LDS, in tiles of 32: 16-byte chunk c of row r at c ^ swz(r)
+template <int HD, class ET>
+struct DirectShape {
+  static constexpr bool F32 = std::is_same<ET, float>::value;
+  static constexpr int QB = F32 ? 1 : 2;                     // blocks of 32 query rows per wave (fp32: three fragments for one)
+  static constexpr int kRows = 32 * QB;                      // query rows of a wave
+  static constexpr int kTiles = F32 && HD == 128 ? 1 : 2;    // tiles a wave has in LDS at a time
+  static constexpr int kRowBytes = HD * (int)sizeof(ET);
+  static constexpr int kSlotBytes = 32 * kRowBytes;
+  static constexpr int kChunksPerRow = kRowBytes / 16;
+  static constexpr int kRowsPerInstr = 64 / kChunksPerRow;   // rows one wave instruction moves
+  __device__ static __forceinline__ int swz(int row) { return kChunksPerRow >= 16 ? (row & 15) : ((row >> 1) & 7); }
+  // The query rows of all waves and the tiles: at most (with one or four row blocks side by side) QB + 4 kTiles tiles, 40 to 80
+  // KiB - no more than half of the LDS of a compute unit: what waves tell each other lies where the query rows were, once these are
+  // in registers.
+  static constexpr int kSlots = QB + 4 * kTiles;
+  static_assert(4 * QB + kTiles <= kSlots && 2 * QB + 2 * kTiles <= kSlots, "any number of row blocks");
+  static_assert(kDirectMaxSlice2 * 4 <= QB * kSlotBytes, "the sums of a row block fit where its rows were");
 };
 
-// 64 x 16 bytes from the lanes' own addresses to consecutive LDS addresses
+// 64 x 16 bytes from the lanes' own addresses to consecutive LDS addresses (lds_addr: the same in all lanes)
 __device__ __forceinline__ void dma16_at(const void* p, uint32_t lds_addr) {
+  lds_addr = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_addr);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(p) : "memory");
 }
-// one 32-row tile by one wave; row(r): address of row r
-template <int HD, class RowAt>
+// one 32-row tile by one wave; row_at(r): address of row r
+template <class SH, class RowAt>
 __device__ __forceinline__ void stage_tile(RowAt&& row_at, uint32_t lds_addr, int lane) {
-  using T = Tiles<HD>;
+  // (fp32 rows of 128 elements: the addresses, worked out ahead of the loop over tiles, would fill the registers)
+  if (SH::F32 && SH::kTiles == 1) asm volatile("" : "+v"(lane));
 #pragma unroll
-  for (int j = 0; j < T::kInstrPerTile; ++j) {
-    const int row = j * T::kRowsPerInstr + lane / T::kChunksPerRow, ch = (lane % T::kChunksPerRow) ^ T::swz(row);
+  for (int j = 0; j < 32 / SH::kRowsPerInstr; ++j) {
+    const int row = j * SH::kRowsPerInstr + lane / SH::kChunksPerRow, ch = (lane % SH::kChunksPerRow) ^ SH::swz(row);
     dma16_at(reinterpret_cast<const char*>(row_at(row)) + ch * 16, lds_addr + j * 1024);
   }
 }
 
-template <int HD, int PASS>
-__global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan pl, const uint16_t* __restrict__ Q,
-                                                              const uint16_t* __restrict__ K, const uint16_t* __restrict__ Kcap,
-                                                              float2* __restrict__ part, const float* __restrict__ lse_given,
-                                                              float* __restrict__ u) {
-  constexpr int KS = HD / 16;
-  constexpr int kSlot = Tiles<HD>::kSlotBytes;
-  __shared__ DirectLds<HD> sm;
-  const int row_blocks = (D.GP + kRowsPerWave - 1) / kRowsPerWave;
+// A fragment: elements 16 ks + 8 half .. + 7 of row `col` (of a tile at `slot`); fp32: split into three
+template <bool F32> struct DirectFrag { bf16x8 s[F32 ? 3 : 1]; };
+template <class SH>
+__device__ __forceinline__ DirectFrag<SH::F32> load_frag(const uint8_t* slot, int ks, int col, int half) {
+  DirectFrag<SH::F32> f;
+  if constexpr (SH::F32) {
+    f32x4 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      v[i] = *reinterpret_cast<const f32x4*>(slot + col * SH::kRowBytes + (((4 * ks + 2 * half + i) ^ SH::swz(col)) << 4));
+    const Split8 x = split8(v);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) f.s[i] = x.s[i];
+  } else {
+    f.s[0] = *reinterpret_cast<const bf16x8*>(slot + col * SH::kRowBytes + (((2 * ks + half) ^ SH::swz(col)) << 4));
+  }
+  return f;
+}
+// logits of a tile against the wave's query rows; PASS 1: D[token][query], PASS 2: D[query][token].  fp32: the six products of
+// ccd_score_split.hip
+template <class SH, int HD, int PASS>
+__device__ __forceinline__ void tile_logits(floatx16 (&acc)[SH::QB], const uint8_t* slot,
+                                            const DirectFrag<SH::F32> (&q)[SH::QB][HD / 16], int col, int half) {
+  auto mma = [](const bf16x8& k, const bf16x8& qv, const floatx16& a) {
+    return PASS == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, qv, a, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, k, a, 0, 0, 0);
+  };
+  floatx16 small;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    small[r] = 0.f;
+#pragma unroll
+    for (int qb = 0; qb < SH::QB; ++qb) acc[qb][r] = 0.f;
+  }
+  DirectFrag<SH::F32> f[2];
+  f[0] = load_frag<SH>(slot, 0, col, half);
+#pragma unroll
+  for (int ks = 0; ks < HD / 16; ++ks) {
+    const DirectFrag<SH::F32>& k = f[ks & 1];
+    if (ks + 1 < HD / 16) f[(ks + 1) & 1] = load_frag<SH>(slot, ks + 1, col, half);
+    if constexpr (SH::F32) {
+      const auto& x = q[0][ks];
+      small = mma(k.s[2], x.s[0], small);
+      small = mma(k.s[1], x.s[1], small);
+      small = mma(k.s[0], x.s[2], small);
+      acc[0] = mma(k.s[0], x.s[0], acc[0]);
+      small = mma(k.s[1], x.s[0], small);
+      small = mma(k.s[0], x.s[1], small);
+      __builtin_amdgcn_sched_barrier(0);       // (no fragments of later steps: they would be kept in scratch memory)
+    } else {
+#pragma unroll
+      for (int qb = 0; qb < SH::QB; ++qb) acc[qb] = mma(k.s[0], q[qb][ks].s[0], acc[qb]);
+    }
+  }
+  if constexpr (SH::F32) acc[0] += small;
+}
+
+template <int HD, class ET, int PASS>
+__global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan pl, const ET* __restrict__ Q, const ET* __restrict__ K,
+                                                              const ET* __restrict__ Kcap, float2* __restrict__ part,
+                                                              float* lse_io, float* __restrict__ u) {
+  using SH = DirectShape<HD, ET>;
+  constexpr int KS = HD / 16, QB = SH::QB;
+  __shared__ __attribute__((aligned(1024))) uint8_t rows[SH::kSlots * SH::kSlotBytes];
+  const int row_blocks = (D.GP + SH::kRows - 1) / SH::kRows;
   const int slices = PASS == 1 ? pl.n_slices1 + (Kcap != nullptr ? 1 : 0) : pl.n_slices2;
   // consecutive blocks go to different XCDs: the workgroups of one slice are eight blocks apart
   const int per_item = PASS == 1 ? row_blocks : 1;
@@ -75,32 +146,26 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
   const float c = D.scale_log2;
   if (PASS == 2) clear_sync(pl, unit, slice == 0);
   const bool cap = PASS == 1 && slice == pl.n_slices1;
-  const uint16_t* Ku = cap ? Kcap + (int64_t)unit * D.P * HD : K + kv_offset(D, ui);
+  const ET* Ku = cap ? Kcap + (int64_t)unit * D.P * HD : K + kv_offset(D, ui);
   const int slice_len = PASS == 1 ? pl.slice1 : pl.slice2;
   const int t0 = cap ? 0 : slice * slice_len, t1 = cap ? D.P : min(D.n, t0 + slice_len);
   // tiles [it0, it1) of the slice: those before are hidden from every query by the window
   const int it1 = (t1 - t0 + kStep - 1) / kStep;
   const int it0 = cap ? 0 : min(it1, max(0, D.head0 - t0) / kStep);
-  const uint32_t rows_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)sm.rows;
-  int koff[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) koff[ks] = col * Tiles<HD>::kRowBytes + (((2 * ks + half) ^ Tiles<HD>::swz(col)) << 4);
-  auto frags = [&](bf16x8 (&a)[KS], int slot) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(sm.rows + slot * kSlot + koff[ks]);
-  };
+  const uint32_t rows_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)rows;
 
-  // waves side by side over 64-row blocks (1, 2 or 4 of them; pass 1: one), the others on other tiles
+  // waves side by side over row blocks (1, 2 or 4 of them; pass 1: one), the others on other tiles
   const int wide = PASS == 1 || row_blocks <= 1 ? 1 : (row_blocks <= 2 ? 2 : 4), groups = 4 / wide;
   const int rb = wave % wide, group = wave / wide;
-  const int q_first = PASS == 1 ? (int)(blockIdx.x >> 3) % per_item * kRowsPerWave : 0;
-  const int q_last = PASS == 1 ? min(D.GP, q_first + kRowsPerWave) : D.GP;
-  float* up = reinterpret_cast<float*>(sm.rows);             // pass 2: token sums per row block
-  float m_raw[kQB], Z[kQB];                  // pass 1
-  int lo[kQB], hi[kQB];                      // pass 1: first and last key the lane's query rows see
+  const int q_first = PASS == 1 ? (int)(blockIdx.x >> 3) % per_item * SH::kRows : 0;
+  const int q_last = PASS == 1 ? min(D.GP, q_first + SH::kRows) : D.GP;
+  float* up = reinterpret_cast<float*>(rows);                // pass 2: token sums per row block
+  bool nan_out = false;                                      // pass 2, fp32: some token's score is NaN
+  float m_raw[QB], Z[QB];                    // pass 1
+  int lo[QB], hi[QB];                        // pass 1: first and last key the lane's query rows see
   if (PASS == 1) {
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
       const int q = q_first + qb * 32 + col;
       m_raw[qb] = kNegHuge;
       Z[qb] = 0.f;
@@ -108,26 +173,26 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
       hi[qb] = cap ? q % D.P : t1 - 1;
     }
   }
-  for (int qc = q_first; qc < q_last; qc += kQPerPass) {
-    const int q0 = qc + rb * kRowsPerWave;
-    // the query rows: 2 wide tiles, dealt to the four waves (rows past G P repeat the last one: nobody reads their statistics,
+  for (int qc = q_first; qc < q_last; qc += 4 * SH::kRows) {
+    const int q0 = qc + rb * SH::kRows;
+    // the query rows: QB wide tiles, dealt to the four waves (rows past G P repeat the last one: nobody reads their statistics,
     // and a normaliser of infinity takes them out of the token sums)
-    for (int b = wave; b < kQB * wide; b += 4)
-      stage_tile<HD>([&](int r) { return Q + q_offset(D, ui, min(qc + b * 32 + r, D.GP - 1)); }, rows_addr + b * kSlot, lane);
-    const int batch = groups * kTilesPerWave;              // tiles in LDS at a time
-    const int slot0 = kQB * wide;
+    for (int b = wave; b < QB * wide; b += 4)
+      stage_tile<SH>([&](int r) { return Q + q_offset(D, ui, min(qc + b * 32 + r, D.GP - 1)); }, rows_addr + b * SH::kSlotBytes, lane);
+    const int batch = groups * SH::kTiles;                 // tiles in LDS at a time
+    const int slot0 = QB * wide;
     auto stage_keys = [&](int it) {
       for (int b = wave; b < batch; b += 4)
         if (it + b < it1)
-          stage_tile<HD>([&](int r) { return Ku + (int64_t)min(t0 + (it + b) * kStep + r, t1 - 1) * HD; },
-                         rows_addr + (slot0 + b) * kSlot, lane);
+          stage_tile<SH>([&](int r) { return Ku + (int64_t)min(t0 + (it + b) * kStep + r, t1 - 1) * HD; },
+                         rows_addr + (slot0 + b) * SH::kSlotBytes, lane);
     };
     stage_keys(it0);
     float neg_lse = -INFINITY;                 // pass 2: of row q0 + lane, the statistics of all slices merged
-    const int q = q0 + lane;
+    const int q = q0 + (SH::kRows == 64 ? lane : col);
     if (PASS == 2 && q < D.GP) {
       if (pl.lse_given) {
-        neg_lse = -(lse_given[(int64_t)unit * D.GP + q] * 1.44269504088896340736f);
+        neg_lse = -(lse_io[(int64_t)unit * D.GP + q] * 1.44269504088896340736f);
       } else {
         float2 cp = make_float2(kNegHuge, 0.f);
         if (pl.cap_block) cp = part[extra_block_index(D, pl, unit, q)];
@@ -148,13 +213,24 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
           for (int j = 0; j < kFly; ++j)
             if (j0 + j < n) z += v[j].y * fast_exp2(v[j].x - M);
         }
+        if constexpr (SH::F32) {
+          if (__builtin_expect(z != z, 0)) {
+            const float2 a = statistics_again<HD>(Q + q_offset(D, ui, q), Ku, pl.cap_block ? Kcap + (int64_t)unit * D.P * HD : nullptr, p,
+                                                  cp, D.GP, n, pl.slice1, D.n, D.window > 0 ? D.win_off + q % D.P : 0, q % D.P, c);
+            M = a.x;
+            z = a.y;
+          }
+        }
         neg_lse = -(M + __log2f(z));
+        if constexpr (SH::F32) {               // for scores_again (all workgroups of a unit write the same)
+          if (lane < SH::kRows) lse_io[(int64_t)unit * D.GP + q] = -neg_lse;
+        }
       }
     }
-    float nl[PASS == 2 ? kQB : 1][16];
+    float nl[PASS == 2 ? QB : 1][16];
     if (PASS == 2) {
 #pragma unroll
-      for (int qb = 0; qb < kQB; ++qb)
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) nl[qb][r] = __shfl(neg_lse, qb * 32 + acc_row(r, half));
     }
@@ -162,9 +238,11 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
     wait_all_dma();
     __syncthreads();
     const bool active = q0 < q_last;
-    bf16x8 bq[kQB][KS];
+    DirectFrag<SH::F32> bq[QB][KS];
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) frags(bq[qb], rb * kQB + qb);
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) bq[qb][ks] = load_frag<SH>(rows + (rb * QB + qb) * SH::kSlotBytes, ks, col, half);
     if (PASS == 2) __syncthreads();            // the query rows make room for token sums
     for (int it = it0; it < it1; it += batch) {
       if (it > it0) {
@@ -174,39 +252,42 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
         __syncthreads();
       }
 #pragma unroll
-      for (int i = 0; i < kTilesPerWave; ++i) {
-        const int b = group * kTilesPerWave + i, t = t0 + (it + b) * kStep;
+      for (int i = 0; i < SH::kTiles; ++i) {
+        const int b = group * SH::kTiles + i, t = t0 + (it + b) * kStep;
         if (active && it + b < it1) {
-          bf16x8 a[KS];
-          frags(a, slot0 + b);
-          floatx16 acc[kQB];
-          logits<HD, PASS>(acc, a, bq);
+          floatx16 acc[QB];
+          tile_logits<SH, HD, PASS>(acc, rows + (slot0 + b) * SH::kSlotBytes, bq, col, half);
           if constexpr (PASS == 1) {
             if (cap || t + kStep > t1 || t < D.head) {            // some row may not see some key
 #pragma unroll
-              for (int qb = 0; qb < kQB; ++qb)
+              for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                   const int tok = t + acc_row(r, half);
                   if (tok < lo[qb] || tok > hi[qb]) acc[qb][r] = -INFINITY;
                 }
             }
-            fold_stats<false>(acc, m_raw, Z, c, half, kStep);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) fold_block(acc[qb], m_raw[qb], Z[qb], c);
           } else {
-            float us = 0.f;
+            float s[2] = {0.f, 0.f};
             if (t < D.head) {
               int f = first;
               asm volatile("" : "+v"(f));               // (32 values that would be kept in registers for all tiles)
 #pragma unroll
-              for (int qb = 0; qb < kQB; ++qb)
+              for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                   const float p = fast_exp2(fmaf(acc[qb][r], c, nl[qb][r]));
-                  us += t + col >= __shfl(f, qb * 32 + acc_row(r, half)) ? p : 0.f;
+                  s[r & 1] += t + col >= __shfl(f, qb * 32 + acc_row(r, half)) ? p : 0.f;
                 }
             } else {
-              us = fold_prob(acc, nl, c);
+#pragma unroll
+              for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r & 1] += fast_exp2(fmaf(acc[qb][r], c, nl[qb][r]));
             }
+            float us = s[0] + s[1];
             us += __shfl_xor(us, 32);
             if (half == 0) up[rb * pl.slice2 + (it + b) * kStep + col] = us;
           }
@@ -215,7 +296,7 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
     }
     __syncthreads();
     if constexpr (PASS == 2) {
-      const int used = min(wide, (D.GP - qc + kRowsPerWave - 1) / kRowsPerWave);
+      const int used = min(wide, (D.GP - qc + SH::kRows - 1) / SH::kRows);
       float* uu = u + (int64_t)unit * D.n + t0;
       for (int t = threadIdx.x; t < t1 - t0; t += kMT) {
         float v = 0.f;                         // (tokens nobody sees)
@@ -223,33 +304,46 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
           v = up[t];
           for (int w = 1; w < used; ++w) v += up[w * pl.slice2 + t];
         }
-        uu[t] = qc == 0 ? v : uu[t] + v;
+        v = qc == 0 ? v : uu[t] + v;
+        uu[t] = v;
+        if (SH::F32) nan_out |= v != v;
       }
       __syncthreads();                         // the next sweep's query rows take the place of the sums
     }
   }
   if constexpr (PASS == 1) {
     // the two lane halves and the four waves hold different tokens of the same query rows
-    float2* stat = reinterpret_cast<float2*>(sm.rows);
+    float2* stat = reinterpret_cast<float2*>(rows);
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
       const float m_o = __shfl_xor(m_raw[qb], 32), z_o = __shfl_xor(Z[qb], 32);
       const float M = fmaxf(m_raw[qb], m_o);
       const float z = Z[qb] * fast_exp2((m_raw[qb] - M) * c) + z_o * fast_exp2((m_o - M) * c);
-      if (half == 0) stat[wave * kRowsPerWave + qb * 32 + col] = make_float2(M * c, z);
+      if (half == 0) stat[wave * SH::kRows + qb * 32 + col] = make_float2(M * c, z);
     }
     __syncthreads();
     const int q = q_first + (int)threadIdx.x;
-    if (threadIdx.x < kRowsPerWave && q < D.GP) {
+    if ((int)threadIdx.x < SH::kRows && q < D.GP) {
       float2 v[4];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) v[w] = stat[w * kRowsPerWave + threadIdx.x];
+      for (int w = 0; w < 4; ++w) v[w] = stat[w * SH::kRows + threadIdx.x];
       const float M = fmaxf(fmaxf(v[0].x, v[1].x), fmaxf(v[2].x, v[3].x));
       float z = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) z += v[w].y * fast_exp2(v[w].x - M);
       part[cap ? extra_block_index(D, pl, unit, q) : ((int64_t)unit * pl.n_slices1 + slice) * D.GP + q] = make_float2(M, z);
     }
+  } else if constexpr (SH::F32) {
+    // (the barrier behind the sums has passed; scores_again waits for the stores)
+    int* again = reinterpret_cast<int*>(rows);
+    if (threadIdx.x == 0) *again = 0;
+    __syncthreads();
+    if (__builtin_expect(nan_out, 0)) *again = 1;
+    __threadfence_block();
+    __syncthreads();
+    if (__builtin_expect(wave == 0 && __builtin_amdgcn_readfirstlane(*again) != 0, 0))
+      scores_again<HD>(D.GP, D.P, D.window > 0 ? D.win_off : -D.P, t0, t1, Q + q_offset(D, ui, 0), D.q_sh, Ku, c,
+                       lse_io + (int64_t)unit * D.GP, pl.lse_given ? 1.44269504088896340736f : 1.0f, u + (int64_t)unit * D.n);
   }
 }
 
@@ -263,12 +357,13 @@ unsigned direct_grid(const Dims& D, int slices, int per_item) {
 // three of them before and behind these - are the time of a pass; a workgroup that has its compute unit to itself is an eighth faster.
 // (Powers of two with at least 1.25 workgroups per compute unit, before: 45 units of 3001 tokens were 540 workgroups on 512 places,
 // two rounds, step by step 52.7 -> 48.3 us; 120 units of 2500 tokens and 256 rows 152 -> 138 us for append + distill.)
-void plan_direct(const Dims& D, int compute_units, int min_slice, ScorePlan& pl) {
-  const int row_blocks = (D.GP + kRowsPerWave - 1) / kRowsPerWave, groups = row_blocks <= 1 ? 4 : (row_blocks <= 2 ? 2 : 1);
-  auto best_slice = [&](int batch, int most, int per_slice) {
-    int best = batch;
+void plan_direct(const Dims& D, int compute_units, ScorePlan& pl) {
+  const int rows = D.dtype == 0 ? 32 : 64, tiles = D.dtype == 0 && D.d == 128 ? 1 : 2;      // per wave: DirectShape
+  const int row_blocks = (D.GP + rows - 1) / rows, groups = row_blocks <= 1 ? 4 : (row_blocks <= 2 ? 2 : 1);
+  auto best_slice = [&](int batch, int least, int most, int per_slice) {
+    int best = least;
     int64_t best_cost = INT64_MAX;
-    for (int slice = batch; slice <= most; slice += batch) {
+    for (int slice = least; slice <= most; slice += batch) {
       const int64_t wgs = (int64_t)D.units_run * ((D.n + slice - 1) / slice) * per_slice;
       const int64_t rounds = (wgs + 2 * compute_units - 1) / (2 * compute_units);
       const int64_t cost = rounds * (3 + slice / batch) * (wgs <= compute_units ? 7 : 8);
@@ -277,8 +372,8 @@ void plan_direct(const Dims& D, int compute_units, int min_slice, ScorePlan& pl)
     }
     return best;
   };
-  pl.slice1 = best_slice(4 * kTilesPerWave * kStep, kDirectMaxSlice1, row_blocks);
-  pl.slice2 = best_slice(groups * kTilesPerWave * kStep, kDirectMaxSlice2, 1);
+  pl.slice1 = best_slice(4 * tiles * kStep, kMinSlice, kDirectMaxSlice1, row_blocks);
+  pl.slice2 = best_slice(groups * tiles * kStep, groups * tiles * kStep, kDirectMaxSlice2, 1);
   pl.n_slices1 = (D.n + pl.slice1 - 1) / pl.slice1;
   pl.n_slices2 = (D.n + pl.slice2 - 1) / pl.slice2;
   pl.direct_kernel = 1;
@@ -286,17 +381,25 @@ void plan_direct(const Dims& D, int compute_units, int min_slice, ScorePlan& pl)
 
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
                          hipStream_t s) {
-  const int row_blocks = (D.GP + kRowsPerWave - 1) / kRowsPerWave;
+  const int rows = D.dtype == 0 ? 32 : 64, row_blocks = (D.GP + rows - 1) / rows;
   const dim3 grid(direct_grid(D, pl.n_slices1 + (K_cap != nullptr ? 1 : 0), row_blocks)), block(kMT);
-  auto* kernel = D.d == 64 ? score_direct_kernel<64, 1> : score_direct_kernel<128, 1>;
-  launch(kernel, grid, block, s, D, pl, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)K_cap, part, nullptr, nullptr);
+#define CCD_LAUNCH(HD, ET)                                                                                                       \
+  launch((score_direct_kernel<HD, ET, 1>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, part, nullptr, \
+         nullptr)
+  if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
+  else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
+#undef CCD_LAUNCH
 }
 
-void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float2* part, const float* lse,
-                        float* u, hipStream_t s) {
+void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,
+                        float* lse_io, float* u, hipStream_t s) {
   const dim3 grid(direct_grid(D, pl.n_slices2, 1)), block(kMT);
-  auto* kernel = D.d == 64 ? score_direct_kernel<64, 2> : score_direct_kernel<128, 2>;
-  launch(kernel, grid, block, s, D, pl, (const uint16_t*)Q, (const uint16_t*)K, nullptr, const_cast<float2*>(part), lse, u);
+#define CCD_LAUNCH(HD, ET)                                                                                          \
+  launch((score_direct_kernel<HD, ET, 2>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, \
+         const_cast<float2*>(part), lse_io, u)
+  if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
+  else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
+#undef CCD_LAUNCH
 }
 
 }  // namespace ccd

@@ -118,16 +118,6 @@ __device__ __forceinline__ void load_k_frags(bf16x8 (&a)[HD / 16], const uint8_t
     a[ks] = *reinterpret_cast<const bf16x8*>(lds + SLOT * Tiles<HD>::kSlotBytes + koff[ks]);
 }
 
-// fragments of one 32-token tile, straight from global memory: lane (col, half) holds elements 16 ks + 8 half .. + 7
-// of token row t_tile + col (rows past t_last re-read row t_last: masked in pass 1, never stored in pass 2)
-template <int HD>
-__device__ __forceinline__ void load_k_tile(bf16x8 (&a)[HD / 16], const uint16_t* __restrict__ Ku, int t_tile, int t_last,
-                                            int col, int half) {
-  const uint16_t* p = Ku + (int64_t)min(t_tile + col, t_last) * HD + half * 8;
-#pragma unroll
-  for (int ks = 0; ks < HD / 16; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(p + ks * 16);
-}
-
 template <int HD>
 __device__ __forceinline__ void load_q_frags(bf16x8 (&bq)[kQB][HD / 16], const Dims& D, UnitIdx ui, const uint16_t* Q,
                                              int qbase, int col, int half) {
@@ -162,7 +152,27 @@ __device__ __forceinline__ void logits(floatx16 (&acc)[kQB], const bf16x8 (&a)[H
     }
 }
 
-// pass 1: fold the 16 token rows a lane holds into its query's running (max, sum); nvalid < 32 masks the tail
+// pass 1: fold the 16 token rows a lane holds into its query's running (max, sum)
+__device__ __forceinline__ void fold_block(const floatx16& acc, float& m_raw, float& Z, float c) {
+  float t0 = fmaxf(fmaxf(acc[0], acc[1]), acc[2]);
+  float t1 = fmaxf(fmaxf(acc[3], acc[4]), acc[5]);
+  float t2 = fmaxf(fmaxf(acc[6], acc[7]), acc[8]);
+  float t3 = fmaxf(fmaxf(acc[9], acc[10]), acc[11]);
+  float t4 = fmaxf(fmaxf(acc[12], acc[13]), acc[14]);
+  t0 = fmaxf(fmaxf(t0, t1), t2);
+  t3 = fmaxf(fmaxf(t3, t4), acc[15]);
+  const float m_new = fmaxf(fmaxf(t0, t3), m_raw);
+  const float negm = -m_new * c;
+  float z0 = Z * fast_exp2((m_raw - m_new) * c), z1 = 0.f;   // exact difference first: m may be huge
+  m_raw = m_new;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    z0 += fast_exp2(fmaf(acc[r], c, negm));
+    z1 += fast_exp2(fmaf(acc[r + 1], c, negm));
+  }
+  Z = z0 + z1;
+}
+// the same for the two blocks of a wave; nvalid < 32 masks the tail
 template <bool MASKED>
 __device__ __forceinline__ void fold_stats(floatx16 (&acc)[kQB], float (&m_raw)[kQB], float (&Z)[kQB], float c, int half,
                                            int nvalid) {
@@ -173,23 +183,7 @@ __device__ __forceinline__ void fold_stats(floatx16 (&acc)[kQB], float (&m_raw)[
       for (int r = 0; r < 16; ++r)
         if (acc_row(r, half) >= nvalid) acc[qb][r] = -INFINITY;
     }
-    float t0 = fmaxf(fmaxf(acc[qb][0], acc[qb][1]), acc[qb][2]);
-    float t1 = fmaxf(fmaxf(acc[qb][3], acc[qb][4]), acc[qb][5]);
-    float t2 = fmaxf(fmaxf(acc[qb][6], acc[qb][7]), acc[qb][8]);
-    float t3 = fmaxf(fmaxf(acc[qb][9], acc[qb][10]), acc[qb][11]);
-    float t4 = fmaxf(fmaxf(acc[qb][12], acc[qb][13]), acc[qb][14]);
-    t0 = fmaxf(fmaxf(t0, t1), t2);
-    t3 = fmaxf(fmaxf(t3, t4), acc[qb][15]);
-    const float m_new = fmaxf(fmaxf(t0, t3), m_raw[qb]);
-    const float negm = -m_new * c;
-    float z0 = Z[qb] * fast_exp2((m_raw[qb] - m_new) * c), z1 = 0.f;   // exact difference first: m may be huge
-    m_raw[qb] = m_new;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      z0 += fast_exp2(fmaf(acc[qb][r], c, negm));
-      z1 += fast_exp2(fmaf(acc[qb][r + 1], c, negm));
-    }
-    Z[qb] = z0 + z1;
+    fold_block(acc[qb], m_raw[qb], Z[qb], c);
   }
 }
 

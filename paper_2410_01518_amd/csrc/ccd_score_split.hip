@@ -27,7 +27,7 @@
 // 2e-6 / 7e-6 / 2.5e-5 / 1e-4.
 #include <algorithm>
 
-#include "ccd_score_mfma.h"
+#include "ccd_fp32.h"
 
 namespace ccd {
 
@@ -38,32 +38,6 @@ constexpr int kSplitWaves = kSplitThreads / 64;
 constexpr int kStage = 2 * kStep;            // tokens per stage: two tiles
 constexpr int kSplitRows = kSplitWaves * 32; // query rows per sweep
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// (bf16(x0), bf16(x1)) packed; x0, x1 <- what the rounding left over
-__device__ __forceinline__ uint32_t take_bf16(float& x0, float& x1) {
-  const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x0, x1}, bf16x2));
-  x0 -= __uint_as_float(p << 16);
-  x1 -= __uint_as_float(p & 0xFFFF0000u);
-  return p;
-}
-struct Split8 { bf16x8 s[3]; };              // h, m, l of eight values
-__device__ __forceinline__ Split8 split8(const f32x4 (&v)[2]) {
-  float x[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
-  Split8 out;
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = take_bf16(x[2 * i], x[2 * i + 1]);
-    out.s[s] = __builtin_bit_cast(bf16x8, (u32x4){w[0], w[1], w[2], w[3]});
-  }
-  return out;
-}
-
 template <int HD>
 struct SplitLds {
   static constexpr int KQ = HD / 16;
@@ -72,48 +46,6 @@ struct SplitLds {
   int first[kSplitRows];                     // pass 2 under a window: the first token a query row sees
   int nan_out;                               // pass 2: some token's score is NaN
 };
-
-// logit of a query row that is held in registers and a key (times the scale), as the vector-ALU kernels take it
-template <int HD>
-__device__ __forceinline__ float plain_dot(const float4 (&a)[HD / 4], const float* __restrict__ b) {
-  float acc = 0.f;
-#pragma unroll
-  for (int i = 0; i < HD / 4; ++i) {
-    const float4 v = load4(b + 4 * i);
-    acc = fmaf(a[i].x, v.x, acc);
-    acc = fmaf(a[i].y, v.y, acc);
-    acc = fmaf(a[i].z, v.z, acc);
-    acc = fmaf(a[i].w, v.w, acc);
-  }
-  return acc;
-}
-template <int HD>
-__device__ __forceinline__ void load_row(float4 (&a)[HD / 4], const float* __restrict__ p) {
-#pragma unroll
-  for (int i = 0; i < HD / 4; ++i) a[i] = load4(p + 4 * i);
-}
-// Scores that came out as NaN again, by a chain of fp32 fmas for every logit (the merge kernel does the same for statistics): u[t] =
-// sum of 2^(x - lse[q]) over the rows q that see token t (first + q % P and later ones), t in [t0, t1).  By one wave.  Not inlined:
-// the kernel around has no registers to spare, and code that is jumped over costs a miss of the instruction cache per launch
-// (inlined: 1 us a pass).
-template <int HD>
-__device__ __noinline__ void scores_again(int GP, int P, int first, int t0, int t1, const float* __restrict__ Q, int64_t q_sh,
-                                          const float* __restrict__ Ku, float c, const float* __restrict__ lse, float lse_mul,
-                                          float* __restrict__ u) {
-  __threadfence_block();
-  for (int t = t0 + (int)(threadIdx.x & 63); t < t1; t += 64) {
-    if (u[t] == u[t]) continue;
-    float4 kr[HD / 4];
-    load_row<HD>(kr, Ku + (int64_t)t * HD);
-    float sum = 0.f;
-    for (int q = 0; q < GP; ++q) {
-      const int g = q / P, i = q - g * P;
-      if (t < first + i) continue;
-      sum += fast_exp2(fmaf(plain_dot<HD>(kr, Q + g * q_sh + (int64_t)i * HD), c, -lse[q] * lse_mul));
-    }
-    u[t] = sum;
-  }
-}
 
 // PASS 1: part[unit, slice, q] = (maximum, sum of 2^(x - maximum)) of the log2-domain logits x of query row q over the slice;
 //   slice n_slices1 (causal variant) stands for the CaP tokens' own keys, of which row g * P + i sees 0 .. i.

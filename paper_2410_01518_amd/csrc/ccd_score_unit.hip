@@ -72,6 +72,16 @@ struct UnitShape {
   static constexpr int chunks_by(int i) { return i < 0 ? 0 : (i == NM - 1 ? NCH : (i * NCH) / NM); }
 };
 
+// fragments of one 32-token tile, straight from global memory: lane (col, half) holds elements 16 ks + 8 half .. + 7
+// of token row t_tile + col (rows past t_last re-read row t_last: masked in pass 1, never stored in pass 2)
+template <int HD>
+__device__ __forceinline__ void load_k_tile(bf16x8 (&a)[HD / 16], const uint16_t* __restrict__ Ku, int t_tile, int t_last,
+                                            int col, int half) {
+  const uint16_t* p = Ku + (int64_t)min(t_tile + col, t_last) * HD + half * 8;
+#pragma unroll
+  for (int ks = 0; ks < HD / 16; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(p + ks * 16);
+}
+
 // fp32 caches: the same elements as 8 floats per k-step (two 16-byte loads), split into hi and lo fragments later
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));

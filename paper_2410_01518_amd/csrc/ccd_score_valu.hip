@@ -6,7 +6,7 @@
 //                   logits x = <q, k_t> * scale * log2(e)        [thread = query, K tile in LDS]
 //   merge:          lse2[q] = log2 sum_t 2^x over all slices
 //   pass 2 (prob):  u_t = sum_q 2^(x - lse2[q])                  [thread = token, Q tile in LDS]
-#include "ccd_common.h"
+#include "ccd_fp32.h"
 
 namespace ccd {
 
@@ -152,38 +152,6 @@ __global__ __launch_bounds__(kThreads) void cap_block_stats_valu_kernel(Dims D, 
   }
 }
 
-// (maximum, sum of 2^(x - maximum)) of a query row over the keys t .. last (a -infinite logit has no part in it), eight keys to a
-// load of the row: it would not fit the registers of the small kernel that calls this, which hardly ever happens
-template <int HD>
-__device__ __noinline__ float2 statistics_of_row(const float* __restrict__ q, const float* __restrict__ Ku, int t, int last, float c) {
-  constexpr int kKeys = 8;
-  float2 a = make_float2(-INFINITY, 0.f);
-  for (; t <= last; t += kKeys) {
-    float x[kKeys];
-#pragma unroll
-    for (int e = 0; e < kKeys; ++e) x[e] = 0.f;
-#pragma unroll 1
-    for (int i = 0; i < HD; i += 4) {
-      const float4 qq = load4(q + i);
-#pragma unroll
-      for (int e = 0; e < kKeys; ++e) {
-        const float4 kk = load4(Ku + (int64_t)min(t + e, last) * HD + i);
-        x[e] = fmaf(qq.x, kk.x, x[e]);
-        x[e] = fmaf(qq.y, kk.y, x[e]);
-        x[e] = fmaf(qq.z, kk.z, x[e]);
-        x[e] = fmaf(qq.w, kk.w, x[e]);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < kKeys; ++e) {
-      const float y = t + e <= last ? x[e] * c : -INFINITY;
-      if (y > a.x) a = make_float2(y, a.y * fast_exp2(a.x - y) + 1.f);
-      else if (y != -INFINITY) a.y += fast_exp2(y - a.x);
-    }
-  }
-  return a;
-}
-
 // Q, K (else null), K_cap: the statistics are those of launch_stats_split, and entries that came out as NaN are taken again
 __global__ __launch_bounds__(kThreads) void merge_kernel(Dims D, ScorePlan pl, const float* __restrict__ Q,
                                                          const float* __restrict__ K, const float* __restrict__ Kcap,
@@ -206,20 +174,15 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(Dims D, ScorePlan pl, c
   }
   if (__builtin_expect(Z != Z && Q != nullptr, 0)) {
     const UnitIdx ui = decode_unit(D, unit);
-    const float* qp = Q + q_offset(D, ui, q);
-    M = -INFINITY;
-    Z = 0.f;
-    for (int j = pl.cap_block ? -1 : 0; j < pl.n_slices1; ++j) {            // -1: the CaP keys, of which the row sees 0 .. q % P
-      const float* Ku = j < 0 ? Kcap + (int64_t)unit * D.P * D.d : K + kv_offset(D, ui);
-      const int t = j < 0 ? 0 : max(j * pl.slice1, D.window > 0 ? D.win_off + q % D.P : 0);
-      const int last = j < 0 ? q % D.P : min(D.n, (j + 1) * pl.slice1) - 1;
-      float2 v = j < 0 ? part[extra_block_index(D, pl, unit, q)] : p[(int64_t)j * D.GP];
-      if (v.y != v.y) v = D.d == 64 ? statistics_of_row<64>(qp, Ku, t, last, D.scale_log2) : statistics_of_row<128>(qp, Ku, t, last, D.scale_log2);
-      if (v.y == 0.f) continue;
-      const float m = fmaxf(M, v.x);
-      Z = Z * fast_exp2(M - m) + v.y * fast_exp2(v.x - m);
-      M = m;
-    }
+    const float* Kc = pl.cap_block ? Kcap + (int64_t)unit * D.P * D.d : nullptr;
+    const float2 cap = pl.cap_block ? part[extra_block_index(D, pl, unit, q)] : make_float2(0.f, 0.f);
+    const int first = D.window > 0 ? D.win_off + q % D.P : 0;
+    auto again = [&](auto* f) {
+      return f(Q + q_offset(D, ui, q), K + kv_offset(D, ui), Kc, p, cap, D.GP, pl.n_slices1, pl.slice1, D.n, first, q % D.P, D.scale_log2);
+    };
+    const float2 a = D.d == 64 ? again(statistics_again<64>) : again(statistics_again<128>);
+    M = a.x;
+    Z = a.y;
   }
   // a query that sees no key at all (window == P at most, no CaP keys): +inf, every probability comes out 0
   lse2[(int64_t)unit * D.GP + q] = Z == 0.f ? INFINITY : M + __log2f(Z);

@@ -95,8 +95,6 @@ static Dims make_dims(const ccd_shape_t* s) {
   return D;
 }
 
-constexpr int kMinSlice = 256;   // smallest token slice any plan uses: sizes the per-slice statistics
-
 // compute units of the current device (asked once; the answer of the first device serves all: one GPU model per node)
 static int compute_units() {
   static int cus = 0;
@@ -159,7 +157,7 @@ static ScorePlan plan_mfma(const Dims& D) {
   } else if (D.score_path == CCD_PATH_AUTO && score_unit_supported(D)) {
     pl.unit_kernel = 5 * D.units_run >= 3 * compute_units() ? 1 : 0;
   }
-  if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel && direct_pays(D, pl)) plan_direct(D, compute_units(), kMinSlice, pl);
+  if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel && direct_pays(D, pl)) plan_direct(D, compute_units(), pl);
   return pl;
 }
 
@@ -181,25 +179,36 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
   pl.cap_block = 0;
   pl.head_block = 0;
   pl.lse_given = 0;
-  // fp32 caches: the unit kernel (fp32 values as sums of bf16 products on the matrix cores) where it exists - head
-  // dimension 64, plain softmax over the cached tokens - when asked for, and by itself unless a few units would leave most of
-  // the chip idle under it for long.  Against the six-product kernels below (append + distill, 16 / 100 / 256 query rows): 140 units
-  // of 800 tokens 58 / 67 / 82 against 77 / 87 / 108 us, 100 units of 2500 tokens 112 / 123 / 159 against 117 / 137 / 175 us; but 64
-  // units of 2500 tokens 94 / 105 / 140 against 80 / 93 / 117 us, 4 units of 2500 tokens 65 / 73 / 108 against 43 / 46 / 53 us.  With few
-  // units they meet at 800 / 650 / 500 tokens and at 300 with 400 rows (4, 24 and 64 units: 35 / 42 / 46 us and 70 us either way).
-  if (D.dtype == CCD_FP32 && score_unit_supported(D) && !cap_keys && D.window == 0) {
-    if (D.score_path == CCD_PATH_MFMA_UNIT) {
+  // fp32 caches: the direct kernels for few blocks of 32 tokens and 32 query rows, and for a single block of rows whatever the number of
+  // tokens (the six-product kernels below split a key once for 256 rows where the direct ones do for 32; one block leaves them mostly
+  // empty).  Append + distill, 64 elements and 128, six-product against direct kernels:
+  //   16 rows   4 units of 820 tokens 34 / 42 against 28 / 33 us, 64 of 2500 81 / 124 against 76 / 119 us, 256 of 4000 (128 elements)
+  //             755 against 726 us
+  //   100 rows  4 units of 9000 tokens (4512 blocks) 79 / 98 against 67 / 81 us, 24 of 2500 (7584) 58 / 84 against 53 / 81 us, 120 of 820
+  //             (12480) 67 / 106 against 73 / 114 us
+  //   256 rows  24 units of 820 tokens (4992) 49 / 71 against 44 / 63 us, 120 of 300 (9600) 52 / 82 against 61 / 89 us
+  //   two blocks of rows meet between 13500 and 19000
+  // The unit kernel (fp32 values as sums of three bf16 products; head dimension 64, plain softmax over the cached tokens) when asked for,
+  // and by itself for a third of the chip's units on, half of them with a single block of rows: 140 units of 1200 tokens and 16 rows 78
+  // (direct) against 76 us; 120 units of 2500 tokens and 100 / 256 rows 145 / 187 (six products) against 134 / 170 us; 64 units 92 / 117
+  // against 105 / 140 us.
+  if (D.dtype == CCD_FP32) {
+    const int cus = compute_units();
+    const int64_t rows = (D.GP + 31) / 32, blocks = (int64_t)D.units_run * ((D.n + 31) / 32) * rows;
+    const bool unit = score_unit_supported(D) && !cap_keys && D.window == 0;
+    if (unit && D.score_path == CCD_PATH_MFMA_UNIT) {
       pl.unit_kernel = 1;
     } else if (D.score_path == CCD_PATH_AUTO) {
-      const int64_t sweeps = (D.GP + 255) / 256, row_blocks = (D.GP + 63) / 64;
-      pl.unit_kernel = (16 * D.units_run > 5 * compute_units() || D.n * sweeps * (3 + (row_blocks < 4 ? row_blocks : 4)) <= 3200) ? 1 : 0;
+      if (unit && (rows == 1 ? 2 * D.units_run >= cus : 16 * D.units_run > 5 * cus)) {
+        pl.unit_kernel = 1;
+      } else if (rows == 1 || blocks <= (rows == 2 ? 16384 : 8192)) {
+        plan_direct(D, cus, pl);
+        return pl;
+      }
     }
   }
   // every other fp32 call: sums of six bf16 products, by token slices (256 units of 4096 tokens, 256 query rows of 128
-  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them).  With handed-in
-  // normalisers there is one pass, and eight query rows leave the matrix tiles mostly empty: the vector ALUs are then even at 100 and
-  // 256 units and 1.1 to 1.25 times faster at 129, 160 and 400, whose last round is short (129 units of 4096 tokens: 63 against 80 us;
-  // 32 query rows: 121 against 86 us).  These calls stay here for accuracy (see ccd_score_split.hip).
+  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them)
   if (D.dtype == CCD_FP32 && D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) plan_split(D, compute_units(), kMinSlice, pl);
   return pl;
 }
@@ -336,7 +345,7 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     pl.lse_given = 1;
     float* lse_rw = const_cast<float*>(lse);   // only read when pl.lse_given
     g_prof.begin(kStProb, st);
-    if (pl.direct_kernel)     launch_prob_direct(D, pl, Q, K, part, lse, u, st);
+    if (pl.direct_kernel)     launch_prob_direct(D, pl, Q, K, nullptr, part, lse_rw, u, st);
     else if (pl.use_mfma)     launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
     else if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse, u, st);
     else                      launch_prob_valu(D, pl, Q, K, lse, u, st);
@@ -354,7 +363,7 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     launch_stats_direct(D, pl, Q, K, K_cap, part, st);
     g_prof.end(st);
     g_prof.begin(kStProb, st);
-    launch_prob_direct(D, pl, Q, K, part, nullptr, u, st);
+    launch_prob_direct(D, pl, Q, K, K_cap, part, lse2, u, st);
     g_prof.end(st);
     return;
   }

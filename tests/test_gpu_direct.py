@@ -52,10 +52,13 @@ def test_edges_of_tiles_blocks_and_slices(units, N, G, P, d):
     _check(_cfg(units, N, G, P, d))
 
 
-# slices of 512 and 1024 tokens in pass 1, up to 512 in pass 2: several rounds of tiles per workgroup
-@pytest.mark.parametrize("units,N,G,P,d", [(40, 4500, 1, 8, 64), (40, 8200, 1, 8, 64), (41, 2100, 2, 40, 128), (80, 1601, 4, 64, 64)])
-def test_long_slices(units, N, G, P, d):
-    _check(_cfg(units, N, G, P, d))
+# slices of several batches of tiles in either pass (fp32 rows of 128 elements: a batch is one tile a wave); fp32 with one block of 32
+# rows (whatever the number of tokens) and with two
+@pytest.mark.parametrize("units,N,G,P,d,dtype", [
+    (40, 4500, 1, 8, 64, "bf16"), (40, 8200, 1, 8, 64, "bf16"), (41, 2100, 2, 40, 128, "bf16"), (80, 1601, 4, 64, 64, "bf16"),
+    (40, 4500, 1, 8, 64, "fp32"), (41, 2100, 1, 32, 128, "fp32"), (30, 2100, 1, 33, 128, "fp32"), (20, 1601, 2, 48, 64, "fp32")])
+def test_long_slices(units, N, G, P, d, dtype):
+    _check(_cfg(units, N, G, P, d, dtype=dtype))
 
 
 @pytest.mark.parametrize("kcat", [False, True])
