@@ -43,10 +43,11 @@ constexpr int kCpUnroll = 4;
 // in 84 us) or, for a few units, by how many compute
 // units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  (Where chunk and pot stay in
 // the memory-side cache from one call to the next, 130 to 270 MB in all, those of 64 KiB were 4 to 11 % faster.)
-// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, copied by the workgroups that move the keys
-// of those tokens (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
+// Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
+// keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
+constexpr int kApNovelty = 1024;       // a multiple of the tokens of a segment (32, 64 or 128)
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
@@ -66,11 +67,21 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
     const int64_t b = b0 + i * (kApThreads * 16);
     if (b < run) v[i] = load_streaming(src + b);
   }
-  const int seg_tokens = kApSegBytes / (D.d * esz), j = seg * seg_tokens + threadIdx.x;      // 32, 64 or 128
-  const bool carry = novelty != nullptr && !isV && (nov_per_head || (ui.l == 0 && ui.h == 0)) &&
-                     (int)threadIdx.x < seg_tokens && j < count;
-  float nv = 0.f;
-  if (carry) nv = nov_new[(int64_t)ui.b * count + j];
+  // (one key workgroup in 8 to 32: those whose segment starts at a multiple of kApNovelty tokens)
+  const int t_seg = seg * (kApSegBytes / (D.d * esz));
+  const bool carry = novelty != nullptr && !isV && t_seg % kApNovelty == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0));
+  if (carry) {
+    const float* ns = nov_new + (int64_t)ui.b * count;
+    float* nd = novelty + nov_offset(D, ui) + D.n;
+    float nv[kApNovelty / kApThreads];
+#pragma unroll
+    for (int i = 0; i < kApNovelty / kApThreads; ++i) nv[i] = ns[min(t_seg + i * kApThreads + (int)threadIdx.x, count - 1)];
+#pragma unroll
+    for (int i = 0; i < kApNovelty / kApThreads; ++i) {
+      const int j = t_seg + i * kApThreads + (int)threadIdx.x;
+      if (j < count) nd[j] = nv[i];
+    }
+  }
 #pragma unroll
   for (int i = 0; i < kApLoads; ++i) {
     const int64_t b = b0 + i * (kApThreads * 16);
@@ -79,7 +90,6 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
       else     *reinterpret_cast<uint4*>(dst + b) = v[i];
     }
   }
-  if (carry) novelty[nov_offset(D, ui) + D.n + j] = nv;
 }
 
 template <int ROWB>
