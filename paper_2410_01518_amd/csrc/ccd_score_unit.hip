@@ -17,8 +17,7 @@
 //           2^((x - reference) c) of its 16 token rows to that row's sum (fixed reference per wave and row: the maximum
 //           over the wave's first tile; a sum that leaves the fp32 range makes the wave redo its tokens with a
 //           running maximum);
-//   merge   the four waves' (reference, sum) pairs, the CaP keys' block (causal variant) and the windowed head become
-//           one log2-sum-exp per query row;
+//   merge   the four waves' (reference, sum) pairs, the CaP keys' block (causal variant) become one log2-sum-exp per query row;
 //   pass 2  D[query][token] = Qfrag x Kfrag: a lane owns one token and adds 2^(x c - lse2[query]) over the 16 query
 //           rows of each accumulator; the negated lse2 values of a block pair are re-read from LDS (two addresses per
 //           wave: a broadcast) one step ahead.  Tiles are walked backwards: what pass 1 read last is still cached.
@@ -52,6 +51,7 @@ template <int HD>
 struct UnitLds {
   float2 stat[4][kUQ];     // per wave: (max2, sum) of every query row of the sweep over the wave's tokens
   float neg_lse[kUQ];      // -log2-sum-exp per query row of the sweep
+  int first[kUQ];          // under a window: the first token a query row sees
   float ubuf[4][kUBlock * kStep];   // per wave: the token sums of the block of tiles it is working on (pass 2)
 };
 
@@ -223,6 +223,14 @@ __device__ __forceinline__ void pipelined_step(floatx16 (&nxt)[kQB], const bf16x
   });
 }
 
+// all ones if i is negative, as a vector value: comparisons put 64-lane masks into scalar registers, and those of a tile's rows do
+// not fit there (254 spilled, and 17 vector registers with them)
+__device__ __forceinline__ uint32_t hidden_bits(int i) {
+  int m = i >> 31;
+  asm volatile("" : "+v"(m));
+  return (uint32_t)m;
+}
+
 __device__ __forceinline__ float max16(const floatx16& v) {
   float t0 = fmaxf(fmaxf(v[0], v[1]), v[2]), t1 = fmaxf(fmaxf(v[3], v[4]), v[5]);
   float t2 = fmaxf(fmaxf(v[6], v[7]), v[8]), t3 = fmaxf(fmaxf(v[9], v[10]), v[11]);
@@ -251,9 +259,8 @@ __device__ __forceinline__ void load_neg_lse(float (&nl)[16], uint32_t lane_base
 template <int HD, class ET, int NP>
 __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl, const ET* __restrict__ Q,
                                                             const ET* __restrict__ K,
-                                                            const float2* __restrict__ part, float* __restrict__ u,
-                                                            const ET* __restrict__ Kcap,
-                                                            float* __restrict__ lse_io) {
+                                                            float* __restrict__ u, const ET* __restrict__ Kcap,
+                                                            const float* __restrict__ lse_given) {
   constexpr bool F32 = std::is_same<ET, float>::value;
   using SH = UnitShape<HD, F32>;
   constexpr int KF = SH::KF;           // fragments of a K tile / of a block of query rows
@@ -269,9 +276,9 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
   const float c = D.scale_log2;
-  // Tokens [D.head, n) are seen by every query row (all of them without a sliding window); the hidden head is left to
-  // its own two small kernels.  Full 32-token tiles are dealt to the four waves in runs; a ragged last tile goes to the
-  // last wave.
+  // Tokens [D.head, n) are seen by every query row (all of them without a sliding window).  Full 32-token tiles are dealt to the four
+  // waves in runs; a ragged last tile goes to the last wave.  The tiles of [D.head0, D.head), hidden from some rows, are
+  // masked and dealt out one by one (as two kernels of their own, one workgroup per unit each, they took 22 us for 256 units).
   const int tb = D.head;
   const int n_main = D.n - tb;
   const int full = n_main / kStep;
@@ -476,6 +483,27 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
           fold_stats<true>(accA, m_ref[p], Zs[p], c, half, n_main - full * kStep);
         });
       }
+      if constexpr (!F32) {          // (fp32 caches under a window take other kernels)
+        for (int t = D.head0 + wave * kStep; t < D.head; t += 4 * kStep) {
+          load_k_tile<HD>(a[0], Ku, t, D.head - 1, col, half);
+          q_frags_arrived();
+          static_for<0, NP>([&](auto Pc) {
+            constexpr int p = decltype(Pc)::value;
+            logits_now<SH, 1, p>(accA, a[0]);
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) {
+              const int first = D.win_off + (qc + (p * kQB + qb) * 32 + col) % D.P - t, past = D.head - t;
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const int row = acc_row(r, half);
+                const uint32_t hidden = hidden_bits(row - first) | hidden_bits(past - 1 - row);
+                accA[qb][r] = __uint_as_float((__float_as_uint(accA[qb][r]) & ~hidden) | (0xFF800000u & hidden));
+              }
+            }
+            fold_stats<false>(accA, m_ref[p], Zs[p], c, half, kStep);
+          });
+        }
+      }
       // the two lane halves hold different token rows of the same query row: merge, lower half writes
 #pragma unroll
       for (int p = 0; p < NP; ++p)
@@ -506,13 +534,8 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       const bool my_row = (int)threadIdx.x < UQ && q < D.GP;     // (threads past the sweep's rows have none)
       float lse = INFINITY;
       if (pl.lse_given) {            // the caller's normalisers (natural log): nothing to merge
-        if (my_row) lse = lse_io[(int64_t)unit * D.GP + q] * 1.44269504088896340736f;
+        if (my_row) lse = lse_given[(int64_t)unit * D.GP + q] * 1.44269504088896340736f;
       } else if (my_row) {
-        if (pl.head_block) {         // statistics of the windowed head, left there by its own kernel
-          const float2 hd = part[extra_block_index(D, pl, unit, q)];
-          const float Mh = fmaxf(cap.x, hd.x);
-          cap = make_float2(Mh, cap.y * fast_exp2(cap.x - Mh) + hd.y * fast_exp2(hd.x - Mh));
-        }
         float M = cap.x;
 #pragma unroll
         for (int w = 0; w < 4; ++w) M = fmaxf(M, sm.stat[w][threadIdx.x].x);
@@ -523,9 +546,9 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
           z += v.y * fast_exp2(v.x - M);
         }
         lse = M + __log2f(z);
-        if (pl.head_block) lse_io[(int64_t)unit * D.GP + q] = lse;   // for the head's probabilities
       }
       sm.neg_lse[threadIdx.x] = -lse;
+      if (D.head > 0) sm.first[threadIdx.x] = D.win_off + q % D.P;
       __syncthreads();
     }
 
@@ -614,6 +637,29 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       const int t_blk = tb + sa * kStep, n_blk = min((sb - sa) * kStep, D.n - t_blk);
       for (int i = lane; i < n_blk; i += 64) uu[t_blk + i] = (qc == 0) ? ub[i] : uu[t_blk + i] + ub[i];
     }
+    if constexpr (!F32) {
+      for (int t = D.head0 + wave * kStep; t < D.head; t += 4 * kStep) {
+        load_k_tile<HD>(a[0], Ku, t, D.head - 1, col, half);
+        float us[2] = {0.f, 0.f};
+        static_for<0, NP>([&](auto Pc) {
+          constexpr int p = decltype(Pc)::value;
+          logits_now<SH, 2, p>(accA, a[0]);
+#pragma unroll
+          for (int qb = 0; qb < kQB; ++qb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int row = (p * kQB + qb) * 32 + acc_row(r, half);
+              const float e = fast_exp2(fmaf(accA[qb][r], c, sm.neg_lse[row]));
+              us[r & 1] += __uint_as_float(__float_as_uint(e) & ~hidden_bits(t + col - sm.first[row]));
+            }
+        });
+        float v = us[0] + us[1];
+        v += __shfl_xor(v, 32);
+        if (half == 0 && t + col < D.head) uu[t + col] = qc == 0 ? v : uu[t + col] + v;
+      }
+      if (qc == 0)                   // tokens nobody sees
+        for (int t = threadIdx.x; t < D.head0; t += kMT) uu[t] = 0.f;
+    }
     __syncthreads();   // the LDS tables are rewritten by the next sweep
 #undef CCD_NEXT_TILE
 #undef CCD_TILE_NOW
@@ -630,19 +676,19 @@ bool score_unit_supported(const Dims& D) { return D.dtype == 1 ? (D.d == 64 || D
 // the kernel for (head dimension, cache type, pairs of query blocks per sweep)
 template <int HD, class ET>
 static void launch_score_unit_as(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
-                                 const float2* part, float* u, float* lse_io, hipStream_t s) {
+                                 const float* lse, float* u, hipStream_t s) {
   dim3 grid((unsigned)D.units_run), block(kMT);
   const ET *q = (const ET*)Q, *k = (const ET*)K, *kc = (const ET*)K_cap;
-  if (D.GP <= 64)       launch((score_unit_kernel<HD, ET, 1>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
-  else if (D.GP <= 128) launch((score_unit_kernel<HD, ET, 2>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
-  else                  launch((score_unit_kernel<HD, ET, 4>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
+  if (D.GP <= 64)       launch((score_unit_kernel<HD, ET, 1>), grid, block, s, D, pl, q, k, u, kc, lse);
+  else if (D.GP <= 128) launch((score_unit_kernel<HD, ET, 2>), grid, block, s, D, pl, q, k, u, kc, lse);
+  else                  launch((score_unit_kernel<HD, ET, 4>), grid, block, s, D, pl, q, k, u, kc, lse);
 }
 
-void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
-                       const float2* part, float* u, float* lse_io, hipStream_t s) {
-  if (D.dtype == 0)    launch_score_unit_as<64, float>(D, pl, Q, K, nullptr, part, u, lse_io, s);
-  else if (D.d == 64)  launch_score_unit_as<64, uint16_t>(D, pl, Q, K, K_cap, part, u, lse_io, s);
-  else                 launch_score_unit_as<128, uint16_t>(D, pl, Q, K, K_cap, part, u, lse_io, s);
+void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float* lse, float* u,
+                       hipStream_t s) {
+  if (D.dtype == 0)    launch_score_unit_as<64, float>(D, pl, Q, K, nullptr, lse, u, s);
+  else if (D.d == 64)  launch_score_unit_as<64, uint16_t>(D, pl, Q, K, K_cap, lse, u, s);
+  else                 launch_score_unit_as<128, uint16_t>(D, pl, Q, K, K_cap, lse, u, s);
 }
 
 }  // namespace ccd

@@ -320,25 +320,11 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
   float* lse2 = reinterpret_cast<float*>(ws + w.off_lse);
   float* u = reinterpret_cast<float*>(ws + w.off_u);
   if (pl.unit_kernel) {
-    // statistics, merge and probabilities of every unit in one kernel; a windowed head keeps its two small kernels
-    float* lse_io = lse2;
-    if (lse != nullptr) {
-      pl.lse_given = 1;
-      lse_io = const_cast<float*>(lse);   // only read when pl.lse_given
-    } else if (D.head > 0) {
-      pl.head_block = 1;
-      g_prof.begin(kStHead, st);
-      launch_head_stats_mfma(D, pl, Q, K, part, st);
-      g_prof.end(st);
-    }
+    // statistics, merge and probabilities of every unit in one kernel
+    pl.lse_given = lse != nullptr ? 1 : 0;
     g_prof.begin(kStUnit, st);
-    launch_score_unit(D, pl, Q, K, K_cap, part, u, lse_io, st);
+    launch_score_unit(D, pl, Q, K, K_cap, lse, u, st);
     g_prof.end(st);
-    if (D.head > 0) {
-      g_prof.begin(kStHead, st);
-      launch_head_prob_mfma(D, pl, Q, K, lse_io, u, st);
-      g_prof.end(st);
-    }
     return;
   }
   if (lse != nullptr) {
