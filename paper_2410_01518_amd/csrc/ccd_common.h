@@ -46,7 +46,7 @@ __device__ __forceinline__ void clear_sync(const ScorePlan& pl, int unit, bool f
   if (pl.sync != nullptr && first && threadIdx.x < kSyncWords) pl.sync[(int64_t)unit * kSyncWords + threadIdx.x] = 0u;
 }
 // where the one extra (max, sum) entry of (unit, query q) lives in `part`, behind the slices of all units: the block of
-// the CaP keys on the vector-ALU path, the windowed head on the matrix-core path
+// the CaP keys (vector ALUs, six-product and direct kernels) or the windowed head (bf16 slice kernels)
 __device__ __forceinline__ int64_t extra_block_index(const Dims& D, const ScorePlan& pl, int unit, int q) {
   return ((int64_t)D.units * pl.n_slices1 + unit) * D.GP + q;
 }

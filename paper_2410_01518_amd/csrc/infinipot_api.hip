@@ -313,7 +313,9 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     run_cap_scores(part, pl, w, Q, K, K_cap, lse, ws, st);
     part.unit0 = D.unit0 + lead;
     part.units_run = D.units_run - lead;
-    run_cap_scores(part, plan_score(part, K_cap != nullptr), w, Q, K, K_cap, lse, ws, st);
+    ScorePlan rest = plan_score(part, K_cap != nullptr);
+    rest.sync = pl.sync;             // (a partition of few compute units: the rest of a call whose units are shared has words to clear too)
+    run_cap_scores(part, rest, w, Q, K, K_cap, lse, ws, st);
     return;
   }
   float2* part = reinterpret_cast<float2*>(ws + w.off_part);
