@@ -92,6 +92,24 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
   }
 }
 
+// All loads have arrived.  The builtin, so that the compiler knows it too: behind inline assembly it took the registers of loads
+// under a condition for still in use and waited before every load and every store of the next rows.  Append + distill: 64 units of 2500 /
+// 20000 tokens 77.7 / 497.6 -> 76.6 / 489.8 us, 128 units of 3000 tokens 142.5 -> 139.1 us; with that four rows per thread where one
+// workgroup has a unit, not two: 256 units of 600 tokens 64.0 -> 62.9 us, 640 units of 2000 tokens 506.7 -> 502.1 us.
+__device__ __forceinline__ void wait_for_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0); expcnt and lgkmcnt as they are
+  asm volatile("" ::: "memory");
+}
+
+// Indices that have arrived before anything is loaded by them under a condition: where the compiler cannot count the loads in flight,
+// the wait for the next index is one for the rows before it.
+template <int N>
+__device__ __forceinline__ void arrived(int (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
 template <int ROWB>
 __global__ __launch_bounds__(kCpThreads) void compact_rows_kernel(Dims D, const char* Ksrc, const char* Vsrc,
                                                                   const int32_t* __restrict__ keep_idx, char* Kdst,
@@ -111,21 +129,19 @@ __global__ __launch_bounds__(kCpThreads) void compact_rows_kernel(Dims D, const 
   for (int base = 0; base < D.k; base += kRowsPerPass * kCpUnroll) {
     uint4 v[kCpUnroll];
     bool move[kCpUnroll];
+    int sidx[kCpUnroll];
+#pragma unroll
+    for (int i = 0; i < kCpUnroll; ++i) sidx[i] = keep[min(base + i * kRowsPerPass + row_in_pass, D.k - 1)];
+    arrived(sidx);
 #pragma unroll
     for (int i = 0; i < kCpUnroll; ++i) {
       const int j = base + i * kRowsPerPass + row_in_pass;
-      move[i] = false;
-      if (j < D.k) {
-        int sidx = keep[j];
-        sidx = min(max(sidx, 0), D.n_cap - 1);   // a corrupt index must not leave the pot
-        move[i] = !(inplace && sidx == j);
-        if (move[i]) v[i] = load_streaming(src + (int64_t)sidx * ROWB + lane_off);
-      }
+      sidx[i] = min(max(sidx[i], 0), D.n_cap - 1);   // a corrupt index must not leave the pot
+      move[i] = j < D.k && !(inplace && sidx[i] == j);
+      if (move[i]) v[i] = load_streaming(src + (int64_t)sidx[i] * ROWB + lane_off);
     }
-    if (inplace) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-    }
+    wait_for_loads();
+    if (inplace) __syncthreads();
 #pragma unroll
     for (int i = 0; i < kCpUnroll; ++i) {
       const int j = base + i * kRowsPerPass + row_in_pass;
@@ -180,7 +196,7 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
     const int j = base + threadIdx.x;
     float v = 0.f;
     if (j < D.k) v = nov[min(max(keep[j], 0), D.n_cap - 1)];
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    wait_for_loads();
     __syncthreads();
     if (j < D.k) nov[j] = v;
   }
@@ -204,7 +220,7 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // carried novelty, which took a kernel of its own; 8 units, 32768 -> 4096: 113 -> 57 us.
 //
 // Threads: the moving of one workgroup per unit wants 16 waves (512 threads with twice the rows each: 2 - 3 us slower on 256
-// units, with a thread's rows loaded one after the other, see kScUnroll), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
+// units), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
 // that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
 constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
 // Waves per SIMD to compile for: 64 registers instead of 72 for rows of up to 4096 tokens, so that two workgroups fit a compute unit
@@ -212,9 +228,8 @@ constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row 
 // distill with given normalisers, 2000 tokens: 400 / 640 units 257 / 438 -> 251 / 427 us, 600 tokens 85 / 129 -> 78 / 121 us; up to 256
 // units the same; 300 units of 2000 tokens 182 -> 186 us).  With CR-RoPE 13 registers would be spilled (256 units 363 -> 383 us).
 constexpr int sc_min_waves(bool shared, int chunks, int rope_row) { return !shared && chunks == 1 && rope_row == 0 ? 8 : 1; }
-// Rows per thread and chunk.  The loads of one row, K and V, travel together, but the next row's wait for them: they stand under a
-// condition, and behind the wait that ends a chunk in inline assembly the compiler takes their registers for still in use.
-constexpr int kScUnroll = 2;
+// Rows per thread and chunk.  ROPE: its coefficients take as many registers again, and four rows spilled 4 of them.
+constexpr int sc_unroll(bool rope) { return rope ? 2 : 4; }
 // Calls that overlap on one workspace are an error of the caller: one call clears the other's words, or leaves anything at all
 // in them where the shapes differ.  Their results are undefined, but every access stays in the pot and their kernels end: a
 // ticket counts only if it names a chunk of this call, a workgroup takes no more of them than there are chunks, and its waits
@@ -273,18 +288,21 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHA
   auto keep = [&](int j) { return kRegs ? (int)keep_lds[j] : min(max(keep_out[j], 0), D.n - 1); };
   if (kRegs && part == 0)
     for (int j = threadIdx.x; j < D.k; j += THREADS) keep_out[j] = keep_lds[j];
-  // (keep[j] >= j: a chunk's sources are read before anything at or above them is written; the eight loads of a thread go out one
-  // after the other)
+  // (keep[j] >= j: a chunk's sources are read before anything at or above them is written)
   auto compact_novelty = [&]() {
     constexpr int kN = 8;
     for (int base = 0; base < D.k; base += kN * THREADS) {
       float v[kN];
+      int sidx[kN];
+#pragma unroll
+      for (int i = 0; i < kN; ++i) sidx[i] = keep(min(base + i * THREADS + (int)threadIdx.x, D.k - 1));
+      arrived(sidx);
 #pragma unroll
       for (int i = 0; i < kN; ++i) {
         const int j = base + i * THREADS + threadIdx.x;
-        if (j < D.k) v[i] = nov[keep(j)];
+        if (j < D.k) v[i] = nov[sidx[i]];
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      wait_for_loads();
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < kN; ++i) {
@@ -305,7 +323,7 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHA
   const int lane_in_row = threadIdx.x & ((1 << lane_shift) - 1);
   const int lane_off = lane_in_row * 16;
   const int row_in_pass = threadIdx.x >> lane_shift, rows_per_pass = THREADS >> lane_shift;
-  constexpr int kUnroll = !SHARED ? kScUnroll : sh_unroll(THREADS, ROPE);
+  constexpr int kUnroll = !SHARED ? sc_unroll(ROPE) : sh_unroll(THREADS, ROPE);
 
   if (SHARED && carry_novelty && threadIdx.x == 0)
     last_lds = agent_add(&sy[kSyncSelected], 1u) == (uint32_t)(wgs_per_unit - 1);
@@ -317,19 +335,25 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHA
     uint4 a[kUnroll], b[kUnroll];
     bool move[kUnroll];
     RopeCoef<ROPE ? ROWB : 128, BF16> coef[ROPE ? kUnroll : 1];
+    int sidx[kUnroll];                            // ascending, in [j, n)
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i) sidx[i] = keep(min(base + i * rows_per_pass + row_in_pass, end - 1));
+    arrived(sidx);
 #pragma unroll
     for (int i = 0; i < kUnroll; ++i) {
       const int j = base + i * rows_per_pass + row_in_pass;
       move[i] = false;
       if (j < end) {
-        const int sidx = keep(j);                 // ascending, in [j, n)
-        move[i] = sidx != j;
-        if (move[i] || ROPE) a[i] = load_streaming(kb + (int64_t)sidx * rowb + lane_off);
-        if (move[i]) b[i] = load_streaming(vb + (int64_t)sidx * rowb + lane_off);
+        move[i] = sidx[i] != j;
+        if (move[i] || ROPE) a[i] = load_streaming(kb + (int64_t)sidx[i] * rowb + lane_off);
+        if (move[i]) b[i] = load_streaming(vb + (int64_t)sidx[i] * rowb + lane_off);
         if constexpr (ROPE) coef[i].load(lane_in_row, rope_cos + (int64_t)j * half_d, rope_sin + (int64_t)j * half_d);
       }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (one workgroup per unit with CR-RoPE: with all loads in flight at once 160 units of 2500 tokens went 189 -> 192 us, 256 to 640 units
+    // stayed the same)
+    if constexpr (ROPE && !SHARED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else wait_for_loads();
     __syncthreads();
     int next = base + kUnroll * rows_per_pass;
     if constexpr (SHARED) {
