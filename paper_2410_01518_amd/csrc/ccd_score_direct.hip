@@ -221,7 +221,8 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
             z = a.y;
           }
         }
-        neg_lse = -(M + __log2f(z));
+        // (a row none of whose visible logits is finite adds nothing: probabilities of 0, not of 2^(-inf + inf))
+        neg_lse = z == 0.f ? -INFINITY : -(M + __log2f(z));
         if constexpr (SH::F32) {               // for scores_again (all workgroups of a unit write the same)
           if (lane < SH::kRows) lse_io[(int64_t)unit * D.GP + q] = -neg_lse;
         }

@@ -147,3 +147,31 @@ def test_elements_beyond_the_largest_bf16(units, G, P, n, d, options, kind):
         _assert_close(got[i], ref, Qu[i], fin, scale, i, rounds=d + 2)      # a chain of d fmas, and the scale
         if kind == "infinite keys":
             assert (got[i][tokens] == 0.0).all()
+
+
+# window == P: the last CaP token of a head sees no cached token, the one before it only the last; one token in all; a call with too many
+# blocks of tokens and query rows for the direct kernels
+@pytest.mark.parametrize("units,G,P,n,d,window,infinite", [
+    (2, 2, 5, 40, 128, 5, 1), (1, 3, 33, 300, 64, 33, 1), (3, 1, 20, 333, 128, 24, 6), (1, 1, 1, 1, 64, 0, 1), (2, 4, 16, 96, 128, 0, 96),
+    (12, 8, 128, 700, 128, 128, 1)])
+def test_a_row_none_of_whose_visible_keys_is_finite_adds_nothing(units, G, P, n, d, window, infinite):
+    """The last `infinite` tokens take every logit to -inf: a row that sees only such tokens has no weight to give, and the scores of
+    the others are what they are without it."""
+    rng = np.random.default_rng(units * n + P)
+    Q = rng.standard_normal((1, 1, units * G, P, d)).astype(np.float32)
+    K = rng.standard_normal((1, 1, units, n, d)).astype(np.float32)
+    Q[..., 7] = np.abs(Q[..., 7]) + np.float32(0.1)
+    K[0, 0, :, n - infinite:, 7] = -np.inf
+    dQ, dK = gu.to_dev(Q), gu.to_dev(K)
+    shape = ip.make_shape(dQ, dK, None, k=n, T=0, pool_w=1, window=window)
+    ws = ip.alloc_workspace(shape)
+    scores = torch.empty((1, 1, units, n), dtype=torch.float32, device="cuda")
+    print(f"rows without a finite key: units={units} G={G} P={P} n={n} d={d} window={window}", flush=True)
+    assert ip.ccd_score(shape, dQ, dK, None, scores, ws) == ip.CCD_OK
+    got = gu.to_host(scores).reshape(units, n).astype(np.float64)
+    scale = 1.0 / math.sqrt(d)
+    Qu, Ku = Q.reshape(units, G * P, d).astype(np.float64), K.reshape(units, n, d).astype(np.float64)
+    for i in range(units):
+        ref = O.cap_scores(Qu[i], Ku[i], scale, P=P, window=window)
+        assert (got[i][n - infinite:] == 0.0).all()
+        _assert_close(got[i], ref, Qu[i], np.where(np.isinf(Ku[i]), 0.0, Ku[i]), scale, i, rounds=d + 2)
