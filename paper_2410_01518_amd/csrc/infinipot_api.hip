@@ -188,10 +188,12 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
   //             (12480) 67 / 106 against 73 / 114 us
   //   256 rows  24 units of 820 tokens (4992) 49 / 71 against 44 / 63 us, 120 of 300 (9600) 52 / 82 against 61 / 89 us
   //   two blocks of rows meet between 13500 and 19000
-  // The unit kernel (fp32 values as sums of three bf16 products; head dimension 64, plain softmax over the cached tokens) when asked for,
-  // and by itself for a third of the chip's units on, half of them with a single block of rows: 140 units of 1200 tokens and 16 rows 78
-  // (direct) against 76 us; 120 units of 2500 tokens and 100 / 256 rows 145 / 187 (six products) against 134 / 170 us; 64 units 92 / 117
-  // against 105 / 140 us.
+  // The unit kernel (fp32 values as sums of three bf16 products, logits good to 2^-16 of sum |q k| only; head dimension 64, plain softmax
+  // over the cached tokens) when asked for, and by itself from half of the chip's units on: 140 units of 1200 tokens and 16 rows 78 (direct)
+  // against 76 us; 127 units and 256 rows, 7000 / 16384 tokens 525 / 1203 (six products) against 452 / 1016 us.  With more
+  // than one block of rows from a third on while the rows are short (120 units of 2500 tokens and 100 / 256 rows 145 / 187 against 134 /
+  // 170 us; 64 units 92 / 117 against 105 / 140 us).  Long rows stay with six products there: they are the more accurate ones, and the
+  // unit kernel is not faster everywhere (81 / 100 units of 7000 tokens and 64 rows 257 / 318 against 276 / 321 us).
   if (D.dtype == CCD_FP32) {
     const int cus = compute_units();
     const int64_t rows = (D.GP + 31) / 32, blocks = (int64_t)D.units_run * ((D.n + 31) / 32) * rows;
@@ -199,7 +201,8 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
     if (unit && D.score_path == CCD_PATH_MFMA_UNIT) {
       pl.unit_kernel = 1;
     } else if (D.score_path == CCD_PATH_AUTO) {
-      if (unit && (rows == 1 ? 2 * D.units_run >= cus : 16 * D.units_run > 5 * cus)) {
+      const int64_t sweeps = (D.GP + 255) / 256;
+      if (unit && (2 * D.units_run >= cus || (rows > 1 && 16 * D.units_run > 5 * cus && sweeps * D.n <= 6000))) {
         pl.unit_kernel = 1;
       } else if (rows == 1 || blocks <= (rows == 2 ? 16384 : 8192)) {
         plan_direct(D, cus, pl);
@@ -225,6 +228,8 @@ static bool path_refused(const Dims& D, const ScorePlan& pl) {
 //   tokens and 256 rows 300 / 321 / 355 against 257 / 294 / 351 us; 300 tokens and 16 rows 58 / 60 / 62 against 61 / 63 / 65 us
 //   rest of 128: 2500 tokens and 256 rows 676 against 695 us, 8192 tokens and 256 rows 1798 against 1768 us, 32768 tokens and 1024
 //   rows 16.9 against 15.9 ms
+//   fp32 (three products for the whole rounds, six for the rest), 16384 tokens and 256 rows, rest of 64 / 80: 2264 / 2324 against 2122 /
+//   2279 us; rest of 100 / 127: 2384 / 2481 against 2437 / 2642 us
 static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_keys) {
   if (!pl.unit_kernel || D.score_path != CCD_PATH_AUTO) return D.units_run;
   const int cus = compute_units(), rest = D.units_run % cus;
@@ -232,7 +237,8 @@ static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_ke
   Dims R = D;
   R.units_run = rest;
   const int64_t work = (int64_t)D.n * ((D.GP + 63) / 64) * D.d;
-  const bool pays = 4 * rest <= cus ? work >= 128 * 1000 : (2 * rest <= cus && work >= 128 * 32768);
+  const bool half = D.dtype == CCD_FP32 && D.GP > 32 ? 16 * rest <= 5 * cus : 2 * rest <= cus;
+  const bool pays = 4 * rest <= cus ? work >= 128 * 1000 : (half && work >= 128 * 32768);
   return pays && !plan_score(R, cap_keys).unit_kernel ? D.units_run - rest : D.units_run;
 }
 

@@ -1,7 +1,11 @@
 """fp32 calls with too many blocks of tokens and query rows for the direct kernels: the six-product kernels by token slices, under every
 option and with elements beyond the largest bf16 (the checks of test_gpu_score_split)."""
-import pytest
+import math
 
+import pytest
+import torch
+
+from paper_2410_01518_amd import infinipot as ip
 from tests import test_gpu_score_split as base
 
 pytestmark = pytest.mark.gpu
@@ -19,3 +23,21 @@ def test_scores(units, G, P, n, d, options):
 @pytest.mark.parametrize("units,G,P,n,d,options", [(12, 8, 128, 700, 128, ""), (13, 8, 129, 650, 64, "kcat window"), (14, 4, 100, 2100, 64, "lse window")])
 def test_elements_beyond_the_largest_bf16(units, G, P, n, d, options, kind):
     base.test_elements_beyond_the_largest_bf16(units, G, P, n, d, options, kind)
+
+
+# 81 to 127 units of 64 elements with more than 6000 tokens times sweeps of 256 rows: beyond these the unit kernel is the quicker one, with
+# logits good to 2^-16 of sum |q k|.  The six products leave 2e-7 to 4e-7 in the 2-norm and 1.3e-6 at most, the unit kernel 1e-5 and
+# 3.4e-5: four times the former is asked for.
+@pytest.mark.parametrize("units,G,P,n", [(81, 4, 64, 6001), (100, 4, 16, 7000), (127, 1, 33, 6016), (96, 5, 60, 3001)])
+def test_long_rows_below_half_of_the_chip_to_fp32_accuracy(units, G, P, n):
+    print(f"long rows {units} {G} {P} {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    K = torch.empty((1, units, 1, n, 64), device="cuda").normal_(generator=g)
+    Q = torch.empty((1, units, G, P, 64), device="cuda").normal_(generator=g)
+    shape = ip.make_shape(Q, K, None, k=n, T=0, pool_w=1)
+    scores = torch.empty((1, units, 1, n), device="cuda")
+    assert ip.ccd_score(shape, Q, K, None, scores, ip.alloc_workspace(shape)) == ip.CCD_OK
+    for i in range(0, units, 20):
+        x = torch.matmul(Q[0, i].reshape(G * P, 64).double(), K[0, i, 0].double().t().contiguous()) / math.sqrt(64)
+        ref, got = torch.softmax(x, -1).sum(0), scores[0, i, 0].double()
+        assert float((got - ref).norm() / ref.norm()) < 1.6e-6 and float(((got - ref).abs() / ref).max()) < 5.2e-6
