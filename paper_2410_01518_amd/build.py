@@ -99,6 +99,63 @@ def check_matrix_operand_distance(asm_path: str) -> None:
         raise RuntimeError(f"{asm_path}: an ALU write directly before the matrix instruction that reads it:\n" + "\n".join(bad[:10]))
 
 
+_WAIT_FOR_ALL_LOADS = re.compile(r"s_waitcnt\b.*\bvmcnt\(0\)")
+
+
+def check_acc_loads_awaited(asm_path: str) -> None:
+    """On every way from a load into an accumulation register to a matrix instruction that reads one there must be a wait for all
+    loads.  These loads are inline assembly: the compiler does not see them, and its own waits count the loads it knows."""
+    blocks, order = {}, []          # label -> (events, labels jumped to, whether the next block follows)
+    events, jumps = [], []
+
+    def close(follows):
+        if order:
+            blocks[order[-1]] = (events[:], jumps[:], follows)
+        events.clear()
+        jumps.clear()
+
+    with open(asm_path) as f:
+        for n, line in enumerate(f, 1):
+            text = line.split(";")[0].strip()
+            if text.endswith(":"):
+                close(follows=True)
+                order.append(text[:-1])
+                continue
+            if not text or text.startswith("."):
+                continue
+            if not order:
+                order.append("")
+            op, _, args = text.partition(" ")
+            if op.startswith(("s_cbranch", "s_branch")) or op == "s_endpgm":
+                if op != "s_endpgm":
+                    jumps.append(args.strip())
+                close(follows=op.startswith("s_cbranch"))
+                order.append(f"{n}")
+            elif _WAIT_FOR_ALL_LOADS.match(text):
+                events.append(("wait", n, text))
+            elif op.startswith("global_load") and _ACC_REG.search(args):
+                events.append(("load", n, text))
+            elif op.startswith("v_mfma") and any(_ACC_REG.search(a) for a in args.split(",")[1:3]):
+                events.append(("use", n, text))
+    close(follows=False)
+    after = {order[i]: ([order[i + 1]] if blocks[order[i]][2] and i + 1 < len(order) else []) + blocks[order[i]][1] for i in range(len(order))}
+    pending, bad, todo = set(), {}, list(order)      # pending: blocks that loads may be under way at the start of
+    while todo:
+        label = todo.pop()
+        under_way = label in pending
+        for kind, n, text in blocks[label][0]:
+            if kind == "use" and under_way:
+                bad[n] = text
+            under_way = kind == "load" or (under_way and kind != "wait")
+        for nxt in after[label] if under_way else []:
+            if nxt in blocks and nxt not in pending:
+                pending.add(nxt)
+                todo.append(nxt)
+    if bad:
+        raise RuntimeError(f"{asm_path}: a matrix instruction may read an accumulation register whose load is under way:\n"
+                           + "\n".join(f"{n}: {bad[n]}" for n in sorted(bad)[:10]))
+
+
 def build_library(verbose: bool = True, extra_flags=()) -> str:
     """Compiles every kernel source and links the shared library; returns its path."""
     hipcc = _hipcc()
@@ -116,6 +173,7 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
                 raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
             check_acc_registers_untouched(asm)
             check_matrix_operand_distance(asm)
+            check_acc_loads_awaited(asm)
         cmd = [hipcc, *flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:

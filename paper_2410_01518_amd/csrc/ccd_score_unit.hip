@@ -640,6 +640,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
     if constexpr (!F32) {
       for (int t = D.head0 + wave * kStep; t < D.head; t += 4 * kStep) {
         load_k_tile<HD>(a[0], Ku, t, D.head - 1, col, half);
+        q_frags_arrived();           // (with given normalisers a wave without a tile of its own has waited for nothing yet)
         float us[2] = {0.f, 0.f};
         static_for<0, NP>([&](auto Pc) {
           constexpr int p = decltype(Pc)::value;

@@ -1,6 +1,6 @@
-"""The two checks build.py runs on the generated assembly of the unit score kernel, on planted text: compiler code
-must stay off the accumulation registers the kernel reserves, and no ALU write may stand within two issue slots of
-the matrix instruction that reads it."""
+"""The checks build.py runs on the generated assembly of the unit score kernel, on planted text: compiler code must stay
+off the accumulation registers the kernel reserves, no ALU write may stand within two issue slots of the matrix
+instruction that reads it, and nothing may read an accumulation register before the wait for its load."""
 import pytest
 
 from paper_2410_01518_amd import build
@@ -53,3 +53,23 @@ def test_compiler_code_on_an_accumulation_register_is_refused(tmp_path):
         build.check_acc_registers_untouched(_write(tmp_path, GOOD + "\tv_accvgpr_write_b32 a5, v1\n"))
     with pytest.raises(RuntimeError, match="accumulation registers"):
         build.check_acc_registers_untouched(_write(tmp_path, GOOD + "\tv_mfma_f32_32x32x16_bf16 a[0:15], v[0:3], v[4:7], a[0:15]\n"))
+
+
+LOAD, WAIT = "\tglobal_load_dwordx4 a[0:3], v[20:21], off\n", "\ts_waitcnt vmcnt(0)\n"
+MMA = "\tv_mfma_f32_32x32x16_bf16 v[34:49], a[0:3], v[82:85], 0\n"
+
+
+def test_matrix_instruction_behind_the_wait_is_accepted(tmp_path):
+    build.check_acc_loads_awaited(_write(tmp_path, "kernel:\n" + LOAD + WAIT + MMA + "\ts_endpgm\n"))
+    # the wait in a loop that loads again; what follows an s_branch is not reached from before it
+    build.check_acc_loads_awaited(_write(tmp_path, "kernel:\n.LBB0_1:\n" + LOAD + WAIT + MMA + "\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n"))
+    build.check_acc_loads_awaited(_write(tmp_path, "kernel:\n" + LOAD + "\ts_branch .LBB0_2\n.LBB0_1:\n" + MMA + ".LBB0_2:\n" + WAIT + MMA))
+
+
+@pytest.mark.parametrize("text", [
+    LOAD + "\ts_waitcnt vmcnt(1)\n" + MMA,                                                    # a wait that counts other loads
+    LOAD + "\ts_cbranch_scc1 .LBB0_2\n" + WAIT + ".LBB0_2:\n" + MMA,                          # a way around the wait
+    ".LBB0_1:\n" + MMA + LOAD + "\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n"])                   # from one round of a loop to the next
+def test_matrix_instruction_that_a_load_may_reach_is_refused(tmp_path, text):
+    with pytest.raises(RuntimeError, match="under way"):
+        build.check_acc_loads_awaited(_write(tmp_path, "kernel:\n" + text))

@@ -90,6 +90,19 @@ def test_score_lse_matches_oracle(case, reading, path):
     np.testing.assert_allclose(ref["scores"][fin], self_norm["scores"][fin], rtol=2e-5, atol=1e-30)
 
 
+# the unit kernel where some or all of its four waves have windowed tiles only: pass 2 is the first to read the query fragments
+@pytest.mark.parametrize("window", [150, 165, 190, 290])
+@pytest.mark.parametrize("d,Hq", [(64, 2), (128, 2), (128, 4)])
+def test_score_lse_of_waves_that_have_windowed_tiles_only(d, Hq, window):
+    cfg = _cfg(L=3, Hq=Hq, Hkv=2, d=d, N=400, P=150, T=20, w=3)
+    print(f"windowed tiles only: window={window} {cfg}", flush=True)
+    inp = synth.make_inputs(cfg)
+    lse = np.random.default_rng(window).normal(5.0, 0.5, (cfg.B, cfg.L, cfg.Hq, cfg.P)).astype(np.float32)
+    got = _score_lse(cfg, inp, lse, window, path=ip.CCD_PATH_MFMA_UNIT)
+    ref = O.compress(inp["Q_cat"], inp["K"], inp["V"], inp["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, lse=lse, window=window)
+    gu.assert_scores_close(got, ref["scores"], cfg.G * cfg.P)
+
+
 def test_score_lse_on_the_vector_alu_path_for_bf16():
     cfg = _cfg(P=17, N=400, k=150)
     inp = synth.make_inputs(cfg)
