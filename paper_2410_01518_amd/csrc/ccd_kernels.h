@@ -51,7 +51,8 @@ struct ScorePlan {
 // smallest token slice any plan uses: sizes the per-slice statistics
 constexpr int kMinSlice = 256;
 
-ScorePlan plan_score(const Dims& D, bool cap_keys);
+// The plan of a call: cap_keys: the CaP tokens' own keys join the softmax; lse_given: no statistics pass
+ScorePlan plan_score(const Dims& D, bool cap_keys, bool lse_given);
 
 // pass 1: per (unit, slice, query) running maximum and sum of exp2 of the log2-domain logits
 void launch_stats_valu(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, float2* part, hipStream_t s);
@@ -92,6 +93,9 @@ void launch_head_prob_mfma(const Dims& D, const ScorePlan& pl, const void* Q, co
 // fp32 caches: the two passes on the matrix cores to fp32 accuracy (any head dimension, window and CaP keys; launch_merge in
 // between).  plan_split chooses the token slices, K_cap as in launch_cap_block_stats_valu (pl.cap_block must be 1 with it).
 void plan_split(const Dims& D, int compute_units, int min_slice, ScorePlan& pl);
+// What the passes of such a plan take, in units of 10 ns: rounds of the grid, times what a workgroup spends per sweep of query rows and on
+// its tokens.  It is compared with the same of other kernels (plan_score); the constants were fitted to measured calls.
+int64_t time_split(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given);
 void launch_stats_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
                         hipStream_t s);
 void launch_prob_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const float* lse2, float* u,
@@ -101,6 +105,7 @@ void launch_prob_split(const Dims& D, const ScorePlan& pl, const void* Q, const 
 // pl.cap_block must be 1 with K_cap).  plan_direct chooses the slices; pass 2 merges the statistics itself.  lse_io: the caller's
 // normalisers when pl.lse_given (read only), else where fp32 calls put those in log2 units.
 void plan_direct(const Dims& D, int compute_units, ScorePlan& pl);
+int64_t time_direct(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given);   // as time_split
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
                          hipStream_t s);
 void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,

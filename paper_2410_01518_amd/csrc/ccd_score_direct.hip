@@ -22,6 +22,7 @@
 // 6.5 us.  fp32, append + distill: 4 units of 820 tokens, 100 rows, 64 / 128 elements 39 / 51 -> 28 / 33 us.  (Steps of one tile per wave
 // with the next ones under way, so that pass 1 can have 256 rows to a workgroup: 2 to 3 us slower on small calls, no faster on
 // longer ones.)  Which calls come here: direct_pays and plan_score in infinipot_api.hip.
+#include <algorithm>
 #include <type_traits>
 
 #include "ccd_fp32.h"
@@ -352,6 +353,13 @@ unsigned direct_grid(const Dims& D, int slices, int per_item) {
   return (unsigned)(((int64_t)D.units_run * slices + 7) / 8 * 8 * per_item);
 }
 
+struct DirectCut { int row_blocks, batch1, batch2; };       // blocks of query rows; tokens per batch of tiles in either pass
+DirectCut direct_cut(const Dims& D) {
+  const int rows = D.dtype == 0 ? 32 : 64, tiles = D.dtype == 0 && D.d == 128 ? 1 : 2;      // per wave: DirectShape
+  const int row_blocks = (D.GP + rows - 1) / rows, groups = row_blocks <= 1 ? 4 : (row_blocks <= 2 ? 2 : 1);
+  return {row_blocks, 4 * tiles * kStep, groups * tiles * kStep};
+}
+
 }  // namespace
 
 // Slices: two workgroups fit a compute unit, so the rounds of the grid times what one takes - its batches of tiles, and as much as
@@ -359,8 +367,7 @@ unsigned direct_grid(const Dims& D, int slices, int per_item) {
 // (Powers of two with at least 1.25 workgroups per compute unit, before: 45 units of 3001 tokens were 540 workgroups on 512 places,
 // two rounds, step by step 52.7 -> 48.3 us; 120 units of 2500 tokens and 256 rows 152 -> 138 us for append + distill.)
 void plan_direct(const Dims& D, int compute_units, ScorePlan& pl) {
-  const int rows = D.dtype == 0 ? 32 : 64, tiles = D.dtype == 0 && D.d == 128 ? 1 : 2;      // per wave: DirectShape
-  const int row_blocks = (D.GP + rows - 1) / rows, groups = row_blocks <= 1 ? 4 : (row_blocks <= 2 ? 2 : 1);
+  const DirectCut g = direct_cut(D);
   auto best_slice = [&](int batch, int least, int most, int per_slice) {
     int best = least;
     int64_t best_cost = INT64_MAX;
@@ -373,11 +380,27 @@ void plan_direct(const Dims& D, int compute_units, ScorePlan& pl) {
     }
     return best;
   };
-  pl.slice1 = best_slice(4 * tiles * kStep, kMinSlice, kDirectMaxSlice1, row_blocks);
-  pl.slice2 = best_slice(groups * tiles * kStep, groups * tiles * kStep, kDirectMaxSlice2, 1);
+  pl.slice1 = best_slice(g.batch1, kMinSlice, kDirectMaxSlice1, g.row_blocks);
+  pl.slice2 = best_slice(g.batch2, g.batch2, kDirectMaxSlice2, 1);
   pl.n_slices1 = (D.n + pl.slice1 - 1) / pl.slice1;
   pl.n_slices2 = (D.n + pl.slice2 - 1) / pl.slice2;
   pl.direct_kernel = 1;
+}
+
+int64_t time_direct(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given) {
+  struct Pass { int start, batch; };               // two workgroups per compute unit start together and then share it
+  struct Cost { Pass stats, prob; };
+  static constexpr Cost c16[2] = {{{127, 54}, {310, 71}}, {{294, 74}, {362, 79}}};          // bf16; 64, 128 elements
+  static constexpr Cost c32[2] = {{{124, 137}, {403, 163}}, {{246, 137}, {665, 167}}};      // fp32
+  const Cost& c = (D.dtype == 0 ? c32 : c16)[D.d == 128];
+  const DirectCut g = direct_cut(D);
+  auto pass = [&](const Pass& p, int64_t workgroups, int slice, int batch) {
+    auto rounds = [&](int64_t places) { return (workgroups + places - 1) / places; };
+    return rounds(2 * compute_units) * p.start + rounds(compute_units) * p.batch * ((std::min(slice, D.n) + batch - 1) / batch);
+  };
+  const int64_t prob = (g.row_blocks + 3) / 4 * pass(c.prob, (int64_t)D.units_run * pl.n_slices2, pl.slice2, g.batch2);
+  if (lse_given) return prob;
+  return prob + pass(c.stats, (int64_t)D.units_run * (pl.n_slices1 + (cap_keys ? 1 : 0)) * g.row_blocks, pl.slice1, g.batch1);
 }
 
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,

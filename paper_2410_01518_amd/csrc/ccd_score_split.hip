@@ -309,6 +309,23 @@ void plan_split(const Dims& D, int compute_units, int min_slice, ScorePlan& pl) 
   pl.split_kernel = 1;
 }
 
+int64_t time_split(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given) {
+  // per sweep; per stage with up to two, four and eight blocks of query rows side by side; the merge kernel and each of its slices
+  struct Pass { int sweep, stage[3]; };
+  struct Cost { Pass stats, prob; int merge, merge_slice; };
+  static constexpr Cost c64{{281, {54, 87, 128}}, {560, {80, 118, 254}}, 87, 35}, c128{{516, {92, 160, 265}}, {844, {154, 239, 475}}, 40, 35};
+  const Cost& c = D.d == 64 ? c64 : c128;
+  const int sweeps = (D.GP + kSplitRows - 1) / kSplitRows, blocks = (D.GP - (sweeps - 1) * kSplitRows + 31) / 32;
+  const int last = blocks <= 2 ? 0 : (blocks <= 4 ? 1 : 2);
+  const int64_t stages = (std::min(pl.slice1, D.n) + kStage - 1) / kStage;
+  auto pass = [&](const Pass& p, int slices) {
+    const int64_t rounds = ((int64_t)D.units_run * slices + compute_units - 1) / compute_units;
+    return rounds * (sweeps * p.sweep + stages * ((sweeps - 1) * p.stage[2] + p.stage[last]));
+  };
+  const int64_t prob = pass(c.prob, pl.n_slices2);
+  return lse_given ? prob : prob + pass(c.stats, pl.n_slices1 + (cap_keys ? 1 : 0)) + c.merge + pl.n_slices1 * c.merge_slice;
+}
+
 void launch_stats_split(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
                         hipStream_t s) {
   const dim3 grid((unsigned)(pl.n_slices1 + (K_cap != nullptr ? 1 : 0)) * D.units_run), block(kSplitThreads);

@@ -121,25 +121,39 @@ static int pick_slice(const Dims& D) {
   return kMinSlice;
 }
 
-// bf16 calls that do not take the unit kernel: do the direct kernels pay, or the slice kernels (whose plan is `pl`)?  The direct
-// ones compute query rows by 64 instead of 256 and start faster, the slice kernels keep the matrix cores busier once they run.
-// Append + distill, slice kernels against direct (128 elements):
-//   up to 192 of every 256 rows in use: 24 / 64 / 150 units of 2500 tokens, 32 rows 49 / 91 / 154 against 42 / 72 / 129 us; 100 rows
-//   50 / 93 / 157 against 46 / 77 / 145 us; 24 units of 30000 tokens 321 (32 rows) and 325 (100 rows) against 273 and 299 us
-//   256 rows, few blocks of 64 tokens and rows (8 units of 2048 tokens are 1024): 39.7 against 30.7 us; 8 units of 32768 tokens
-//   (16384) 163 against 157 us
-//   256 rows, more of them: the slice kernels where their grid fills its rounds of two workgroups per compute unit (128 units of 4096
-//   tokens: 208 against 231 us), the direct ones where it does not (64 units of 9000 tokens, 576 workgroups on 512 places: 275
-//   against 262 us), up to where either takes many rounds (120 units of 9000 tokens: 474 against 505 us)
-static bool direct_pays(const Dims& D, const ScorePlan& pl) {
-  const int64_t rows = (D.GP + 63) / 64, rows_slices = (D.GP + 255) / 256 * 4;
-  if (4 * rows <= 3 * rows_slices) return true;
-  const int64_t blocks = (int64_t)D.units_run * ((D.n + 63) / 64) * rows, slots = score_slots();
-  const int64_t wgs = (int64_t)(D.units_run + 7) / 8 * 8 * pl.n_slices1, room = (wgs + slots - 1) / slots * slots * pl.slice1;
-  return blocks <= 16384 || (blocks <= 40000 && 100 * (int64_t)D.units_run * D.n < 85 * room);
+// What the two passes of the bf16 slice kernels take, in units of 10 ns (as time_direct, with which it is compared): per round of two
+// workgroups per compute unit and sweep of 256 query rows, which then share the unit for their tiles of 32 tokens; pass 2 merges the
+// statistics of all slices and computes with the CaP keys in every workgroup; a window takes two kernels more.
+static int64_t time_mfma(const Dims& D, const ScorePlan& pl, bool cap_keys, bool lse_given) {
+  struct Pass { int start, tile; };
+  struct Cost { Pass stats, prob; int merge_slice, cap_token, head; };
+  static constexpr Cost c64{{260, 13}, {310, 18}, 7, 4, 475}, c128{{480, 13}, {420, 17}, 14, 4, 515};
+  const Cost& c = D.d == 64 ? c64 : c128;
+  const int64_t wgs = (int64_t)(D.units_run + 7) / 8 * 8 * pl.n_slices1, cus = compute_units();
+  const int64_t rounds = (wgs + 2 * cus - 1) / (2 * cus), shares = rounds + (wgs + cus - 1) / cus;
+  const int64_t sweeps = (D.GP + 255) / 256, tiles = ((pl.slice1 < D.n ? pl.slice1 : D.n) + 31) / 32;
+  int64_t t = rounds * (c.prob.start + (cap_keys ? D.P * c.cap_token : 0)) + shares * tiles * c.prob.tile;
+  if (!lse_given) t += rounds * (c.stats.start + pl.n_slices1 * c.merge_slice) + shares * tiles * c.stats.tile;
+  return sweeps * t + (D.head > 0 ? (lse_given ? 1 : 2) * c.head : 0);
 }
 
-static ScorePlan plan_mfma(const Dims& D) {
+// Calls that do not take the unit kernel: do the direct kernels pay against those that cut by longer slices, which take `other`?  They
+// compute query rows by 64 (fp32: 32) instead of 256 and start faster; the others keep the matrix cores busier once their grid
+// fills its rounds, and split an fp32 key once for 256 rows.  Both sides were timed on 11000 calls, 1 to 400 units, 256 to 32768 tokens, 4
+// to 1600 rows, both types and head dimensions, with every option.  A 25th less is asked for: of those that then go to the direct kernels, 1 in
+// 150 is more than 1.5 % slower with them (append + distill; 8 % at most), of those that do not, 1 in 9 would have been that much faster (14 %
+// at most).  Append + distill, others against direct, us:
+//   bf16, 128 elements, 256 rows   8 units of 2048 tokens 39.7 / 30.7, of 32768 135 / 131; 16 / 64 / 128 units of 16384 / 4096 / 2048 tokens,
+//                                  grids of whole rounds, 132 / 113 / 110 against 137 / 122 / 118; 64 units of 2560 tokens, a fifth beyond one
+//                                  round, 103 / 89; the same with given normalisers, of 1024 / 2560 tokens 36.5 / 71.0 against 40.5 / 68.6
+//   bf16, 64 elements, 132 rows    82 units of 31297 tokens, given normalisers 418 / 446
+//   fp32, 128 elements             4 units of 820 tokens, 100 rows 51 / 33; 256 units of 4000, 16 rows 755 / 726; 48 units of 1024, 160 rows 13 %
+//                                  slower direct; 4 units of 12000, 160 rows 16 % faster
+static bool direct_pays(const Dims& D, const ScorePlan& direct, int64_t other, bool cap_keys, bool lse_given) {
+  return 26 * time_direct(D, compute_units(), direct, cap_keys, lse_given) < 25 * other;
+}
+
+static ScorePlan plan_mfma(const Dims& D, bool cap_keys, bool lse_given) {
   ScorePlan pl{};
   pl.use_mfma = 1;
   pl.slice1 = pl.slice2 = pick_slice(D);   // multiples of 32, at most mfma_max_slice()
@@ -157,19 +171,22 @@ static ScorePlan plan_mfma(const Dims& D) {
   } else if (D.score_path == CCD_PATH_AUTO && score_unit_supported(D)) {
     pl.unit_kernel = 5 * D.units_run >= 3 * compute_units() ? 1 : 0;
   }
-  if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel && direct_pays(D, pl)) plan_direct(D, compute_units(), pl);
+  if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) {
+    ScorePlan direct = pl;
+    plan_direct(D, compute_units(), direct);
+    if (direct_pays(D, direct, time_mfma(D, pl, cap_keys, lse_given), cap_keys, lse_given)) return direct;
+  }
   return pl;
 }
 
-// cap_keys: the call puts the CaP tokens' own keys into the softmax
-ScorePlan plan_score(const Dims& D, bool cap_keys) {
+ScorePlan plan_score(const Dims& D, bool cap_keys, bool lse_given) {
   ScorePlan pl{};
   pl.use_mfma = (D.dtype == CCD_BF16 && D.score_path != CCD_PATH_VALU) ? 1 : 0;
   // a windowed head longer than the head kernels of the matrix-core paths take (about 2000 CaP tokens under a window):
   // the vector-ALU kernels mask inside their loops and take any, so the automatic choice goes there
   if (pl.use_mfma && D.score_path == CCD_PATH_AUTO && D.head - D.head0 > mfma_max_slice()) pl.use_mfma = 0;
   if (pl.use_mfma) {
-    return plan_mfma(D);
+    return plan_mfma(D, cap_keys, lse_given);
   } else {
     pl.slice1 = kMinSlice;
     pl.slice2 = 256;   // one token per thread
@@ -179,40 +196,33 @@ ScorePlan plan_score(const Dims& D, bool cap_keys) {
   pl.cap_block = 0;
   pl.head_block = 0;
   pl.lse_given = 0;
-  // fp32 caches: the direct kernels for few blocks of 32 tokens and 32 query rows, and for a single block of rows whatever the number of
-  // tokens (the six-product kernels below split a key once for 256 rows where the direct ones do for 32; one block leaves them mostly
-  // empty).  Append + distill, 64 elements and 128, six-product against direct kernels:
-  //   16 rows   4 units of 820 tokens 34 / 42 against 28 / 33 us, 64 of 2500 81 / 124 against 76 / 119 us, 256 of 4000 (128 elements)
-  //             755 against 726 us
-  //   100 rows  4 units of 9000 tokens (4512 blocks) 79 / 98 against 67 / 81 us, 24 of 2500 (7584) 58 / 84 against 53 / 81 us, 120 of 820
-  //             (12480) 67 / 106 against 73 / 114 us
-  //   256 rows  24 units of 820 tokens (4992) 49 / 71 against 44 / 63 us, 120 of 300 (9600) 52 / 82 against 61 / 89 us
-  //   two blocks of rows meet between 13500 and 19000
   // The unit kernel (fp32 values as sums of three bf16 products, logits good to 2^-16 of sum |q k| only; head dimension 64, plain softmax
   // over the cached tokens) when asked for, and by itself from half of the chip's units on: 140 units of 1200 tokens and 16 rows 78 (direct)
   // against 76 us; 127 units and 256 rows, 7000 / 16384 tokens 525 / 1203 (six products) against 452 / 1016 us.  With more
   // than one block of rows from a third on while the rows are short (120 units of 2500 tokens and 100 / 256 rows 145 / 187 against 134 /
   // 170 us; 64 units 92 / 117 against 105 / 140 us).  Long rows stay with six products there: they are the more accurate ones, and the
   // unit kernel is not faster everywhere (81 / 100 units of 7000 tokens and 64 rows 257 / 318 against 276 / 321 us).
+  // Every other fp32 call: six bf16 products (256 units of 4096 tokens, 256 query rows of 128 elements: append + distill 1.16 ms
+  // against 3.61 ms on the vector ALUs, which stay for those who name them), in the direct kernels for a single block of 32 rows, which leaves
+  // the kernels by longer slices mostly empty, and where these do not pay (direct_pays).
   if (D.dtype == CCD_FP32) {
     const int cus = compute_units();
-    const int64_t rows = (D.GP + 31) / 32, blocks = (int64_t)D.units_run * ((D.n + 31) / 32) * rows;
+    const int64_t rows = (D.GP + 31) / 32, sweeps = (D.GP + 255) / 256;
     const bool unit = score_unit_supported(D) && !cap_keys && D.window == 0;
     if (unit && D.score_path == CCD_PATH_MFMA_UNIT) {
       pl.unit_kernel = 1;
     } else if (D.score_path == CCD_PATH_AUTO) {
-      const int64_t sweeps = (D.GP + 255) / 256;
       if (unit && (2 * D.units_run >= cus || (rows > 1 && 16 * D.units_run > 5 * cus && sweeps * D.n <= 6000))) {
         pl.unit_kernel = 1;
-      } else if (rows == 1 || blocks <= (rows == 2 ? 16384 : 8192)) {
-        plan_direct(D, cus, pl);
         return pl;
       }
+      ScorePlan direct = pl;
+      plan_direct(D, cus, direct);
+      if (rows == 1) return direct;
+      plan_split(D, cus, kMinSlice, pl);
+      if (direct_pays(D, direct, time_split(D, cus, pl, cap_keys, lse_given), cap_keys, lse_given)) return direct;
     }
   }
-  // every other fp32 call: sums of six bf16 products, by token slices (256 units of 4096 tokens, 256 query rows of 128
-  // elements: append + distill 1.16 ms against 3.61 ms on the vector ALUs, which stay for those who name them)
-  if (D.dtype == CCD_FP32 && D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) plan_split(D, compute_units(), kMinSlice, pl);
   return pl;
 }
 // a path the caller named that this call cannot take
@@ -230,7 +240,7 @@ static bool path_refused(const Dims& D, const ScorePlan& pl) {
 //   rows 16.9 against 15.9 ms
 //   fp32 (three products for the whole rounds, six for the rest), 16384 tokens and 256 rows, rest of 64 / 80: 2264 / 2324 against 2122 /
 //   2279 us; rest of 100 / 127: 2384 / 2481 against 2437 / 2642 us
-static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_keys) {
+static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_keys, bool lse_given) {
   if (!pl.unit_kernel || D.score_path != CCD_PATH_AUTO) return D.units_run;
   const int cus = compute_units(), rest = D.units_run % cus;
   if (rest == 0 || rest == D.units_run) return D.units_run;
@@ -239,7 +249,7 @@ static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_ke
   const int64_t work = (int64_t)D.n * ((D.GP + 63) / 64) * D.d;
   const bool half = D.dtype == CCD_FP32 && D.GP > 32 ? 16 * rest <= 5 * cus : 2 * rest <= cus;
   const bool pays = 4 * rest <= cus ? work >= 128 * 1000 : (half && work >= 128 * 32768);
-  return pays && !plan_score(R, cap_keys).unit_kernel ? D.units_run - rest : D.units_run;
+  return pays && !plan_score(R, cap_keys, lse_given).unit_kernel ? D.units_run - rest : D.units_run;
 }
 
 struct Workspace {
@@ -312,14 +322,14 @@ static int launch_status() { return hipGetLastError() == hipSuccess ? CCD_OK : C
 // with it K_cap) is not needed, the probabilities follow from one pass over K.
 static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, const void* Q, const void* K,
                            const void* K_cap, const float* lse, char* ws, hipStream_t st) {
-  const int lead = units_in_whole_rounds(D, pl, K_cap != nullptr);
+  const int lead = units_in_whole_rounds(D, pl, K_cap != nullptr, lse != nullptr);
   if (lead < D.units_run) {
     Dims part = D;
     part.units_run = lead;
     run_cap_scores(part, pl, w, Q, K, K_cap, lse, ws, st);
     part.unit0 = D.unit0 + lead;
     part.units_run = D.units_run - lead;
-    ScorePlan rest = plan_score(part, K_cap != nullptr);
+    ScorePlan rest = plan_score(part, K_cap != nullptr, lse != nullptr);
     rest.sync = pl.sync;             // (a partition of few compute units: the rest of a call whose units are shared has words to clear too)
     run_cap_scores(part, rest, w, Q, K, K_cap, lse, ws, st);
     return;
@@ -419,7 +429,7 @@ static int score_impl(const ccd_shape_t* shape, const void* Q_cat, const void* K
   if (novelty == nullptr && shape->T > 0) return CCD_EINVAL;
   if (!aligned16(Q_cat) || !aligned16(K) || !aligned16(K_cap) || !aligned16(lse)) return CCD_EALIGN;
   const Dims D = make_dims(shape);
-  const ScorePlan pl = plan_score(D, K_cap != nullptr);
+  const ScorePlan pl = plan_score(D, K_cap != nullptr, lse != nullptr);
   if (path_refused(D, pl)) return CCD_EUNSUPPORTED;
   if (pl.use_mfma && D.head - D.head0 > mfma_max_slice()) return CCD_EUNSUPPORTED;   // (a matrix-core path was named)
   const Workspace w = layout_workspace(D);
@@ -522,7 +532,7 @@ static int compress_impl(const ccd_shape_t* shape, const void* Q_cat, void* K, v
   if (!aligned16(lse)) return CCD_EALIGN;
   const void* K_attn = K_score != nullptr ? K_score : K;     // the keys the CaP queries attend to
   const Dims D = make_dims(shape);
-  ScorePlan pl = plan_score(D, K_cap != nullptr);
+  ScorePlan pl = plan_score(D, K_cap != nullptr, lse != nullptr);
   if (path_refused(D, pl)) return CCD_EUNSUPPORTED;
   if (pl.use_mfma && D.head - D.head0 > mfma_max_slice()) return CCD_EUNSUPPORTED;   // (a matrix-core path was named)
   const Workspace w = layout_workspace(D);

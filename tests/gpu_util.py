@@ -70,3 +70,16 @@ def replay_select(gpu_scores, k):
     """Oracle selection run on the GPU's own fp32 scores (must equal the GPU's keep_idx bit for bit)."""
     flat = gpu_scores.reshape(-1, gpu_scores.shape[-1])
     return np.stack([O.select(row, k) for row in flat]).reshape(gpu_scores.shape[:-1] + (k,))
+
+
+def stages_run(call):
+    """The library's stages (kernels or groups of them) that `call` ran, by name."""
+    ip.ccd_profile_enable(True)
+    try:
+        ip.ccd_profile_collect()
+        call()
+        torch.cuda.synchronize()
+        ms, _ = ip.ccd_profile_collect()
+    finally:
+        ip.ccd_profile_enable(False)
+    return {name for name, t in ms.items() if t > 0.0}

@@ -73,3 +73,33 @@ def test_windows(units, N, G, P, d, window, kcat):
 @pytest.mark.parametrize("units,N,G,P,d,window", [(3, 257, 1, 65, 128, 0), (7, 500, 4, 60, 64, 0), (4, 333, 2, 64, 128, 200)])
 def test_given_normalisers(units, N, G, P, d, window):
     _check(_cfg(units, N, G, P, d), window=window, lse=True)
+
+
+# Calls on either side of the rule that sends them to the direct kernels.  bf16: the scores of the slice kernels, which can be named,
+# bit for bit or not.  fp32: the six-product kernels by longer slices have a merge kernel, the direct ones have none.
+@pytest.mark.parametrize("units,N,G,P,d,dtype,option,direct", [
+    (8, 2048, 4, 64, 128, "bf16", "", True), (64, 2560, 4, 64, 128, "bf16", "", True), (12, 20000, 4, 25, 128, "bf16", "", True),
+    (64, 2048, 4, 64, 128, "bf16", "", False), (64, 1024, 4, 64, 128, "bf16", "lse", False), (64, 4096, 4, 64, 64, "bf16", "", False),
+    (128, 1024, 3, 44, 128, "bf16", "", False), (110, 1024, 4, 50, 128, "bf16", "kcat", False),
+    (4, 820, 4, 25, 128, "fp32", "", True), (4, 12000, 4, 40, 64, "fp32", "", True), (256, 700, 1, 2, 128, "fp32", "kcat", True),
+    (48, 1024, 4, 40, 128, "fp32", "", False), (120, 256, 4, 50, 128, "fp32", "kcat", False), (87, 376, 4, 42, 64, "fp32", "kcat", False)])
+def test_calls_that_the_direct_kernels_take(units, N, G, P, d, dtype, option, direct):
+    print(f"route {units} {N} {G} {P} {d} {dtype} {option}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(units + N)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K, K_cap = (torch.empty((1, units, h, m, d), dtype=dt, device="cuda").normal_(generator=g) for h, m in ((G, P), (1, N), (1, P)))
+    lse = torch.full((1, units, G, P), 8.0, device="cuda")
+
+    def run(path):
+        shape = ip.make_shape(Q, K, None, k=N, score_path=path)
+        scores, ws = torch.empty((1, units, 1, N), device="cuda"), ip.alloc_workspace(shape)
+        call = {"": lambda: ip.ccd_score(shape, Q, K, None, scores, ws), "lse": lambda: ip.ccd_score_lse(shape, Q, K, lse, None, scores, ws),
+                "kcat": lambda: ip.ccd_score_kcat(shape, Q, K, K_cap, None, scores, ws)}[option]
+        return gu.stages_run(call), scores
+
+    stages, scores = run(ip.CCD_PATH_AUTO)
+    assert "score_prob" in stages and "score_unit" not in stages
+    if dtype == "fp32":
+        assert ("score_merge" in stages) == (not direct)
+    else:
+        assert torch.equal(scores, run(ip.CCD_PATH_MFMA_SLICES)[1]) == (not direct)
