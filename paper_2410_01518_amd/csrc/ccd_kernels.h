@@ -40,7 +40,8 @@ struct ScorePlan {
   int slice2;     // tokens per workgroup in the probability pass
   int n_slices2;
   int cap_block;  // 1 (fp32 caches, vector-ALU path): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
-  int head_block; // 1 (matrix-core path by token slices): `part` also holds the statistics of the windowed head (sliding window)
+  int head_block; // 1 (bf16 slice kernels; unit kernel with head_apart): `part` also holds the statistics of the windowed head (sliding window)
+  int head_apart; // 1 (unit kernel): the windowed head is left to launch_head_stats_mfma and launch_head_prob_mfma
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass
   uint32_t* sync;   // kSyncWords words per unit that the first score kernel of a call clears (null: none)
   int unit_kernel;  // 1 (matrix-core path): both passes in one kernel, one workgroup per unit (launch_score_unit)
@@ -77,11 +78,12 @@ void launch_stats_mfma(const Dims& D, const ScorePlan& pl, const void* Q, const 
 void launch_prob_mfma(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
                       const float2* part, float* u, float* lse_io, hipStream_t s);
 // Both passes in one kernel, one workgroup per unit (bf16, any shape; it pays when the units fill the chip round by
-// round).  K_cap as in launch_prob_mfma; a windowed head is masked inside; lse: the caller's normalisers when pl.lse_given.
+// round).  Same roles of K_cap and lse_io as in launch_prob_mfma; a windowed head is masked inside, or with pl.head_apart taken from its
+// entry of `part`, which is not used otherwise.
 bool score_unit_supported(const Dims& D);
-void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float* lse, float* u,
-                       hipStream_t s);
-// Sliding attention window on the path by token slices: the first D.head tokens are hidden from some CaP tokens and are
+void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
+                       const float2* part, float* u, float* lse_io, hipStream_t s);
+// Sliding attention window on the path by token slices, and for the unit kernel with pl.head_apart: the first D.head tokens are hidden from some CaP tokens and are
 // left out of the two passes above.  launch_head_stats_mfma (before pass 2) leaves their (max, sum) statistics per
 // query in the extra entry of `part` (pl.head_block must be 1); launch_head_prob_mfma (after pass 2) writes
 // u[unit, 0 .. D.head) from the final log2-sum-exps.

@@ -259,8 +259,9 @@ __device__ __forceinline__ void load_neg_lse(float (&nl)[16], uint32_t lane_base
 template <int HD, class ET, int NP>
 __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl, const ET* __restrict__ Q,
                                                             const ET* __restrict__ K,
-                                                            float* __restrict__ u, const ET* __restrict__ Kcap,
-                                                            const float* __restrict__ lse_given) {
+                                                            const float2* __restrict__ part, float* __restrict__ u,
+                                                            const ET* __restrict__ Kcap,
+                                                            float* __restrict__ lse_io) {
   constexpr bool F32 = std::is_same<ET, float>::value;
   using SH = UnitShape<HD, F32>;
   constexpr int KF = SH::KF;           // fragments of a K tile / of a block of query rows
@@ -278,8 +279,8 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
   const float c = D.scale_log2;
   // Tokens [D.head, n) are seen by every query row (all of them without a sliding window).  Full 32-token tiles are dealt to the four
   // waves in runs; a ragged last tile goes to the last wave.  The tiles of [D.head0, D.head), hidden from some rows, are
-  // masked and dealt out one by one (as two kernels of their own, one workgroup per unit each, they took 22 us for 256 units).
-  const int tb = D.head;
+  // masked and dealt out one by one, or left to two small kernels (pl.head_apart).
+  const int tb = D.head, head_end = pl.head_apart ? D.head0 : D.head;
   const int n_main = D.n - tb;
   const int full = n_main / kStep;
   const bool ragged = n_main > full * kStep;
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
         });
       }
       if constexpr (!F32) {          // (fp32 caches under a window take other kernels)
-        for (int t = D.head0 + wave * kStep; t < D.head; t += 4 * kStep) {
+        for (int t = D.head0 + wave * kStep; t < head_end; t += 4 * kStep) {
           load_k_tile<HD>(a[0], Ku, t, D.head - 1, col, half);
           q_frags_arrived();
           static_for<0, NP>([&](auto Pc) {
@@ -534,8 +535,13 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       const bool my_row = (int)threadIdx.x < UQ && q < D.GP;     // (threads past the sweep's rows have none)
       float lse = INFINITY;
       if (pl.lse_given) {            // the caller's normalisers (natural log): nothing to merge
-        if (my_row) lse = lse_given[(int64_t)unit * D.GP + q] * 1.44269504088896340736f;
+        if (my_row) lse = lse_io[(int64_t)unit * D.GP + q] * 1.44269504088896340736f;
       } else if (my_row) {
+        if (pl.head_block) {         // statistics of the windowed head, left there by its own kernel
+          const float2 hd = part[extra_block_index(D, pl, unit, q)];
+          const float Mh = fmaxf(cap.x, hd.x);
+          cap = make_float2(Mh, cap.y * fast_exp2(cap.x - Mh) + hd.y * fast_exp2(hd.x - Mh));
+        }
         float M = cap.x;
 #pragma unroll
         for (int w = 0; w < 4; ++w) M = fmaxf(M, sm.stat[w][threadIdx.x].x);
@@ -546,6 +552,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
           z += v.y * fast_exp2(v.x - M);
         }
         lse = M + __log2f(z);
+        if (pl.head_block) lse_io[(int64_t)unit * D.GP + q] = lse;   // for the head's probabilities
       }
       sm.neg_lse[threadIdx.x] = -lse;
       if (D.head > 0) sm.first[threadIdx.x] = D.win_off + q % D.P;
@@ -638,7 +645,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       for (int i = lane; i < n_blk; i += 64) uu[t_blk + i] = (qc == 0) ? ub[i] : uu[t_blk + i] + ub[i];
     }
     if constexpr (!F32) {
-      for (int t = D.head0 + wave * kStep; t < D.head; t += 4 * kStep) {
+      for (int t = D.head0 + wave * kStep; t < head_end; t += 4 * kStep) {
         load_k_tile<HD>(a[0], Ku, t, D.head - 1, col, half);
         q_frags_arrived();           // (with given normalisers a wave without a tile of its own has waited for nothing yet)
         float us[2] = {0.f, 0.f};
@@ -658,7 +665,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
         v += __shfl_xor(v, 32);
         if (half == 0 && t + col < D.head) uu[t + col] = qc == 0 ? v : uu[t + col] + v;
       }
-      if (qc == 0)                   // tokens nobody sees
+      if (qc == 0 && !pl.head_apart) // tokens nobody sees
         for (int t = threadIdx.x; t < D.head0; t += kMT) uu[t] = 0.f;
     }
     __syncthreads();   // the LDS tables are rewritten by the next sweep
@@ -677,19 +684,19 @@ bool score_unit_supported(const Dims& D) { return D.dtype == 1 ? (D.d == 64 || D
 // the kernel for (head dimension, cache type, pairs of query blocks per sweep)
 template <int HD, class ET>
 static void launch_score_unit_as(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
-                                 const float* lse, float* u, hipStream_t s) {
+                                 const float2* part, float* u, float* lse_io, hipStream_t s) {
   dim3 grid((unsigned)D.units_run), block(kMT);
   const ET *q = (const ET*)Q, *k = (const ET*)K, *kc = (const ET*)K_cap;
-  if (D.GP <= 64)       launch((score_unit_kernel<HD, ET, 1>), grid, block, s, D, pl, q, k, u, kc, lse);
-  else if (D.GP <= 128) launch((score_unit_kernel<HD, ET, 2>), grid, block, s, D, pl, q, k, u, kc, lse);
-  else                  launch((score_unit_kernel<HD, ET, 4>), grid, block, s, D, pl, q, k, u, kc, lse);
+  if (D.GP <= 64)       launch((score_unit_kernel<HD, ET, 1>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
+  else if (D.GP <= 128) launch((score_unit_kernel<HD, ET, 2>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
+  else                  launch((score_unit_kernel<HD, ET, 4>), grid, block, s, D, pl, q, k, part, u, kc, lse_io);
 }
 
-void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float* lse, float* u,
-                       hipStream_t s) {
-  if (D.dtype == 0)    launch_score_unit_as<64, float>(D, pl, Q, K, nullptr, lse, u, s);
-  else if (D.d == 64)  launch_score_unit_as<64, uint16_t>(D, pl, Q, K, K_cap, lse, u, s);
-  else                 launch_score_unit_as<128, uint16_t>(D, pl, Q, K, K_cap, lse, u, s);
+void launch_score_unit(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap,
+                       const float2* part, float* u, float* lse_io, hipStream_t s) {
+  if (D.dtype == 0)    launch_score_unit_as<64, float>(D, pl, Q, K, nullptr, part, u, lse_io, s);
+  else if (D.d == 64)  launch_score_unit_as<64, uint16_t>(D, pl, Q, K, K_cap, part, u, lse_io, s);
+  else                 launch_score_unit_as<128, uint16_t>(D, pl, Q, K, K_cap, part, u, lse_io, s);
 }
 
 }  // namespace ccd

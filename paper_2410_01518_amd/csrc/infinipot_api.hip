@@ -153,6 +153,16 @@ static bool direct_pays(const Dims& D, const ScorePlan& direct, int64_t other, b
   return 26 * time_direct(D, compute_units(), direct, cap_keys, lse_given) < 25 * other;
 }
 
+// Does the unit kernel leave a windowed head to the two head kernels?  It deals the head's tiles of 32 tokens to its four waves one by one,
+// masked and not pipelined, once per sweep of 256 query rows; the head kernels run several workgroups per compute unit, but cost two
+// launches and the normalisers' way through memory.  Append + distill of 160 to 512 units, 512 to 4096 tokens, head kernels against masks:
+//   one sweep        up to 128 tokens 1.02 to 1.13 times faster by masks (median 1.05), 160 tokens 0.81 to 1.03, 1900 tokens 0.64 to 1.02
+//   several sweeps   96 and 128 tokens 1.02 to 1.08 (medians), 32 and 64 tokens 0.93 to 1.01, 160 tokens 0.81 to 1.00
+static bool head_apart(const Dims& D) {
+  const int head = D.head - D.head0;
+  return head > 128 || (head > 0 && head <= 64 && D.GP > 256);
+}
+
 static ScorePlan plan_mfma(const Dims& D, bool cap_keys, bool lse_given) {
   ScorePlan pl{};
   pl.use_mfma = 1;
@@ -338,11 +348,24 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
   float* lse2 = reinterpret_cast<float*>(ws + w.off_lse);
   float* u = reinterpret_cast<float*>(ws + w.off_u);
   if (pl.unit_kernel) {
-    // statistics, merge and probabilities of every unit in one kernel
+    // statistics, merge and probabilities of every unit in one kernel; a windowed head inside, or before and behind it by two small kernels
     pl.lse_given = lse != nullptr ? 1 : 0;
+    pl.head_apart = head_apart(D) ? 1 : 0;
+    pl.head_block = pl.head_apart && lse == nullptr ? 1 : 0;
+    float* lse_io = lse != nullptr ? const_cast<float*>(lse) : lse2;   // only read when pl.lse_given
+    if (pl.head_block) {
+      g_prof.begin(kStHead, st);
+      launch_head_stats_mfma(D, pl, Q, K, part, st);
+      g_prof.end(st);
+    }
     g_prof.begin(kStUnit, st);
-    launch_score_unit(D, pl, Q, K, K_cap, lse, u, st);
+    launch_score_unit(D, pl, Q, K, K_cap, part, u, lse_io, st);
     g_prof.end(st);
+    if (pl.head_apart) {
+      g_prof.begin(kStHead, st);
+      launch_head_prob_mfma(D, pl, Q, K, lse_io, u, st);
+      g_prof.end(st);
+    }
     return;
   }
   if (lse != nullptr) {

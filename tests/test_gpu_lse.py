@@ -91,10 +91,10 @@ def test_score_lse_matches_oracle(case, reading, path):
 
 
 # the unit kernel where some or all of its four waves have windowed tiles only: pass 2 is the first to read the query fragments
-@pytest.mark.parametrize("window", [150, 165, 190, 290])
-@pytest.mark.parametrize("d,Hq", [(64, 2), (128, 2), (128, 4)])
+@pytest.mark.parametrize("window", [100, 107, 121, 149])
+@pytest.mark.parametrize("d,Hq", [(64, 2), (128, 2), (128, 4), (128, 8)])
 def test_score_lse_of_waves_that_have_windowed_tiles_only(d, Hq, window):
-    cfg = _cfg(L=3, Hq=Hq, Hkv=2, d=d, N=400, P=150, T=20, w=3)
+    cfg = _cfg(L=3, Hq=Hq, Hkv=2, d=d, N=400, P=100, T=20, w=3)
     print(f"windowed tiles only: window={window} {cfg}", flush=True)
     inp = synth.make_inputs(cfg)
     lse = np.random.default_rng(window).normal(5.0, 0.5, (cfg.B, cfg.L, cfg.Hq, cfg.P)).astype(np.float32)

@@ -66,6 +66,33 @@ def test_scores_under_a_sliding_window(case, with_cap, path):
     gu.assert_scores_close(got, ref["scores"], cfg.G * cfg.P)
 
 
+# The unit kernel: heads of up to 128 tokens under its own masks (with one sweep of 256 query rows, or with several from 65 tokens on), the
+# others by the head kernels, before and behind it.  (P, heads per unit, window of 400 tokens)
+@pytest.mark.parametrize("option", ["", "kcat", "lse"])
+@pytest.mark.parametrize("P,G,window,apart", [
+    (20, 2, 390, False), (64, 4, 400, False), (100, 2, 100, False), (100, 1, 142, False), (100, 4, 121, False),
+    (100, 2, 114, True), (150, 1, 150, True), (130, 3, 260, True), (33, 16, 390, True), (20, 13, 390, True), (210, 2, 400, True)])
+def test_windowed_heads_of_the_unit_kernel(P, G, window, apart, option):
+    cfg = _cfg(Hq=2 * G, N=400, P=P, T=20, w=3)
+    print(f"windowed head P={P} G={G} window={window} {option}", flush=True)
+    inp = synth.make_inputs(cfg)
+    K_cap = synth.cap_keys(cfg) if option == "kcat" else None
+    lse = np.random.default_rng(P).normal(5.0, 0.5, (cfg.B, cfg.L, cfg.Hq, cfg.P)).astype(np.float32) if option == "lse" else None
+    dev = {k: gu.to_dev(v) for k, v in inp.items()}
+    shape = ip.make_shape(dev["Q_cat"], dev["K"], dev["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, window=window, score_path=ip.CCD_PATH_MFMA_UNIT)
+    ws = ip.alloc_workspace(shape)
+    ws.fill_(0xFF)
+    scores = torch.empty((cfg.B, cfg.L, cfg.Hkv, cfg.N), dtype=torch.float32, device="cuda")
+    rest = (dev["novelty"], scores, ws)
+    call = {"": lambda: ip.ccd_score(shape, dev["Q_cat"], dev["K"], *rest),
+            "kcat": lambda: ip.ccd_score_kcat(shape, dev["Q_cat"], dev["K"], gu.to_dev(K_cap), *rest),
+            "lse": lambda: ip.ccd_score_lse(shape, dev["Q_cat"], dev["K"], gu.to_dev(lse), *rest)}[option]
+    stages = gu.stages_run(call)
+    assert "score_unit" in stages and ("window_head" in stages) == apart
+    ref = O.compress(inp["Q_cat"], inp["K"], inp["V"], inp["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, K_cap=K_cap, window=window, lse=lse)
+    gu.assert_scores_close(gu.to_host(scores), ref["scores"], cfg.G * cfg.P)
+
+
 def test_window_on_the_vector_alu_path_for_bf16():
     cfg = _cfg(N=400, k=150, P=17)
     print(f"swa valu {cfg}", flush=True)
