@@ -180,6 +180,15 @@ static ScorePlan plan_mfma(const Dims& D, bool cap_keys, bool lse_given) {
     pl.unit_kernel = 1;
   } else if (D.score_path == CCD_PATH_AUTO && score_unit_supported(D)) {
     pl.unit_kernel = 5 * D.units_run >= 3 * compute_units() ? 1 : 0;
+    // A few units beyond one round that fit one round of the slice kernels: with one slice per unit these are done before a unit
+    // kernel and its rest have started.  Append + distill of 257 to 307 units, unit kernel and rest against slice kernels for all, medians by
+    // up to 64 / 128 / 256 / 512 query rows: up to 256 tokens 0.98 / 1.10 / 1.26 / 1.25 (given normalisers 1.12 / 1.26 / 1.45 / 1.66) times
+    // longer, 257 to 512 tokens 0.80 / 0.90 / 0.96 / 0.88 (0.96 / 1.05 / 1.13 / 1.04).
+    const bool one_round = D.units_run > compute_units() && 5 * D.units_run < 6 * compute_units();
+    if (one_round && (lse_given ? pl.n_slices1 == 1 || (pl.n_slices1 == 2 && D.GP > 64) : pl.n_slices1 == 1 && D.GP > 64)) {
+      pl.unit_kernel = 0;
+      return pl;
+    }
   }
   if (D.score_path == CCD_PATH_AUTO && !pl.unit_kernel) {
     ScorePlan direct = pl;

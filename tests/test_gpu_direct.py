@@ -81,6 +81,7 @@ def test_given_normalisers(units, N, G, P, d, window):
     (8, 2048, 4, 64, 128, "bf16", "", True), (64, 2560, 4, 64, 128, "bf16", "", True), (12, 20000, 4, 25, 128, "bf16", "", True),
     (64, 2048, 4, 64, 128, "bf16", "", False), (64, 1024, 4, 64, 128, "bf16", "lse", False), (64, 4096, 4, 64, 64, "bf16", "", False),
     (128, 1024, 3, 44, 128, "bf16", "", False), (110, 1024, 4, 50, 128, "bf16", "kcat", False),
+    (280, 250, 4, 64, 128, "bf16", "", False), (264, 256, 1, 80, 64, "bf16", "kcat", False), (300, 500, 2, 64, 128, "bf16", "lse", False),
     (4, 820, 4, 25, 128, "fp32", "", True), (4, 12000, 4, 40, 64, "fp32", "", True), (256, 700, 1, 2, 128, "fp32", "kcat", True),
     (48, 1024, 4, 40, 128, "fp32", "", False), (120, 256, 4, 50, 128, "fp32", "kcat", False), (87, 376, 4, 42, 64, "fp32", "kcat", False)])
 def test_calls_that_the_direct_kernels_take(units, N, G, P, d, dtype, option, direct):
