@@ -36,6 +36,9 @@ def test_rest_of_a_round_matches_oracle(option):
         rc = ip.ccd_compress(shape, dev["Q_cat"], dev["K"], dev["V"], dev["novelty"], keep, ws, scores=scores)
     assert rc == ip.CCD_OK
     torch.cuda.synchronize()
+    alone = ip.make_shape(dev["Q_cat"], dev["K"], dev["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, window=window)
+    ran = gu.stages_run(lambda: ip.ccd_score(alone, dev["Q_cat"], dev["K"], dev["novelty"], torch.empty_like(scores), ws))
+    assert {"score_unit", "score_prob"} <= ran                    # (1030 * 128 is just above what a rest has to be worth: 128000)
     ref = O.compress(inp["Q_cat"], inp["K"], inp["V"], inp["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, K_cap=K_cap, window=window,
                      lse=lse)
     got, kh = gu.to_host(scores), gu.to_host(keep)
@@ -45,23 +48,36 @@ def test_rest_of_a_round_matches_oracle(option):
     np.testing.assert_array_equal(gu.to_host(dev["K"])[..., :cfg.k, :], want)
 
 
-# rests up to half of the chip when a unit is long work: against the unit kernel for all units.  Two orders of fp32 sums of fp32
-# exponentials: 2e-7 to 4e-7 apart in the 2-norm, 1.3e-6 at most (four times that is asked for).  fp32: the unit kernel's logits are
-# good to 2^-16 of sum |q k| (1e-5 and 3.4e-5 apart, four times that).
-@pytest.mark.parametrize("units,N,GP,d,dtype,rel,most", [
-    (384, 4100, 1024, 64, torch.bfloat16, 1.6e-6, 1e-5), (320, 1100, 256, 128, torch.bfloat16, 1.6e-6, 1e-5),
-    (264, 2100, 16, 64, torch.float32, 4e-5, 1.4e-4)])
-def test_rest_of_a_round_against_the_unit_kernel(units, N, GP, d, dtype, rel, most):
-    print(f"rounds {units} {N} {GP} {d}", flush=True)
+# Rests up to half of the chip when a unit is long work, by each of the kernels that take one: against the unit kernel for all units.
+# Two orders of fp32 sums of fp32 exponentials: 2e-7 to 4e-7 apart in the 2-norm, 1.3e-6 at most (four times that is asked for).  fp32:
+# the unit kernel's logits are good to 2^-16 of sum |q k| (1e-5 and 3.4e-5 apart, four times that).  The stages tell the kernels: a rest
+# under a window by slice kernels has head kernels (the unit kernel masks a head of 64 tokens itself), an fp32 rest by longer slices
+# without given normalisers a merge.
+@pytest.mark.parametrize("units,N,G,P,d,dtype,option,window,stage,rel,most", [
+    (384, 4100, 1, 1024, 64, torch.bfloat16, "", 0, None, 1.6e-6, 1e-5), (320, 1100, 1, 256, 128, torch.bfloat16, "", 0, None, 1.6e-6, 1e-5),
+    (320, 1100, 4, 64, 128, torch.bfloat16, "kcat", 0, None, 1.6e-6, 1e-5), (320, 2048, 4, 64, 128, torch.bfloat16, "lse", 0, None, 1.6e-6, 1e-5),
+    (320, 8192, 4, 64, 128, torch.bfloat16, "kcat", 8100, "window_head", 1.6e-6, 1e-5),
+    (320, 8192, 4, 64, 128, torch.bfloat16, "lse", 8192, "window_head", 1.6e-6, 1e-5),
+    (320, 8192, 4, 64, 128, torch.bfloat16, "", 8192, "window_head", 1.6e-6, 1e-5),
+    (264, 2100, 1, 16, 64, torch.float32, "", 0, None, 4e-5, 1.4e-4), (300, 2500, 4, 64, 64, torch.float32, "", 0, "score_merge", 4e-5, 1.4e-4),
+    (300, 2500, 4, 64, 64, torch.float32, "lse", 0, None, 4e-5, 1.4e-4)])
+def test_rest_of_a_round_against_the_unit_kernel(units, N, G, P, d, dtype, option, window, stage, rel, most):
+    print(f"rounds {units} {N} {G} {P} {d} {option} {window}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(units)
-    K = torch.empty((1, units, 1, N, d), dtype=dtype, device="cuda").normal_(generator=g)
-    Q = torch.empty((1, units, 1, GP, d), dtype=dtype, device="cuda").normal_(generator=g)
+    K, Q, K_cap = (torch.empty((1, units, h, m, d), dtype=dtype, device="cuda").normal_(generator=g) for h, m in ((1, N), (G, P), (1, P)))
+    lse = torch.full((1, units, G, P), 8.0, device="cuda")
     out = []
     for path in (ip.CCD_PATH_AUTO, ip.CCD_PATH_MFMA_UNIT):
-        shape = ip.make_shape(Q, K, None, k=N // 2, score_path=path)
-        scores = torch.empty((1, units, 1, N), dtype=torch.float32, device="cuda")
-        assert ip.ccd_score(shape, Q, K, None, scores, ip.alloc_workspace(shape)) == ip.CCD_OK
+        shape = ip.make_shape(Q, K, None, k=N // 2, window=window, score_path=path)
+        scores, ws = torch.empty((1, units, 1, N), dtype=torch.float32, device="cuda"), ip.alloc_workspace(shape)
+        call = {"": lambda: ip.ccd_score(shape, Q, K, None, scores, ws), "lse": lambda: ip.ccd_score_lse(shape, Q, K, lse, None, scores, ws),
+                "kcat": lambda: ip.ccd_score_kcat(shape, Q, K, K_cap, None, scores, ws)}[option]
+        stages = gu.stages_run(call)
+        assert "score_unit" in stages and ("score_prob" in stages) == (path == ip.CCD_PATH_AUTO)
+        assert ("window_head" in stages, "score_merge" in stages) == ((stage == "window_head", stage == "score_merge") if path == ip.CCD_PATH_AUTO else (False, False))
         out.append(scores.double())
     torch.cuda.synchronize()
     a, b = out
-    assert float((a - b).norm() / b.norm()) < rel and float(((a - b).abs() / b).max()) < most
+    seen = b > 0.0
+    assert torch.equal(a > 0.0, seen)
+    assert float((a - b).norm() / b.norm()) < rel and float(((a - b).abs()[seen] / b[seen]).max()) < most

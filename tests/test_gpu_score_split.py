@@ -1,5 +1,5 @@
-"""fp32 caches scored as sums of six bf16 products (token slices): the edges of its stages, slices, row blocks and sweeps under
-every option, against the oracle and to fp32 accuracy."""
+"""fp32 caches scored as sums of six bf16 products under every option, against the oracle and to fp32 accuracy: the automatic choice,
+which sends most of these calls to the direct kernels (those that stay with longer slices: test_gpu_score_split_large)."""
 import math
 
 import numpy as np
@@ -12,9 +12,8 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-# (units, G, P, n, d, options).  Row blocks of 32 query rows: one, two, three, four, five to eight, a second sweep of 256;
-# stages of 64 tokens: one row, just around a tile and a stage, several slices of 256; 260 units: one slice of eleven stages.
-# (Head dimension 64 takes this path with CaP keys, a window or few long rows only.)
+# (units, G, P, n, d, options).  Row blocks of 32 query rows: one, two, three, four, five to eight, more than 256 rows; one
+# token, just around a tile of 32 and a stage of 64, several slices of 256; 260 units: more than places on the chip.
 CASES = [
     (1, 1, 1, 1, 128, ""), (2, 1, 5, 31, 128, ""), (2, 1, 32, 33, 128, "lse"), (1, 1, 33, 64, 128, "kcat"),
     (2, 2, 40, 65, 128, "kcat"), (1, 3, 32, 255, 128, "window"), (1, 4, 32, 257, 128, "kcat window"),
