@@ -39,7 +39,7 @@ struct ScorePlan {
   int n_slices1;
   int slice2;     // tokens per workgroup in the probability pass
   int n_slices2;
-  int cap_block;  // 1 (fp32 caches, vector-ALU path): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
+  int cap_block;  // 1 (vector ALUs, six-product and direct kernels): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
   int head_block; // 1 (bf16 slice kernels; unit kernel with head_apart): `part` also holds the statistics of the windowed head (sliding window)
   int head_apart; // 1 (unit kernel): the windowed head is left to launch_head_stats_mfma and launch_head_prob_mfma
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass

@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
     // ---------------- merge: one log2-sum-exp per query row (thread = row of the sweep) ----------------
     {
       float2 cap = make_float2(kNegHuge, 0.f);     // the block of the CaP keys (causal variant), else nothing
-      if constexpr (!F32) {          // (fp32 caches with CaP keys take the vector-ALU kernels: the host sees to that)
+      if constexpr (!F32) {          // (fp32 caches with CaP keys take the six-product kernels: the host sees to that)
         if (Kcap != nullptr && wave < NP) {
           const uint16_t* Kc = Kcap + (int64_t)unit * D.P * HD;
           // the thread's own query row is one of the 2 x 32 rows of block pair `wave`: their fragments once more, in

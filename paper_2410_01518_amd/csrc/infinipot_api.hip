@@ -201,8 +201,9 @@ static ScorePlan plan_mfma(const Dims& D, bool cap_keys, bool lse_given) {
 ScorePlan plan_score(const Dims& D, bool cap_keys, bool lse_given) {
   ScorePlan pl{};
   pl.use_mfma = (D.dtype == CCD_BF16 && D.score_path != CCD_PATH_VALU) ? 1 : 0;
-  // a windowed head longer than the head kernels of the matrix-core paths take (about 2000 CaP tokens under a window):
-  // the vector-ALU kernels mask inside their loops and take any, so the automatic choice goes there
+  // a windowed head longer than the head kernels take (about 2000 CaP tokens under a window), which the slice kernels need for any
+  // head and the unit kernel for long ones: the vector-ALU kernels mask inside their loops, so the automatic choice goes there (also
+  // the few units that the direct kernels, which mask a head of any length, could have)
   if (pl.use_mfma && D.score_path == CCD_PATH_AUTO && D.head - D.head0 > mfma_max_slice()) pl.use_mfma = 0;
   if (pl.use_mfma) {
     return plan_mfma(D, cap_keys, lse_given);
@@ -335,8 +336,8 @@ static Profiler g_prof;
 static int launch_status() { return hipGetLastError() == hipSuccess ? CCD_OK : CCD_ELAUNCH; }
 
 // Raw CaP score u[unit, t] (Eq. 2, before pooling).  With K_cap the CaP tokens' own keys join the softmax (causally): their
-// statistics become one more entry per unit of `part` on the vector-ALU path (the matrix-core pass 2 computes them
-// itself).  (The NuC slots, Sec. 3.3.3 step 1, are found by the selection kernels from the novelty row.)
+// statistics become one more entry per unit of `part` (vector ALUs, six-product and direct kernels; the bf16 slice and unit kernels
+// compute them in pass 2).  (The NuC slots, Sec. 3.3.3 step 1, are found by the selection kernels from the novelty row.)
 // lse (nullable): the caller's natural-log-sum-exp of every CaP query row [units, G*P]: the statistics pass (and
 // with it K_cap) is not needed, the probabilities follow from one pass over K.
 static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, const void* Q, const void* K,
