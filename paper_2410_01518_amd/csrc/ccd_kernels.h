@@ -33,6 +33,7 @@ struct Dims {
 constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgroups / 2;
 constexpr int kSyncTicket = 0, kSyncSelected = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16;
 
+// (an argument of every score kernel: 8 bytes more, for one int that left padding, took 0.1 us a launch)
 struct ScorePlan {
   int use_mfma;   // 1: bf16 matrix-core kernels, 0: vector-ALU kernels
   int slice1;     // tokens per workgroup in the statistics pass
@@ -41,12 +42,12 @@ struct ScorePlan {
   int n_slices2;
   int cap_block;  // 1 (vector ALUs, six-product and direct kernels): `part` also holds the statistics of the CaP keys' block (causal Eq. 2)
   int head_block; // 1 (bf16 slice kernels; unit kernel with head_apart): `part` also holds the statistics of the windowed head (sliding window)
-  int head_apart; // 1 (unit kernel): the windowed head is left to launch_head_stats_mfma and launch_head_prob_mfma
   int lse_given;  // 1: the caller handed in the natural-log-sum-exp of every query row: no statistics pass
   uint32_t* sync;   // kSyncWords words per unit that the first score kernel of a call clears (null: none)
   int unit_kernel;  // 1 (matrix-core path): both passes in one kernel, one workgroup per unit (launch_score_unit)
   int direct_kernel;  // 1 (calls that do not fill the chip): the two passes of launch_stats_direct, launch_prob_direct
   int split_kernel; // 1 (fp32 caches): the two passes as sums of bf16 products (launch_stats_split, launch_prob_split)
+  int head_apart; // 1 (unit kernel): the windowed head is left to launch_head_stats_mfma and launch_head_prob_mfma
 };
 
 // smallest token slice any plan uses: sizes the per-slice statistics
