@@ -38,11 +38,14 @@ constexpr int kCpUnroll = 4;
 
 // Appending a chunk of new context behind the cached tokens (Sec. 3.2: the pot is filled until it is full): rows
 // [n, n + count) of every unit of K and V take the chunk's rows, dense [units, count, d] on the source side.  A unit's
-// share is one contiguous run on both sides; the grid is (unit, tensor, segment of 16 KiB), 16 bytes per lane and
+// share is one contiguous run on both sides; the grid is (tensor, unit, segment of 16 KiB), 16 bytes per lane and
 // four loads in flight (a store waits for all of them, and for the store before it).  Bound by HBM (256 units, 2048 tokens: 537 MB
 // in 84 us) or, for a few units, by how many compute
 // units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  (Where chunk and pot stay in
 // the memory-side cache from one call to the next, 130 to 270 MB in all, those of 64 KiB were 4 to 11 % faster.)
+// The values of all units go first and the keys last: the score pass that comes next reads the keys, and finds twice as many of them in the
+// memory-side cache as with keys and values in turn (append + distill, 256 units of 4096 tokens, the score kernel after the append and the
+// rest the same: given normalisers 337 -> 329 us, window and CaP keys 404 -> 389 us; 640 units 922 -> 911 us; 64 units 94.1 -> 94.0 us).
 // Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
 // keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
 constexpr int kApThreads = 256;
@@ -52,10 +55,11 @@ constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgro
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
                                                                  const float* nov_new, int nov_per_head) {
-  const int seg = blockIdx.x % segs;
-  const int ut = blockIdx.x / segs;
-  const int unit = D.unit0 + (ut >> 1);
-  const bool isV = ut & 1;
+  const int per_tensor = D.units_run * segs;
+  const bool isV = (int)blockIdx.x < per_tensor;
+  const int us = isV ? (int)blockIdx.x : (int)blockIdx.x - per_tensor;
+  const int seg = us % segs;
+  const int unit = D.unit0 + us / segs;
   const UnitIdx ui = decode_unit(D, unit);
   const int64_t run = (int64_t)count * D.d * esz;                         // bytes of a unit's share
   char* dst = (isV ? V : K) + (kv_offset(D, ui) + (int64_t)D.n * D.d) * esz;
