@@ -10,13 +10,14 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libinfinipot.so")
-SOURCES = ["infinipot_api.hip", "ccd_score_valu.hip", "ccd_score_mfma.hip", "ccd_score_unit.hip", "ccd_score_split.hip", "ccd_score_direct.hip", "ccd_select.hip", "ccd_compact.hip",
+SOURCES = ["infinipot_api.hip", "ccd_score_valu.hip", "ccd_score_mfma.hip", "ccd_score_unit.hip", "ccd_score_unit_1.hip", "ccd_score_unit_2.hip",
+           "ccd_score_unit_4.hip", "ccd_score_split.hip", "ccd_score_direct.hip", "ccd_select.hip", "ccd_compact.hip",
            "ccd_nuc.hip"]
-# ccd_score_unit.hip keeps its query fragments at fixed places in the accumulation registers (named in its inline
+# The unit kernel (ccd_score_unit.h) keeps its query fragments at fixed places in the accumulation registers (named in its inline
 # assembly): the compiler must put nothing of its own there, so matrix-instruction results go to vector registers and
 # the generated code is checked for accumulation registers outside the assembly statements.
-SOURCE_FLAGS = {"ccd_score_unit.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
-ACC_REGISTERS_RESERVED = {"ccd_score_unit.hip"}
+ACC_REGISTERS_RESERVED = {"ccd_score_unit.hip", "ccd_score_unit_1.hip", "ccd_score_unit_2.hip", "ccd_score_unit_4.hip"}
+SOURCE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for src in ACC_REGISTERS_RESERVED}
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]
 
@@ -67,7 +68,7 @@ def _vgprs(token: str) -> set:
 def check_matrix_operand_distance(asm_path: str) -> None:
     """A matrix instruction must not read, as its first or second operand, a vector register that an ALU instruction
     wrote in the two issue slots before it.  The compiler keeps that distance for matrix instructions it generates; the
-    ones in ccd_score_unit.hip are inline assembly, which it schedules around without knowing what they are.  Checked on
+    ones in ccd_score_unit.h are inline assembly, which it schedules around without knowing what they are.  Checked on
     straight-line code (history is dropped at every label)."""
     bad, hist = [], []
     with open(asm_path) as f:

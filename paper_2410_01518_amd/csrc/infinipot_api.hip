@@ -154,10 +154,12 @@ static bool direct_pays(const Dims& D, const ScorePlan& direct, int64_t other, b
 }
 
 // Does the unit kernel leave a windowed head to the two head kernels?  It deals the head's tiles of 32 tokens to its four waves one by one,
-// masked and not pipelined, once per sweep of 256 query rows; the head kernels run several workgroups per compute unit, but cost two
+// masked and not pipelined, once per sweep of query rows; the head kernels run several workgroups per compute unit, but cost two
 // launches and the normalisers' way through memory.  Append + distill of 160 to 512 units, 512 to 4096 tokens, head kernels against masks:
 //   one sweep        up to 128 tokens 1.02 to 1.13 times faster by masks (median 1.05), 160 tokens 0.81 to 1.03, 1900 tokens 0.64 to 1.02
-//   several sweeps   96 and 128 tokens 1.02 to 1.08 (medians), 32 and 64 tokens 0.93 to 1.01, 160 tokens 0.81 to 1.00
+//   several sweeps   96 and 128 tokens 1.02 to 1.08 (medians), 32 and 64 tokens 0.93 to 1.01, 160 tokens 0.81 to 1.00 (sweeps of 256 rows; with
+//                    320 to 1024 rows in one sweep the masks are 1.03 to 1.16 times faster for 32 and 64 tokens as well: 512 rows, 4096 / 600
+//                    tokens 524 / 131 against 503 / 114 us.  The line has stayed where it was.)
 static bool head_apart(const Dims& D) {
   const int head = D.head - D.head0;
   return head > 128 || (head > 0 && head <= 64 && D.GP > 256);
