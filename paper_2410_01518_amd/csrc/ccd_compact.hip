@@ -43,23 +43,25 @@ constexpr int kCpUnroll = 4;
 // in 84 us) or, for a few units, by how many compute
 // units take part: segments of 64 KiB gave 85 us, and 8.8 instead of 5.4 us for 8 units of 2048 tokens.  (Where chunk and pot stay in
 // the memory-side cache from one call to the next, 130 to 270 MB in all, those of 64 KiB were 4 to 11 % faster.)
-// The values of all units go first and the keys last: the score pass that comes next reads the keys, and finds twice as many of them in the
-// memory-side cache as with keys and values in turn (append + distill, 256 units of 4096 tokens, the score kernel after the append and the
-// rest the same: given normalisers 337 -> 329 us, window and CaP keys 404 -> 389 us; 640 units 922 -> 911 us; 64 units 94.1 -> 94.0 us).
+// values_first: the values of all units and then the keys, when chunk and pot together are more than the memory-side cache holds: the score
+// pass that comes next reads the keys, and finds twice as many of them there as with keys and values in turn (append + distill, 256 units of
+// 4096 tokens: given normalisers 337 -> 329 us, window and CaP keys 404 -> 389 us; 640 units 922 -> 911 us; 48 units of 13504 tokens 256 -> 239 us).
+// Where it holds all of them, keys last is slower: they are what is left to write back when the kernel ends (33 units of 1376 tokens 37.2 ->
+// 37.8 us, 8 of 7232 tokens 57.4 -> 58.1 us).
 // Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
 // keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
 constexpr int kApNovelty = 1024;       // a multiple of the tokens of a segment (32, 64 or 128)
+constexpr int64_t kMemorySideCache = 256 << 20;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
-                                                                 const float* nov_new, int nov_per_head) {
-  const int per_tensor = D.units_run * segs;
-  const bool isV = (int)blockIdx.x < per_tensor;
-  const int us = isV ? (int)blockIdx.x : (int)blockIdx.x - per_tensor;
-  const int seg = us % segs;
-  const int unit = D.unit0 + us / segs;
+                                                                 const float* nov_new, int nov_per_head, int values_first) {
+  const int seg = blockIdx.x % segs;
+  const int ut = blockIdx.x / segs;
+  const bool isV = values_first ? ut < D.units_run : ut & 1;
+  const int unit = D.unit0 + (values_first ? (isV ? ut : ut - D.units_run) : ut >> 1);
   const UnitIdx ui = decode_unit(D, unit);
   const int64_t run = (int64_t)count * D.d * esz;                         // bytes of a unit's share
   char* dst = (isV ? V : K) + (kv_offset(D, ui) + (int64_t)D.n * D.d) * esz;
@@ -506,12 +508,13 @@ void launch_append(const Dims& D, int count, void* K, void* V, const void* K_new
   const int segs = (int)((run + kApSegBytes - 1) / kApSegBytes);
   // (a grid has fewer than 2^32 threads: millions of units go in several launches)
   const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 31) / ((int64_t)2 * segs * kApThreads));
+  const bool values_first = 4 * D.units * run >= kMemorySideCache;
   Dims R = D;
   for (int64_t u0 = 0; u0 < D.units; u0 += most) {
     R.unit0 = (int)u0;
     R.units_run = (int)std::min<int64_t>(most, D.units - u0);
     launch(append_rows_kernel, dim3(2u * R.units_run * segs), dim3(kApThreads), s, R, esz, count, segs, (char*)K, (char*)V,
-           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0);
+           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, values_first ? 1 : 0);
   }
 }
 

@@ -119,3 +119,22 @@ def test_append_to_more_units_than_one_grid_has_threads_for():
     torch.cuda.empty_cache()
     for t in (K, V):
         assert bool((t[0] == 1.0).all()) and bool((t[1] == 2.0).all())
+
+
+# chunk and pot are just less than what the memory-side cache holds, and just as much: keys and values in turn, values first
+@pytest.mark.parametrize("m", [8191, 8192])
+def test_append_of_chunks_as_large_as_the_memory_side_cache(m):
+    B, L, Hkv, d, n_valid = 2, 16, 2, 64, 5
+    print(f"append m={m}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    K_new, V_new = (torch.randint(-32768, 32767, (B, L, Hkv, m, d), generator=g, device="cuda", dtype=torch.int16).view(torch.bfloat16) for _ in range(2))
+    nov_new = torch.rand((B, m), generator=g, device="cuda")
+    K, V = (torch.zeros((B, L, Hkv, m + 9, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    nov = torch.zeros((B, L, Hkv, m + 9), device="cuda")
+    shape = ip.make_shape(None, K, nov, k=1, n_valid=n_valid)
+    assert ip.ccd_append(shape, K, V, nov, K_new, V_new, nov_new) == ip.CCD_OK
+    torch.cuda.synchronize()
+    for have, new in ((K.view(torch.int16), K_new.view(torch.int16)), (V.view(torch.int16), V_new.view(torch.int16)),
+                      (nov[..., None], nov_new[:, None, None, :, None].expand(B, L, Hkv, m, 1))):
+        assert torch.equal(have[..., n_valid:n_valid + m, :], new)
+        assert not bool(have[..., :n_valid, :].any()) and not bool(have[..., n_valid + m:, :].any())
