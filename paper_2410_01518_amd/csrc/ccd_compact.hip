@@ -226,9 +226,12 @@ __global__ __launch_bounds__(kCpThreads) void compact_novelty_kernel(Dims D, con
 // carried novelty, which took a kernel of its own; 8 units, 32768 -> 4096: 113 -> 57 us.
 //
 // Threads: the moving of one workgroup per unit wants 16 waves (512 threads with twice the rows each: 2 - 3 us slower on 256
-// units), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us), except
-// that of a row held in LDS, which has more latency to hide (8 units of 32768 tokens: the call 203 -> 191 us).
-constexpr int sc_threads(bool shared, bool lds_row) { return shared && !lds_row ? 512 : 1024; }
+// units), a selection on a unit's share of the chip is faster with eight (tiny and single-layer calls: 1 - 2 us) as long as the row
+// gives a thread little to do.  SHARED, append + distill with eight against 16 waves: 8 units of 3000 / 4096 tokens 38.2 / 40.5 against 37.6 /
+// 40.9 us, of 4500 / 6000 / 8192 tokens 51.6 / 56.2 / 61.9 against 50.5 / 53.5 / 59.3; 64 of 8000 196 against 194; rows held in LDS 203 against 191.  (16 waves, 9000 / 16384 tokens in LDS against registers: 70.8 / 91.3
+// against 68.9 / 89.1 us; one workgroup per unit the same.)
+constexpr int kFewWavesTokens = 4096;
+constexpr int sc_threads(bool shared, int n) { return shared && n <= kFewWavesTokens ? 512 : 1024; }      // (at most two chunks of tokens per thread)
 // Waves per SIMD to compile for: 64 registers instead of 72 for rows of up to 4096 tokens, so that two workgroups fit a compute unit
 // when there are more units than these: one selects while the other one moves rows, and the last round is not alone (append +
 // distill with given normalisers, 2000 tokens: 400 / 640 units 257 / 438 -> 251 / 427 us, 600 tokens 85 / 129 -> 78 / 121 us; up to 256
@@ -255,8 +258,8 @@ __device__ __forceinline__ uint32_t agent_add(uint32_t* p, uint32_t v) {
 // j < k (rows that stay where they are included, so every kept K row is read); the pot itself keeps the plain keys.
 // ROWB, BF16: row bytes and cache type where ROPE needs them at compile time (ROWB is 0 without: `row_shift` = log2 of the
 // 16-byte lanes of a row).
-template <int CH, int ROWB, bool BF16, bool SHARED>
-__global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHARED, CH, ROWB)) void select_compact_kernel(Dims D, const float* __restrict__ u,
+template <int THREADS, int CH, int ROWB, bool BF16, bool SHARED>
+__global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void select_compact_kernel(Dims D, const float* __restrict__ u,
                                                                      float* novelty, int carry_novelty, float* scores,
                                                                      int32_t* __restrict__ keep_idx, char* Kbuf,
                                                                      char* Vbuf, const float* __restrict__ rope_cos,
@@ -264,7 +267,6 @@ __global__ __launch_bounds__(sc_threads(SHARED, CH == kLdsRow), sc_min_waves(SHA
                                                                      int row_shift, int wgs_per_unit, int chunks,
                                                                      int chunk_rows, uint32_t* sync) {
   constexpr bool ROPE = ROWB > 0;
-  constexpr int THREADS = sc_threads(SHARED, CH == kLdsRow);
   constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
   __shared__ SelectShared<THREADS, CH> sh;
   // The kept list: in LDS for short rows; a long row leaves no room for it, and it is read back from keep_idx, where this
@@ -450,9 +452,9 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   const int row_shift = rowb == 128 ? 3 : (rowb == 256 ? 4 : 5);
   // Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
   // sh_unroll rows per thread; 32 marks per word bound the number of chunks.
-  const bool lds_row = D.n > 16 * sc_threads(true, false);
-  const int rows_per_pass = sc_threads(true, lds_row) >> row_shift;
-  const int max_rows = rows_per_pass * sh_unroll(sc_threads(true, lds_row), Krot != nullptr);
+  const int shared_threads = sc_threads(true, D.n);
+  const int rows_per_pass = shared_threads >> row_shift;
+  const int max_rows = rows_per_pass * sh_unroll(shared_threads, Krot != nullptr);
   int per_unit = std::min(kSharedFillWorkgroups / std::max(D.units_run, 1), (D.k + rows_per_pass - 1) / rows_per_pass);
   int chunk_rows = 0;
   if (per_unit > 1) {
@@ -464,23 +466,24 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   const bool shared = per_unit > 1;
   if (!shared) per_unit = 1;
   const int chunks = shared ? (D.k + chunk_rows - 1) / chunk_rows : 0;
-  const int threads = sc_threads(shared, shared && lds_row);
+  const int threads = sc_threads(shared, D.n);
   const dim3 grid((unsigned)D.units_run * per_unit), block(threads);
-#define CCD_LAUNCH(CH, RB, BF, SHARED)                                                                                  \
-  launch((select_compact_kernel<CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
+#define CCD_LAUNCH(THREADS, CH, RB, BF, SHARED)                                                                                  \
+  launch((select_compact_kernel<THREADS, CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
          keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync)
-#define CCD_LAUNCH_RB(CH, SHARED)                                          \
-  if (Krot == nullptr) CCD_LAUNCH(CH, 0, true, SHARED);                    \
-  else if (rowb == 128) CCD_LAUNCH(CH, 128, true, SHARED);                 \
-  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(CH, 256, true, SHARED); \
-  else if (rowb == 256) CCD_LAUNCH(CH, 256, false, SHARED);                \
-  else CCD_LAUNCH(CH, 512, false, SHARED)
+#define CCD_LAUNCH_RB(THREADS, CH, SHARED)                                          \
+  if (Krot == nullptr) CCD_LAUNCH(THREADS, CH, 0, true, SHARED);                    \
+  else if (rowb == 128) CCD_LAUNCH(THREADS, CH, 128, true, SHARED);                 \
+  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(THREADS, CH, 256, true, SHARED); \
+  else if (rowb == 256) CCD_LAUNCH(THREADS, CH, 256, false, SHARED);                \
+  else CCD_LAUNCH(THREADS, CH, 512, false, SHARED)
 #define CCD_LAUNCH_SHARED(CH) \
-  if (shared) { CCD_LAUNCH_RB(CH, true); } else { CCD_LAUNCH_RB(CH, false); }
-  const int token_chunks = shared && lds_row ? 8 : (D.n + 4 * threads - 1) / (4 * threads);     // per thread
-  if (token_chunks <= 1)      { CCD_LAUNCH_SHARED(1); }
+  if (shared) { CCD_LAUNCH_RB(1024, CH, true); } else { CCD_LAUNCH_RB(1024, CH, false); }
+  const int token_chunks = (D.n + 4 * threads - 1) / (4 * threads);     // per thread
+  if (threads == 512)         { if (token_chunks <= 1) { CCD_LAUNCH_RB(512, 1, true); } else { CCD_LAUNCH_RB(512, 2, true); } }
+  else if (token_chunks <= 1) { CCD_LAUNCH_RB(1024, 1, false); }
   else if (token_chunks <= 2) { CCD_LAUNCH_SHARED(2); }
-  else if (token_chunks <= 4 && shared) { CCD_LAUNCH_RB(4, true); }
+  else if (token_chunks <= 4 && shared) { CCD_LAUNCH_RB(1024, 4, true); }
   else                        { CCD_LAUNCH_SHARED(kLdsRow); }
 #undef CCD_LAUNCH_SHARED
 #undef CCD_LAUNCH_RB

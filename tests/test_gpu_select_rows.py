@@ -127,3 +127,8 @@ def test_pooling_windows_wider_than_a_register_window(n, w):
             want = want / np.float32(w)
         assert np.array_equal(got, want)
         assert np.array_equal(keep, np.stack([O.select(row, keep.shape[1]) for row in got]))
+
+
+@pytest.mark.parametrize("n,rope", [(4096, False), (8192, True), (16384, False), (16385, False)])
+def test_rows_at_the_limits_of_the_kernels_that_share_a_unit(n, rope):
+    test_compress_moves_what_the_scores_say(3, n, n // 3, False, rope, True)
