@@ -42,13 +42,19 @@ __device__ __forceinline__ int64_t q_offset(const Dims& D, UnitIdx u, int q) {
   return u.b * D.q_sb + u.l * D.q_sl + (int64_t)(u.h * D.G + g) * D.q_sh + (int64_t)i * D.d;
 }
 // the first kernel of a call clears the words its last kernel counts in (one workgroup per unit: `first`)
-__device__ __forceinline__ void clear_sync(const ScorePlan& pl, int unit, bool first) {
-  if (pl.sync != nullptr && first && threadIdx.x < kSyncWords) pl.sync[(int64_t)unit * kSyncWords + threadIdx.x] = 0u;
+__device__ __forceinline__ void clear_sync(const Dims& D, const ScorePlan& pl, int unit, bool first) {
+  const int w = threadIdx.x;
+  if (pl.sync != nullptr && first && w < kSyncWords && w != kSyncNovelty && (w != kSyncNoveltyTies || D.k > kNoveltyMaxKept))
+    pl.sync[(int64_t)unit * kSyncWords + w] = 0u;
 }
 // where the one extra (max, sum) entry of (unit, query q) lives in `part`, behind the slices of all units: the block of
 // the CaP keys (vector ALUs, six-product and direct kernels) or the windowed head (bf16 slice kernels)
 __device__ __forceinline__ int64_t extra_block_index(const Dims& D, const ScorePlan& pl, int unit, int q) {
   return ((int64_t)D.units * pl.n_slices1 + unit) * D.GP + q;
+}
+// the unit whose word kSyncNovelty holds for a unit: its own, or the first one of its sequence when all share one novelty row
+__device__ __forceinline__ int novelty_unit(const Dims& D, int unit) {
+  return D.nov_sl != 0 || D.nov_sh != 0 ? unit : unit / (D.L * D.Hkv) * (D.L * D.Hkv);
 }
 __device__ __forceinline__ int64_t nov_offset(const Dims& D, UnitIdx u) {
   return u.b * D.nov_sb + u.l * D.nov_sl + u.h * D.nov_sh;

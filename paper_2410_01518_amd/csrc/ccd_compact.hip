@@ -265,7 +265,7 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
                                                                      char* Vbuf, const float* __restrict__ rope_cos,
                                                                      const float* __restrict__ rope_sin, char* Krot,
                                                                      int row_shift, int wgs_per_unit, int chunks,
-                                                                     int chunk_rows, uint32_t* sync) {
+                                                                     int chunk_rows, uint32_t* sync, int nuc_known) {
   constexpr bool ROPE = ROWB > 0;
   constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
   __shared__ SelectShared<THREADS, CH> sh;
@@ -278,12 +278,13 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
   const int unit = D.unit0 + (SHARED ? blockIdx.x / wgs_per_unit : blockIdx.x);
   const UnitIdx ui = decode_unit(D, unit);
   uint32_t* sy = SHARED ? sync + (int64_t)unit * kSyncWords : nullptr;
-  if (SHARED && threadIdx.x == 0) ticket_lds = agent_add(&sy[kSyncTicket], 1u);
+  if (SHARED && threadIdx.x == 0) ticket_lds = agent_add(&sy[kSyncTicket], 1u) & 0xFFFFu;
   int32_t* keep_out = keep_idx + (int64_t)unit * D.k;
   float* nov = (D.T > 0 || carry_novelty) ? novelty + nov_offset(D, ui) : nullptr;
   {
     Row<THREADS, CH> row(D, sh, unit, u, nullptr, nov);
-    select_row<THREADS, CH, true>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr,
+    const uint32_t* nuc_words = nuc_known ? sync + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
+    select_row<THREADS, CH, true, SHARED>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, nuc_words,
                          [&](int pos, int t, int c, int i) {
                            if (kRegs) keep_lds[pos] = (uint16_t)t;
                            else       keep_out[pos] = t;
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
   constexpr int kUnroll = !SHARED ? sc_unroll(ROPE) : sh_unroll(THREADS, ROPE);
 
   if (SHARED && carry_novelty && threadIdx.x == 0)
-    last_lds = agent_add(&sy[kSyncSelected], 1u) == (uint32_t)(wgs_per_unit - 1);
+    last_lds = agent_add(&sy[kSyncTicket], kSyncOneSelected) >> 16 == (uint32_t)(wgs_per_unit - 1);
   uint32_t ticket = SHARED ? ticket_lds : 0u;
   int base = SHARED ? chunk_first_row(ticket, chunks, chunk_rows, D.k) : 0;
   int taken = 0, polls = kMarkPolls;
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
         const int chunk = (int)ticket, lane = threadIdx.x;
         if (lane == 0) {
           __hip_atomic_fetch_or(&sy[kSyncMarks + chunk / 32], 1u << (chunk % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ticket_lds = agent_add(&sy[kSyncTicket], 1u);
+          ticket_lds = agent_add(&sy[kSyncTicket], 1u) & 0xFFFFu;
         }
         const int below = chunk - 32 * lane;      // chunks before this one that lane's word of marks holds
         const uint32_t want = below >= 32 ? 0xFFFFFFFFu : (below > 0 ? (1u << below) - 1u : 0u);
@@ -447,7 +448,7 @@ bool select_compact_supported(const Dims& D) { return D.n <= kLdsRowTokens; }
 // sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units.
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
-                           uint32_t* sync, hipStream_t s) {
+                           uint32_t* sync, bool nuc_known, hipStream_t s) {
   const int rowb = D.d * (D.dtype == 0 ? 4 : 2);
   const int row_shift = rowb == 128 ? 3 : (rowb == 256 ? 4 : 5);
   // Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
@@ -470,7 +471,7 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   const dim3 grid((unsigned)D.units_run * per_unit), block(threads);
 #define CCD_LAUNCH(THREADS, CH, RB, BF, SHARED)                                                                                  \
   launch((select_compact_kernel<THREADS, CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
-         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync)
+         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync, nuc_known ? 1 : 0)
 #define CCD_LAUNCH_RB(THREADS, CH, SHARED)                                          \
   if (Krot == nullptr) CCD_LAUNCH(THREADS, CH, 0, true, SHARED);                    \
   else if (rowb == 128) CCD_LAUNCH(THREADS, CH, 128, true, SHARED);                 \

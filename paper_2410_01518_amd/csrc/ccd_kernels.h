@@ -31,7 +31,13 @@ struct Dims {
 // shared while there are two compute units for each: calls with more units need no such words.
 // (256 compute units: a constant, since it sizes a part of the workspace, which is asked for without a device.)
 constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgroups / 2;
-constexpr int kSyncTicket = 0, kSyncSelected = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16;
+// kSyncTicket: tickets in the lower half, workgroups that have selected in the upper one.  kSyncNovelty, kSyncNoveltyTies: tokens with a larger
+// novelty key than the one have a NuC slot, those with this key before token number the other (launch_*_direct; of the sequence's first unit
+// when novelty is shared by layers and heads).  The last word belongs to the marks of calls that keep more than kNoveltyMaxKept tokens:
+// chunks are of at least 64 rows where there are more of them than workgroups.
+constexpr int kSyncTicket = 0, kSyncNovelty = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16, kSyncNoveltyTies = 15;
+constexpr int kNoveltyMaxKept = (kSyncMarkWords - 1) * 32 * 64;
+constexpr uint32_t kSyncOneSelected = 1u << 16;
 
 // (an argument of every score kernel: 8 bytes more, for one int that left padding, took 0.1 us a launch)
 struct ScorePlan {
@@ -109,10 +115,14 @@ void launch_prob_split(const Dims& D, const ScorePlan& pl, const void* Q, const 
 // normalisers when pl.lse_given (read only), else where fp32 calls put those in log2 units.
 void plan_direct(const Dims& D, int compute_units, ScorePlan& pl);
 int64_t time_direct(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given);   // as time_split
+// nov_wgs > 0: the kernel also finds, in so many workgroups of its own, which tokens have a NuC slot, and says so in pl.sync.
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
-                         hipStream_t s);
+                         const float* novelty, int nov_wgs, hipStream_t s);
 void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,
-                        float* lse_io, float* u, hipStream_t s);
+                        float* lse_io, float* u, const float* novelty, int nov_wgs, hipStream_t s);
+// how many such workgroups the first kernel of a call has: one for every novelty row (the call's units have words, and a row fits the
+// workgroup's registers), or none where they would make one more round of its grid
+int novelty_workgroups(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given);
 
 // The same on the vector-ALU path: statistics of CaP key j under CaP query i for j <= i, written to `part` behind
 // the slices of all units (pl.cap_block must be 1; launch_merge then takes them in).  K_cap as above.
@@ -121,16 +131,17 @@ void launch_cap_block_stats_valu(const Dims& D, const ScorePlan& pl, const void*
 
 // NuC slots of the unit's novelty row + pooling + NuC lift -> scores (when `u` != null; novelty may be null when
 // D.T == 0), top-k -> keep_idx (when `keep_idx` != null)
+// nuc_words (nullable): words of the units in which the score kernels have left kSyncNovelty
 void launch_finalize_select(const Dims& D, const float* u, const float* novelty, float* scores,
-                            int32_t* keep_idx, hipStream_t s);
+                            int32_t* keep_idx, const uint32_t* nuc_words, hipStream_t s);
 
 // selection and compaction of a unit in one workgroup (rows short enough to be staged in LDS)
 bool select_compact_supported(const Dims& D);
 // (sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units; carry_novelty: the novelty is carried per head
-// and its kept entries are compacted in place like the rows)
+// and its kept entries are compacted in place like the rows; nuc_known: the words hold kSyncNovelty)
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
-                           uint32_t* sync, hipStream_t s);
+                           uint32_t* sync, bool nuc_known, hipStream_t s);
 // CR-RoPE of the first `count` rows of every unit (Sec. 3.5): Krot[j] = rotary embedding at position j of K[j]
 void launch_rope_rows(const Dims& D, const void* K, const float* rope_cos, const float* rope_sin, int count, void* Krot,
                       hipStream_t s);

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "ccd_fp32.h"
+#include "ccd_select_body.h"
 
 namespace ccd {
 
@@ -52,6 +53,7 @@ struct DirectShape {
   static constexpr int kSlots = QB + 4 * kTiles;
   static_assert(4 * QB + kTiles <= kSlots && 2 * QB + 2 * kTiles <= kSlots, "any number of row blocks");
   static_assert(kDirectMaxSlice2 * 4 <= QB * kSlotBytes, "the sums of a row block fit where its rows were");
+  static_assert(kSlots * kSlotBytes >= 16 << 10, "what find_novelty_key keeps fits");
 };
 
 // 64 x 16 bytes from the lanes' own addresses to consecutive LDS addresses (lds_addr: the same in all lanes)
@@ -127,10 +129,88 @@ __device__ __forceinline__ void tile_logits(floatx16 (&acc)[SH::QB], const uint8
   if constexpr (SH::F32) acc[0] += small;
 }
 
+// Which tokens of a row have a NuC slot (Sec. 3.3.3 step 1), as the key of the T-th most novel one and where its equals end, by a workgroup
+// of its own beside those that score.  It depends on nothing that the call computes, and in the selection, where every workgroup of a unit
+// found it for itself behind the scores, it was two of six barriers and a third of the passes over the row.  Append + distill: 4 units of 512
+// fp32 tokens 26.5 -> 25.4 us, 8 units of 2048 / 8192 tokens 31.4 / 59.6 -> 30.2 / 57.0, 2 units of 5000 tokens and 16 rows 37.5 -> 35.1; 45
+// units of 3000 tokens step by step 48.2 -> 45.5.  Bound by latency; rows are kept in registers.  (Rows of 16384 tokens: 8 units and
+// 256 rows 89.3 -> 85.8, but 1 unit 49.2 -> 53.7, whose score pass is shorter than this.)
+// Not inlined: the kernel around it has no registers to spare.
+// The longest row.  (32 tokens a thread are 180 registers; bf16 rows of 64 elements are scored with 126, four workgroups to a compute unit.)
+constexpr int kNoveltyRow = 32 * kMT;
+constexpr int novelty_row(int d, bool f32) { return d == 64 && !f32 ? 16 * kMT : kNoveltyRow; }
+struct NoveltyLds {
+  TopkShared<kMT> topk;
+  uint32_t sums[kNoveltyRow / (4 * 64)];
+};
+template <int CHUNKS>
+__device__ __noinline__ void find_novelty_key(const float* __restrict__ nov, int n, int T, uint32_t lds_addr, uint32_t* words) {
+  auto& sh = *(NoveltyLds*)(__attribute__((address_space(3))) NoveltyLds*)(uintptr_t)lds_addr;
+  auto token = [&](int c) { return 4 * (c * kMT + (int)threadIdx.x); };
+  uint32_t kept[CHUNKS][4];                                        // keys, 0 past the end
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    float f[4];
+    load_row4(f, nov, token(c), n, -INFINITY);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kept[c][i] = novelty_key(f[i]);
+  }
+  auto chunks = [&](auto&& use) {
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      // (what a pass makes of a key is not kept for the next one)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(kept[c][i]));
+      use(kept[c], c);
+    }
+  };
+  auto each_key = [&](auto&& f) {
+    chunks([&](const uint32_t (&k)[4], int) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f(k[i]);
+    });
+  };
+  topk_clear(sh.topk);
+  KeyClasses cn{0xFFFFFFFFu, 0u, 0u, 0u};
+  each_key([&](uint32_t k) { classify(k, cn); });
+  publish_classes(cn, sh.topk, 1);
+  __syncthreads();
+  cn = combine_classes(sh.topk, 1);
+  const uint32_t slots = min((uint32_t)T, cn.n_hi + cn.n_mid);     // NaN and -inf never take a slot
+  Threshold th{0xFFFFFFFFu, 0u, 0u};                               // (above every key)
+  if (slots > 0)
+    th = slots <= cn.n_hi ? Threshold{kHiFrom, slots, cn.n_hi} : radix_threshold(each_key, cn.mn, cn.mx, slots - cn.n_hi, cn.n_mid, sh.topk, 0);
+  if (th.need < th.n_eq) {                                         // only some of the equal tokens: the first ones
+    auto equal_before = [&](const uint32_t (&k)[4], uint32_t& mine) {
+      mine = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mine += k[i] == th.tau ? 1u : 0u;
+      return wave_inclusive_scan(mine, 0u, OpAdd{});
+    };
+    chunks([&](const uint32_t (&k)[4], int c) {
+      uint32_t mine;
+      put_round_sum<kMT>(equal_before(k, mine), sh.sums, c);
+    });
+    __syncthreads();
+    const RoundBases<kMT, CHUNKS> bases(sh.sums, CHUNKS);
+    chunks([&](const uint32_t (&k)[4], int c) {
+      uint32_t mine;
+      const uint32_t inc = equal_before(k, mine);
+      uint32_t eq = bases.of(c) + inc - mine;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (k[i] == th.tau && eq++ == th.need) words[kSyncNoveltyTies] = (uint32_t)(token(c) + i);
+    });
+  } else if (threadIdx.x == 0) {
+    words[kSyncNoveltyTies] = 0xFFFFFFFFu;
+  }
+  if (threadIdx.x == 0) words[kSyncNovelty] = th.tau;
+}
+
 template <int HD, class ET, int PASS>
 __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan pl, const ET* __restrict__ Q, const ET* __restrict__ K,
                                                               const ET* __restrict__ Kcap, float2* __restrict__ part,
-                                                              float* lse_io, float* __restrict__ u) {
+                                                              float* lse_io, float* __restrict__ u, const float* novelty, int nov_wgs) {
   using SH = DirectShape<HD, ET>;
   constexpr int KS = HD / 16, QB = SH::QB;
   __shared__ __attribute__((aligned(1024))) uint8_t rows[SH::kSlots * SH::kSlotBytes];
@@ -138,14 +218,28 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
   const int slices = PASS == 1 ? pl.n_slices1 + (Kcap != nullptr ? 1 : 0) : pl.n_slices2;
   // consecutive blocks go to different XCDs: the workgroups of one slice are eight blocks apart
   const int per_item = PASS == 1 ? row_blocks : 1;
-  const int item = (int)(blockIdx.x >> 3) / per_item * 8 + (int)(blockIdx.x & 7);
+  // (the workgroups for novelty come first: they are done long before the others)
+  const int bid = (int)blockIdx.x - (nov_wgs + 7) / 8 * 8;
+  if (bid < 0) {
+    if ((int)blockIdx.x < nov_wgs) {
+      const int nu = (int)blockIdx.x * (D.units / nov_wgs);           // every unit's own row, or one for each sequence
+      const float* row = novelty + nov_offset(D, decode_unit(D, nu));
+      const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)rows;
+      uint32_t* words = pl.sync + (int64_t)nu * kSyncWords;
+      if (D.n <= 8 * kMT)       find_novelty_key<2>(row, D.n, D.T, lds, words);
+      else if (D.n <= 16 * kMT) find_novelty_key<4>(row, D.n, D.T, lds, words);
+      else if constexpr (novelty_row(HD, SH::F32) > 16 * kMT) find_novelty_key<8>(row, D.n, D.T, lds, words);
+    }
+    return;
+  }
+  const int item = (bid >> 3) / per_item * 8 + (bid & 7);
   if (item >= D.units_run * slices) return;
   const int slice = item % slices, unit = D.unit0 + item / slices;
   const UnitIdx ui = decode_unit(D, unit);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
   const float c = D.scale_log2;
-  if (PASS == 2) clear_sync(pl, unit, slice == 0);
+  if (PASS == 2) clear_sync(D, pl, unit, slice == 0);
   const bool cap = PASS == 1 && slice == pl.n_slices1;
   const ET* Ku = cap ? Kcap + (int64_t)unit * D.P * HD : K + kv_offset(D, ui);
   const int slice_len = PASS == 1 ? pl.slice1 : pl.slice2;
@@ -158,7 +252,7 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
   // waves side by side over row blocks (1, 2 or 4 of them; pass 1: one), the others on other tiles
   const int wide = PASS == 1 || row_blocks <= 1 ? 1 : (row_blocks <= 2 ? 2 : 4), groups = 4 / wide;
   const int rb = wave % wide, group = wave / wide;
-  const int q_first = PASS == 1 ? (int)(blockIdx.x >> 3) % per_item * SH::kRows : 0;
+  const int q_first = PASS == 1 ? (bid >> 3) % per_item * SH::kRows : 0;
   const int q_last = PASS == 1 ? min(D.GP, q_first + SH::kRows) : D.GP;
   float* up = reinterpret_cast<float*>(rows);                // pass 2: token sums per row block
   bool nan_out = false;                                      // pass 2, fp32: some token's score is NaN
@@ -387,6 +481,15 @@ void plan_direct(const Dims& D, int compute_units, ScorePlan& pl) {
   pl.direct_kernel = 1;
 }
 
+int novelty_workgroups(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given) {
+  if (D.T <= 0 || D.units > kMaxSharedUnits || D.units_run != D.units || D.k > kNoveltyMaxKept || D.n > novelty_row(D.d, D.dtype == 0)) return 0;
+  const int wgs = D.nov_sl != 0 || D.nov_sh != 0 ? D.units : D.B;
+  const int scores = lse_given ? direct_grid(D, pl.n_slices2, 1) : direct_grid(D, pl.n_slices1 + (cap_keys ? 1 : 0), direct_cut(D).row_blocks);
+  const int all = scores + (wgs + 7) / 8 * 8;
+  auto rounds = [&](int n) { return (n + compute_units - 1) / compute_units; };
+  return all <= 2 * compute_units || rounds(all) == rounds(scores) ? wgs : 0;
+}
+
 int64_t time_direct(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given) {
   struct Pass { int start, batch; };               // two workgroups per compute unit start together and then share it
   struct Cost { Pass stats, prob; };
@@ -404,23 +507,23 @@ int64_t time_direct(const Dims& D, int compute_units, const ScorePlan& pl, bool 
 }
 
 void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, float2* part,
-                         hipStream_t s) {
+                         const float* novelty, int nov_wgs, hipStream_t s) {
   const int rows = D.dtype == 0 ? 32 : 64, row_blocks = (D.GP + rows - 1) / rows;
-  const dim3 grid(direct_grid(D, pl.n_slices1 + (K_cap != nullptr ? 1 : 0), row_blocks)), block(kMT);
+  const dim3 grid(direct_grid(D, pl.n_slices1 + (K_cap != nullptr ? 1 : 0), row_blocks) + (nov_wgs + 7) / 8 * 8), block(kMT);
 #define CCD_LAUNCH(HD, ET)                                                                                                       \
   launch((score_direct_kernel<HD, ET, 1>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, part, nullptr, \
-         nullptr)
+         nullptr, novelty, nov_wgs)
   if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
   else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
 #undef CCD_LAUNCH
 }
 
 void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const void* K, const void* K_cap, const float2* part,
-                        float* lse_io, float* u, hipStream_t s) {
-  const dim3 grid(direct_grid(D, pl.n_slices2, 1)), block(kMT);
+                        float* lse_io, float* u, const float* novelty, int nov_wgs, hipStream_t s) {
+  const dim3 grid(direct_grid(D, pl.n_slices2, 1) + (nov_wgs + 7) / 8 * 8), block(kMT);
 #define CCD_LAUNCH(HD, ET)                                                                                          \
   launch((score_direct_kernel<HD, ET, 2>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, \
-         const_cast<float2*>(part), lse_io, u)
+         const_cast<float2*>(part), lse_io, u, novelty, nov_wgs)
   if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
   else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
 #undef CCD_LAUNCH

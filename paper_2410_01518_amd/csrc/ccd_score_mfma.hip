@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kMT, 2) void score_pass_kernel(Dims D, ScorePlan pl
   // memory-side cache
   if (PASS == 2) unit = D.units_run - 1 - unit;
   unit += D.unit0;
-  clear_sync(pl, unit, slice == 0);
+  clear_sync(D, pl, unit, slice == 0);
   score_pass_body<HD, PASS>(D, pl, unit, slice, Q, K, part, u, Kcap, lse_out, sm);
 }
 

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void score_split_kernel(Dims D, S
   const int slices = PASS == 1 ? pl.n_slices1 + (Kcap != nullptr ? 1 : 0) : pl.n_slices2;
   const int slice = blockIdx.x % slices, unit = D.unit0 + blockIdx.x / slices, tid = threadIdx.x;
   const UnitIdx ui = decode_unit(D, unit);
-  if (PASS == 2) clear_sync(pl, unit, slice == 0);
+  if (PASS == 2) clear_sync(D, pl, unit, slice == 0);
   const bool cap = PASS == 1 && slice == pl.n_slices1;
   const float* Ku = cap ? Kcap + (int64_t)unit * D.P * HD : K + kv_offset(D, ui);
   const int t0 = cap ? 0 : slice * pl.slice1, t1 = cap ? D.P : min(D.n, t0 + pl.slice1);

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
   __shared__ UnitLds<RG> sm;
   const int unit = D.unit0 + blockIdx.x;
   const UnitIdx ui = decode_unit(D, unit);
-  clear_sync(pl, unit, true);
+  clear_sync(D, pl, unit, true);
   const ET* Ku = K + kv_offset(D, ui);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;

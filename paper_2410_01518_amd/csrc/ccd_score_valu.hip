@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void prob_valu_kernel(Dims D, ScorePlan p
   __shared__ float4 Qs[kQryTile][HD / 4];
   __shared__ float Ls[kQryTile];
   const int unit = D.unit0 + blockIdx.x / pl.n_slices2, tid = threadIdx.x;
-  clear_sync(pl, unit, blockIdx.x % pl.n_slices2 == 0);
+  clear_sync(D, pl, unit, blockIdx.x % pl.n_slices2 == 0);
   const UnitIdx ui = decode_unit(D, unit);
   const int tok = (blockIdx.x % pl.n_slices2) * kThreads + tid;   // one token per thread
   const bool active = tok < D.n;

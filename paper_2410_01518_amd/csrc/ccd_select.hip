@@ -17,13 +17,14 @@ constexpr int kSelThreads = 1024;
 template <int CH, bool SELECT, bool GIVEN>
 __global__ __launch_bounds__(kSelThreads) void finalize_select_kernel(Dims D, const float* __restrict__ u,
                                                                       const float* __restrict__ novelty, float* scores,
-                                                                      int32_t* __restrict__ keep_idx) {
+                                                                      int32_t* __restrict__ keep_idx, const uint32_t* nuc_words) {
   __shared__ SelectShared<kSelThreads, CH> sh;
   const int unit = D.unit0 + blockIdx.x;
   const float* nov = (!GIVEN && D.T > 0) ? novelty + nov_offset(D, decode_unit(D, unit)) : nullptr;
   Row<kSelThreads, CH> row(D, sh, unit, GIVEN ? nullptr : u, GIVEN ? scores : nullptr, nov);
   int32_t* out = SELECT ? keep_idx + (int64_t)unit * D.k : nullptr;
-  select_row<kSelThreads, CH, SELECT>(row, scores != nullptr ? scores + (int64_t)unit * D.n : nullptr,
+  const uint32_t* words = nuc_words != nullptr ? nuc_words + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
+  select_row<kSelThreads, CH, SELECT, !GIVEN && CH != kLongRow>(row, scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, words,
                          [&](int pos, int t, int, int) {
                            // (a row that is pooled anew in every step may be overwritten meanwhile by a call that overlaps on
                            // the workspace: the list is undefined then, but stays in its place)
@@ -36,17 +37,17 @@ __global__ __launch_bounds__(kSelThreads) void finalize_select_kernel(Dims D, co
 int select_max_tokens() { return kMaxTokens; }
 
 void launch_finalize_select(const Dims& D, const float* u, const float* novelty, float* scores, int32_t* keep_idx,
-                            hipStream_t s) {
+                            const uint32_t* nuc_words, hipStream_t s) {
   const dim3 grid(D.units_run), block(kSelThreads);
   // (raw scores and a kept list: long rows only, others go through launch_select_compact)
 #define CCD_LAUNCH(CH)                                                                                                     \
-  if (u == nullptr) launch((finalize_select_kernel<CH, true, true>), grid, block, s, D, u, novelty, scores, keep_idx);      \
-  else              launch((finalize_select_kernel<CH, false, false>), grid, block, s, D, u, novelty, scores, keep_idx)
+  if (u == nullptr) launch((finalize_select_kernel<CH, true, true>), grid, block, s, D, u, novelty, scores, keep_idx, nullptr);       \
+  else              launch((finalize_select_kernel<CH, false, false>), grid, block, s, D, u, novelty, scores, keep_idx, nuc_words)
   if (D.n <= 4 * kSelThreads)       { CCD_LAUNCH(1); }
   else if (D.n <= 8 * kSelThreads)  { CCD_LAUNCH(2); }
   else if (D.n <= kLdsRowTokens)    { CCD_LAUNCH(kLdsRow); }
   else if (u != nullptr && keep_idx != nullptr)
-    launch((finalize_select_kernel<kLongRow, true, false>), grid, block, s, D, u, novelty, scores, keep_idx);
+    launch((finalize_select_kernel<kLongRow, true, false>), grid, block, s, D, u, novelty, scores, keep_idx, nullptr);
   else                              { CCD_LAUNCH(kLongRow); }
 #undef CCD_LAUNCH
 }

@@ -188,7 +188,7 @@ struct Row {
   int rounds;              // chunks per thread, whole groups
   uint32_t key[kRegs ? 4 * CH : 1];
   float nv[kRegs ? 4 * CH : 1];      // the thread's novelty
-  uint64_t slots = 0;                // kLds: bit 4 c + i: token i of chunk c has a NuC slot
+  uint64_t slots = 0;                // bit 4 c + i: token i of chunk c has a NuC slot (kLds, or where the slots are known)
 
   __device__ __forceinline__ Row(const Dims& D_, SelectShared<THREADS, CH>& sh_, int unit, const float* u_, const float* given_,
                                  const float* nov_)
@@ -251,6 +251,25 @@ struct Row {
           }
         },
         use);
+  }
+  // slots <- the tokens that the words of find_novelty_key give one
+  __device__ __forceinline__ void take_slots(const uint32_t* words) {
+    const uint32_t from = max(words[kSyncNovelty], 1u), ties_end = words[kSyncNoveltyTies];      // (the keys past the end are 0)
+    auto take = [&](const uint32_t (&k)[4], int c) {
+      uint32_t slot = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) slot |= k[i] > from || (k[i] == from && (uint32_t)(token(c) + i) < ties_end) ? 1u << i : 0u;
+      slots |= (uint64_t)slot << (4 * c);
+    };
+    if constexpr (kRegs) {
+      each_novelty_chunk(take);
+    } else {
+      chunks<Vals4>([&](float (&f)[4], int c) { load_row4(f, nov, token(c), D.n, -INFINITY); },
+                    [&](float (&f)[4], int c) {
+                      const uint32_t k[4] = {novelty_key(f[0]), novelty_key(f[1]), novelty_key(f[2]), novelty_key(f[3])};
+                      take(k, c);
+                    });
+    }
   }
   __device__ __forceinline__ void load_novelty() {
     if constexpr (kRegs) {
@@ -337,10 +356,13 @@ struct Row {
 // SELECT: emit(place, token, c, i) is called by the thread that owns it for every kept token (the top-k of score), in
 // ascending order of a thread's tokens; c, i: its chunk and place in it.  Ends without a barrier.
 //
+// NUC: nuc_words, if not null, are what find_novelty_key has left for the row: the slots are known before the scores are read.
+//
 // Barriers, when the row's keys are ordinary, no bin holds more than 64 candidates and T > 0: classes (of novelty and
-// scores together; one after the other where they take turns in LDS), two per threshold, ranks - six in all, or seven.
-template <int THREADS, int CH, bool SELECT, class Emit>
-__device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_row, Emit&& emit) {
+// scores together; one after the other where they take turns in LDS), two per threshold, ranks - six in all, or seven; four with known slots.
+template <int THREADS, int CH, bool SELECT, bool NUC, class Emit>
+__device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_row, const uint32_t* nuc_words, Emit&& emit) {
+  static_assert(!NUC || CH != kLongRow, "a long row keeps no slots in registers");
   using R = Row<THREADS, CH>;
   const Dims& D = row.D;
   SelectShared<THREADS, CH>& sh = row.sh;
@@ -349,7 +371,8 @@ __device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_
   topk_clear(sh.topk);
 
   const bool lift = row.u != nullptr && D.T > 0;
-  const bool score_first = !R::kLds || !lift;
+  const bool known = NUC && lift && nuc_words != nullptr, find = lift && !known;
+  const bool score_first = !R::kLds || !find;
   KeyClasses cs{0xFFFFFFFFu, 0u, 0u, 0u}, cn{0xFFFFFFFFu, 0u, 0u, 0u};
   auto score_stage = [&]() {
     row.template chunks<typename R::Window>(
@@ -360,13 +383,13 @@ __device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_
           uint32_t k[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) k[i] = row.token(c) + i < n ? score_key(f[i]) : 0u;
-          if constexpr (R::kLds) {
+          if (R::kLds || known) {
             const uint32_t slot = (uint32_t)(row.slots >> (4 * c)) & 15u;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
               if ((slot >> i) & 1u) { k[i] = kHiFrom; f[i] = INFINITY; }
           }
-          // (elsewhere the slots of the NuC tokens are overwritten below)
+          // (else the slots of the NuC tokens are overwritten below)
           if (row.u != nullptr && scores_row != nullptr) store_row4(scores_row, row.token(c), n, f);
           if constexpr (SELECT) {
             row.put_keys(k, c);
@@ -376,18 +399,19 @@ __device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_
         });
     if (SELECT) publish_classes(cs, sh.topk, 0);
   };
+  if (known) row.take_slots(nuc_words);
   if (score_first) score_stage();
-  if (lift) {
+  if (find) {
     row.first_novelty_chunks([&](const uint32_t (&k)[4], int) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) classify(k[i], cn);
     });
     publish_classes(cn, sh.topk, 1);
   }
-  if (SELECT || lift) __syncthreads();
+  if (SELECT || find) __syncthreads();
 
   uint32_t n_slots = 0;
-  if (lift) {
+  if (find) {
     cn = combine_classes(sh.topk, 1);
     n_slots = min((uint32_t)D.T, cn.n_hi + cn.n_mid);     // NaN and -inf never take a slot
   }
@@ -447,7 +471,7 @@ __device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_
       });
     };
     cs = combine_classes(sh.topk, 0);
-    if (lift && score_first) {
+    if (find && score_first) {
       if (cs.n_mid < (uint32_t)n) {
         // rows with -inf, NaN or +inf among the pooled scores: which of them were lifted is only known now
         KeyClasses c2{0xFFFFFFFFu, 0u, 0u, 0u};

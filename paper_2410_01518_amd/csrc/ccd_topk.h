@@ -56,13 +56,13 @@ template <class Op>
 __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t identity, Op op) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v, identity, op), 63);
 }
-// the operation over each aligned group of N = 8 or 16 lanes, as a scalar; all groups hold the same values
+// the operation over each aligned group of N = 4, 8 or 16 lanes, as a scalar; all groups hold the same values
 template <int N, class Op>
 __device__ __forceinline__ uint32_t reduce_group(uint32_t v, Op op) {
-  static_assert(N == 8 || N == 16, "");
+  static_assert(N == 4 || N == 8 || N == 16, "");
   v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]
   v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));    // quad_perm [2,3,0,1]
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));   // row_half_mirror
+  if (N >= 8) v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));    // row_half_mirror
   if (N == 16) v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // row_mirror
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }

@@ -342,20 +342,23 @@ static int launch_status() { return hipGetLastError() == hipSuccess ? CCD_OK : C
 // compute them in pass 2).  (The NuC slots, Sec. 3.3.3 step 1, are found by the selection kernels from the novelty row.)
 // lse (nullable): the caller's natural-log-sum-exp of every CaP query row [units, G*P]: the statistics pass (and
 // with it K_cap) is not needed, the probabilities follow from one pass over K.
-static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, const void* Q, const void* K,
-                           const void* K_cap, const float* lse, char* ws, hipStream_t st) {
+// novelty (nullable): its keys at the NuC slots are found along the way where a kernel does that; returns whether.
+static bool run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, const void* Q, const void* K,
+                           const void* K_cap, const float* lse, const float* novelty, char* ws, hipStream_t st) {
   const int lead = units_in_whole_rounds(D, pl, K_cap != nullptr, lse != nullptr);
   if (lead < D.units_run) {
     Dims part = D;
     part.units_run = lead;
-    run_cap_scores(part, pl, w, Q, K, K_cap, lse, ws, st);
+    run_cap_scores(part, pl, w, Q, K, K_cap, lse, nullptr, ws, st);
     part.unit0 = D.unit0 + lead;
     part.units_run = D.units_run - lead;
     ScorePlan rest = plan_score(part, K_cap != nullptr, lse != nullptr);
     rest.sync = pl.sync;             // (a partition of few compute units: the rest of a call whose units are shared has words to clear too)
-    run_cap_scores(part, rest, w, Q, K, K_cap, lse, ws, st);
-    return;
+    run_cap_scores(part, rest, w, Q, K, K_cap, lse, nullptr, ws, st);
+    return false;
   }
+  const int nov_wgs = pl.direct_kernel && pl.sync != nullptr && novelty != nullptr
+                          ? novelty_workgroups(D, compute_units(), pl, K_cap != nullptr && lse == nullptr, lse != nullptr) : 0;
   float2* part = reinterpret_cast<float2*>(ws + w.off_part);
   float* lse2 = reinterpret_cast<float*>(ws + w.off_lse);
   float* u = reinterpret_cast<float*>(ws + w.off_u);
@@ -378,13 +381,13 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
       launch_head_prob_mfma(D, pl, Q, K, lse_io, u, st);
       g_prof.end(st);
     }
-    return;
+    return false;
   }
   if (lse != nullptr) {
     pl.lse_given = 1;
     float* lse_rw = const_cast<float*>(lse);   // only read when pl.lse_given
     g_prof.begin(kStProb, st);
-    if (pl.direct_kernel)     launch_prob_direct(D, pl, Q, K, nullptr, part, lse_rw, u, st);
+    if (pl.direct_kernel)     launch_prob_direct(D, pl, Q, K, nullptr, part, lse_rw, u, novelty, nov_wgs, st);
     else if (pl.use_mfma)     launch_prob_mfma(D, pl, Q, K, nullptr, part, u, lse_rw, st);
     else if (pl.split_kernel) launch_prob_split(D, pl, Q, K, lse, u, st);
     else                      launch_prob_valu(D, pl, Q, K, lse, u, st);
@@ -394,17 +397,17 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
       launch_head_prob_mfma(D, pl, Q, K, lse, u, st);
       g_prof.end(st);
     }
-    return;
+    return nov_wgs > 0;
   }
   if (K_cap != nullptr && (!pl.use_mfma || pl.direct_kernel)) pl.cap_block = 1;   // (launch_prob_mfma takes the CaP keys in its prologue)
   if (pl.direct_kernel) {
     g_prof.begin(kStStats, st);
-    launch_stats_direct(D, pl, Q, K, K_cap, part, st);
+    launch_stats_direct(D, pl, Q, K, K_cap, part, novelty, nov_wgs, st);
     g_prof.end(st);
     g_prof.begin(kStProb, st);
-    launch_prob_direct(D, pl, Q, K, K_cap, part, lse2, u, st);
+    launch_prob_direct(D, pl, Q, K, K_cap, part, lse2, u, nullptr, 0, st);
     g_prof.end(st);
-    return;
+    return nov_wgs > 0;
   }
   if (pl.cap_block && !pl.split_kernel) {
     g_prof.begin(kStCapBlock, st);
@@ -442,6 +445,7 @@ static void run_cap_scores(const Dims& D, ScorePlan pl, const Workspace& w, cons
     else                 launch_prob_valu(D, pl, Q, K, lse2, u, st);
     g_prof.end(st);
   }
+  return false;
 }
 
 }  // namespace ccd
@@ -464,7 +468,7 @@ static int score_impl(const ccd_shape_t* shape, const void* Q_cat, const void* K
   if (novelty == nullptr && shape->T > 0) return CCD_EINVAL;
   if (!aligned16(Q_cat) || !aligned16(K) || !aligned16(K_cap) || !aligned16(lse)) return CCD_EALIGN;
   const Dims D = make_dims(shape);
-  const ScorePlan pl = plan_score(D, K_cap != nullptr, lse != nullptr);
+  ScorePlan pl = plan_score(D, K_cap != nullptr, lse != nullptr);
   if (path_refused(D, pl)) return CCD_EUNSUPPORTED;
   if (pl.use_mfma && D.head - D.head0 > mfma_max_slice()) return CCD_EUNSUPPORTED;   // (a matrix-core path was named)
   const Workspace w = layout_workspace(D);
@@ -472,8 +476,9 @@ static int score_impl(const ccd_shape_t* shape, const void* Q_cat, const void* K
   if (rc != CCD_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(workspace);
-  run_cap_scores(D, pl, w, Q_cat, K, K_cap, lse, ws, st);
-  launch_finalize_select(D, reinterpret_cast<const float*>(ws + w.off_u), novelty, scores, nullptr, st);
+  pl.sync = D.units <= kMaxSharedUnits ? reinterpret_cast<uint32_t*>(ws + w.off_sync) : nullptr;
+  const bool nuc_known = run_cap_scores(D, pl, w, Q_cat, K, K_cap, lse, novelty, ws, st);
+  launch_finalize_select(D, reinterpret_cast<const float*>(ws + w.off_u), novelty, scores, nullptr, nuc_known ? pl.sync : nullptr, st);
   return launch_status();
 }
 
@@ -499,7 +504,7 @@ int ccd_select(const ccd_shape_t* shape, const float* scores, int32_t* keep_idx,
   if (rc != CCD_OK) return rc;
   if (scores == nullptr || keep_idx == nullptr) return CCD_EINVAL;
   const Dims D = make_dims(shape);
-  launch_finalize_select(D, nullptr, nullptr, const_cast<float*>(scores), keep_idx,
+  launch_finalize_select(D, nullptr, nullptr, const_cast<float*>(scores), keep_idx, nullptr,
                          static_cast<hipStream_t>(hip_stream));
   return launch_status();
 }
@@ -581,15 +586,15 @@ static int compress_impl(const ccd_shape_t* shape, const void* Q_cat, void* K, v
   if (g_prof.on) ++g_prof.calls;
   uint32_t* sync = D.units <= kMaxSharedUnits ? reinterpret_cast<uint32_t*>(ws + w.off_sync) : nullptr;
   pl.sync = sync;
-  run_cap_scores(D, pl, w, Q_cat, K_attn, K_cap, lse, ws, st);
+  const bool nuc_known = run_cap_scores(D, pl, w, Q_cat, K_attn, K_cap, lse, novelty, ws, st);
   if (select_compact_supported(D)) {
     g_prof.begin(kStSelCompact, st);
-    launch_select_compact(D, u, novelty, per_head, scores_opt, keep_idx, K, V, rope_cos, rope_sin, K_rot, sync, st);
+    launch_select_compact(D, u, novelty, per_head, scores_opt, keep_idx, K, V, rope_cos, rope_sin, K_rot, sync, nuc_known, st);
     g_prof.end(st);
     return launch_status();
   }
   g_prof.begin(kStSelect, st);
-  launch_finalize_select(D, u, novelty, scores_opt, keep_idx, st);
+  launch_finalize_select(D, u, novelty, scores_opt, keep_idx, nullptr, st);
   g_prof.end(st);
   g_prof.begin(kStCompact, st);
   launch_compact(D, K, V, keep_idx, K, V, per_head ? novelty : nullptr, st);

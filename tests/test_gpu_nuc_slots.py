@@ -1,0 +1,75 @@
+"""NuC slots of calls with few units, which the first score kernel finds beside the scores: the +inf entries of the scores against a stable
+sort of the novelty, at the limits of what a thread keeps of a row, with ties, with values that never take a slot, for every novelty layout."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ccd_oracle as O
+from paper_2410_01518_amd import infinipot as ip
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _slots(nov, T):
+    """T most novel tokens, lower index first among equals; NaN and -inf never."""
+    valid = ~(np.isnan(nov) | np.isneginf(nov))
+    order = np.argsort(np.where(valid, -nov.astype(np.float64), np.inf), kind="stable")[: min(T, int(valid.sum()))]
+    out = np.zeros(nov.shape, bool)
+    out[order] = True
+    return out
+
+
+@pytest.mark.parametrize("kind", ["spread", "ties", "special"])
+@pytest.mark.parametrize("option", ["", "lse"])
+@pytest.mark.parametrize("n,d,fp32,per_head", [
+    (1, 64, False, True), (5, 128, True, False), (2047, 128, False, True), (2049, 64, False, False), (4096, 128, True, True),
+    (4097, 128, False, True), (8192, 128, False, False), (4097, 64, False, True), (8193, 128, False, True)])
+def test_slots_are_the_most_novel_tokens(n, d, fp32, per_head, option, kind):
+    B, L, Hkv, P = 2, 1, 3, 4
+    g, rng = torch.Generator(device="cuda").manual_seed(n), np.random.default_rng(n + len(kind))
+    dt = torch.float32 if fp32 else torch.bfloat16
+    Q, K = (torch.randn((B, L, Hkv, m, d), generator=g, device="cuda").to(dt) for m in (P, n))
+    nov = rng.standard_normal((B, L, Hkv, n) if per_head else (B, n)).astype(np.float32)
+    if kind == "ties":
+        nov = np.round(nov * 1.5) / 1.5
+    if kind == "special":
+        for value, share in ((np.inf, 0.3), (-np.inf, 0.2), (np.nan, 0.2)):
+            nov[rng.random(nov.shape) < share] = value
+    lse = torch.full((B, L, Hkv, P), 6.0, device="cuda")
+    for T in sorted({0, 1, n // 7, n // 2, n}):
+        shape = ip.make_shape(Q, K, gu.to_dev(nov), k=n, T=T, pool_w=5)
+        ws = ip.alloc_workspace(shape)
+        ws.fill_(0xA5)
+        scores = torch.empty((B, L, Hkv, n), dtype=torch.float32, device="cuda")
+        print(f"slots n={n} d={d} fp32={fp32} per_head={per_head} {option} {kind} T={T}", flush=True)
+        if option == "lse":
+            ip.ccd_score_lse(shape, Q, K, lse, gu.to_dev(nov), scores, ws)
+        else:
+            ip.ccd_score(shape, Q, K, gu.to_dev(nov), scores, ws)
+        got = np.isposinf(gu.to_host(scores))
+        for b in range(B):
+            for h in range(Hkv):
+                assert np.array_equal(got[b, 0, h], _slots(nov[b, 0, h] if per_head else nov[b], T))
+
+
+@pytest.mark.parametrize("units,n,k", [(100, 600, 300), (128, 256, 100), (3, 5000, 2500), (1, 27000, 26625)])
+def test_compress_keeps_what_the_scores_say(units, n, k):
+    """Selection and compaction by several workgroups per unit on slots found before, against the oracle's selection of the same scores;
+    more kept tokens than leave the last word of a unit free."""
+    g = torch.Generator(device="cuda").manual_seed(units + n)
+    Q, K, V = (torch.randn((1, 1, units, m, 64), generator=g, device="cuda").to(torch.bfloat16) for m in (3, n, n))
+    nov = torch.round(torch.rand((1, 1, units, n), generator=g, device="cuda") * 64) / 64
+    K0, nov0 = K.clone(), nov.clone()
+    shape = ip.make_shape(Q, K, nov, k=k, T=k // 2, pool_w=3)
+    ws = ip.alloc_workspace(shape)
+    ws.fill_(0xA5)
+    keep, scores = torch.empty((1, 1, units, k), dtype=torch.int32, device="cuda"), torch.empty((1, 1, units, n), device="cuda")
+    print(f"compress on known slots units={units} n={n} k={k}", flush=True)
+    assert ip.ccd_compress(shape, Q, K, V, nov, keep, ws, scores=scores) == ip.CCD_OK
+    kh, sh = gu.to_host(keep).reshape(units, k), gu.to_host(scores).reshape(units, n)
+    for i in range(units):
+        assert np.array_equal(np.isposinf(sh[i]), _slots(gu.to_host(nov0).reshape(units, n)[i], k // 2))
+    assert np.array_equal(kh, np.stack([O.select(r, k) for r in sh]))
+    assert torch.equal(K[..., :k, :], torch.gather(K0, 3, keep.long()[..., None].expand(-1, -1, -1, -1, 64)))
+    assert torch.equal(nov[..., :k], torch.gather(nov0, 3, keep.long()))
