@@ -586,9 +586,9 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
     // every wait for K fragments would become a wait for everything.
     // (Row groups: a token's sum is that of its groups, added up in this order by the waves of the part behind a barrier.  Every part
     // then counts the same number of blocks, some of them without a tile.)
-    const int n_blocks = RG == 1 ? (s1p - s0 + kUBlock - 1) / kUBlock : (per + (rem > 0 || ragged ? 1 : 0) + kUBlock - 1) / kUBlock;
-    for (int blk = 0; blk < n_blocks; ++blk) {
-      const int sb = max(s0, s1p - blk * kUBlock), sa = max(s0, sb - kUBlock);        // this block: tiles [sa, sb)
+    const int s_end = RG == 1 ? s0 : s1p - (per + (rem > 0 || ragged ? 1 : 0));       // (not above s0)
+    for (int s_blk = s1p; s_blk > s_end; s_blk -= kUBlock) {
+      const int sb = RG == 1 ? s_blk : max(s0, s_blk), sa = max(s0, sb - kUBlock);    // this block: tiles [sa, sb)
       float* ub = sm.ubuf[wave];
       if (RG == 1 || sa < sb) {
       float nl[kQB][16];      // normalisers of the pair being folded; each half is reloaded as soon as it is done with
