@@ -268,6 +268,7 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
                                                                      int chunk_rows, uint32_t* sync, int nuc_known) {
   constexpr bool ROPE = ROWB > 0;
   constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
+  constexpr bool kNuc = SHARED && kRegs && 4 * CH * THREADS <= kNoveltyMaxRow;       // the slots may be known
   __shared__ SelectShared<THREADS, CH> sh;
   // The kept list: in LDS for short rows; a long row leaves no room for it, and it is read back from keep_idx, where this
   // workgroup has just put it
@@ -283,8 +284,8 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
   float* nov = (D.T > 0 || carry_novelty) ? novelty + nov_offset(D, ui) : nullptr;
   {
     Row<THREADS, CH> row(D, sh, unit, u, nullptr, nov);
-    const uint32_t* nuc_words = nuc_known ? sync + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
-    select_row<THREADS, CH, true, SHARED>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, nuc_words,
+    const uint32_t* nuc_words = kNuc && nuc_known ? sync + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
+    select_row<THREADS, CH, true, kNuc>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, nuc_words,
                          [&](int pos, int t, int c, int i) {
                            if (kRegs) keep_lds[pos] = (uint16_t)t;
                            else       keep_out[pos] = t;

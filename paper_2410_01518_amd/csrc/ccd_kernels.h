@@ -36,6 +36,7 @@ constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgrou
 // when novelty is shared by layers and heads).  The last word belongs to the marks of calls that keep more than kNoveltyMaxKept tokens:
 // chunks are of at least 64 rows where there are more of them than workgroups.
 constexpr int kSyncTicket = 0, kSyncNovelty = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16, kSyncNoveltyTies = 15;
+constexpr int kNoveltyMaxRow = 8192;      // the longest row whose slots are found beside the scores
 constexpr int kNoveltyMaxKept = (kSyncMarkWords - 1) * 32 * 64;
 constexpr uint32_t kSyncOneSelected = 1u << 16;
 

@@ -137,7 +137,8 @@ __device__ __forceinline__ void tile_logits(floatx16 (&acc)[SH::QB], const uint8
 // 256 rows 89.3 -> 85.8, but 1 unit 49.2 -> 53.7, whose score pass is shorter than this.)
 // Not inlined: the kernel around it has no registers to spare.
 // The longest row.  (32 tokens a thread are 180 registers; bf16 rows of 64 elements are scored with 126, four workgroups to a compute unit.)
-constexpr int kNoveltyRow = 32 * kMT;
+constexpr int kNoveltyRow = kNoveltyMaxRow;
+static_assert(kNoveltyRow == 32 * kMT, "");
 constexpr int novelty_row(int d, bool f32) { return d == 64 && !f32 ? 16 * kMT : kNoveltyRow; }
 struct NoveltyLds {
   TopkShared<kMT> topk;

@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kSelThreads) void finalize_select_kernel(Dims D, co
   Row<kSelThreads, CH> row(D, sh, unit, GIVEN ? nullptr : u, GIVEN ? scores : nullptr, nov);
   int32_t* out = SELECT ? keep_idx + (int64_t)unit * D.k : nullptr;
   const uint32_t* words = nuc_words != nullptr ? nuc_words + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
-  select_row<kSelThreads, CH, SELECT, !GIVEN && CH != kLongRow>(row, scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, words,
+  select_row<kSelThreads, CH, SELECT, !GIVEN && (CH > 0 && 4 * CH * kSelThreads <= kNoveltyMaxRow)>(row, scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, words,
                          [&](int pos, int t, int, int) {
                            // (a row that is pooled anew in every step may be overwritten meanwhile by a call that overlaps on
                            // the workspace: the list is undefined then, but stays in its place)

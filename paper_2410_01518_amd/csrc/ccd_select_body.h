@@ -261,15 +261,7 @@ struct Row {
       for (int i = 0; i < 4; ++i) slot |= k[i] > from || (k[i] == from && (uint32_t)(token(c) + i) < ties_end) ? 1u << i : 0u;
       slots |= (uint64_t)slot << (4 * c);
     };
-    if constexpr (kRegs) {
-      each_novelty_chunk(take);
-    } else {
-      chunks<Vals4>([&](float (&f)[4], int c) { load_row4(f, nov, token(c), D.n, -INFINITY); },
-                    [&](float (&f)[4], int c) {
-                      const uint32_t k[4] = {novelty_key(f[0]), novelty_key(f[1]), novelty_key(f[2]), novelty_key(f[3])};
-                      take(k, c);
-                    });
-    }
+    each_novelty_chunk(take);
   }
   __device__ __forceinline__ void load_novelty() {
     if constexpr (kRegs) {
@@ -362,7 +354,7 @@ struct Row {
 // scores together; one after the other where they take turns in LDS), two per threshold, ranks - six in all, or seven; four with known slots.
 template <int THREADS, int CH, bool SELECT, bool NUC, class Emit>
 __device__ __forceinline__ void select_row(Row<THREADS, CH>& row, float* scores_row, const uint32_t* nuc_words, Emit&& emit) {
-  static_assert(!NUC || CH != kLongRow, "a long row keeps no slots in registers");
+  static_assert(!NUC || CH > 0, "rows in registers");
   using R = Row<THREADS, CH>;
   const Dims& D = row.D;
   SelectShared<THREADS, CH>& sh = row.sh;
