@@ -364,6 +364,17 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) { nm[p][qb] = -kNegHuge * c; Z[p][qb][0] = 0.f; Z[p][qb][1] = 0.f; }
       float m_ref[NP][kQB], Zs[NP][kQB];       // (reference, sum) pairs once the sweep is done
+      // Row groups: the wave's part of the tokens is RG quarters, so its sums are taken in RG runs of tiles, or their chains of additions would
+      // be RG times as long (rms error of the log-sum-exp of 32768 tokens, relative: 1.6e-7 by quarters or runs, 3.5e-7 by halves and 6.8e-7 in one
+      // piece; of 4096 tokens 0.8e-7, 1.4e-7, 2.4e-7).  Finished runs wait in LDS, where pass 2 will have its token sums: there is no register
+      // left.  (Append + distill without and with the runs: 256 units, 4096 tokens and 512 / 1024 rows 477.7 / 702.2 and
+      // 477.8 / 702.4 us, 600 tokens and 1024 rows 125.1 and 125.3; 640 units of 32768 tokens and 1024 rows 14.01 and 14.01 ms.)
+      [[maybe_unused]] const int run = ((s1 - s0 + RG - 1) / RG + 1) & ~1;          // tiles: two per round of the loop
+      [[maybe_unused]] float* z_runs = sm.ubuf[wave] + lane;
+      if constexpr (RG > 1) {
+#pragma unroll
+        for (int e = 0; e < NP * kQB; ++e) z_runs[e * 64] = 0.f;
+      }
       // chunk j of the fold of pair P: elements j EPC .. + EPC - 1 of the 32 accumulator registers
 #define CCD_FOLD1(CUR, P)                                                                 \
       [&](int j) {                                                                        \
@@ -433,16 +444,28 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
         // (No branch inside a tile and none between the two tiles of the loop body: with straight-line code the
         // compiler can tell how many loads are in flight at every wait.  Behind the wave's last tile the last step
         // computes the logits of that tile's first pair once more; nobody reads them.)
-        while (s + 1 < s1) {
-          CCD_P1_TILE(1, 0, accA, accB)
-          ++s;
-          if constexpr (NP % 2 == 1) {
-            CCD_P1_TILE(0, 1, accB, accA)
-          } else {
-            CCD_P1_TILE(0, 1, accA, accB)
+        do {
+          const int s_run = RG == 1 ? s1 : min(s + run, s1);
+          while (s + 1 < s_run) {
+            CCD_P1_TILE(1, 0, accA, accB)
+            ++s;
+            if constexpr (NP % 2 == 1) {
+              CCD_P1_TILE(0, 1, accB, accA)
+            } else {
+              CCD_P1_TILE(0, 1, accA, accB)
+            }
+            ++s;
           }
-          ++s;
-        }
+          if constexpr (RG > 1) {
+#pragma unroll
+            for (int e = 0; e < NP * kQB; ++e) {
+              float(&z)[2] = Z[e / kQB][e % kQB];
+              z_runs[e * 64] += z[0] + z[1];
+              z[0] = 0.f;
+              z[1] = 0.f;
+            }
+          }
+        } while (RG > 1 && s + 1 < s1);
         if (s < s1) {
           CCD_P1_TILE(1, 0, accA, accB)
         }
@@ -458,22 +481,41 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
 #pragma unroll
           for (int qb = 0; qb < kQB; ++qb) {
             Zs[p][qb] = Z[p][qb][0] + Z[p][qb][1];
+            if constexpr (RG > 1) Zs[p][qb] += z_runs[(p * kQB + qb) * 64];
             m_ref[p][qb] = -nm[p][qb] * inv_c;
             bad |= !(Zs[p][qb] < INFINITY);
           }
         if (__any(bad)) {
+          int t = s0;
+          do {
+            const int t_run = t, t_end = RG == 1 ? s1 : min(t + run, s1);
 #pragma unroll
-          for (int p = 0; p < NP; ++p)
+            for (int p = 0; p < NP; ++p)
 #pragma unroll
-            for (int qb = 0; qb < kQB; ++qb) { m_ref[p][qb] = kNegHuge; Zs[p][qb] = 0.f; }
-          for (int t = s0; t < s1; ++t) {
-            CCD_TILE_NOW(0, t)
-            static_for<0, NP>([&](auto Pc) {
-              constexpr int p = decltype(Pc)::value;
-              logits_now<SH, 1, p>(accA, a[0]);
-              fold_stats<false>(accA, m_ref[p], Zs[p], c, half, kStep);
-            });
-          }
+              for (int qb = 0; qb < kQB; ++qb) { m_ref[p][qb] = kNegHuge; Zs[p][qb] = 0.f; }
+            for (; t < t_end; ++t) {
+              CCD_TILE_NOW(0, t)
+              static_for<0, NP>([&](auto Pc) {
+                constexpr int p = decltype(Pc)::value;
+                logits_now<SH, 1, p>(accA, a[0]);
+                fold_stats<false>(accA, m_ref[p], Zs[p], c, half, kStep);
+              });
+            }
+            if constexpr (RG > 1) {          // one (maximum, sum) pair with those of the runs before
+#pragma unroll
+              for (int e = 0; e < NP * kQB; ++e) {
+                float &m = m_ref[e / kQB][e % kQB], &z = Zs[e / kQB][e % kQB];
+                float* pair = z_runs + 2 * e * 64;
+                if (t_run > s0) {
+                  const float M = fmaxf(m, pair[0]);
+                  z = z * fast_exp2((m - M) * c) + pair[64] * fast_exp2((pair[0] - M) * c);
+                  m = M;
+                }
+                pair[0] = m;
+                pair[64] = z;
+              }
+            }
+          } while (RG > 1 && t < s1);
         } else {
           // move each reference to where its sum is of order one (Z = mant * 2^e -> reference + e / c): the ragged
           // tile and the merges expect the magnitudes of a (maximum, sum) pair
