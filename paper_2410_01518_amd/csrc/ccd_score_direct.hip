@@ -135,7 +135,9 @@ __device__ __forceinline__ void tile_logits(floatx16 (&acc)[SH::QB], const uint8
 // fp32 tokens 26.5 -> 25.4 us, 8 units of 2048 / 8192 tokens 31.4 / 59.6 -> 30.2 / 57.0, 2 units of 5000 tokens and 16 rows 37.5 -> 35.1; 45
 // units of 3000 tokens step by step 48.2 -> 45.5.  Bound by latency; rows are kept in registers.  (Rows of 16384 tokens: 8 units and
 // 256 rows 89.3 -> 85.8, but 1 unit 49.2 -> 53.7, whose score pass is shorter than this.)
-// Not inlined: the kernel around it has no registers to spare.
+// Not inlined: the kernel around it has no registers to spare.  NOV = false: the same kernel without these workgroups, for the other calls and
+// for pass 2 behind a pass 1 that had them; the call costs up to 18 spilled scalar registers and 12 bytes of scratch per lane (without
+// NuC slots, 4 units of 512 / 16 of 1000 fp32 tokens 24.5 / 36.6 us with it, 23.8 / 35.8 without).
 // The longest row.  (32 tokens a thread are 180 registers; bf16 rows of 64 elements are scored with 126, four workgroups to a compute unit.)
 constexpr int kNoveltyRow = kNoveltyMaxRow;
 static_assert(kNoveltyRow == 32 * kMT, "");
@@ -208,20 +210,23 @@ __device__ __noinline__ void find_novelty_key(const float* __restrict__ nov, int
   if (threadIdx.x == 0) words[kSyncNovelty] = th.tau;
 }
 
-template <int HD, class ET, int PASS>
+template <int HD, class ET, int PASS, bool NOV>
 __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan pl, const ET* __restrict__ Q, const ET* __restrict__ K,
                                                               const ET* __restrict__ Kcap, float2* __restrict__ part,
                                                               float* lse_io, float* __restrict__ u, const float* novelty, int nov_wgs) {
   using SH = DirectShape<HD, ET>;
   constexpr int KS = HD / 16, QB = SH::QB;
   __shared__ __attribute__((aligned(1024))) uint8_t rows[SH::kSlots * SH::kSlotBytes];
+  // (one value from each of the arguments' five lines: all are asked for together here and not, one miss after the other, where they are used.
+  // 8 units of 2048 tokens 30.0 -> 29.4 us, 48 units of 800 under a window with CaP keys 36.1 -> 35.3; fp32, 4 units of 512 24.8 -> 24.3)
+  asm volatile("" ::"s"(D.GP), "s"(D.unit0), "s"(D.q_sl), "s"(Q), "s"(u));
   const int row_blocks = (D.GP + SH::kRows - 1) / SH::kRows;
   const int slices = PASS == 1 ? pl.n_slices1 + (Kcap != nullptr ? 1 : 0) : pl.n_slices2;
   // consecutive blocks go to different XCDs: the workgroups of one slice are eight blocks apart
   const int per_item = PASS == 1 ? row_blocks : 1;
   // (the workgroups for novelty come first: they are done long before the others)
-  const int bid = (int)blockIdx.x - (nov_wgs + 7) / 8 * 8;
-  if (bid < 0) {
+  const int bid = (int)blockIdx.x - (NOV ? (nov_wgs + 7) / 8 * 8 : 0);
+  if (NOV && bid < 0) {
     if ((int)blockIdx.x < nov_wgs) {
       const int nu = (int)blockIdx.x * (D.units / nov_wgs);           // every unit's own row, or one for each sequence
       const float* row = novelty + nov_offset(D, decode_unit(D, nu));
@@ -512,7 +517,7 @@ void launch_stats_direct(const Dims& D, const ScorePlan& pl, const void* Q, cons
   const int rows = D.dtype == 0 ? 32 : 64, row_blocks = (D.GP + rows - 1) / rows;
   const dim3 grid(direct_grid(D, pl.n_slices1 + (K_cap != nullptr ? 1 : 0), row_blocks) + (nov_wgs + 7) / 8 * 8), block(kMT);
 #define CCD_LAUNCH(HD, ET)                                                                                                       \
-  launch((score_direct_kernel<HD, ET, 1>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, part, nullptr, \
+  launch((nov_wgs > 0 ? score_direct_kernel<HD, ET, 1, true> : score_direct_kernel<HD, ET, 1, false>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, part, nullptr, \
          nullptr, novelty, nov_wgs)
   if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
   else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
@@ -523,7 +528,7 @@ void launch_prob_direct(const Dims& D, const ScorePlan& pl, const void* Q, const
                         float* lse_io, float* u, const float* novelty, int nov_wgs, hipStream_t s) {
   const dim3 grid(direct_grid(D, pl.n_slices2, 1) + (nov_wgs + 7) / 8 * 8), block(kMT);
 #define CCD_LAUNCH(HD, ET)                                                                                          \
-  launch((score_direct_kernel<HD, ET, 2>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, \
+  launch((nov_wgs > 0 ? score_direct_kernel<HD, ET, 2, true> : score_direct_kernel<HD, ET, 2, false>), grid, block, s, D, pl, (const ET*)Q, (const ET*)K, (const ET*)K_cap, \
          const_cast<float2*>(part), lse_io, u, novelty, nov_wgs)
   if (D.dtype == 0) { if (D.d == 64) CCD_LAUNCH(64, float); else CCD_LAUNCH(128, float); }
   else              { if (D.d == 64) CCD_LAUNCH(64, uint16_t); else CCD_LAUNCH(128, uint16_t); }
