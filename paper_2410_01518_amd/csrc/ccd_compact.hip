@@ -444,29 +444,32 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(Dims D, const char* __re
 
 bool select_compact_supported(const Dims& D) { return D.n <= kLdsRowTokens; }
 
+// Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
+// sh_unroll rows per thread; 32 marks per word bound the number of chunks.
+static int log2_row_lanes(const Dims& D) { return (D.d == 128 ? 4 : 3) + (D.dtype == 0 ? 1 : 0); }      // 16-byte lanes of a row
+struct SharedCut { int per_unit, chunk_rows; };            // (one workgroup per unit: not shared)
+static SharedCut shared_cut(const Dims& D, bool rope) {
+  const int threads = sc_threads(true, D.n), rows_per_pass = threads >> log2_row_lanes(D);
+  const int max_rows = rows_per_pass * sh_unroll(threads, rope);
+  const int per_unit = std::min(kSharedFillWorkgroups / std::max(D.units_run, 1), (D.k + rows_per_pass - 1) / rows_per_pass);
+  if (per_unit <= 1) return {1, 0};
+  const int rows = std::min((D.k + per_unit - 1) / per_unit, max_rows);
+  const int chunk_rows = (rows + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
+  if (D.k > chunk_rows * 32 * kSyncMarkWords) return {1, 0};
+  return {std::min(per_unit, (D.k + chunk_rows - 1) / chunk_rows), chunk_rows};
+}
+bool select_compact_shares_units(const Dims& D, bool rope) { return shared_cut(D, rope).per_unit > 1; }
+
 // pooling + NuC lift + top-k + in-place compaction of K and V (and of carried per-head novelty).
 // Krot != nullptr: CR-RoPE of the kept keys on the side (rope_cos / rope_sin: [>= k, d/2] fp32).
-// sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units.
+// sync: kSyncWords words per unit, as the first score kernel of the call leaves them; null for more than kMaxSharedUnits units.
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
                            uint32_t* sync, bool nuc_known, hipStream_t s) {
-  const int rowb = D.d * (D.dtype == 0 ? 4 : 2);
-  const int row_shift = rowb == 128 ? 3 : (rowb == 256 ? 4 : 5);
-  // Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
-  // sh_unroll rows per thread; 32 marks per word bound the number of chunks.
-  const int shared_threads = sc_threads(true, D.n);
-  const int rows_per_pass = shared_threads >> row_shift;
-  const int max_rows = rows_per_pass * sh_unroll(shared_threads, Krot != nullptr);
-  int per_unit = std::min(kSharedFillWorkgroups / std::max(D.units_run, 1), (D.k + rows_per_pass - 1) / rows_per_pass);
-  int chunk_rows = 0;
-  if (per_unit > 1) {
-    chunk_rows = std::min((D.k + per_unit - 1) / per_unit, max_rows);
-    chunk_rows = (chunk_rows + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
-    if (D.k > chunk_rows * 32 * kSyncMarkWords) per_unit = 1;
-    else per_unit = std::min(per_unit, (D.k + chunk_rows - 1) / chunk_rows);
-  }
+  const int rowb = D.d * (D.dtype == 0 ? 4 : 2), row_shift = log2_row_lanes(D);
+  const SharedCut cut = shared_cut(D, Krot != nullptr);
+  const int per_unit = cut.per_unit, chunk_rows = cut.chunk_rows;
   const bool shared = per_unit > 1;
-  if (!shared) per_unit = 1;
   const int chunks = shared ? (D.k + chunk_rows - 1) / chunk_rows : 0;
   const int threads = sc_threads(shared, D.n);
   const dim3 grid((unsigned)D.units_run * per_unit), block(threads);

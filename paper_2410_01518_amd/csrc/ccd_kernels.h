@@ -33,8 +33,8 @@ struct Dims {
 constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgroups / 2;
 // kSyncTicket: tickets in the lower half, workgroups that have selected in the upper one.  kSyncNovelty, kSyncNoveltyTies: tokens with a larger
 // novelty key than the one have a NuC slot, those with this key before token number the other (launch_*_direct; of the sequence's first unit
-// when novelty is shared by layers and heads).  The last word belongs to the marks of calls that keep more than kNoveltyMaxKept tokens:
-// chunks are of at least 64 rows where there are more of them than workgroups.
+// when novelty is shared by layers and heads).  The last word belongs to the marks of calls that keep more than kNoveltyMaxKept tokens
+// (chunks are of at least 64 rows where there are more of them than workgroups).
 constexpr int kSyncTicket = 0, kSyncNovelty = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16, kSyncNoveltyTies = 15;
 constexpr int kNoveltyMaxRow = 8192;      // the longest row whose slots are found beside the scores
 constexpr int kNoveltyMaxKept = (kSyncMarkWords - 1) * 32 * 64;
@@ -138,8 +138,10 @@ void launch_finalize_select(const Dims& D, const float* u, const float* novelty,
 
 // selection and compaction of a unit in one workgroup (rows short enough to be staged in LDS)
 bool select_compact_supported(const Dims& D);
-// (sync: kSyncWords zeros per unit, null for more than kMaxSharedUnits units; carry_novelty: the novelty is carried per head
-// and its kept entries are compacted in place like the rows; nuc_known: the words hold kSyncNovelty)
+// ... or in several workgroups per unit, which take NuC slots that are known (one finds them for itself, beside the scores' classes)
+bool select_compact_shares_units(const Dims& D, bool rope);
+// (sync: kSyncWords words per unit as the first score kernel leaves them, null for more than kMaxSharedUnits units; carry_novelty: the novelty
+// is carried per head and its kept entries are compacted in place like the rows; nuc_known: the words hold kSyncNovelty)
 void launch_select_compact(const Dims& D, const float* u, float* novelty, bool carry_novelty, float* scores,
                            int32_t* keep_idx, void* K, void* V, const float* rope_cos, const float* rope_sin, void* Krot,
                            uint32_t* sync, bool nuc_known, hipStream_t s);

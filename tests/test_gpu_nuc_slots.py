@@ -53,6 +53,26 @@ def test_slots_are_the_most_novel_tokens(n, d, fp32, per_head, option, kind):
                 assert np.array_equal(got[b, 0, h], _slots(nov[b, 0, h] if per_head else nov[b], T))
 
 
+@pytest.mark.parametrize("d,dtype,rope,most", [(64, torch.bfloat16, False, 64), (128, torch.bfloat16, True, 32), (128, torch.float32, False, 16)])
+def test_slots_are_found_only_for_units_that_are_shared(d, dtype, rope, most):
+    """A unit whose kept rows one workgroup moves in one go (512 threads, 16 bytes each) is not shared, and its selection finds the slots
+    itself: nothing is written to its words of the workspace (the last 64 bytes per unit, rounded up to 256)."""
+    units, n = 4, 1000
+    for k in (most, most + 1):
+        Q, K, V = (torch.randn((1, 1, units, m, d), device="cuda").to(dtype) for m in (3, n, n))
+        nov = torch.rand((1, n), device="cuda")
+        shape = ip.make_shape(Q, K, nov, k=k, T=k // 2, pool_w=3)
+        ws, keep = ip.alloc_workspace(shape), torch.empty((1, 1, units, k), dtype=torch.int32, device="cuda")
+        ws.fill_(0xA5)
+        if rope:
+            tables = torch.ones((n, d // 2), device="cuda")
+            ip.ccd_compress_rope(shape, Q, K, V, nov, keep, tables, tables, torch.empty_like(K), ws)
+        else:
+            ip.ccd_compress(shape, Q, K, V, nov, keep, ws)
+        words = ws[-256:].view(torch.int32).reshape(units, 16)
+        assert (int(words[0, 1]) == -0x5A5A5A5B) == (k == most)          # (shared novelty: the words of the sequence's first unit)
+
+
 @pytest.mark.parametrize("units,n,k", [(100, 600, 300), (128, 256, 100), (3, 5000, 2500), (1, 27000, 26625)])
 def test_compress_keeps_what_the_scores_say(units, n, k):
     """Selection and compaction by several workgroups per unit on slots found before, against the oracle's selection of the same scores;
