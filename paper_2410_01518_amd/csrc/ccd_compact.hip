@@ -446,6 +446,11 @@ bool select_compact_supported(const Dims& D) { return D.n <= kLdsRowTokens; }
 
 // Several workgroups per unit as long as there is a compute unit for each, in chunks of at least one and at most
 // sh_unroll rows per thread; 32 marks per word bound the number of chunks.
+// A call with more chunks than workgroups has the largest ones.  The last word of marks, which holds something else where slots are found
+// beside the scores, is therefore only reached by calls that keep more than kNoveltyMaxKept tokens:
+constexpr int largest_chunk(int threads) { return (threads >> 5) * sh_unroll(threads, true); }         // rows of 512 bytes, CR-RoPE
+static_assert(std::min(largest_chunk(512), largest_chunk(1024)) * 32 * (kSyncMarkWords - 1) >= kNoveltyMaxKept, "");
+static_assert(kSharedFillWorkgroups <= 32 * (kSyncMarkWords - 1), "");
 static int log2_row_lanes(const Dims& D) { return (D.d == 128 ? 4 : 3) + (D.dtype == 0 ? 1 : 0); }      // 16-byte lanes of a row
 struct SharedCut { int per_unit, chunk_rows; };            // (one workgroup per unit: not shared)
 static SharedCut shared_cut(const Dims& D, bool rope) {

@@ -34,10 +34,11 @@ constexpr int kSharedFillWorkgroups = 256, kMaxSharedUnits = kSharedFillWorkgrou
 // kSyncTicket: tickets in the lower half, workgroups that have selected in the upper one.  kSyncNovelty, kSyncNoveltyTies: tokens with a larger
 // novelty key than the one have a NuC slot, those with this key before token number the other (launch_*_direct; of the sequence's first unit
 // when novelty is shared by layers and heads).  The last word belongs to the marks of calls that keep more than kNoveltyMaxKept tokens
-// (chunks are of at least 64 rows where there are more of them than workgroups).
+// (shared_cut in ccd_compact.hip); slots are found beside the scores of rows of at most kNoveltyMaxRow tokens.
 constexpr int kSyncTicket = 0, kSyncNovelty = 1, kSyncMarks = 2, kSyncMarkWords = 14, kSyncWords = 16, kSyncNoveltyTies = 15;
 constexpr int kNoveltyMaxRow = 8192;      // the longest row whose slots are found beside the scores
 constexpr int kNoveltyMaxKept = (kSyncMarkWords - 1) * 32 * 64;
+static_assert(kNoveltyMaxRow <= kNoveltyMaxKept, "no call uses the last word for both");
 constexpr uint32_t kSyncOneSelected = 1u << 16;
 
 // (an argument of every score kernel: 8 bytes more, for one int that left padding, took 0.1 us a launch)

@@ -53,7 +53,6 @@ struct DirectShape {
   static constexpr int kSlots = QB + 4 * kTiles;
   static_assert(4 * QB + kTiles <= kSlots && 2 * QB + 2 * kTiles <= kSlots, "any number of row blocks");
   static_assert(kDirectMaxSlice2 * 4 <= QB * kSlotBytes, "the sums of a row block fit where its rows were");
-  static_assert(kSlots * kSlotBytes >= 16 << 10, "what find_novelty_key keeps fits");
 };
 
 // 64 x 16 bytes from the lanes' own addresses to consecutive LDS addresses (lds_addr: the same in all lanes)
@@ -220,6 +219,7 @@ __global__ __launch_bounds__(kMT, 2) void score_direct_kernel(Dims D, ScorePlan 
   // (one value from each of the arguments' five lines: all are asked for together here and not, one miss after the other, where they are used.
   // 8 units of 2048 tokens 30.0 -> 29.4 us, 48 units of 800 under a window with CaP keys 36.1 -> 35.3; fp32, 4 units of 512 24.8 -> 24.3)
   asm volatile("" ::"s"(D.GP), "s"(D.unit0), "s"(D.q_sl), "s"(Q), "s"(u));
+  static_assert(sizeof(NoveltyLds) <= sizeof(rows), "what find_novelty_key keeps fits");
   const int row_blocks = (D.GP + SH::kRows - 1) / SH::kRows;
   const int slices = PASS == 1 ? pl.n_slices1 + (Kcap != nullptr ? 1 : 0) : pl.n_slices2;
   // consecutive blocks go to different XCDs: the workgroups of one slice are eight blocks apart
@@ -488,7 +488,7 @@ void plan_direct(const Dims& D, int compute_units, ScorePlan& pl) {
 }
 
 int novelty_workgroups(const Dims& D, int compute_units, const ScorePlan& pl, bool cap_keys, bool lse_given) {
-  if (D.T <= 0 || D.units > kMaxSharedUnits || D.units_run != D.units || D.k > kNoveltyMaxKept || D.n > novelty_row(D.d, D.dtype == 0)) return 0;
+  if (D.T <= 0 || D.units > kMaxSharedUnits || D.units_run != D.units || D.n > novelty_row(D.d, D.dtype == 0)) return 0;
   const int wgs = D.nov_sl != 0 || D.nov_sh != 0 ? D.units : D.B;
   const int scores = lse_given ? direct_grid(D, pl.n_slices2, 1) : direct_grid(D, pl.n_slices1 + (cap_keys ? 1 : 0), direct_cut(D).row_blocks);
   const int all = scores + (wgs + 7) / 8 * 8;
