@@ -30,7 +30,7 @@ def _score(cfg, gain=1.0, path=0, K_cap=None):
 
 
 # P: one CaP token, a ragged block, exactly one and two key tiles, one past them, more than two tiles;
-# G * P: below one wave's share, one sweep, more than one sweep of 256 query rows
+# G * P: below one wave's share, one sweep, more than 256 query rows
 KCAT_CASES = [
     dict(P=1, Hq=2, Hkv=2),
     dict(P=9),

@@ -56,7 +56,7 @@ def _score_lse(cfg, inp, lse, window=0, path=0):
 LSE_CASES = [
     dict(),
     dict(P=1, Hq=2, Hkv=2, d=64, N=513, k=100, T=0, w=1),
-    dict(P=40, Hq=16, Hkv=2, d=64, N=515, k=200),                                  # G*P = 320: two sweeps
+    dict(P=40, Hq=16, Hkv=2, d=64, N=515, k=200),                                  # G*P = 320: two row groups
     dict(B=2, L=1, N=1111, k=10, T=3, w=5, keys="zipf"),
     dict(dtype="fp32", d=64, Hq=4, Hkv=4, N=512, k=256, P=16, T=128, w=1),
     dict(dtype="fp32", N=300, k=120, T=30, P=33, w=3),

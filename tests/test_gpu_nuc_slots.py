@@ -53,6 +53,46 @@ def test_slots_are_the_most_novel_tokens(n, d, fp32, per_head, option, kind):
                 assert np.array_equal(got[b, 0, h], _slots(nov[b, 0, h] if per_head else nov[b], T))
 
 
+@pytest.mark.parametrize("n", [4097, 5000, 8192])
+@pytest.mark.parametrize("d,dtype", [(128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("per_head,rope", [(False, False), (True, False), (True, True), (False, True)])
+def test_compress_of_long_shared_rows(n, d, dtype, per_head, rope):
+    """Rows of 4097 to 8192 tokens: the shared selection with two chunks per thread, which takes slots found beside the scores (its words of
+    the workspace say so).  Novelty in steps of 1/32 that the last slot and the tokens behind it share, and values that never take one."""
+    units, k, T = 3, n // 2, n // 5
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    Q, K, V = (torch.randn((1, 1, units, m, d), generator=g, device="cuda").to(dtype) for m in (5, n, n))
+    nov = torch.round(torch.rand((1, 1, units, n) if per_head else (1, n), generator=g, device="cuda") * 32) / 32
+    nov[..., 7::97], nov[..., 11::89], nov[..., 3::1013] = float("nan"), float("-inf"), float("inf")
+    K0, V0, nov0 = K.clone(), V.clone(), nov.clone()
+    shape = ip.make_shape(Q, K, nov, k=k, T=T, pool_w=5)
+    ws = ip.alloc_workspace(shape)
+    ws.fill_(0xA5)
+    keep, scores = torch.empty((1, 1, units, k), dtype=torch.int32, device="cuda"), torch.empty((1, 1, units, n), device="cuda")
+    print(f"long shared rows n={n} d={d} {dtype} per_head={per_head} rope={rope}", flush=True)
+    if rope:
+        ang = torch.outer(torch.arange(k, device="cuda", dtype=torch.float32), torch.rand(d // 2, generator=g, device="cuda"))
+        K_rot, want_rot = torch.zeros_like(K), torch.zeros_like(K)
+        ip.ccd_compress_rope(shape, Q, K, V, nov, keep, ang.cos(), ang.sin(), K_rot, ws, scores=scores)
+        ip.ccd_cr_rope(shape, K, ang.cos(), ang.sin(), k, want_rot)
+        assert torch.equal(K_rot, want_rot)
+    else:
+        ip.ccd_compress(shape, Q, K, V, nov, keep, ws, scores=scores)
+    words = ws[-256:].view(torch.int32).reshape(4, 16)[: units if per_head else 1]
+    assert not (words[:, 1] == -0x5A5A5A5B).any()
+    kh, sh, nh = gu.to_host(keep).reshape(units, k), gu.to_host(scores).reshape(units, n), gu.to_host(nov0).reshape(-1, n)
+    for i in range(units):
+        assert np.array_equal(np.isposinf(sh[i]), _slots(nh[i if per_head else 0], T))
+    assert np.array_equal(kh, np.stack([O.select(r, k) for r in sh]))
+    at = keep.long()
+    for moved, src in ((K, K0), (V, V0)):
+        assert torch.equal(moved[..., :k, :], torch.gather(src, 3, at[..., None].expand(-1, -1, -1, -1, d)))
+    if per_head:
+        assert torch.equal(nov[..., :k].view(torch.int32), torch.gather(nov0, 3, at).view(torch.int32))
+    else:
+        assert torch.equal(nov.view(torch.int32), nov0.view(torch.int32))
+
+
 @pytest.mark.parametrize("d,dtype,rope,most", [(64, torch.bfloat16, False, 64), (128, torch.bfloat16, True, 32), (128, torch.float32, False, 16)])
 def test_slots_are_found_only_for_units_that_are_shared(d, dtype, rope, most):
     """A unit whose kept rows one workgroup moves in one go (512 threads, 16 bytes each) is not shared, and its selection finds the slots
@@ -75,8 +115,8 @@ def test_slots_are_found_only_for_units_that_are_shared(d, dtype, rope, most):
 
 @pytest.mark.parametrize("units,n,k", [(100, 600, 300), (128, 256, 100), (3, 5000, 2500), (1, 27000, 26625)])
 def test_compress_keeps_what_the_scores_say(units, n, k):
-    """Selection and compaction by several workgroups per unit on slots found before, against the oracle's selection of the same scores;
-    more kept tokens than leave the last word of a unit free."""
+    """Selection and compaction by several workgroups per unit, against the oracle's selection of the same scores: on slots found before (600 and
+    256 tokens), on its own (5000 tokens of 64 bf16 elements), and with more kept tokens than leave the last word of a unit free."""
     g = torch.Generator(device="cuda").manual_seed(units + n)
     Q, K, V = (torch.randn((1, 1, units, m, 64), generator=g, device="cuda").to(torch.bfloat16) for m in (3, n, n))
     nov = torch.round(torch.rand((1, 1, units, n), generator=g, device="cuda") * 64) / 64

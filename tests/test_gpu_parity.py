@@ -104,7 +104,7 @@ SCORE_CASES = [
     dict(keys="outlier1pct", Hq=8, Hkv=2, N=2048, k=1024, P=32, T=512),           # config-2 shape, fewer heads
     dict(B=2, L=1, Hq=16, Hkv=2, N=1111, k=10, P=40, T=3, w=5),                   # G*P = 320 > one workgroup of queries
     dict(keys="zipf", B=2, L=1, N=900, k=128, P=16, T=64),
-    dict(dtype="fp32", d=64, B=2, L=1, Hq=16, Hkv=2, N=1111, k=10, P=40, T=3, w=5),   # fp32, two query sweeps, ragged
+    dict(dtype="fp32", d=64, B=2, L=1, Hq=16, Hkv=2, N=1111, k=10, P=40, T=3, w=5),   # fp32, two row groups, ragged
     dict(dtype="fp32", d=64, keys="zipf", N=2600, k=900, T=100),                   # fp32, many tiles per wave
 ]
 
@@ -150,8 +150,8 @@ def test_scores_and_staged_calls(case, pool_mode, score_path):
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 64)])
 @pytest.mark.parametrize("G,P", [(1, 64), (1, 65), (4, 32), (3, 43), (4, 33), (2, 96), (8, 33)])
 def test_unit_kernel_sweep_widths(G, P, dtype, d):
-    """The unit score kernel is built for sweeps of 64, 128 and 256 query rows: G * P at and around the limits (64, 65,
-    128, 129, 132, 192) and beyond one sweep (264), with K_cap for bf16 (the CaP block is computed by the waves that
+    """The unit score kernel is built for waves of 64, 128, 192 and 256 query rows: G * P at and around the limits (64, 65,
+    128, 129, 132, 192) and beyond one wave's rows (264: two row groups), with K_cap for bf16 (the CaP block is computed by the waves that
     own query rows)."""
     cfg = _cfg(dtype=dtype, d=d, B=1, L=2, Hq=2 * G, Hkv=2, P=P, N=777, k=300, T=50, w=3, seed=100 + G * P)
     print(f"sweep widths G*P={G * P} {cfg}", flush=True)

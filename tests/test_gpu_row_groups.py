@@ -31,7 +31,8 @@ def _check(units, N, G, P, d, dtype="bf16", option="", window=0, gains=None):
     call = {"": lambda: ip.ccd_score(shape, dev["Q_cat"], dev["K"], dev["novelty"], scores, ws),
             "kcat": lambda: ip.ccd_score_kcat(shape, dev["Q_cat"], dev["K"], gu.to_dev(K_cap), dev["novelty"], scores, ws),
             "lse": lambda: ip.ccd_score_lse(shape, dev["Q_cat"], dev["K"], gu.to_dev(given), dev["novelty"], scores, ws)}[option]
-    assert "score_unit" in gu.stages_run(call)
+    stages = gu.stages_run(call)
+    assert "score_unit" in stages
     ref = O.compress(inp["Q_cat"], inp["K"], inp["V"], inp["novelty"], k=cfg.k, T=cfg.T, pool_w=cfg.w, K_cap=K_cap,
                      window=window, lse=given)
     if gains and dtype == "fp32":
@@ -40,8 +41,9 @@ def _check(units, N, G, P, d, dtype="bf16", option="", window=0, gains=None):
         got, want = gu.to_host(scores), ref["scores"]
         assert np.array_equal(np.isposinf(got), np.isposinf(want))
         np.testing.assert_allclose(got[np.isfinite(want)], want[np.isfinite(want)], rtol=5e-2, atol=2 * G * P * gu.FLT_MIN)
-        return
+        return stages
     gu.assert_scores_close(gu.to_host(scores), ref["scores"], G * P)
+    return stages
 
 
 # rows: one over a sweep of 256, a sweep of 384 / 512 / 768 / 1024 one short, whole and one over, three sweeps of 384, five of 256;
@@ -68,6 +70,28 @@ def test_cap_keys_and_given_normalisers(N, G, P, d, option):
     (100, 10, 75, 64, 75)])
 def test_windows(N, G, P, d, window, option):
     _check(2, N, G, P, d, option=option, window=window)
+
+
+# two sweeps of 768 and of 1024 rows, the last one partly filled: token sums of several sweeps and several groups
+@pytest.mark.parametrize("N,G,P,d,dtype,option", [(*case, option) for case in [
+    (1, 13, 100, 128, "bf16"), (333, 13, 100, 128, "bf16"), (4129, 10, 130, 64, "bf16"), (255, 16, 96, 64, "bf16"), (161, 16, 125, 128, "bf16"),
+    (4100, 15, 129, 64, "bf16"), (200, 16, 128, 128, "bf16"), (333, 13, 100, 64, "fp32"), (4129, 16, 125, 64, "fp32")]
+    for option in (["", "kcat", "lse"] if case[4] == "bf16" else ["", "lse"])])        # (CaP keys of fp32 caches go to other kernels)
+def test_several_sweeps_of_row_groups(N, G, P, d, dtype, option):
+    _check(2, N, G, P, d, dtype, option)
+
+
+# windowed heads over several sweeps, of 384 (1025, 1026 and 1152 rows), 256 (1280), 768 (1300) and 1024 rows (2000): of 64 tokens, by kernels of
+# their own, and of 96 and 128 tokens inside
+@pytest.mark.parametrize("option", ["", "kcat", "lse"])
+@pytest.mark.parametrize("G,P,d,apart", [
+    (25, 41, 128, True), (9, 114, 64, False), (12, 96, 128, False), (20, 64, 64, True), (10, 128, 128, False), (26, 50, 64, True), (20, 65, 128, False),
+    (13, 100, 64, False), (40, 50, 128, True), (16, 125, 64, False), (25, 80, 128, False)])
+def test_windowed_heads_over_several_sweeps(G, P, d, apart, option):
+    for N, window in ((301, 301), (160, 140)):
+        stages = _check(2, N, G, P, d, option=option, window=window)
+        if window == N:
+            assert ("window_head" in stages) == apart
 
 
 # logits that leave the range of the first tile's reference in the first run of a part, in a later one, in its last or ragged tile; and where

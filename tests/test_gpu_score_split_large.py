@@ -54,7 +54,7 @@ def test_a_row_none_of_whose_visible_keys_is_finite_adds_nothing_by_longer_slice
     _by_longer_slices("", base.test_a_row_none_of_whose_visible_keys_is_finite_adds_nothing, 100, 8, 32, 600, 128, 32, 1)
 
 
-# 81 to 127 units of 64 elements with more than 6000 tokens times sweeps of 256 rows: beyond these the unit kernel is the quicker one, with
+# 81 to 127 units of 64 elements with more than 6000 tokens times blocks of 256 rows: beyond these the unit kernel is the quicker one, with
 # logits good to 2^-16 of sum |q k|.  The six products leave 2e-7 to 4e-7 in the 2-norm and 1.3e-6 at most, the unit kernel 1e-5 and
 # 3.4e-5: four times the former is asked for.
 @pytest.mark.parametrize("units,G,P,n", [(81, 4, 64, 6001), (100, 4, 16, 7000), (127, 1, 33, 6016), (96, 5, 60, 3001)])

@@ -40,7 +40,7 @@ def _score(cfg, window, path=0, with_cap=False, inp=None):
 SWA_CASES = [
     dict(cfg=dict(), window=lambda c: c.N + c.P - 1),
     dict(cfg=dict(), window=lambda c: c.N),
-    dict(cfg=dict(P=40, Hq=16, Hkv=2, d=64, N=515, k=200), window=lambda c: c.N),            # G*P = 320: two sweeps
+    dict(cfg=dict(P=40, Hq=16, Hkv=2, d=64, N=515, k=200), window=lambda c: c.N),            # G*P = 320: two row groups
     dict(cfg=dict(N=1100, k=500, P=33), window=lambda c: c.N - 100),
     dict(cfg=dict(B=2, L=4, Hq=4, Hkv=4, N=900, k=300, P=16, T=50), window=lambda c: c.N - 300),  # many units: short slices
     dict(cfg=dict(N=333, k=100, T=50, P=20), window=lambda c: c.P + 10),                      # nearly everything hidden
@@ -66,7 +66,7 @@ def test_scores_under_a_sliding_window(case, with_cap, path):
     gu.assert_scores_close(got, ref["scores"], cfg.G * cfg.P)
 
 
-# The unit kernel: heads of up to 128 tokens under its own masks (with one sweep of 256 query rows, or with several from 65 tokens on), the
+# The unit kernel: heads of up to 128 tokens under its own masks (from 65 tokens on if there are more than 256 query rows), the
 # others by the head kernels, before and behind it.  (P, heads per unit, window of 400 tokens)
 @pytest.mark.parametrize("option", ["", "kcat", "lse"])
 @pytest.mark.parametrize("P,G,window,apart", [
