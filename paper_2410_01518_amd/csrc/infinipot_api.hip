@@ -156,10 +156,11 @@ static bool direct_pays(const Dims& D, const ScorePlan& direct, int64_t other, b
 // Does the unit kernel leave a windowed head to the two head kernels?  It deals the head's tiles of 32 tokens to its four waves one by one,
 // masked and not pipelined, once per sweep of query rows; the head kernels run several workgroups per compute unit, but cost two
 // launches and the normalisers' way through memory.  Append + distill of 160 to 512 units, 512 to 4096 tokens, head kernels against masks:
-//   one sweep        up to 128 tokens 1.02 to 1.13 times faster by masks (median 1.05), 160 tokens 0.81 to 1.03, 1900 tokens 0.64 to 1.02
-//   several sweeps   96 and 128 tokens 1.02 to 1.08 (medians), 32 and 64 tokens 0.93 to 1.01, 160 tokens 0.81 to 1.00 (sweeps of 256 rows; with
-//                    320 to 1024 rows in one sweep the masks are 1.03 to 1.16 times faster for 32 and 64 tokens as well: 512 rows, 4096 / 600
-//                    tokens 524 / 131 against 503 / 114 us.  The line has stayed where it was.)
+//   one sweep of up to 256 rows   up to 128 tokens 1.02 to 1.13 times faster by masks (median 1.05), 160 tokens 0.81 to 1.03, 1900 tokens 0.64 to 1.02
+//   several sweeps of 256         96 and 128 tokens 1.02 to 1.08 (medians), 32 and 64 tokens 0.93 to 1.01, 160 tokens 0.81 to 1.00
+//   one sweep of 384 to 1024      32 and 64 tokens, 170 to 512 units of 600 to 4096 tokens: 1.02 to 1.21 in all of 76 calls (median 1.05)
+//   two sweeps of 1024            64 tokens 0.98 to 1.16 (median 1.06)
+// The line for 32 and 64 tokens is the one of sweeps of 256 rows, and on the safe side for wider ones: 257 to 1024 rows could go by masks.
 static bool head_apart(const Dims& D) {
   const int head = D.head - D.head0;
   return head > 128 || (head > 0 && head <= 64 && D.GP > 256);
@@ -184,8 +185,10 @@ static ScorePlan plan_mfma(const Dims& D, bool cap_keys, bool lse_given) {
     pl.unit_kernel = 5 * D.units_run >= 3 * compute_units() ? 1 : 0;
     // A few units beyond one round that fit one round of the slice kernels: with one slice per unit these are done before a unit
     // kernel and its rest have started.  Append + distill of 257 to 307 units, unit kernel and rest against slice kernels for all, medians by
-    // up to 64 / 128 / 256 / 512 query rows: up to 256 tokens 0.98 / 1.10 / 1.26 / 1.25 (given normalisers 1.12 / 1.26 / 1.45 / 1.66) times
-    // longer, 257 to 512 tokens 0.80 / 0.90 / 0.96 / 0.88 (0.96 / 1.05 / 1.13 / 1.04).
+    // up to 64 / 128 / 256 query rows: up to 256 tokens 0.98 / 1.10 / 1.26 (given normalisers 1.12 / 1.26 / 1.45) times longer, 257 to 512
+    // tokens 0.80 / 0.90 / 0.96 (0.96 / 1.05 / 1.13).  Five sweeps of 256 rows: up to 256 tokens 1.06 to 1.25 (1.33 to 1.7), 500 tokens (1.07).  With
+    // 264 to 1024 rows in one sweep the unit kernel has overtaken: up to 256 tokens 0.83 to 1.01 (CaP keys and 100 tokens to 1.13; given
+    // normalisers 1.04 to 1.25), 257 to 512 tokens (0.80 to 0.97); the line does not make that difference yet.
     const bool one_round = D.units_run > compute_units() && 5 * D.units_run < 6 * compute_units();
     if (one_round && (lse_given ? pl.n_slices1 == 1 || (pl.n_slices1 == 2 && D.GP > 64) : pl.n_slices1 == 1 && D.GP > 64)) {
       pl.unit_kernel = 0;
@@ -223,7 +226,9 @@ ScorePlan plan_score(const Dims& D, bool cap_keys, bool lse_given) {
   // against 76 us; 127 units and 256 rows, 7000 / 16384 tokens 525 / 1203 (six products) against 452 / 1016 us.  With more
   // than one block of rows from a third on while the rows are short (120 units of 2500 tokens and 100 / 256 rows 145 / 187 against 134 /
   // 170 us; 64 units 92 / 117 against 105 / 140 us).  Long rows stay with six products there: they are the more accurate ones, and the
-  // unit kernel is not faster everywhere (81 / 100 units of 7000 tokens and 64 rows 257 / 318 against 276 / 321 us).
+  // unit kernel is not faster everywhere (81 / 100 units of 7000 tokens and 64 rows 257 / 318 against 276 / 321 us).  The bound counts in 256 rows, also
+  // where the unit kernel sweeps more at once and would be faster with less accurate logits: 384 to 1024 rows, 4000 and 6000 tokens, 81
+  // units 0.93 to 0.97, 90 and 100 units 1.05 to 1.16, 115 and 127 units 1.19 to 1.33 times.
   // Every other fp32 call: six bf16 products (256 units of 4096 tokens, 256 query rows of 128 elements: append + distill 1.16 ms
   // against 3.61 ms on the vector ALUs, which stay for those who name them), in the direct kernels for a single block of 32 rows, which leaves
   // the kernels by longer slices mostly empty, and where these do not pay (direct_pays).
@@ -259,7 +264,9 @@ static bool path_refused(const Dims& D, const ScorePlan& pl) {
 //   rest of 8 / 32 / 64 (at most a quarter of the chip): 1200 tokens and 16 rows 133 / 138 / 145 against 124 / 130 / 140 us, 2500
 //   tokens and 256 rows 300 / 321 / 355 against 257 / 294 / 351 us; 300 tokens and 16 rows 58 / 60 / 62 against 61 / 63 / 65 us
 //   rest of 128: 2500 tokens and 256 rows 676 against 695 us, 8192 tokens and 256 rows 1798 against 1768 us, 32768 tokens and 1024
-//   rows 16.9 against 15.9 ms
+//   rows 15.0 against 14.2 ms
+//   384 to 1024 rows in one sweep, 300 / 1200 / 4096 / 16384 tokens: rests of 8 and 32 0.88 to 0.95 / 0.78 to 0.92 / 0.75 to 0.85 / 0.69 to 0.90
+//   of the time, of 64 1.02 to 1.04 (512 rows 0.98) / 0.94 to 0.98 / 0.88 to 0.93 / 0.80 to 0.91, of 128 and 16384 tokens 0.91 to 0.99
 //   fp32 (three products for the whole rounds, six for the rest), 16384 tokens and 256 rows, rest of 64 / 80: 2264 / 2324 against 2122 /
 //   2279 us; rest of 100 / 127: 2384 / 2481 against 2437 / 2642 us
 static int units_in_whole_rounds(const Dims& D, const ScorePlan& pl, bool cap_keys, bool lse_given) {
