@@ -47,7 +47,11 @@ constexpr int kCpUnroll = 4;
 // pass that comes next reads the keys, and finds twice as many of them there as with keys and values in turn (append + distill, 256 units of
 // 4096 tokens: given normalisers 337 -> 329 us, window and CaP keys 404 -> 389 us; 640 units 922 -> 911 us; 48 units of 13504 tokens 256 -> 239 us).
 // Where it holds all of them, keys last is slower: they are what is left to write back when the kernel ends (33 units of 1376 tokens 37.2 ->
-// 37.8 us, 8 of 7232 tokens 57.4 -> 58.1 us).
+// 37.8 us, 8 of 7232 tokens 57.4 -> 58.1 us).  And only if a unit's last segment is whole or nearly: the segments of consecutive units, which
+// are one stretch of memory, are otherwise out of step with the workgroups, and the append itself takes up to 9 % longer than in turn.  In turn against
+// values first, last segment whole or at least 7/8 full, 37 sizes of 400 MB to 2.9 GB: append + distill 0.990 to 1.061 times faster, median
+// 1.016; less full, 44 sizes: 0.962 to 1.077, 17 of them below 0.99 (208 / 256 units of 13710 tokens, a fifth full: append 529 -> 584 / 657 ->
+// 717 us, all 1083 -> 1120 / 1325 -> 1377; 208 units of 13696 tokens, whole: 517 -> 502, all 1068 -> 1054).
 // Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
 // keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
 constexpr int kApThreads = 256;
@@ -521,7 +525,8 @@ void launch_append(const Dims& D, int count, void* K, void* V, const void* K_new
   const int segs = (int)((run + kApSegBytes - 1) / kApSegBytes);
   // (a grid has fewer than 2^32 threads: millions of units go in several launches)
   const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 31) / ((int64_t)2 * segs * kApThreads));
-  const bool values_first = 4 * D.units * run >= kMemorySideCache;
+  const int64_t last_seg = run - (int64_t)(segs - 1) * kApSegBytes;
+  const bool values_first = 4 * D.units * run >= kMemorySideCache && 8 * last_seg >= 7 * kApSegBytes;
   Dims R = D;
   for (int64_t u0 = 0; u0 < D.units; u0 += most) {
     R.unit0 = (int)u0;
