@@ -262,17 +262,18 @@ __device__ __forceinline__ uint32_t agent_add(uint32_t* p, uint32_t v) {
 // j < k (rows that stay where they are included, so every kept K row is read); the pot itself keeps the plain keys.
 // ROWB, BF16: row bytes and cache type where ROPE needs them at compile time (ROWB is 0 without: `row_shift` = log2 of the
 // 16-byte lanes of a row).
-template <int THREADS, int CH, int ROWB, bool BF16, bool SHARED>
+// NUC (SHARED, rows of up to kNoveltyMaxRow tokens): the unit's words say which tokens have a NuC slot.  (In one kernel with the way that finds
+// them, calls without paid for it: 80 units of 2912 tokens 96.7 -> 97.4 us, 84 of 896 fp32 tokens 100.0 -> 101.0.)
+template <int THREADS, int CH, int ROWB, bool BF16, bool SHARED, bool NUC>
 __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void select_compact_kernel(Dims D, const float* __restrict__ u,
                                                                      float* novelty, int carry_novelty, float* scores,
                                                                      int32_t* __restrict__ keep_idx, char* Kbuf,
                                                                      char* Vbuf, const float* __restrict__ rope_cos,
                                                                      const float* __restrict__ rope_sin, char* Krot,
                                                                      int row_shift, int wgs_per_unit, int chunks,
-                                                                     int chunk_rows, uint32_t* sync, int nuc_known) {
+                                                                     int chunk_rows, uint32_t* sync) {
   constexpr bool ROPE = ROWB > 0;
   constexpr bool kRegs = RowStore<THREADS, CH>::kRegs;
-  constexpr bool kNuc = SHARED && kRegs && 4 * CH * THREADS <= kNoveltyMaxRow;       // the slots may be known
   __shared__ SelectShared<THREADS, CH> sh;
   // The kept list: in LDS for short rows; a long row leaves no room for it, and it is read back from keep_idx, where this
   // workgroup has just put it
@@ -288,8 +289,8 @@ __global__ __launch_bounds__(THREADS, sc_min_waves(SHARED, CH, ROWB)) void selec
   float* nov = (D.T > 0 || carry_novelty) ? novelty + nov_offset(D, ui) : nullptr;
   {
     Row<THREADS, CH> row(D, sh, unit, u, nullptr, nov);
-    const uint32_t* nuc_words = kNuc && nuc_known ? sync + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
-    select_row<THREADS, CH, true, kNuc>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, nuc_words,
+    const uint32_t* nuc_words = NUC ? sync + (int64_t)novelty_unit(D, unit) * kSyncWords : nullptr;
+    select_row<THREADS, CH, true, NUC>(row, part == 0 && scores != nullptr ? scores + (int64_t)unit * D.n : nullptr, nuc_words,
                          [&](int pos, int t, int c, int i) {
                            if (kRegs) keep_lds[pos] = (uint16_t)t;
                            else       keep_out[pos] = t;
@@ -482,24 +483,28 @@ void launch_select_compact(const Dims& D, const float* u, float* novelty, bool c
   const int chunks = shared ? (D.k + chunk_rows - 1) / chunk_rows : 0;
   const int threads = sc_threads(shared, D.n);
   const dim3 grid((unsigned)D.units_run * per_unit), block(threads);
-#define CCD_LAUNCH(THREADS, CH, RB, BF, SHARED)                                                                                  \
-  launch((select_compact_kernel<THREADS, CH, RB, BF, SHARED>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
-         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync, nuc_known ? 1 : 0)
-#define CCD_LAUNCH_RB(THREADS, CH, SHARED)                                          \
-  if (Krot == nullptr) CCD_LAUNCH(THREADS, CH, 0, true, SHARED);                    \
-  else if (rowb == 128) CCD_LAUNCH(THREADS, CH, 128, true, SHARED);                 \
-  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(THREADS, CH, 256, true, SHARED); \
-  else if (rowb == 256) CCD_LAUNCH(THREADS, CH, 256, false, SHARED);                \
-  else CCD_LAUNCH(THREADS, CH, 512, false, SHARED)
+#define CCD_LAUNCH(THREADS, CH, RB, BF, SHARED, NUC)                                                                                  \
+  launch((select_compact_kernel<THREADS, CH, RB, BF, SHARED, NUC>), grid, block, s, D, u, novelty, carry_novelty ? 1 : 0, scores,       \
+         keep_idx, (char*)K, (char*)V, rope_cos, rope_sin, (char*)Krot, row_shift, per_unit, chunks, chunk_rows, sync)
+#define CCD_LAUNCH_RB(THREADS, CH, SHARED, NUC)                                          \
+  if (Krot == nullptr) CCD_LAUNCH(THREADS, CH, 0, true, SHARED, NUC);                    \
+  else if (rowb == 128) CCD_LAUNCH(THREADS, CH, 128, true, SHARED, NUC);                 \
+  else if (rowb == 256 && D.dtype == 1) CCD_LAUNCH(THREADS, CH, 256, true, SHARED, NUC); \
+  else if (rowb == 256) CCD_LAUNCH(THREADS, CH, 256, false, SHARED, NUC);                \
+  else CCD_LAUNCH(THREADS, CH, 512, false, SHARED, NUC)
 #define CCD_LAUNCH_SHARED(CH) \
-  if (shared) { CCD_LAUNCH_RB(1024, CH, true); } else { CCD_LAUNCH_RB(1024, CH, false); }
+  if (shared) { CCD_LAUNCH_RB(1024, CH, true, false); } else { CCD_LAUNCH_RB(1024, CH, false, false); }
+#define CCD_LAUNCH_NUC(THREADS, CH)          /* rows of up to kNoveltyMaxRow tokens */ \
+  if (nuc_known) { CCD_LAUNCH_RB(THREADS, CH, true, true); } else { CCD_LAUNCH_RB(THREADS, CH, true, false); }
+  static_assert(kNoveltyMaxRow <= 2 * 4 * 1024, "");
   const int token_chunks = (D.n + 4 * threads - 1) / (4 * threads);     // per thread
-  if (threads == 512)         { if (token_chunks <= 1) { CCD_LAUNCH_RB(512, 1, true); } else { CCD_LAUNCH_RB(512, 2, true); } }
-  else if (token_chunks <= 1) { CCD_LAUNCH_RB(1024, 1, false); }
-  else if (token_chunks <= 2) { CCD_LAUNCH_SHARED(2); }
-  else if (token_chunks <= 4 && shared) { CCD_LAUNCH_RB(1024, 4, true); }
+  if (threads == 512)         { if (token_chunks <= 1) { CCD_LAUNCH_NUC(512, 1); } else { CCD_LAUNCH_NUC(512, 2); } }
+  else if (token_chunks <= 1) { CCD_LAUNCH_RB(1024, 1, false, false); }
+  else if (token_chunks <= 2) { if (shared) { CCD_LAUNCH_NUC(1024, 2); } else { CCD_LAUNCH_RB(1024, 2, false, false); } }
+  else if (token_chunks <= 4 && shared) { CCD_LAUNCH_RB(1024, 4, true, false); }
   else                        { CCD_LAUNCH_SHARED(kLdsRow); }
 #undef CCD_LAUNCH_SHARED
+#undef CCD_LAUNCH_NUC
 #undef CCD_LAUNCH_RB
 #undef CCD_LAUNCH
 }
