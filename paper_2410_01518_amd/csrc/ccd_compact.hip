@@ -47,13 +47,16 @@ constexpr int kCpUnroll = 4;
 // pass that comes next reads the keys, and finds twice as many of them there as with keys and values in turn (append + distill, 256 units of
 // 4096 tokens: given normalisers 337 -> 329 us, window and CaP keys 404 -> 389 us; 640 units 922 -> 911 us; 48 units of 13504 tokens 256 -> 239 us).
 // Where it holds all of them, keys last is slower: they are what is left to write back when the kernel ends (33 units of 1376 tokens 37.2 ->
-// 37.8 us, 8 of 7232 tokens 57.4 -> 58.1 us).  And only if a unit's last segment is whole or nearly: the segments of consecutive units, which
-// are one stretch of memory, are otherwise out of step with the workgroups, and the append itself takes up to 9 % longer than in turn.  In turn against
-// values first, last segment whole or at least 7/8 full, 37 sizes of 400 MB to 2.9 GB: append + distill 0.990 to 1.061 times faster, median
-// 1.016; less full, 44 sizes: 0.962 to 1.077, 17 of them below 0.99 (208 / 256 units of 13710 tokens, a fifth full: append 529 -> 584 / 657 ->
-// 717 us, all 1083 -> 1120 / 1325 -> 1377; 208 units of 13696 tokens, whole: 517 -> 502, all 1068 -> 1054).
+// 37.8 us, 8 of 7232 tokens 57.4 -> 58.1 us).
+// stretch: a chunk that fills an empty pot is one stretch of memory on both sides, and cut into segments as a whole.  With segments of its own for
+// every unit, whose last one is not full, the workgroups fall out of step with the 16 KiB that follow each other in memory, which costs
+// more in one walk over the values than in turn: 208 units of 13710 tokens (214.2 segments each), in turn / values first / in one stretch
+// 529 / 586 / 496 us, with their distillation 1083 / 1120 / 1043; 400 of 4144 (64.75) 319 / 336 / 294 and 660 / 668 / 630; 72 of 18528 (289.5) 255 /
+// 246 / 235 and 554 / 525 / 515; 208 of 13696 (214) 516 / 504 / 504 and 1075 / 1061 / 1060.  (Into a pot that holds tokens already, values
+// first: 14 sizes 0.997 to 1.038 times faster, whatever the last segment.)
 // Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
-// keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).
+// keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).  In a stretch every
+// nov_spread-th key workgroup takes the next kApNovelty tokens of the rows of novelty.
 constexpr int kApThreads = 256;
 constexpr int kApLoads = 4;
 constexpr int kApNovelty = 1024;       // a multiple of the tokens of a segment (32, 64 or 128)
@@ -61,13 +64,15 @@ constexpr int64_t kMemorySideCache = 256 << 20;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
-                                                                 const float* nov_new, int nov_per_head, int values_first) {
+                                                                 const float* nov_new, int nov_per_head, int values_first, int nov_spread) {
+  const bool stretch = nov_spread > 0;           // (all units are one: segs of the whole stretch, offsets of unit 0)
+  const int units = stretch ? 1 : D.units_run;
   const int seg = blockIdx.x % segs;
   const int ut = blockIdx.x / segs;
-  const bool isV = values_first ? ut < D.units_run : ut & 1;
-  const int unit = D.unit0 + (values_first ? (isV ? ut : ut - D.units_run) : ut >> 1);
+  const bool isV = values_first ? ut < units : ut & 1;
+  const int unit = D.unit0 + (values_first ? (isV ? ut : ut - units) : ut >> 1);
   const UnitIdx ui = decode_unit(D, unit);
-  const int64_t run = (int64_t)count * D.d * esz;                         // bytes of a unit's share
+  const int64_t run = (int64_t)count * D.d * esz * (stretch ? D.units : 1);      // bytes of a unit's share
   char* dst = (isV ? V : K) + (kv_offset(D, ui) + (int64_t)D.n * D.d) * esz;
   const char* src = (isV ? Vnew : Knew) + (int64_t)unit * run;
   const int64_t b0 = (int64_t)seg * kApSegBytes + threadIdx.x * 16;
@@ -78,11 +83,20 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
     if (b < run) v[i] = load_streaming(src + b);
   }
   // (one key workgroup in 8 to 32: those whose segment starts at a multiple of kApNovelty tokens)
-  const int t_seg = seg * (kApSegBytes / (D.d * esz));
-  const bool carry = novelty != nullptr && !isV && t_seg % kApNovelty == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0));
+  int t_seg = seg * (kApSegBytes / (D.d * esz));
+  UnitIdx un = ui;
+  bool carry = novelty != nullptr && !isV;
+  if (!stretch) {
+    carry = carry && t_seg % kApNovelty == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0));
+  } else if (carry) {
+    const int per_row = (count + kApNovelty - 1) / kApNovelty, piece = seg / nov_spread, row = piece / per_row;
+    carry = seg % nov_spread == 0 && row < (nov_per_head ? D.units : D.B);
+    t_seg = (piece - row * per_row) * kApNovelty;
+    un = decode_unit(D, nov_per_head ? row : row * (D.L * D.Hkv));
+  }
   if (carry) {
-    const float* ns = nov_new + (int64_t)ui.b * count;
-    float* nd = novelty + nov_offset(D, ui) + D.n;
+    const float* ns = nov_new + (int64_t)un.b * count;
+    float* nd = novelty + nov_offset(D, un) + D.n;
     float nv[kApNovelty / kApThreads];
 #pragma unroll
     for (int i = 0; i < kApNovelty / kApThreads; ++i) nv[i] = ns[min(t_seg + i * kApThreads + (int)threadIdx.x, count - 1)];
@@ -530,14 +544,22 @@ void launch_append(const Dims& D, int count, void* K, void* V, const void* K_new
   const int segs = (int)((run + kApSegBytes - 1) / kApSegBytes);
   // (a grid has fewer than 2^32 threads: millions of units go in several launches)
   const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 31) / ((int64_t)2 * segs * kApThreads));
-  const int64_t last_seg = run - (int64_t)(segs - 1) * kApSegBytes;
-  const bool values_first = 4 * D.units * run >= kMemorySideCache && 8 * last_seg >= 7 * kApSegBytes;
+  const bool values_first = 4 * D.units * run >= kMemorySideCache;
   Dims R = D;
+  const int64_t all_segs = (D.units * run + kApSegBytes - 1) / kApSegBytes;
+  const bool dense = D.kv_sh == (int64_t)D.n_cap * D.d && (D.L == 1 || D.kv_sl == D.Hkv * D.kv_sh) && (D.B == 1 || D.kv_sb == D.L * D.Hkv * D.kv_sh);
+  if (values_first && D.n == 0 && count == D.n_cap && dense && run >= kApSegBytes && 2 * all_segs * kApThreads <= (int64_t)1 << 31) {
+    // (units of at least a segment: there are no fewer segments than pieces of novelty)
+    const int64_t pieces = (int64_t)(nov_per_head ? D.units : D.B) * ((count + kApNovelty - 1) / kApNovelty);
+    launch(append_rows_kernel, dim3(2u * (unsigned)all_segs), dim3(kApThreads), s, R, esz, count, (int)all_segs, (char*)K, (char*)V,
+           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, 1, (int)(all_segs / pieces));
+    return;
+  }
   for (int64_t u0 = 0; u0 < D.units; u0 += most) {
     R.unit0 = (int)u0;
     R.units_run = (int)std::min<int64_t>(most, D.units - u0);
     launch(append_rows_kernel, dim3(2u * R.units_run * segs), dim3(kApThreads), s, R, esz, count, segs, (char*)K, (char*)V,
-           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, values_first ? 1 : 0);
+           (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, values_first ? 1 : 0, 0);
   }
 }
 

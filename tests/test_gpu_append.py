@@ -121,6 +121,36 @@ def test_append_to_more_units_than_one_grid_has_threads_for():
         assert bool((t[0] == 1.0).all()) and bool((t[1] == 2.0).all())
 
 
+# chunks that fill an empty pot and are more than the memory-side cache holds, moved as one stretch: units that end inside a segment, rows of novelty that
+# end inside a piece of 1024 tokens, units of just a segment; and pots that are no stretch (heads further apart, a token left empty, units
+# of less than a segment)
+@pytest.mark.parametrize("novelty", ["per_head", "shared", "none"])
+@pytest.mark.parametrize("B,L,Hkv,m,d,fp32,apart,left", [
+    (2, 4, 2, 33001, 64, False, 0, 0), (1, 3, 3, 29129, 128, False, 0, 0), (3, 1, 2, 22999, 128, True, 0, 0), (1, 16, 8, 1025, 128, True, 0, 0),
+    (2, 253, 8, 130, 64, False, 0, 0), (1, 510, 8, 129, 64, False, 0, 0), (2, 4, 2, 33001, 64, False, 3, 0), (2, 4, 2, 33001, 64, False, 0, 1),
+    (1, 640, 8, 103, 64, False, 0, 0)])
+def test_append_that_fills_an_empty_pot(B, L, Hkv, m, d, fp32, apart, left, novelty):
+    print(f"append whole pot {B} {L} {Hkv} {m} {d} {fp32} {apart} {left} {novelty}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    dt, it = (torch.float32, torch.int32) if fp32 else (torch.bfloat16, torch.int16)
+    assert 4 * B * L * Hkv * m * d * (4 if fp32 else 2) >= 256 << 20
+    K_new, V_new = (torch.randint(-32768, 32767, (B, L, Hkv, m, d), generator=g, device="cuda", dtype=torch.int16).to(it) for _ in range(2))
+    nov_new = torch.rand((B, m), generator=g, device="cuda")
+    cap = m + left
+    K, V = (torch.zeros((B, L, Hkv + apart, cap, d), dtype=it, device="cuda") for _ in range(2))
+    nov = torch.zeros((B, L, Hkv, cap) if novelty == "per_head" else (B, cap), device="cuda")
+    Kh = K[:, :, :Hkv]
+    shape = ip.make_shape(None, Kh.view(dt), None if novelty == "none" else nov, k=1, n_valid=0)
+    has = novelty != "none"
+    assert ip.ccd_append(shape, Kh.view(dt), V[:, :, :Hkv].view(dt), nov if has else None, K_new.view(dt), V_new.view(dt), nov_new if has else None) == ip.CCD_OK
+    torch.cuda.synchronize()
+    for have, new in ((K, K_new), (V, V_new)):
+        assert torch.equal(have[:, :, :Hkv, :m], new) and not bool(have[:, :, Hkv:].any()) and not bool(have[..., m:, :].any())
+    if has:
+        assert torch.equal(nov[..., :m], nov_new[:, None, None, :].expand(B, L, Hkv, m) if novelty == "per_head" else nov_new)
+        assert not bool(nov[..., m:].any())
+
+
 # chunk and pot are just less than what the memory-side cache holds, and just as much: keys and values in turn, values first
 @pytest.mark.parametrize("m", [8191, 8192])
 def test_append_of_chunks_as_large_as_the_memory_side_cache(m):
