@@ -538,13 +538,15 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       if (ragged && tp == PARTS - 1) {
         CCD_TILE_NOW(0, full)
         q_frags_arrived();
-        int n_ragged = n_main - full * kStep;
-        asm volatile("" : "+s"(n_ragged));          // (or its 16 masks are worked out at the start of the kernel, ragged or not, and spilled:
-                                                    // 156 units of 4192 tokens 109.4 -> 110.0 us)
+        int n_ragged = n_main - full * kStep, row_half = half;
+        // (opaque, or the tile's 16 masks are worked out at the start of the kernel, ragged or not, and spilled: 156 units of 4192 tokens 109.4
+        // -> 110.0 us; and if only the masks cannot be, then the 16 rows that they compare: fp32, 256 units of 600 tokens and 192 / 768 rows
+        // 79.1 / 134.4 -> 87.0 / 140.2, most of it for 88 bytes of scratch memory per lane)
+        asm volatile("" : "+s"(n_ragged), "+v"(row_half));
         static_for<0, NP>([&](auto Pc) {
           constexpr int p = decltype(Pc)::value;
           logits_now<SH, 1, p>(accA, a[0]);
-          fold_stats<true>(accA, m_ref[p], Zs[p], c, half, n_ragged);
+          fold_stats<true>(accA, m_ref[p], Zs[p], c, row_half, n_ragged);
         });
       }
       if constexpr (!F32) {          // (fp32 caches under a window take other kernels)
