@@ -367,9 +367,11 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
       // Row groups: the wave's part of the tokens is RG quarters, so its sums are taken in RG runs of tiles, or their chains of additions would
       // be RG times as long (rms error of the log-sum-exp of 32768 tokens, relative: 1.6e-7 by quarters or runs, 3.5e-7 by halves and 6.8e-7 in one
       // piece; of 4096 tokens 0.8e-7, 1.4e-7, 2.4e-7).  Finished runs wait in LDS, where pass 2 will have its token sums: there is no register
-      // left.  (Append + distill without and with the runs: 256 units, 4096 tokens and 512 / 1024 rows 477.7 / 702.2 and
-      // 477.8 / 702.4 us, 600 tokens and 1024 rows 125.1 and 125.3; 640 units of 32768 tokens and 1024 rows 14.01 and 14.01 ms.)
-      [[maybe_unused]] const int run = ((s1 - s0 + RG - 1) / RG + 1) & ~1;          // tiles: two per round of the loop
+      // left.  A run has at least eight tiles, 64 additions, whose error is at most a quarter of what the log-sum-exp's own rounding leaves; the last one
+      // goes from its registers to the merge.  (Append + distill of 256 units without and with the runs, 4096 tokens and 1024 rows 677.1 and 676.7 us;
+      // 520 tokens of 64 elements and 384 / 512 / 768 / 1024 rows 51.5 / 57.3 / 65.7 / 76.7 and 51.6 / 57.3 / 66.4 / 77.4, where runs of four
+      // tiles were 52.0 / 57.7 / 66.8 / 77.2.)
+      [[maybe_unused]] const int run = max(((s1 - s0 + RG - 1) / RG + 1) & ~1, 8);          // tiles: two per round of the loop
       [[maybe_unused]] float* z_runs = sm.ubuf[wave] + lane;
       if constexpr (RG > 1) {
 #pragma unroll
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
         // (No branch inside a tile and none between the two tiles of the loop body: with straight-line code the
         // compiler can tell how many loads are in flight at every wait.  Behind the wave's last tile the last step
         // computes the logits of that tile's first pair once more; nobody reads them.)
-        do {
+        for (;;) {
           const int s_run = RG == 1 ? s1 : min(s + run, s1);
           while (s + 1 < s_run) {
             CCD_P1_TILE(1, 0, accA, accB)
@@ -456,16 +458,15 @@ __global__ __launch_bounds__(kMT, 1) void score_unit_kernel(Dims D, ScorePlan pl
             }
             ++s;
           }
-          if constexpr (RG > 1) {
-#pragma unroll
-            for (int e = 0; e < NP * kQB; ++e) {
-              float(&z)[2] = Z[e / kQB][e % kQB];
-              z_runs[e * 64] += z[0] + z[1];
-              z[0] = 0.f;
-              z[1] = 0.f;
-            }
-          }
-        } while (RG > 1 && s + 1 < s1);
+          if (RG == 1 || s + 1 >= s1) break;          // (the last run stays in its registers)
+          static_for<0, NP * kQB>([&](auto Ec) {
+            constexpr int e = decltype(Ec)::value;
+            float(&z)[2] = Z[e / kQB][e % kQB];
+            z_runs[e * 64] += z[0] + z[1];
+            z[0] = 0.f;
+            z[1] = 0.f;
+          });
+        }
         if (s < s1) {
           CCD_P1_TILE(1, 0, accA, accB)
         }
