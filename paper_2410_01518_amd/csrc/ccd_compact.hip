@@ -54,6 +54,9 @@ constexpr int kCpUnroll = 4;
 // 529 / 586 / 496 us, with their distillation 1083 / 1120 / 1043; 400 of 4144 (64.75) 319 / 336 / 294 and 660 / 668 / 630; 72 of 18528 (289.5) 255 /
 // 246 / 235 and 554 / 525 / 515; 208 of 13696 (214) 516 / 504 / 504 and 1075 / 1061 / 1060.  (Into a pot that holds tokens already, values
 // first: 14 sizes 0.997 to 1.038 times faster, whatever the last segment.)
+// Append + distill of 128 to 640 units of 1536 to 9001 tokens, with and without CR-RoPE (whose scores read other keys), in one stretch against
+// in turn: 1.02 to 1.085 times faster above 1 GB; up to there 1.00 to 1.04, but for six calls of 568 MB and 1 GB (0.977 to 0.998), whose compaction
+// finds less in the cache.
 // Carried novelty follows: entry n + j of every head takes the chunk's novelty of token j, kApNovelty tokens to a workgroup that also moves
 // keys (one workgroup per head, one entry per thread after the other: 32768 tokens of 8 units 57 instead of 37 us).  In a stretch every
 // nov_spread-th key workgroup takes the next kApNovelty tokens of the rows of novelty.
