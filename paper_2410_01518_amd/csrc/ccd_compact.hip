@@ -65,17 +65,17 @@ constexpr int kApLoads = 4;
 constexpr int kApNovelty = 1024;       // a multiple of the tokens of a segment (32, 64 or 128)
 constexpr int64_t kMemorySideCache = 256 << 20;
 constexpr int kApSegBytes = kApThreads * 16 * kApLoads;     // bytes one workgroup moves: 16 KiB
+template <bool STRETCH>
 __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz, int count, int segs, char* K, char* V,
                                                                  const char* Knew, const char* Vnew, float* novelty,
                                                                  const float* nov_new, int nov_per_head, int values_first, int nov_spread) {
-  const bool stretch = nov_spread > 0;           // (all units are one: segs of the whole stretch, offsets of unit 0)
-  const int units = stretch ? 1 : D.units_run;
+  const int units = STRETCH ? 1 : D.units_run;   // (all units are one: segs of the whole stretch, offsets of unit 0)
   const int seg = blockIdx.x % segs;
   const int ut = blockIdx.x / segs;
   const bool isV = values_first ? ut < units : ut & 1;
   const int unit = D.unit0 + (values_first ? (isV ? ut : ut - units) : ut >> 1);
   const UnitIdx ui = decode_unit(D, unit);
-  const int64_t run = (int64_t)count * D.d * esz * (stretch ? D.units : 1);      // bytes of a unit's share
+  const int64_t run = (int64_t)count * D.d * esz * (STRETCH ? D.units : 1);      // bytes of a unit's share
   char* dst = (isV ? V : K) + (kv_offset(D, ui) + (int64_t)D.n * D.d) * esz;
   const char* src = (isV ? Vnew : Knew) + (int64_t)unit * run;
   const int64_t b0 = (int64_t)seg * kApSegBytes + threadIdx.x * 16;
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kApThreads) void append_rows_kernel(Dims D, int esz
   int t_seg = seg * (kApSegBytes / (D.d * esz));
   UnitIdx un = ui;
   bool carry = novelty != nullptr && !isV;
-  if (!stretch) {
+  if (!STRETCH) {
     carry = carry && t_seg % kApNovelty == 0 && (nov_per_head || (ui.l == 0 && ui.h == 0));
   } else if (carry) {
     const int per_row = (count + kApNovelty - 1) / kApNovelty, piece = seg / nov_spread, row = piece / per_row;
@@ -551,17 +551,17 @@ void launch_append(const Dims& D, int count, void* K, void* V, const void* K_new
   Dims R = D;
   const int64_t all_segs = (D.units * run + kApSegBytes - 1) / kApSegBytes;
   const bool dense = D.kv_sh == (int64_t)D.n_cap * D.d && (D.L == 1 || D.kv_sl == D.Hkv * D.kv_sh) && (D.B == 1 || D.kv_sb == D.L * D.Hkv * D.kv_sh);
-  if (values_first && D.n == 0 && count == D.n_cap && dense && run >= kApSegBytes && 2 * all_segs * kApThreads <= (int64_t)1 << 31) {
-    // (units of at least a segment: there are no fewer segments than pieces of novelty)
+  if (values_first && D.n == 0 && count == D.n_cap && dense && run > kApSegBytes && run % kApSegBytes != 0 && 2 * all_segs * kApThreads <= (int64_t)1 << 31) {
+    // (units of more than a segment: there are no fewer segments than pieces of novelty; of whole segments: the cut is the same either way)
     const int64_t pieces = (int64_t)(nov_per_head ? D.units : D.B) * ((count + kApNovelty - 1) / kApNovelty);
-    launch(append_rows_kernel, dim3(2u * (unsigned)all_segs), dim3(kApThreads), s, R, esz, count, (int)all_segs, (char*)K, (char*)V,
+    launch(append_rows_kernel<true>, dim3(2u * (unsigned)all_segs), dim3(kApThreads), s, R, esz, count, (int)all_segs, (char*)K, (char*)V,
            (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, 1, (int)(all_segs / pieces));
     return;
   }
   for (int64_t u0 = 0; u0 < D.units; u0 += most) {
     R.unit0 = (int)u0;
     R.units_run = (int)std::min<int64_t>(most, D.units - u0);
-    launch(append_rows_kernel, dim3(2u * R.units_run * segs), dim3(kApThreads), s, R, esz, count, segs, (char*)K, (char*)V,
+    launch(append_rows_kernel<false>, dim3(2u * R.units_run * segs), dim3(kApThreads), s, R, esz, count, segs, (char*)K, (char*)V,
            (const char*)K_new, (const char*)V_new, novelty, novelty_new, nov_per_head ? 1 : 0, values_first ? 1 : 0, 0);
   }
 }
